@@ -22,9 +22,10 @@ extern "C" {
  * without passing through LDS; 7 = 256x256 by four waves of 128x128 whose operands are loaded from memory straight
  * into LDS (what "automatic" picks whenever it picks 256x256 tiles, K + K2 >= 2560 and M, N > 64 -- 1 always names
  * the eight-wave kernel that stages its operands through registers; the two give bit-identical results).
- * split_ws [dev, split_ws_bytes] or NULL: scratch for a reduction split.  An accumulating fp32 product (out_f32 1 with
- * beta) whose 256x256 tiles would leave most compute units idle is cut into up to 16 slices along K when the scratch
- * holds slices * M * N floats; the slices' partial products are added to C in slice order by a second kernel, so the
+ * "Automatic" takes the tile and the number of slices that a cost model finds cheapest (also 64x64 tiles).
+ * split_ws [dev, split_ws_bytes] or NULL: scratch for a reduction split.  A bf16 product (out_f32 0) or an accumulating
+ * fp32 product (out_f32 1 with beta) that would leave compute units idle is cut into up to 16 slices along K when the
+ * scratch holds slices * M * N floats; the slices' partial products are added in slice order by a second kernel, so the
  * result is reproducible run to run (the weight-gradient accumulation of Sec. 4.1.1).  out_f32 3: as 1, but the merged
  * sum is written to C as bf16 [M, N] (overwritten; needs M * N floats of scratch; one direct pass when nothing splits). */
 RP_API rp_status rp_op_gemm(void* stream, int layout, int out_f32, const void* A, const void* B, void* C, int M, int N, int K,

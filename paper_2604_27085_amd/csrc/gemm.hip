@@ -4,8 +4,9 @@
 // such waves.  Two waves per SIMD keep the matrix pipeline fed: while one wave waits at a barrier, on LDS or on HBM,
 // the other one issues MFMAs.
 //
-//   256x256 (2x4 waves, K tile 64, the whole LDS of a CU), 256x128 (2x2), 128x128 (1x2), 128x64 (one wave; K tile 32),
-//   256x128 with two groups of 2x2 waves (K tile 64)
+//   256x256 (2x4 waves, K tile 64, the whole LDS of a CU), 256x128 with two groups of 2x2 waves (K tile 64)
+//
+// The smaller tiles are in gemm_mid.hip; which one a product takes is decided by the cost model of choose() below.
 //
 // Operands are staged through registers (16-byte buffer loads; rows outside the matrix read as zero through the
 // descriptor, so the loop has no branch) and LDS is double buffered.  The K loop is written slot by slot -- one MFMA
@@ -22,8 +23,8 @@
 // LDS); this file keeps every other tile and layout, and the eight-wave 256x256 NT instance as the reference it is
 // tested against bit for bit.
 // Outputs too small to fill the chip with 256x256 tiles use a 256x128 tile worked
-// on by two wave groups that split every K tile (merged through LDS); GEMMs that accumulate into an fp32 output and
-// would still leave CUs idle are split along the reduction: the slices write partial products to scratch memory and a
+// on by two wave groups that split every K tile (merged through LDS) or the small tiles; products that would still leave
+// CUs idle are split along the reduction: the slices write partial products to scratch memory and a
 // second kernel adds them in slice order (reproducible run to run).  A variant keeps the B operand out of LDS (BD).
 //
 // Operands whose reduction index is not contiguous in memory (the weight in an activation-gradient GEMM, both operands
@@ -368,17 +369,17 @@ hipError_t launch_tile(hipStream_t st, const GemmArgs& a, int tile) {
   }
   switch (tile) {
     case 1: return launch_one<2, 4, 64, TA, TB>(st, a);
-    case 2: return launch_one<2, 2, 32, TA, TB>(st, a);
-    case 3: return launch_one<1, 2, 32, TA, TB>(st, a);
     case 5: return launch_one<2, 2, 64, TA, TB, 2>(st, a);
-    default: return launch_one<1, 1, 32, TA, TB>(st, a);
+    default: return gemm_mid_launch(st, a, TA ? GEMM_TN : TB ? GEMM_NN : GEMM_NT, tile);
   }
 }
 
-// Merge of a reduction split: C (+)= sum over the slices, added in slice order (one thread per four columns).
+// Merge of a reduction split: C (+)= sum over the slices, added in slice order (one thread per four columns); a bf16
+// result takes the residual R (optional) here.
 template <bool OUT_BF16>
 __global__ void __launch_bounds__(256) splitk_merge_kernel(const float* __restrict__ ws, int splits, long slice_stride,
-                                                           void* __restrict__ Cout, long ldc, int M, int N, int beta) {
+                                                           void* Cout, long ldc, int M, int N, int beta,
+                                                           const bf16* R, long ldr) {
   const int n4 = N >> 2;
   const long total = (long)M * n4;
   for (long idx = (long)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (long)gridDim.x * 256) {
@@ -391,6 +392,10 @@ __global__ void __launch_bounds__(256) splitk_merge_kernel(const float* __restri
       acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
     }
     if constexpr (OUT_BF16) {
+      if (R) {
+        const uint2 r = *reinterpret_cast<const uint2*>(R + row * ldr + c);
+        acc.x += bf16_lo(r.x); acc.y += bf16_hi(r.x); acc.z += bf16_lo(r.y); acc.w += bf16_hi(r.y);
+      }
       *reinterpret_cast<uint2*>(reinterpret_cast<bf16*>(Cout) + row * ldc + c) = make_uint2(pack_bf16x2(acc.x, acc.y), pack_bf16x2(acc.z, acc.w));
     } else {
       float4* dst = reinterpret_cast<float4*>(reinterpret_cast<float*>(Cout) + row * ldc + c);
@@ -427,32 +432,42 @@ __global__ void __launch_bounds__(256) gemm_arrange_kernel(const bf16* __restric
   out[idx] = v;
 }
 
-// Picks the tile with the smallest modelled time: n = workgroups on the busiest CU, each costing its area divided by
-// a relative efficiency that was measured with one workgroup per CU and with the CU fully occupied.
-// atomic_nk: K tiles of 64 when the output accumulates in fp32, so that an under-filled 256x256 launch can be split
-// along the reduction (merged by atomic adds, which only pays off for long reductions); else 0.
-// k_tiles: K tiles of 64 in the reduction.  The two-group tile pays a fixed accumulator exchange per output tile, so its
-// efficiency against the 256x256 tile grows with the length of the reduction: measured 0.75-0.84 at K = 2048, 0.94 at
-// K = 4096, 1.0 at K = 12288 -- modelled as 0.75 at 32 K tiles rising to 0.85 at 96.
-int choose_tile(int M, int N, bool plain_epilogue, int atomic_nk, int k_tiles) {
-  static const int bm[5] = {256, 256, 128, 128, 256}, bn[5] = {256, 128, 128, 64, 128};
-  static const int per_cu[5] = {1, 2, 3, 5, 1};
-  const double k2 = 0.75 + 0.1 * (k_tiles <= 32 ? 0.0 : k_tiles >= 96 ? 1.0 : (k_tiles - 32) / 64.0);
-  const double eff_full[5] = {1.0, 0.7, 0.6, 0.4, k2}, eff_single[5] = {1.0, 0.375, 0.25, 0.15, k2};
-  int best = 1;
-  double best_cost = 1e300;
-  for (int t = 0; t < (plain_epilogue ? 5 : 4); ++t) {
-    const long tiles = (long)((M + bm[t] - 1) / bm[t]) * ((N + bn[t] - 1) / bn[t]);
-    const long n = (tiles + 255) / 256;
-    double e = eff_full[t];
-    if (n < per_cu[t]) e = eff_single[t] + (eff_full[t] - eff_single[t]) * (double)(n - 1) / (per_cu[t] - 1);
-    double rounds = (double)n;
-    if (t == 0 && atomic_nk >= 128 && tiles <= 128) rounds = 0.55;
-    const double cost = rounds * bm[t] * bn[t] / e;
-    if (cost < best_cost) { best_cost = cost; best = t + 1; }
+// Modelled cost of a product on one tile, in microseconds.  Elapsed time = launch + rounds * (K tiles * time per K tile +
+// epilogue), rounds = workgroups on the busiest CU.  The constants are fits to measured times (K = 128 to 24576, 16 to 1500
+// workgroups, weights coming from HBM; within 10 % of the measurement on most shapes):
+//   - the 256x256 and 256x128 tiles are bound by the matrix pipe and the power it draws: their K tile takes longer the more
+//     of the chip is busy;
+//   - the small tiles are bound by what a CU can fetch -- 50 bytes/ns of data that comes from HBM, however many loads are
+//     in flight (80 from the Infinity Cache, 150 from L2) -- so their K tile costs its operand bytes.
+// A split into `splits` slices adds the merge kernel and its traffic.  Added to the elapsed time is the chip time the
+// workgroups use up (their summed time over 256 CUs): what is left over belongs to other streams, so a small tile has to buy
+// enough latency for the extra operand traffic it causes.  The weight of that term, both ends measured on whole stage calls,
+// one stream | three streams at once, against choosing by elapsed time alone: a backward stage of 928 tokens at h = 2048
+// takes 730 | 507 us at weight 1, 786 | 478 at 2; one of 4096 tokens 1959 | 1764 and 2083 | 1632 (the larger tile on half of
+// the chip); one of 2 x 508 tokens at h = 4096 1288 | 968 and 1307 | 962.  1.3 is the last value at which no call on one
+// stream loses.
+constexpr double CHIP_WEIGHT = 1.3;
+struct TileModel { int bm, bn; double tau, tau_fill, epi; };
+constexpr TileModel TILE_MODEL[9] = {{},                          // by tile number
+                                     {256, 256, 0.95, 0.60, 6.0}, {256, 128, 0.60, 0.35, 4.0}, {128, 128, 0.55, 0.0, 3.5},
+                                     {128, 64, 0.36, 0.0, 3.5},   {256, 128, 0.53, 0.40, 5.0}, {}, {}, {64, 64, 0.31, 0.0, 3.5}};
+
+double tile_cost(int tile, int splits, int M, int N, int k_tiles, bool out_f32) {
+  const TileModel& t = TILE_MODEL[tile];
+  const long wg = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * splits;
+  const double rounds = (double)((wg + 255) / 256), fill = wg < 256 ? wg / 256.0 : 1.0;
+  double tau = t.tau + t.tau_fill * fill;
+  if (t.tau_fill == 0.0) {   // rows and columns past the end of a skinny output are not fetched
+    const double part = (double)((M < t.bm ? M : t.bm) + (N < t.bn ? N : t.bn)) / (t.bm + t.bn);
+    tau *= part > 0.6 ? part : 0.6;
   }
-  return best;
+  const int per = (k_tiles + splits - 1) / splits;
+  double us = 3.0 + rounds * (per * tau + t.epi) + CHIP_WEIGHT * wg / 256.0 * (per * (tau + t.tau_fill * (1.0 - fill)) + t.epi);
+  if (splits > 1) us += 4.0 + (double)M * N * (8.0 * splits + (out_f32 ? 8.0 : 2.0)) / 4.0e6;
+  return us;
 }
+
+struct Choice { int tile, splits; };
 
 // Bytes spanned by a [rows, cols] bf16 view with row stride ld; 0 for an empty view, ~0 when it does not fit 31 bits.
 unsigned extent_bytes(long rows, long cols, long ld) {
@@ -481,16 +496,35 @@ hipError_t gemm_arrange(hipStream_t st, const void* B, long ldb, int N, int K, i
   return hipGetLastError();
 }
 
-int gemm_pick_tile(const GemmArgs& a, int tile_hint) {
-  if (a.b_direct) return 1;
-  if (a.epi == EPI_CE_STATS || a.epi == EPI_F32_COLMAX || a.epi == EPI_CE_P || a.epi == EPI_SWIGLU_FWD) return 1;   // the partial-row numbering assumes 256-row tiles of two wave rows
-  if (tile_hint) return tile_hint;
-  // the eight-wave 256x128 tile is used for the plain epilogues
-  const bool plain = a.epi == EPI_BF16 || a.epi == EPI_F32 || a.epi == EPI_F32_ATOMIC;
-  const bool can_split = a.epi == EPI_F32 && (a.beta || a.split_out_bf16) && a.split_ws;
-  const int atomic_nk = can_split ? (a.K + 63) / 64 + (a.K2 + 63) / 64 : 0;
-  return choose_tile(a.M, a.N, plain, atomic_nk, (a.K + 63) / 64 + (a.K2 + 63) / 64);
+// Tile and reduction slices of a product, the cheapest by the model above.  Cross-entropy epilogues are written for the
+// 256x256 tile (their partial rows are numbered by it), SwiGLU epilogues are not part of the 256x128 two-group tile, and only
+// plain outputs can be summed from slices.  A slice keeps at least four K tiles of a small tile, sixteen of a large one (four
+// for a skinny output, which is bound by reading the other operand).
+static Choice choose(const GemmArgs& a, int tile_hint) {
+  if (a.b_direct || a.epi == EPI_CE_STATS || a.epi == EPI_CE_DZ || a.epi == EPI_F32_COLMAX || a.epi == EPI_CE_P) return {1, 1};
+  const bool swiglu = a.epi == EPI_SWIGLU_FWD || a.epi == EPI_SWIGLU_BWD;
+  const bool may_split = a.split_ws && !a.grp_tab && a.run_flag == nullptr &&
+                         ((a.epi == EPI_BF16 && (long)((a.M + 255) / 256) * ((a.N + 127) / 128) < 256) || (a.epi == EPI_F32 && a.beta));
+  const int k_tiles = (a.K + 63) / 64 + (a.K2 + 63) / 64;
+  const bool skinny = a.N <= 64 || a.M <= 64;
+  Choice best{1, 1};
+  double best_cost = 1e300;
+  static const int order[5] = {1, 5, 3, 4, 8};
+  for (int i = 0; i < 5; ++i) {
+    const int t = tile_hint ? (tile_hint == 7 ? 1 : tile_hint) : order[i];
+    if (!tile_hint && swiglu && t == 5) continue;
+    const int min_per = (t == 1 || t == 5) && !skinny ? 16 : 4;
+    for (int sp = 1; sp <= (may_split ? 16 : 1); ++sp) {
+      if (sp > 1 && (k_tiles / sp < min_per || (size_t)sp * a.M * a.N * 4 > a.split_ws_bytes)) break;
+      const double c = tile_cost(t, sp, a.M, a.N, k_tiles, a.epi != EPI_BF16);
+      if (c < best_cost) { best_cost = c; best = {t, sp}; }
+    }
+    if (tile_hint) break;
+  }
+  return best;
 }
+
+int gemm_pick_tile(const GemmArgs& a, int tile_hint) { return choose(a, tile_hint).tile; }
 
 hipError_t gemm_launch(hipStream_t st, int layout, const GemmArgs& a_in, int tile_hint) {
   if (a_in.M <= 0 || a_in.N <= 0) return hipSuccess;
@@ -524,7 +558,12 @@ hipError_t gemm_launch(hipStream_t st, int layout, const GemmArgs& a_in, int til
   }
   // operands are addressed with 32-bit byte offsets
   if (a.bytesA == ~0u || a.bytesB == ~0u || a.bytesA2 == ~0u || a.bytesB2 == ~0u) return hipErrorInvalidValue;
-  int tile = gemm_pick_tile(a, tile_hint == 7 ? 1 : tile_hint);
+  if (a.split_out_bf16) {   // a bf16 result that may be summed from slices
+    if (a.epi != EPI_F32 || !a.split_ws || a.ldc % 4 || (size_t)a.M * a.N * 4 > a.split_ws_bytes) return hipErrorInvalidValue;
+    a.epi = EPI_BF16;
+  }
+  const Choice ch = choose(a, tile_hint);
+  int tile = ch.tile;
   if (a.grp_tab) {   // grouped: 256-row tiles as in the table, rows of A are tile rows, one operand pair
     if (ta || a.K2 || !a.grp_ntiles || a.grp_max_tiles <= 0 || (a.epi != EPI_BF16 && a.epi != EPI_F32 && a.epi != EPI_SWIGLU_FWD)) return hipErrorInvalidValue;
     tile = 1;
@@ -533,34 +572,18 @@ hipError_t gemm_launch(hipStream_t st, int layout, const GemmArgs& a_in, int til
       if (a.bytesA == ~0u || a.row_map_rows <= 0) return hipErrorInvalidValue;
     }
   }
-  // Reduction split: only for outputs that accumulate in fp32 (or skinny products merged into bf16) and only when the
-  // caller gave scratch memory for the slices' partial products, when the 256x256 tiling would leave at least half of
-  // the CUs without work and every slice still gets a long K loop.  The slices are added in a fixed order by a second
-  // kernel: results are reproducible run to run.
-  a.splits = 1;
+  // Reduction split: the slices' partial products go to scratch memory and a second kernel adds them in a fixed order, so
+  // results are reproducible run to run.
+  a.splits = ch.splits;
   a.c_slice_stride = 0;
-  if (a.split_out_bf16 && (a.epi != EPI_F32 || !a.split_ws || a.ldc % 4 || (size_t)a.M * a.N * 4 > a.split_ws_bytes)) return hipErrorInvalidValue;
-  if ((tile == 1 || tile == 5) && a.epi == EPI_F32 && (a.beta || a.split_out_bf16) && a.split_ws) {
-    const int bn = tile == 1 ? 256 : 128;
-    const long tiles = (long)((a.M + 255) / 256) * ((a.N + bn - 1) / bn);
-    const int nk = (a.K + 63) / 64 + (a.K2 + 63) / 64;
-    int sp = (int)(256 / tiles);
-    // a skinny output (few rows or few columns) is bound by reading the other operand once: short slices are fine,
-    // idle CUs are not
-    const bool skinny = a.N <= 64 || a.M <= 64;
-    const int min_slice = skinny ? 4 : 16;
-    while (sp > 1 && nk / sp < min_slice) --sp;
-    if (sp > (skinny ? 16 : 8)) sp = skinny ? 16 : 8;
-    while (sp > 1 && (size_t)sp * a.M * a.N * 4 > a.split_ws_bytes) --sp;
-    a.splits = sp;
-  }
-  if (a.split_out_bf16 && a.splits == 1) { a.epi = EPI_BF16; a.split_out_bf16 = 0; }   // nothing to merge: one direct pass
+  const bool out_bf16 = a.epi == EPI_BF16;
   void* const C_final = a.C;
   const long ldc_final = a.ldc;
   const int beta_final = a.beta;
   const bool merged = a.splits > 1;
   if (merged) {   // the slices write fp32 partials [slice][M][N]
     a.C = a.split_ws; a.ldc = a.N; a.beta = 0; a.c_slice_stride = (long)a.M * a.N;
+    a.epi = EPI_F32; a.R = nullptr;
   }
   hipError_t e;
   // Products on 256x256 tiles run the four-wave kernel that loads its operands straight into LDS (gemm_dtl.hip) when
@@ -582,9 +605,11 @@ hipError_t gemm_launch(hipStream_t st, int layout, const GemmArgs& a_in, int til
   if (e != hipSuccess || !merged) return e;
   const long quads = (long)a.M * (a.N / 4);
   const int grid = (int)((quads + 255) / 256 < 4096 ? (quads + 255) / 256 : 4096);
-  if (a.split_out_bf16)
-    RP_LAUNCH(splitk_merge_kernel<true>, dim3(grid), dim3(256), 0, st, a.split_ws, a.splits, a.c_slice_stride, C_final, ldc_final, a.M, a.N, 0);
+  if (out_bf16)
+    RP_LAUNCH(splitk_merge_kernel<true>, dim3(grid), dim3(256), 0, st, a.split_ws, a.splits, a.c_slice_stride, C_final, ldc_final, a.M, a.N, 0,
+              (const bf16*)a_in.R, a_in.ldr);
   else
-    RP_LAUNCH(splitk_merge_kernel<false>, dim3(grid), dim3(256), 0, st, a.split_ws, a.splits, a.c_slice_stride, C_final, ldc_final, a.M, a.N, beta_final);
+    RP_LAUNCH(splitk_merge_kernel<false>, dim3(grid), dim3(256), 0, st, a.split_ws, a.splits, a.c_slice_stride, C_final, ldc_final, a.M, a.N, beta_final,
+              (const bf16*)nullptr, 0L);
   return hipGetLastError();
 }

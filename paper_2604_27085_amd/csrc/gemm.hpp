@@ -66,10 +66,10 @@ struct GemmArgs {
   int b_direct;
   int splits;                  // reduction slices (grid.y), chosen by gemm_launch
   int part_row0;               // first partial row this launch writes (2 per M tile)
-  // Reduction split (EPI_F32 with beta): with a scratch buffer of at least splits * M * N floats the slices write
-  // their partial products there ([slice][M][N]) and a second kernel adds them to C in slice order, so the result does
-  // not depend on scheduling.  Without the buffer the GEMM is not split.  out_bf16: the merged sum is written to C
-  // as bf16 (overwritten, not accumulated) -- the skinny LoRA projections.
+  // Reduction split (EPI_F32 with beta, EPI_BF16): with a scratch buffer of at least splits * M * N floats the slices write
+  // their partial products there ([slice][M][N]) and a second kernel adds them to C (or writes their sum plus the residual
+  // as bf16) in slice order, so the result does not depend on scheduling.  Without the buffer the GEMM is not split.
+  // split_out_bf16: with EPI_F32, asks for the bf16 result.
   float* split_ws; size_t split_ws_bytes; int split_out_bf16;
   long c_slice_stride;         // set by gemm_launch: elements between the partial outputs of consecutive slices
 };
@@ -85,9 +85,11 @@ void gemm_zero_args(GemmArgs& a);
 // The 256x256 product (layout GEMM_NT, GEMM_NN or GEMM_TN) with operands loaded straight into LDS and four waves of
 // 128x128 (gemm_dtl.hip); arguments as prepared by gemm_launch (extents, slices).
 hipError_t gemm_dtl_launch(hipStream_t st, const GemmArgs& a, int layout);
-// Tile gemm_launch picks for these arguments: 1..4 = 256x256, 256x128, 128x128, 128x64 (8, 4, 2, 1 waves),
-// 5 = 256x128 with eight waves in two groups that split every K tile.  (A product on tile 1 with a long enough
-// reduction and an output that is not skinny runs gemm_dtl_launch unless tile_hint is 1; hint 7 asks for it by name.)
+// The product on small tiles with operands loaded straight into LDS (gemm_mid.hip); arguments as prepared by gemm_launch.
+hipError_t gemm_mid_launch(hipStream_t st, const GemmArgs& a, int layout, int tile);
+// Tile gemm_launch picks for these arguments: 1..4 = 256x256, 256x128, 128x128, 128x64, 5 = 256x128 with eight waves in two
+// groups that split every K tile, 8 = 64x64.  (A product on tile 1 with a long enough reduction and an output that is not
+// skinny runs gemm_dtl_launch unless tile_hint is 1; hint 7 asks for it by name.)
 int gemm_pick_tile(const GemmArgs& a, int tile_hint = 0);
 
 // Fragment order of a B operand for b_direct: blocks of 64 output columns x K tiles of 64, each 8 KB = 4 steps x 2

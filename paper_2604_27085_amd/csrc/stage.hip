@@ -188,7 +188,7 @@ struct Exec {
   void mark_gemm(int layout, const GemmArgs& g) {
     if (!ctx->tracing) return;
     static const char* lay[3] = {"NT", "NN", "TN"};
-    static const char* til[6] = {"", "256x256", "256x128", "128x128", "128x64", "256x128k2"};
+    static const char* til[9] = {"", "256x256", "256x128", "128x128", "128x64", "256x128k2", "", "", "64x64"};
     char nm[40];
     snprintf(nm, sizeof(nm), "gemm_%s_%s", til[gemm_pick_tile(g)], lay[layout]);
     const double out_b = (g.epi == EPI_BF16 || g.epi == EPI_CE_DZ || g.epi == EPI_CE_P) ? 2.0
@@ -209,19 +209,9 @@ struct Exec {
     GemmArgs g; gemm_zero_args(g);
     g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc; g.M = M; g.N = N; g.K = K; g.alpha = alpha;
     g.A2 = A2; g.lda2 = lda2; g.B2 = B2; g.ldb2 = ldb2; g.K2 = K2; g.R = R; g.ldr = ldr; g.epi = epi; g.C2 = C2; g.ldc2 = ldc2;
+    give_split_ws(g);
     mark_gemm(layout, g);
     chk(gemm_launch(st, layout, g), "gemm_bf16");
-  }
-  // C[M,N] (bf16) = alpha * A * op(B) for a skinny N (the LoRA down-projections, N = a few ranks): the product is bound by
-  // reading A once, and with so few output tiles only a reduction split puts enough workgroups on the chip.  The
-  // slices write fp32 partial products that are added in slice order and converted by the merge kernel.
-  void gemm_skinny_bf16(int layout, const void* A, long lda, const void* B, long ldb, void* C, int M, int N, int K, float alpha) {
-    GemmArgs g; gemm_zero_args(g);
-    g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = N; g.M = M; g.N = N; g.K = K; g.alpha = alpha;
-    g.epi = EPI_BF16;
-    if (has_split && (size_t)M * N * 4 <= RP_SPLITK_WS_BYTES) { g.epi = EPI_F32; g.split_out_bf16 = 1; give_split_ws(g); }
-    mark_gemm(layout, g);
-    chk(gemm_launch(st, layout, g), "gemm_skinny");
   }
   // Grouped GEMM over expert-sorted slot rows: C[slot, N] = A[row_map ? row_map[slot] : slot, K] * op(B_e), B_e the
   // matrix of the expert that owns the slot.  set = the layer's saved internals (routing plan).
@@ -309,7 +299,7 @@ void linear_fwd(Exec& X, const LayerW& W, int w_id, const FusedLora& f, size_t b
   const void* Bm = nullptr;
   if (f.n) {
     Bm = lora_b_matrix(W, f, N, bd_off);
-    X.gemm_skinny_bf16(GEMM_NT, x, K, W.t(f.a_id[0]), K, u_buf, (int)X.T, nr, K, X.ctx->cfg.lora_scale);
+    X.gemm_bf16(GEMM_NT, x, K, W.t(f.a_id[0]), K, u_buf, nr, (int)X.T, nr, K, X.ctx->cfg.lora_scale);
   }
   X.gemm_bf16(GEMM_NT, x, K, W.t(w_id), K, y, N, (int)X.T, N, K, 1.f, f.n ? u_buf : nullptr, nr, Bm, nr, f.n ? nr : 0, R, N,
               act ? EPI_SWIGLU_FWD : EPI_BF16, act, N / 2);
@@ -325,7 +315,7 @@ void linear_bwd(Exec& X, const LayerW& W, const LayerG& G, int w_id, const Fused
   const void* Bm = nullptr;
   if (f.n) {
     Bm = lora_b_matrix(W, f, N, bd_off);
-    X.gemm_skinny_bf16(GEMM_NN, dy, N, Bm, nr, ud, (int)X.T, nr, N, X.ctx->cfg.lora_scale);
+    X.gemm_bf16(GEMM_NN, dy, N, Bm, nr, ud, nr, (int)X.T, nr, N, X.ctx->cfg.lora_scale);
   }
   if (sw_gu)
     X.gemm_bf16(GEMM_NN, dy, N, W.t(w_id), K, sw_dgu, 2 * K, (int)X.T, K, N, 1.f, f.n ? ud : nullptr, nr,
@@ -674,7 +664,8 @@ rp_status rp_stage_forward(rp_ctx* ctx, int slot_id, const void* x_in, void* x_o
   Slot& sl = ctx->slots[slot_id];
   Exec X{ctx, ctx->compute, dims_of(ctx->cfg), batch, seq, (long)batch * seq, static_cast<char*>(workspace), P};
   X.fwd_only = true;
-  X.split_off = P.split_fwd; X.has_split = X.D.r > 0;
+  // (a workspace of rp_query_sizes always holds the scratch behind the forward plan, whose own size counts it with adapters only)
+  X.split_off = P.split_fwd; X.has_split = workspace_bytes_in >= P.split_fwd + RP_SPLITK_WS_BYTES;
   const int L = ctx->cfg.n_layers;
   const size_t act_bytes = (size_t)X.T * X.D.h * 2;
   RUN(X, "rope_table", 0, 4.0 * seq * X.D.d, k_rope_table(X.st, X.at<float2>(P.rope), seq, X.D.d, ctx->cfg.rope_base));
