@@ -375,7 +375,7 @@ __global__ void __launch_bounds__(256) swiglu_fwd_kernel(const bf16* __restrict_
     unpack8(r[c], g);
     unpack8(r[mc + c], u);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = g[e] / (1.f + __expf(-g[e])) * u[e];
+    for (int e = 0; e < 8; ++e) o[e] = silu_f32(g[e]) * u[e];
     reinterpret_cast<uint4*>(act + row * m)[c] = pack8(o);
   }
 }
@@ -394,7 +394,7 @@ __global__ void __launch_bounds__(256) swiglu_bwd_kernel(const bf16* __restrict_
     unpack8(reinterpret_cast<const uint4*>(dact + row * m)[c], d);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const float sg = 1.f / (1.f + __expf(-g[e]));
+      const float sg = sigmoid_f32(g[e]);
       dg[e] = d[e] * u[e] * sg * (1.f + g[e] * (1.f - sg));
       du[e] = d[e] * g[e] * sg;
     }

@@ -60,9 +60,11 @@ struct TileLoader {
     for (int it = 0; it < NREG; ++it) {
       const int row = row0 + it * RSTEP;
       if constexpr (!TR) {
-        const int gx = fold_half ? (x0 >> 1) + (row < BX / 2 ? row : fold_half + row - BX / 2) : x0 + row;
-        const long src = (row_map && gx < Xdim) ? row_map[gx] : gx;
-        voff[it] = gx < Xdim ? (uint32_t)(src * ld + ch * 8) * 2u : OOB;
+        const int gl = fold_half ? (x0 >> 1) + (row < BX / 2 ? row : row - BX / 2) : x0 + row;
+        const int gx = fold_half && row >= BX / 2 ? fold_half + gl : gl;
+        const bool in = gl < (fold_half ? fold_half : Xdim);
+        const long src = (row_map && in) ? row_map[gx] : gx;
+        voff[it] = in ? (uint32_t)(src * ld + ch * 8) * 2u : OOB;
       } else {
         const int gx = x0 + ch * 8;
         voff[it] = gx < Xdim ? (uint32_t)((long)row * ld + gx) * 2u : OOB;
@@ -538,7 +540,7 @@ hipError_t gemm_launch(hipStream_t st, int layout, const GemmArgs& a_in, int til
   if (a.N % 8 || a.K % 8 || a.lda % 8 || (!a.b_direct && a.ldb % 8)) return hipErrorInvalidValue;
   if (a.epi != EPI_CE_STATS && a.ldc % (out_f32 ? 4 : 8)) return hipErrorInvalidValue;
   if (a.R && a.ldr % 4) return hipErrorInvalidValue;
-  if (a.epi == EPI_SWIGLU_FWD && (layout != GEMM_NT || !a.C2 || a.R || a.b_direct || a.N % 256 || a.ldc2 % 8 || a.alpha != 1.f))
+  if (a.epi == EPI_SWIGLU_FWD && (layout != GEMM_NT || !a.C2 || a.R || a.b_direct || a.N % 16 || a.ldc2 % 8 || a.alpha != 1.f))
     return hipErrorInvalidValue;
   if (a.epi == EPI_SWIGLU_BWD && (!a.R || a.ldr % 8 || a.ldc % 8 || a.grp_tab)) return hipErrorInvalidValue;
   const bool ta = layout == GEMM_TN, tb = layout != GEMM_NT;

@@ -28,7 +28,7 @@ enum {
   // NT, 256x256 tile, the N = 2m columns are gate | up of a SwiGLU MLP: an output tile takes 128 gate columns and the 128
   // up columns that belong to them (B rows t*128.. and m + t*128..), C [M, 2m] bf16 is written as by EPI_BF16 (no
   // residual) and C2 [M, m] bf16 = silu(gate) * up from the rounded values, as the separate SwiGLU kernel would compute
-  // it from C.  m must be a multiple of 128.
+  // it from C.  m is a multiple of 8.
   EPI_SWIGLU_FWD = 8
 };
 // exp argument beyond which EPI_CE_P saturates; a chunk whose maximum exceeds ref + CE_P_LIMIT is redone the slow way

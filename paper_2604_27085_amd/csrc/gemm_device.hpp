@@ -280,7 +280,7 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
             for (int hh = 0; hh < 2; ++hh) {
               const float d = hh ? bf16_hi(dw[e]) : bf16_lo(dw[e]), g = hh ? bf16_hi(gw[e]) : bf16_lo(gw[e]),
                           up = hh ? bf16_hi(uw[e]) : bf16_lo(uw[e]);
-              const float sg = 1.f / (1.f + __expf(-g));
+              const float sg = sigmoid_f32(g);
               dg2[hh] = d * up * sg * (1.f + g * (1.f - sg));
               du2[hh] = d * g * sg;
             }
@@ -295,10 +295,12 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
       }
     } else if (j1 - j0 == TN) {
       const int gcol = wcol0 + cc * 8;
+      // SwiGLU forward: the gate columns (waves 0, 1 of a tile row) end where the up columns begin
+      const int nlim = p.epi == EPI_SWIGLU_FWD && (wave & 3) < 2 ? p.N >> 1 : p.N;
 #pragma unroll
       for (int t = 0; t < WAVE_M / 8; ++t) {
         const int row = t * 8 + rr, grow = wrow0 + row;
-        if (grow < M && gcol < p.N)
+        if (grow < M && gcol < nlim)
           *reinterpret_cast<uint4*>(Cp + (long)grow * p.ldc + gcol) = *reinterpret_cast<const uint4*>(s16 + row * STG_LD + cc * 8);
       }
     } else {   // one half: 16 rows per pass, 4 chunks of 16 bytes per row
@@ -329,9 +331,9 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float g0 = bf16_lo(gw[e]), g1 = bf16_hi(gw[e]);
-          o[e] = pack_bf16x2(g0 / (1.f + __expf(-g0)) * bf16_lo(uw[e]), g1 / (1.f + __expf(-g1)) * bf16_hi(uw[e]));
+          o[e] = pack_bf16x2(silu_f32(g0) * bf16_lo(uw[e]), silu_f32(g1) * bf16_hi(uw[e]));
         }
-        if (grow < M) *reinterpret_cast<uint4*>(Ap + (long)grow * p.ldc2 + acol) = make_uint4(o[0], o[1], o[2], o[3]);
+        if (grow < M && acol < (p.N >> 1)) *reinterpret_cast<uint4*>(Ap + (long)grow * p.ldc2 + acol) = make_uint4(o[0], o[1], o[2], o[3]);
       }
     }
   } else if (p.epi == EPI_BF16 || p.epi == EPI_F32 || p.epi == EPI_F32_COLMAX) {

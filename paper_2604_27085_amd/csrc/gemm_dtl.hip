@@ -131,8 +131,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
     if constexpr (!TB) {
       const int r = 8 * (8 * wave + i) + (lane >> 3);
       const int ch = (lane & 7) ^ ((r >> 1) & 7);
-      const int gn = fold ? (n0 >> 1) + (r >> 7) * 64 + (r & 63) + ((r >> 6) & 1) * fold : n0 + r;
-      return gn < p.N ? (uint32_t)((long)gn * ldb + ch * 8) * 2u : OOB;
+      const int gl = fold ? (n0 >> 1) + (r >> 7) * 64 + (r & 63) : n0 + r;    // gate column, or output column
+      const int gn = fold ? gl + ((r >> 6) & 1) * fold : gl;
+      return gl < (fold ? fold : p.N) ? (uint32_t)((long)gn * ldb + ch * 8) * 2u : OOB;
     } else {
       const int kr = 2 * (8 * wave + i) + (lane >> 5);
       const int pos = lane & 31;
@@ -523,6 +524,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
     const int gcol = (n0 >> 1) + wn * 64;
     fetch(1);
     epilogue(q, Mlim, half, smem, wave, lane, wrow, gcol + fold, part_row);
+    q.N = fold;     // the last tile's gate columns end where the up columns begin
     fetch(0);
     epilogue(q, Mlim, half, smem, wave, lane, wrow, gcol, part_row);
 #pragma unroll
@@ -534,11 +536,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
           float up;
           asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(up) : "a"(acc[1][i][j][v]));
           const float g = bf16_bits_to_f32(f32_to_bf16_bits(half[i][j][v])), u = bf16_bits_to_f32(f32_to_bf16_bits(up));
-          half[i][j][v] = g / (1.f + __expf(-g)) * u;
+          half[i][j][v] = silu_f32(g) * u;
         }
     q.C = p.C2;
     q.ldc = p.ldc2;
-    q.N = fold;
     epilogue(q, Mlim, half, smem, wave, lane, wrow, gcol, part_row);
     return;
   }

@@ -161,8 +161,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG * KI)
     };
   };
   auto b_row = [&](int r) -> long {
-    const int gn = fold ? (n0 >> 1) + (r < BN / 2 ? r : fold + r - BN / 2) : n0 + r;
-    return gn < p.N ? gn : -1;
+    if (!fold) return n0 + r < p.N ? n0 + r : -1;
+    const int gl = (n0 >> 1) + (r < BN / 2 ? r : r - BN / 2);
+    return gl < fold ? (r < BN / 2 ? gl : fold + gl) : -1;
   };
   ua.offsets(va, wg, lane, p.lda, a_row(true));
   ub.offsets(vb, wg, lane, p.ldb, b_row);
@@ -349,14 +350,14 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG * KI)
       float g[8], u[8], a[8];
       take(row, col, g);
       take(row, col + BN / 2, u);
-      if (grow < Mlim) {
+      if (grow < Mlim && gcol < fold) {
         const uint4 gp = pack(g), up = pack(u);
         *reinterpret_cast<uint4*>(Cp + (long)grow * p.ldc + gcol) = gp;
         *reinterpret_cast<uint4*>(Cp + (long)grow * p.ldc + fold + gcol) = up;
         unpack(gp, g);      // the activation is that of the rounded values, as a kernel reading them back computes it
         unpack(up, u);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) a[e] = g[e] / (1.f + __expf(-g[e])) * u[e];
+        for (int e = 0; e < 8; ++e) a[e] = silu_f32(g[e]) * u[e];
         *reinterpret_cast<uint4*>(Ap + (long)grow * p.ldc2 + gcol) = pack(a);
       }
     }
@@ -403,7 +404,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG * KI)
         unpack(r1[u], up);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const float sg = 1.f / (1.f + __expf(-g[e]));
+          const float sg = sigmoid_f32(g[e]);
           dg[e] = d[e] * up[e] * sg * (1.f + g[e] * (1.f - sg));
           du[e] = d[e] * g[e] * sg;
         }

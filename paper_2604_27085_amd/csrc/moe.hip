@@ -231,7 +231,7 @@ __global__ void __launch_bounds__(256) moe_swiglu_bwd_kernel(const bf16* __restr
     unpack8(dr[c], d);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const float sg = 1.f / (1.f + __expf(-g[e]));
+      const float sg = sigmoid_f32(g[e]);
       dot += d[e] * g[e] * sg * u[e];
       const float ds = d[e] * wr;
       dg[e] = ds * u[e] * sg * (1.f + g[e] * (1.f - sg));

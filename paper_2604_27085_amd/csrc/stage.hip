@@ -369,24 +369,15 @@ void layer_forward(Exec& X, const LayerW& W, char* set, const void* x, void* z, 
     RUN(X, "moe_route", 0, 4.0 * Td * D.E + 8.0 * Tkd, k_moe_route(X.st, X.router, idx, w, T, D.E, D.topk));
     RUN(X, "moe_plan", 0, 16.0 * Tkd, k_moe_plan(X.st, idx, T, D.E, D.topk, (int*)S(b.m_cnt), (int*)S(b.m_seg), S(b.m_tab),
                                                      (int*)S(b.m_ntiles), slot_of, (int*)S(b.m_tok), (int*)S(b.m_hist)));
-    if (D.m % 128 == 0) {   // SwiGLU in the epilogue, as in the dense layer
-      X.gemm_grouped(GEMM_NT, set, S(b.n2), D.h, T, true, W.t(RP_T_WGU), D.h, (long)2 * D.m * D.h, S(b.gu), 2 * D.m, 2 * D.m, D.h, S(b.act));
-    } else {
-      X.gemm_grouped(GEMM_NT, set, S(b.n2), D.h, T, true, W.t(RP_T_WGU), D.h, (long)2 * D.m * D.h, S(b.gu), 2 * D.m, 2 * D.m, D.h);
-      RUN(X, "swiglu_fwd", 0, 6.0 * Tkd * D.m, k_swiglu_fwd(X.st, S(b.gu), S(b.act), Tk, D.m));
-    }
+    // SwiGLU in the epilogue, as in the dense layer
+    X.gemm_grouped(GEMM_NT, set, S(b.n2), D.h, T, true, W.t(RP_T_WGU), D.h, (long)2 * D.m * D.h, S(b.gu), 2 * D.m, 2 * D.m, D.h, S(b.act));
     X.gemm_grouped(GEMM_NT, set, S(b.act), D.m, (int)Tk, false, W.t(RP_T_WD), D.m, (long)D.h * D.m, f, D.h, D.h, D.m);
     RUN(X, "moe_combine", 0, 2.0 * Tkd * D.h + 4.0 * Td * D.h, k_moe_combine(X.st, f, slot_of, w, S(b.y), z, T, D.h, D.topk));
     return;
   }
-  // SwiGLU rides in the gate/up product's epilogue when the column blocks pair up (m a multiple of 128): gate | up are
-  // still stored for the backward, the activation is not read back from them by a kernel of its own
-  if (D.m % 128 == 0) {
-    linear_fwd(X, W, RP_T_WGU, fused_gu(D), X.ctx->dl.bd3, S(b.n2), D.h, S(b.gu), 2 * D.m, S(b.u3), nullptr, S(b.act));
-  } else {
-    linear_fwd(X, W, RP_T_WGU, fused_gu(D), X.ctx->dl.bd3, S(b.n2), D.h, S(b.gu), 2 * D.m, S(b.u3), nullptr);
-    RUN(X, "swiglu_fwd", 0, 6.0 * Td * D.m, k_swiglu_fwd(X.st, S(b.gu), S(b.act), T, D.m));
-  }
+  // SwiGLU rides in the gate/up product's epilogue: gate | up are still stored for the backward, the activation is not read
+  // back from them by a kernel of its own
+  linear_fwd(X, W, RP_T_WGU, fused_gu(D), X.ctx->dl.bd3, S(b.n2), D.h, S(b.gu), 2 * D.m, S(b.u3), nullptr, S(b.act));
   linear_fwd(X, W, RP_T_WD, fused_single(D.lora[6], RP_T_LA_DOWN, RP_T_LB_DOWN, D.h), 0, S(b.act), D.m, z, D.h, S(b.u4), S(b.y));
 }
 

@@ -61,10 +61,13 @@ def test_small_tiles_at_their_edges(rp, layout, tile):
         assert rel_l2(Ca.cpu().numpy(), ref + 1.0) < 1e-5, (M, N, K, K2)
 
 
-@pytest.mark.parametrize("seq,batch", [(8, 1), (36, 2), (136, 1), (264, 1)])
-def test_short_stage_with_swiglu_epilogues(rp, seq, batch):
-    """ffn a multiple of 128: the SwiGLU forward and backward ride in small-tile epilogues; adapters on all projections."""
-    c = synth.shrink(synth.CONFIGS["C1"], ffn=384, vocab=0, seq=seq, batch=batch, lora=synth.LORA_ORDER, x_from="normal")
+@pytest.mark.parametrize("seq,batch,ffn,hidden", [(8, 1, 384, 256), (36, 2, 64, 256), (136, 1, 328, 256), (264, 1, 72, 256),
+                                                  (1040, 1, 4680, 512), (520, 1, 8264, 2560)])
+def test_short_stage_with_swiglu_epilogues(rp, seq, batch, ffn, hidden):
+    """The SwiGLU forward and backward ride in the epilogues of the small tiles, and of the two 256x256 kernels in the last
+    two (reductions of 512 and 2560); gate and up columns that end inside a tile; adapters on all projections."""
+    c = synth.shrink(synth.CONFIGS["C1"], n_layers=1, hidden=hidden, ffn=ffn, vocab=0, seq=seq, batch=batch, lora=synth.LORA_ORDER,
+                     x_from="normal")
     wl = synth.make_workload(c, 4242 + seq, gains_random=True)
-    errs = pu.compare_chain(pu.oracle_chain(c, wl), pu.gpu_chain(c, wl, rp[1]), c)
+    errs = pu.compare_chain(pu.oracle_chain(c, wl, dtype=np.float32), pu.gpu_chain(c, wl, rp[1]), c)
     assert max(errs.values()) <= 2e-2
