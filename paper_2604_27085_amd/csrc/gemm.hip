@@ -407,6 +407,38 @@ __global__ void __launch_bounds__(256) splitk_merge_kernel(const float* __restri
   }
 }
 
+// The merges of a group's split products in one launch: 256 quads of columns per workgroup.
+struct MergeOne { const float* ws; void* C; const bf16* R; long stride, ldc, ldr; int splits, M, N, beta, out_bf16, first; };
+struct MergeArgs { int n; MergeOne m[GEMM_GROUP_MAX]; };
+__global__ void __launch_bounds__(256) group_merge_kernel(const MergeArgs a) {
+  int i = 0;
+  while (i + 1 < a.n && (int)blockIdx.x >= a.m[i + 1].first) ++i;
+  i = __builtin_amdgcn_readfirstlane(i);
+  const MergeOne& q = a.m[i];
+  const int n4 = q.N >> 2;
+  const long idx = (long)((int)blockIdx.x - q.first) * 256 + threadIdx.x;
+  if (idx >= (long)q.M * n4) return;
+  const long row = idx / n4;
+  const int c = (int)(idx - row * n4) * 4;
+  const float* src = q.ws + row * q.N + c;
+  float4 acc = *reinterpret_cast<const float4*>(src);
+  for (int s = 1; s < q.splits; ++s) {
+    const float4 v = *reinterpret_cast<const float4*>(src + (long)s * q.stride);
+    acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+  }
+  if (q.out_bf16) {
+    if (q.R) {
+      const uint2 r = *reinterpret_cast<const uint2*>(q.R + row * q.ldr + c);
+      acc.x += bf16_lo(r.x); acc.y += bf16_hi(r.x); acc.z += bf16_lo(r.y); acc.w += bf16_hi(r.y);
+    }
+    *reinterpret_cast<uint2*>(reinterpret_cast<bf16*>(q.C) + row * q.ldc + c) = make_uint2(pack_bf16x2(acc.x, acc.y), pack_bf16x2(acc.z, acc.w));
+  } else {
+    float4* dst = reinterpret_cast<float4*>(reinterpret_cast<float*>(q.C) + row * q.ldc + c);
+    if (q.beta) { const float4 o = *dst; acc.x += o.x; acc.y += o.y; acc.z += o.z; acc.w += o.w; }
+    *dst = acc;
+  }
+}
+
 // One 16-byte chunk of the fragment order per thread (see gemm_arranged_bytes).
 __global__ void __launch_bounds__(256) gemm_arrange_kernel(const bf16* __restrict__ B, long ldb, int N, int K, int transposed,
                                                            uint4* __restrict__ out, long chunks, int nkt) {
@@ -528,10 +560,8 @@ static Choice choose(const GemmArgs& a, int tile_hint) {
 
 int gemm_pick_tile(const GemmArgs& a, int tile_hint) { return choose(a, tile_hint).tile; }
 
-hipError_t gemm_launch(hipStream_t st, int layout, const GemmArgs& a_in, int tile_hint) {
-  if (a_in.M <= 0 || a_in.N <= 0) return hipSuccess;
-  if (layout < GEMM_NT || layout > GEMM_TN) return hipErrorInvalidValue;
-  GemmArgs a = a_in;
+// Argument checks and the derived fields (byte extents, the form of a bf16 result that may be summed from slices).
+static hipError_t prepare(int layout, GemmArgs& a) {
   // 16-byte accesses everywhere: the output width and every leading dimension must keep rows aligned
   const bool out_f32 = a.epi == EPI_F32 || a.epi == EPI_F32_ATOMIC || a.epi == EPI_F32_COLMAX;
   if (a.epi == EPI_F32_COLMAX && (a.beta || !a.part || !a.labels || !a.zlab)) return hipErrorInvalidValue;
@@ -564,6 +594,16 @@ hipError_t gemm_launch(hipStream_t st, int layout, const GemmArgs& a_in, int til
     if (a.epi != EPI_F32 || !a.split_ws || a.ldc % 4 || (size_t)a.M * a.N * 4 > a.split_ws_bytes) return hipErrorInvalidValue;
     a.epi = EPI_BF16;
   }
+  return hipSuccess;
+}
+
+hipError_t gemm_launch(hipStream_t st, int layout, const GemmArgs& a_in, int tile_hint) {
+  if (a_in.M <= 0 || a_in.N <= 0) return hipSuccess;
+  if (layout < GEMM_NT || layout > GEMM_TN) return hipErrorInvalidValue;
+  GemmArgs a = a_in;
+  const bool ta = layout == GEMM_TN;
+  hipError_t e = prepare(layout, a);
+  if (e != hipSuccess) return e;
   const Choice ch = choose(a, tile_hint);
   int tile = ch.tile;
   if (a.grp_tab) {   // grouped: 256-row tiles as in the table, rows of A are tile rows, one operand pair
@@ -587,7 +627,6 @@ hipError_t gemm_launch(hipStream_t st, int layout, const GemmArgs& a_in, int til
     a.C = a.split_ws; a.ldc = a.N; a.beta = 0; a.c_slice_stride = (long)a.M * a.N;
     a.epi = EPI_F32; a.R = nullptr;
   }
-  hipError_t e;
   // Products on 256x256 tiles run the four-wave kernel that loads its operands straight into LDS (gemm_dtl.hip) when
   // the reduction is at least 40 K tiles long -- its per-tile fixed cost (four waves doing the epilogue in two halves, a
   // deeper prologue) is higher, and at K = 2048 with a cross-entropy or SwiGLU epilogue the eight-wave kernel is 9 %
@@ -613,5 +652,64 @@ hipError_t gemm_launch(hipStream_t st, int layout, const GemmArgs& a_in, int til
   else
     RP_LAUNCH(splitk_merge_kernel<false>, dim3(grid), dim3(256), 0, st, a.split_ws, a.splits, a.c_slice_stride, C_final, ldc_final, a.M, a.N, beta_final,
               (const bf16*)nullptr, 0L);
+  return hipGetLastError();
+}
+
+// Skinny products (the adapters') and outputs of at most 128 tiles of 64x64: neither fills the chip, and a launch of its own
+// is most of what either costs.
+bool gemm_groupable(const GemmArgs& a) {
+  if (a.M <= 0 || a.N <= 0 || a.grp_tab || a.b_direct || a.run_flag) return false;
+  if (a.epi != EPI_BF16 && a.epi != EPI_F32 && a.epi != EPI_SWIGLU_BWD) return false;
+  return a.M <= 64 || a.N <= 64 || (long)((a.M + 63) / 64) * ((a.N + 63) / 64) <= 128;
+}
+
+hipError_t gemm_group_launch(hipStream_t st, int n, const int* layouts, const GemmArgs* g) {
+  if (n < 0 || n > GEMM_GROUP_MAX) return hipErrorInvalidValue;
+  GemmArgs q[GEMM_GROUP_MAX];
+  int lay[GEMM_GROUP_MAX], cnt = 0;
+  for (int i = 0; i < n; ++i)
+    if (gemm_groupable(g[i])) { q[cnt] = g[i]; lay[cnt++] = layouts[i]; }
+  for (int i = 0; i < n; ++i) {
+    if (cnt > 1 && gemm_groupable(g[i])) continue;
+    const hipError_t e = gemm_launch(st, layouts[i], g[i]);
+    if (e != hipSuccess) return e;
+  }
+  if (cnt <= 1) return hipSuccess;
+  // Slices: every workgroup gets about the same share of the group's K tiles (weighted by what a tile fetches), with some 320
+  // workgroups in all and at least six K tiles each; the partial products share the scratch.
+  double total = 0.0, weight[GEMM_GROUP_MAX];
+  for (int i = 0; i < cnt; ++i) {
+    const hipError_t e = prepare(lay[i], q[i]);
+    if (e != hipSuccess) return e;
+    const double w = ((q[i].M < 64 ? q[i].M : 64) + (q[i].N < 64 ? q[i].N : 64)) / 128.0;
+    weight[i] = w > 0.6 ? w : 0.6;
+    total += weight[i] * ((q[i].M + 63) / 64) * ((q[i].N + 63) / 64) * (double)((q[i].K + 63) / 64 + (q[i].K2 + 63) / 64);
+  }
+  const double per = total / 320.0 > 6.0 ? total / 320.0 : 6.0;
+  MergeArgs ma{};
+  size_t used = 0;
+  int merge_blocks = 0;
+  float* const ws = g[0].split_ws;
+  for (int i = 0; i < cnt; ++i) {
+    GemmArgs& a = q[i];
+    const int nk = (a.K + 63) / 64 + (a.K2 + 63) / 64;
+    const bool may = ws && a.split_ws == ws && (a.epi == EPI_BF16 || (a.epi == EPI_F32 && a.beta));
+    int sp = may ? (int)(nk * weight[i] / per + 0.999) : 1;
+    if (sp > 16) sp = 16;
+    while (sp > 1 && (nk / sp < 4 || used + (size_t)sp * a.M * a.N * 4 > a.split_ws_bytes)) --sp;
+    if (sp < 1) sp = 1;
+    a.splits = sp;
+    a.c_slice_stride = 0;
+    if (sp > 1) {
+      MergeOne& m = ma.m[ma.n++];
+      m = {ws + used / 4, a.C, (const bf16*)a.R, (long)a.M * a.N, a.ldc, a.ldr, sp, a.M, a.N, a.beta, a.epi == EPI_BF16, merge_blocks};
+      merge_blocks += (int)(((long)a.M * (a.N / 4) + 255) / 256);
+      a.C = ws + used / 4; a.ldc = a.N; a.beta = 0; a.R = nullptr; a.epi = EPI_F32; a.c_slice_stride = (long)a.M * a.N;
+      used += (size_t)sp * m.M * m.N * 4;
+    }
+  }
+  hipError_t e = gemm_multi_run(st, cnt, lay, q);
+  if (e != hipSuccess || ma.n == 0) return e;
+  RP_LAUNCH(group_merge_kernel, dim3(merge_blocks), dim3(256), 0, st, ma);
   return hipGetLastError();
 }

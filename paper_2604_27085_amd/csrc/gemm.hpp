@@ -87,6 +87,14 @@ void gemm_zero_args(GemmArgs& a);
 hipError_t gemm_dtl_launch(hipStream_t st, const GemmArgs& a, int layout);
 // The product on small tiles with operands loaded straight into LDS (gemm_mid.hip); arguments as prepared by gemm_launch.
 hipError_t gemm_mid_launch(hipStream_t st, const GemmArgs& a, int layout, int tile);
+// Several products that do not depend on each other (layouts[i], g[i]).  Those for which gemm_groupable holds share one launch
+// (and one merge launch when any of them is cut along the reduction, through the scratch of g[0].split_ws); the others are
+// launched one by one.
+#define GEMM_GROUP_MAX 8
+bool gemm_groupable(const GemmArgs& a);
+hipError_t gemm_group_launch(hipStream_t st, int n, const int* layouts, const GemmArgs* g);
+// The shared launch itself (gemm_mid.hip): arguments prepared, g[i].splits slices each.
+hipError_t gemm_multi_run(hipStream_t st, int n, const int* layouts, const GemmArgs* g);
 // Tile gemm_launch picks for these arguments: 1..4 = 256x256, 256x128, 128x128, 128x64, 5 = 256x128 with eight waves in two
 // groups that split every K tile, 8 = 64x64.  (A product on tile 1 with a long enough reduction and an output that is not
 // skinny runs gemm_dtl_launch unless tile_hint is 1; hint 7 asks for it by name.)

@@ -203,15 +203,47 @@ struct Exec {
   }
 
   // C[M,N] (bf16) = alpha * A * op(B) (+ second pair) (+ R)
-  void gemm_bf16(int layout, const void* A, long lda, const void* B, long ldb, void* C, long ldc, int M, int N, int K,
-                 float alpha = 1.f, const void* A2 = nullptr, long lda2 = 0, const void* B2 = nullptr, long ldb2 = 0,
-                 int K2 = 0, const void* R = nullptr, long ldr = 0, int epi = EPI_BF16, void* C2 = nullptr, long ldc2 = 0) {
+  GemmArgs bf16_args(const void* A, long lda, const void* B, long ldb, void* C, long ldc, int M, int N, int K, float alpha = 1.f,
+                     const void* A2 = nullptr, long lda2 = 0, const void* B2 = nullptr, long ldb2 = 0, int K2 = 0,
+                     const void* R = nullptr, long ldr = 0, int epi = EPI_BF16, void* C2 = nullptr, long ldc2 = 0) const {
     GemmArgs g; gemm_zero_args(g);
     g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc; g.M = M; g.N = N; g.K = K; g.alpha = alpha;
     g.A2 = A2; g.lda2 = lda2; g.B2 = B2; g.ldb2 = ldb2; g.K2 = K2; g.R = R; g.ldr = ldr; g.epi = epi; g.C2 = C2; g.ldc2 = ldc2;
     give_split_ws(g);
+    return g;
+  }
+  template <class... Args>
+  void gemm_bf16(int layout, Args... args) {
+    const GemmArgs g = bf16_args(args...);
     mark_gemm(layout, g);
     chk(gemm_launch(st, layout, g), "gemm_bf16");
+  }
+  // Independent products, collected and then run together (see gemm_group_launch).
+  struct Group { int n = 0; int layout[GEMM_GROUP_MAX]; GemmArgs g[GEMM_GROUP_MAX]; };
+  void add(Group& q, int layout, const GemmArgs& g) { q.layout[q.n] = layout; q.g[q.n++] = g; }
+  void run(Group& q) {
+    int small = 0;
+    for (int i = 0; i < q.n; ++i) small += gemm_groupable(q.g[i]);
+    if (small < 2 || !ctx->tracing) {
+      if (small < 2) {
+        for (int i = 0; i < q.n; ++i) { mark_gemm(q.layout[i], q.g[i]); chk(gemm_launch(st, q.layout[i], q.g[i]), "gemm"); }
+      } else {
+        chk(gemm_group_launch(st, q.n, q.layout, q.g), "gemm group");
+      }
+    } else {   // the timeline shows the shared launch as one op
+      Group s;
+      double fl = 0.0, by = 0.0;
+      for (int i = 0; i < q.n; ++i) {
+        const GemmArgs& g = q.g[i];
+        if (!gemm_groupable(g)) { mark_gemm(q.layout[i], g); chk(gemm_launch(st, q.layout[i], g), "gemm"); continue; }
+        fl += 2.0 * g.M * (double)g.N * ((double)g.K + g.K2);
+        by += 2.0 * ((double)g.M + g.N) * ((double)g.K + g.K2) + (g.epi == EPI_BF16 ? 2.0 : 8.0) * g.M * (double)g.N;
+        add(s, q.layout[i], g);
+      }
+      mark("gemm_group", fl, by);
+      chk(gemm_group_launch(st, s.n, s.layout, s.g), "gemm group");
+    }
+    q.n = 0;
   }
   // Grouped GEMM over expert-sorted slot rows: C[slot, N] = A[row_map ? row_map[slot] : slot, K] * op(B_e), B_e the
   // matrix of the expert that owns the slot.  set = the layer's saved internals (routing plan).
@@ -241,14 +273,13 @@ struct Exec {
     mark_gemm(GEMM_NT, g);
     chk(gemm_launch(st, GEMM_NT, g), "gemm_f32_nt");
   }
-  // C[M,N] (fp32) (+)= A^T * B : weight-gradient form, reduction over the rows of A and B
-  void gemm_wgrad(const void* A, long lda, const void* B, long ldb, float* C, long ldc, int M, int N, int K) {
+  // C[M,N] (fp32) += A^T * B : weight-gradient form, reduction over the rows of A and B
+  void add_wgrad(Group& q, const void* A, long lda, const void* B, long ldb, float* C, long ldc, int M, int N, int K) {
     if (!C) return;
     GemmArgs g; gemm_zero_args(g);
     g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc; g.M = M; g.N = N; g.K = K; g.beta = 1; g.epi = EPI_F32;
     give_split_ws(g);
-    mark_gemm(GEMM_TN, g);
-    chk(gemm_launch(st, GEMM_TN, g), "gemm_wgrad");
+    add(q, GEMM_TN, g);
   }
 };
 
@@ -310,27 +341,33 @@ void linear_fwd(Exec& X, const LayerW& W, int w_id, const FusedLora& f, size_t b
 // then writes d gate | d up into sw_dgu ([T, 2K]) from its epilogue.
 void linear_bwd(Exec& X, const LayerW& W, const LayerG& G, int w_id, const FusedLora& f, size_t bd_off, const void* dy,
                 int N, const void* x, int K, void* dx, const void* u_buf, const void* sw_gu = nullptr, void* sw_dgu = nullptr) {
-  const int nr = f.n * X.D.r;
+  const int nr = f.n * X.D.r, T = (int)X.T;
   void* ud = X.at<void>(X.P.ud);
-  const void* Bm = nullptr;
+  Exec::Group q;
+  // the weight gradient joins the first group when it is small enough to share a launch, else it runs behind dX
+  auto wgrad = [&](bool first) {
+    Exec::Group w;
+    X.add_wgrad(w, dy, N, x, K, G.t(w_id), K, N, K, T);
+    if (w.n && gemm_groupable(w.g[0]) == first) X.add(q, GEMM_TN, w.g[0]);
+  };
   if (f.n) {
-    Bm = lora_b_matrix(W, f, N, bd_off);
-    X.gemm_bf16(GEMM_NN, dy, N, Bm, nr, ud, nr, (int)X.T, nr, N, X.ctx->cfg.lora_scale);
-  }
-  if (sw_gu)
-    X.gemm_bf16(GEMM_NN, dy, N, W.t(w_id), K, sw_dgu, 2 * K, (int)X.T, K, N, 1.f, f.n ? ud : nullptr, nr,
-                f.n ? W.t(f.a_id[0]) : nullptr, K, f.n ? nr : 0, sw_gu, 2 * K, EPI_SWIGLU_BWD);
-  else
-    X.gemm_bf16(GEMM_NN, dy, N, W.t(w_id), K, dx, K, (int)X.T, K, N, 1.f, f.n ? ud : nullptr, nr, f.n ? W.t(f.a_id[0]) : nullptr,
-                K, f.n ? nr : 0);
-  X.gemm_wgrad(dy, N, x, K, G.t(w_id), K, N, K, (int)X.T);
-  if (f.n) {
-    // the adapted A matrices are adjacent in both blobs, so one product fills all of them
-    X.gemm_wgrad(ud, nr, x, K, G.t(f.a_id[0]), K, nr, K, (int)X.T);
+    // what needs dy and the forward's U only: dU = s dY B, dB += dY^T U per adapter
+    X.add(q, GEMM_NN, X.bf16_args(dy, N, lora_b_matrix(W, f, N, bd_off), nr, ud, nr, T, nr, N, X.ctx->cfg.lora_scale));
     for (int i = 0; i < f.n; ++i)
-      X.gemm_wgrad(reinterpret_cast<const bf16_t*>(dy) + f.row0[i], N, reinterpret_cast<const bf16_t*>(u_buf) + i * X.D.r, nr,
-                   G.t(f.b_id[i]), X.D.r, f.row1[i] - f.row0[i], X.D.r, (int)X.T);
+      X.add_wgrad(q, reinterpret_cast<const bf16_t*>(dy) + f.row0[i], N, reinterpret_cast<const bf16_t*>(u_buf) + i * X.D.r, nr,
+                  G.t(f.b_id[i]), X.D.r, f.row1[i] - f.row0[i], X.D.r, T);
+    wgrad(true);
+    X.run(q);
+  } else {
+    wgrad(true);
   }
+  const void* lora_a = f.n ? W.t(f.a_id[0]) : nullptr;
+  if (sw_gu) X.add(q, GEMM_NN, X.bf16_args(dy, N, W.t(w_id), K, sw_dgu, 2 * K, T, K, N, 1.f, f.n ? ud : nullptr, nr, lora_a, K, f.n ? nr : 0, sw_gu, 2 * K, EPI_SWIGLU_BWD));
+  else X.add(q, GEMM_NN, X.bf16_args(dy, N, W.t(w_id), K, dx, K, T, K, N, 1.f, f.n ? ud : nullptr, nr, lora_a, K, f.n ? nr : 0));
+  wgrad(false);
+  // the adapted A matrices are adjacent in both blobs, so one product fills all of them
+  if (f.n) X.add_wgrad(q, ud, nr, x, K, G.t(f.a_id[0]), K, nr, K, T);
+  X.run(q);
 }
 
 // moe_f_off: workspace offset of the per-slot expert output buffer of the plan in use (forward or backward stage).
