@@ -68,24 +68,21 @@ hipError_t k_moe_dlogits(hipStream_t st, const int* idx, const float* w, const i
 
 // Cross-entropy helpers.  part [P, T] (max, sumexp) partials -> lse[T]; then loss / coef from lse, label logits, labels.
 hipError_t k_ce_lse(hipStream_t st, const float2* part, int P, long part_ld, float* lse, int T);
-// Frozen head, one sweep over the vocabulary: per chunk, z [vc, T] fp32 -> p = exp(z - m_t) [vc, T] bf16 against the
-// per-token reference exponent m (moved, with l rescaled and alpha set, when the chunk outgrows it by more than e^8),
-// l += row sums.  pmax [nparts][T]: the chunk's per-column maxima (.x), as the logits GEMM left them, one row per 128
-// vocabulary rows; the .y halves are overwritten (per-block row sums, added to l in row order: no atomics).
-// flag (optional, device): the reference and probability kernels return at once when *flag == 0 (the partial sums
-// already there are then added to l as they are).
-hipError_t k_ce_chunk_update(hipStream_t st, const float* z, int vc, int T, float2* pmax, int nparts, int first, float* m,
-                             float* l, float* alpha, void* p, const int* flag);
-// m[t] = max over the partial rows' .x, l[t] = 0, alpha[t] = 1: the reference exponents a sweep starts from.
-hipError_t k_ce_ref_init(hipStream_t st, const float2* pmax, int nparts, int T, float* m, float* l, float* alpha);
-// *flag = 1 when some token's maximum over the chunk (pmax .x) lies more than RP_CE_P_LIMIT above its reference m.
-hipError_t k_ce_chunk_check(hipStream_t st, const float2* pmax, int nparts, int T, const float* m, int* flag);
-// acc[t, :] *= alpha[t] where alpha[t] != 1 (nothing when flag is given and *flag == 0).
-hipError_t k_ce_rescale_rows(hipStream_t st, float* acc, const float* alpha, int T, int h, const int* flag);
+// One sweep over the vocabulary.  zlab [T], acc [n] (n a multiple of 4) and flags [nflags <= 256] become zero.
+hipError_t k_ce_init(hipStream_t st, float* zlab, int T, float* acc, long n, int* flags, int nflags);
+// m[t] = max over the rows of z [rows, T] fp32, l[t] = 0, alpha[t] = 1: the reference exponents a sweep starts from.
+hipError_t k_ce_ref_init(hipStream_t st, const float* z, int rows, int T, float* m, float* l, float* alpha);
+// part [nparts][T]: what EPI_CE_P left, maxima in .x and sums of exponentials in .y.  l_out = l_in + the sums in a fixed order;
+// *flag = 1 when some token's maximum lies more than RP_CE_P_LIMIT above its reference m.
+hipError_t k_ce_chunk_stats(hipStream_t st, const float2* part, int nparts, int T, const float* m, const float* l_in, float* l_out, int* flag);
+// Nothing unless *flag: the chunk again from its fp32 logits z [vc, T].  The reference m moves where the chunk outgrows it by more
+// than e^8 (alpha = the factor), p = exp(z - m_t) [vc, T] bf16, l_out = alpha l_in + row sums (through the .y halves of pmax,
+// whose .x halves hold the column maxima, one row per 128 vocabulary rows), acc [T, h] and the probabilities stored before
+// the chunk (p_all, `rows` rows, or NULL) times alpha.
+hipError_t k_ce_chunk_redo(hipStream_t st, const float* z, int vc, int T, float2* pmax, int nparts, float* m, const float* l_in, float* l_out,
+                           float* alpha, void* p, float* acc, int h, void* p_all, long rows, const int* flag);
 hipError_t k_ce_lse_from_ref(hipStream_t st, const float* m, const float* l, float* lse, int T);
 // One sweep with a trainable head (the probabilities of all chunks stay in memory, [V, T] bf16):
-// p[r, t] *= alpha[t] for r < rows (nothing when flag is given and *flag == 0);
-hipError_t k_ce_rescale_p(hipStream_t st, void* p, long rows, int T, const float* alpha, const int* flag);
 // p[labels[t], t] -= l[t] for tokens with coef != 0 and a label inside the vocabulary;
 hipError_t k_ce_patch_label(hipStream_t st, void* p, int T, int V, const int* labels, const float* l, const float* coef);
 // xs[t, :] = xf[t, :] * coef[t] / l[t] (bf16).

@@ -79,36 +79,82 @@ __global__ void __launch_bounds__(1024) ce_finalize_kernel(const float* __restri
 
 constexpr int CE_PROB_ROWS = 128;
 
-// Moves the reference exponent of every token if this chunk needs it and rescales l; alpha[t] is the factor acc_t must
-// be multiplied with (1 for most tokens and chunks).
-__global__ void __launch_bounds__(256) ce_chunk_ref_kernel(const float2* __restrict__ pmax, int nslab, int T, int first,
-                                                           float* __restrict__ m, float* __restrict__ l,
+// Zeroes what a sweep accumulates into: the label logits [T], acc [n], the chunks' flags.
+__global__ void __launch_bounds__(256) ce_init_kernel(float* __restrict__ zlab, int T, float4* __restrict__ acc, long n4, int* __restrict__ flags, int nflags) {
+  const long i0 = (long)blockIdx.x * 256 + threadIdx.x;
+  for (long i = i0; i < n4; i += (long)gridDim.x * 256) acc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (long i = i0; i < T; i += (long)gridDim.x * 256) zlab[i] = 0.f;
+  if (i0 < nflags) flags[i0] = 0;
+}
+
+// Sixteen waves share 64 tokens (lane = token) and split the rows of a [rows][T] array; red[wave][token] is theirs to merge.
+constexpr int CE_SLICES = 16;
+
+// m[t] = max over the rows of z [rows][T], l[t] = 0, alpha[t] = 1: the reference exponents a sweep starts from.
+__global__ void __launch_bounds__(1024) ce_ref_init_kernel(const float* __restrict__ z, int rows, int T, float* __restrict__ m,
+                                                           float* __restrict__ l, float* __restrict__ alpha) {
+  __shared__ float red[CE_SLICES][64];
+  const int lane = threadIdx.x & 63, sl = threadIdx.x >> 6, t = blockIdx.x * 64 + lane;
+  float mx = -INFINITY;
+  if (t < T)
+    for (int r = sl; r < rows; r += CE_SLICES) mx = fmaxf(mx, z[(long)r * T + t]);
+  red[sl][lane] = mx;
+  __syncthreads();
+  if (sl == 0 && t < T) {
+    for (int k = 1; k < CE_SLICES; ++k) mx = fmaxf(mx, red[k][lane]);
+    m[t] = mx; l[t] = 0.f; alpha[t] = 1.f;
+  }
+}
+
+// What EPI_CE_P left per token: l_out[t] = l_in[t] + the chunk's sum (.y of the partial rows, sixteen interleaved chains merged
+// in a fixed order), and *flag = 1 when some token's maximum (.x) lies more than RP_CE_P_LIMIT above its reference exponent:
+// the chunk is then done again by the kernels behind the flag.  Bound by reading the partials once: 10 + 5.6 us in two kernels
+// before (one thread per token in the sum), 5 us, at 2040 tokens and 32768 vocabulary rows.
+__global__ void __launch_bounds__(1024) ce_chunk_stats_kernel(const float2* __restrict__ part, int nslab, int T, const float* __restrict__ m,
+                                                              const float* __restrict__ l_in, float* __restrict__ l_out, int* __restrict__ flag) {
+  __shared__ float2 red[CE_SLICES][64];
+  const int lane = threadIdx.x & 63, sl = threadIdx.x >> 6, t = blockIdx.x * 64 + lane;
+  float mx = -INFINITY, sum = 0.f;
+  if (t < T)
+    for (int i = sl; i < nslab; i += CE_SLICES) {
+      const float2 v = part[(long)i * T + t];
+      mx = fmaxf(mx, v.x);
+      sum += v.y;
+    }
+  red[sl][lane] = make_float2(mx, sum);
+  __syncthreads();
+  if (sl == 0 && t < T) {
+    for (int k = 1; k < CE_SLICES; ++k) { mx = fmaxf(mx, red[k][lane].x); sum += red[k][lane].y; }
+    l_out[t] = l_in[t] + sum;
+    if (mx > m[t] + RP_CE_P_LIMIT) *flag = 1;   // every writer stores the same value
+  }
+}
+
+// Behind the flag.  Moves the reference exponent of every token that this chunk outgrew and rescales what was summed before the
+// chunk; alpha[t] is the factor acc_t and the stored probabilities must be multiplied with (1 for most tokens).
+__global__ void __launch_bounds__(256) ce_chunk_ref_kernel(const float2* __restrict__ pmax, int nslab, int T, float* __restrict__ m,
+                                                           const float* __restrict__ l_in, float* __restrict__ l_out,
                                                            float* __restrict__ alpha, const int* __restrict__ run_flag) {
-  if (run_flag && *run_flag == 0) return;
+  if (*run_flag == 0) return;
   const int t = blockIdx.x * 256 + threadIdx.x;
   if (t >= T) return;
   float cm = -INFINITY;
   for (int i = 0; i < nslab; ++i) cm = fmaxf(cm, pmax[(long)i * T + t].x);
-  if (first) { m[t] = cm; l[t] = 0.f; alpha[t] = 1.f; return; }
   const float mo = m[t];
-  if (cm > mo + 8.f) {
-    const float a = __expf(mo - cm);
-    m[t] = cm; l[t] *= a; alpha[t] = a;
-  } else {
-    alpha[t] = 1.f;
-  }
+  const float a = cm > mo + 8.f ? __expf(mo - cm) : 1.f;
+  if (cm > mo + 8.f) m[t] = cm;
+  l_out[t] = l_in[t] * a;
+  alpha[t] = a;
 }
 
 // p[r][t] = exp(z[r][t] - m[t]) as bf16; the fp32 sum over the block's CE_PROB_ROWS rows goes to the .y half of the
 // block's row of the partial array (whose .x half holds the column maxima the logits GEMM left there, one row of
 // partials per CE_PROB_ROWS vocabulary rows): no atomics, ce_chunk_sum_kernel adds the rows in order.
-__global__ void __launch_bounds__(256) ce_chunk_prob_kernel(const float* __restrict__ z, int vc, int T,
-                                                            const float* __restrict__ m, bf16* __restrict__ p,
-                                                            float2* __restrict__ part, const int* __restrict__ run_flag) {
-  if (run_flag && *run_flag == 0) return;
-  const int t = (blockIdx.x * 256 + threadIdx.x) * 4;      // four tokens per thread: 16-byte loads, 8-byte stores
+RP_DEV void chunk_prob(int bx, int by, const float* __restrict__ z, int vc, int T, const float* __restrict__ m, bf16* __restrict__ p,
+                       float2* __restrict__ part) {
+  const int t = (bx * 256 + threadIdx.x) * 4;      // four tokens per thread: 16-byte loads, 8-byte stores
   if (t >= T) return;
-  const int r0 = blockIdx.y * CE_PROB_ROWS, r1 = min(r0 + CE_PROB_ROWS, vc);
+  const int r0 = by * CE_PROB_ROWS, r1 = min(r0 + CE_PROB_ROWS, vc);
   const float4 mm = *reinterpret_cast<const float4*>(m + t);
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   auto one = [&](const float4& zz, int r) {
@@ -125,25 +171,14 @@ __global__ void __launch_bounds__(256) ce_chunk_prob_kernel(const float* __restr
     for (int k = 0; k < 8; ++k) one(zz[k], r + k);
   }
   for (; r < r1; ++r) one(*reinterpret_cast<const float4*>(z + (long)r * T + t), r);
-  float2* const row = part + (long)blockIdx.y * T + t;
+  float2* const row = part + (long)by * T + t;
   row[0].y = s.x; row[1].y = s.y; row[2].y = s.z; row[3].y = s.w;
 }
 
-// Sets *flag when a token's maximum over the chunk (the .x halves of the partial rows) lies more than RP_CE_P_LIMIT
-// above its reference exponent: the probabilities EPI_CE_P wrote for this chunk are then replaced.
-__global__ void __launch_bounds__(256) ce_chunk_check_kernel(const float2* __restrict__ pmax, int nslab, int T,
-                                                             const float* __restrict__ m, int* __restrict__ flag) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t >= T) return;
-  const int r0 = blockIdx.y * 8, r1 = min(r0 + 8, nslab);   // eight partial rows per thread
-  const float lim = m[t] + RP_CE_P_LIMIT;
-  bool over = false;
-  for (int i = r0; i < r1; ++i) over |= pmax[(long)i * T + t].x > lim;
-  if (over) *flag = 1;   // every writer stores the same value
-}
-
 // l[t] += sum over the chunk's partial rows of part[i][t].y, in row order.
-__global__ void __launch_bounds__(256) ce_chunk_sum_kernel(const float2* __restrict__ part, int nslab, int T, float* __restrict__ l) {
+__global__ void __launch_bounds__(256) ce_chunk_sum_kernel(const float2* __restrict__ part, int nslab, int T, float* __restrict__ l,
+                                                           const int* __restrict__ run_flag) {
+  if (*run_flag == 0) return;
   const int t = blockIdx.x * 256 + threadIdx.x;
   if (t >= T) return;
   float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;   // four chains, merged in a fixed order
@@ -156,29 +191,26 @@ __global__ void __launch_bounds__(256) ce_chunk_sum_kernel(const float2* __restr
   l[t] += (s0 + s1) + (s2 + s3);
 }
 
-// acc[t, :] *= alpha[t] for the rows whose reference moved.  One wave per row.
-__global__ void __launch_bounds__(256) ce_rescale_rows_kernel(float* __restrict__ acc, const float* __restrict__ alpha, int T, int h,
-                                                              const int* __restrict__ run_flag) {
-  if (run_flag && *run_flag == 0) return;
-  const int t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (t >= T) return;
-  const float a = alpha[t];
-  if (a == 1.f) return;
-  float4* row = reinterpret_cast<float4*>(acc + (long)t * h);
-  for (int c = lane; c < h / 4; c += 64) { float4 v = row[c]; v.x *= a; v.y *= a; v.z *= a; v.w *= a; row[c] = v; }
+// acc[t, :] *= alpha[t] for the rows whose reference moved.  One wave per row, blocks bx of nb.
+RP_DEV void rescale_rows(int bx, int nb, float* __restrict__ acc, const float* __restrict__ alpha, int T, int h) {
+  const int lane = threadIdx.x & 63;
+  for (int t = bx * 4 + (threadIdx.x >> 6); t < T; t += nb * 4) {
+    const float a = alpha[t];
+    if (a == 1.f) continue;
+    float4* row = reinterpret_cast<float4*>(acc + (long)t * h);
+    for (int c = lane; c < h / 4; c += 64) { float4 v = row[c]; v.x *= a; v.y *= a; v.z *= a; v.w *= a; row[c] = v; }
+  }
 }
 
 // One sweep with a trainable head: the probabilities of every chunk stay in memory ([V, T] bf16, against the reference
 // exponent), and the weight gradient is formed afterwards as  dW = P'^T^T xs,  P'[v, t] = p[v, t] - l_t [v = y_t],
 // xs_t = (coef_t / l_t) xf_t  (= sum_t coef_t (p_tv / l_t - [v = y_t]) xf_t).
 //
-// p[r, t] *= alpha[t] for the rows r < rows stored so far, where a token's reference moved (alpha != 1).  Grid-stride.
-__global__ void __launch_bounds__(256) ce_rescale_p_kernel(bf16* __restrict__ p, long rows, int T, const float* __restrict__ alpha,
-                                                           const int* __restrict__ run_flag) {
-  if (run_flag && *run_flag == 0) return;
+// p[r, t] *= alpha[t] for the rows r < rows stored so far, where a token's reference moved (alpha != 1).  Blocks bx of nb.
+RP_DEV void rescale_p(int bx, int nb, bf16* __restrict__ p, long rows, int T, const float* __restrict__ alpha) {
   const int t8 = T >> 3;
   const long total = rows * t8;
-  for (long idx = (long)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (long)gridDim.x * 256) {
+  for (long idx = (long)bx * 256 + threadIdx.x; idx < total; idx += (long)nb * 256) {
     const int c = (int)(idx % t8);
     const float4 a0 = *reinterpret_cast<const float4*>(alpha + c * 8), a1 = *reinterpret_cast<const float4*>(alpha + c * 8 + 4);
     if (a0.x == 1.f && a0.y == 1.f && a0.z == 1.f && a0.w == 1.f && a1.x == 1.f && a1.y == 1.f && a1.z == 1.f && a1.w == 1.f) continue;
@@ -187,6 +219,19 @@ __global__ void __launch_bounds__(256) ce_rescale_p_kernel(bf16* __restrict__ p,
     *q = make_uint4(pack_bf16x2(bf16_lo(v.x) * a0.x, bf16_hi(v.x) * a0.y), pack_bf16x2(bf16_lo(v.y) * a0.z, bf16_hi(v.y) * a0.w),
                     pack_bf16x2(bf16_lo(v.z) * a1.x, bf16_hi(v.z) * a1.y), pack_bf16x2(bf16_lo(v.w) * a1.z, bf16_hi(v.w) * a1.w));
   }
+}
+
+// Behind the flag, in one launch: the chunk's probabilities from its fp32 logits, and the rescale of the rows of acc and of the
+// probabilities stored before the chunk (p_all, `rows` of them).  Blocks [0, np) probabilities, [np, np + nr) acc, then p_all.
+__global__ void __launch_bounds__(256) ce_chunk_apply_kernel(const float* __restrict__ z, int vc, int T, const float* __restrict__ m,
+                                                             bf16* p, float2* __restrict__ part, const float* __restrict__ alpha,
+                                                             float* __restrict__ acc, int h, bf16* p_all, long rows, int bx_prob, int np,
+                                                             int nr, const int* __restrict__ run_flag) {
+  if (*run_flag == 0) return;
+  const int b = (int)blockIdx.x;
+  if (b < np) chunk_prob(b % bx_prob, b / bx_prob, z, vc, T, m, p, part);
+  else if (b < np + nr) rescale_rows(b - np, nr, acc, alpha, T, h);
+  else rescale_p(b - np - nr, (int)gridDim.x - np - nr, p_all, rows, T, alpha);
 }
 
 // p[y_t, t] -= l_t for every token whose label takes part in the loss (coef != 0) and lies inside the vocabulary.  One
@@ -249,40 +294,37 @@ __global__ void __launch_bounds__(256) ce_frozen_dx_kernel(float* __restrict__ a
 
 }  // namespace
 
-hipError_t k_ce_chunk_update(hipStream_t st, const float* z, int vc, int T, float2* pmax, int nparts, int first, float* m,
-                             float* l, float* alpha, void* p, const int* flag) {
+hipError_t k_ce_init(hipStream_t st, float* zlab, int T, float* acc, long n, int* flags, int nflags) {
+  if (T == 0) return hipSuccess;
+  if (n % 4 || nflags > 256) return hipErrorInvalidValue;
+  const long blocks = (n / 4 + 255) / 256;
+  RP_LAUNCH(ce_init_kernel, dim3((unsigned)(blocks < 1 ? 1 : blocks > 4096 ? 4096 : blocks)), dim3(256), 0, st, zlab, T, reinterpret_cast<float4*>(acc),
+            n / 4, flags, nflags);
+  return hipGetLastError();
+}
+
+hipError_t k_ce_ref_init(hipStream_t st, const float* z, int rows, int T, float* m, float* l, float* alpha) {
+  if (T == 0) return hipSuccess;
+  RP_LAUNCH(ce_ref_init_kernel, dim3((T + 63) / 64), dim3(1024), 0, st, z, rows, T, m, l, alpha);
+  return hipGetLastError();
+}
+
+hipError_t k_ce_chunk_stats(hipStream_t st, const float2* part, int nparts, int T, const float* m, const float* l_in, float* l_out, int* flag) {
+  if (T == 0) return hipSuccess;
+  RP_LAUNCH(ce_chunk_stats_kernel, dim3((T + 63) / 64), dim3(1024), 0, st, part, nparts, T, m, l_in, l_out, flag);
+  return hipGetLastError();
+}
+
+hipError_t k_ce_chunk_redo(hipStream_t st, const float* z, int vc, int T, float2* pmax, int nparts, float* m, const float* l_in, float* l_out,
+                           float* alpha, void* p, float* acc, int h, void* p_all, long rows, const int* flag) {
   if (T == 0 || vc == 0) return hipSuccess;
   const int nblk = (vc + CE_PROB_ROWS - 1) / CE_PROB_ROWS;
-  if (T % 4 || nblk > nparts) return hipErrorInvalidValue;   // one partial row per CE_PROB_ROWS vocabulary rows
-  RP_LAUNCH(ce_chunk_ref_kernel, dim3((T + 255) / 256), dim3(256), 0, st, (const float2*)pmax, nparts, T, first, m, l, alpha, flag);
-  RP_LAUNCH(ce_chunk_prob_kernel, dim3((T / 4 + 255) / 256, nblk), dim3(256), 0, st, z, vc, T, (const float*)m, (bf16*)p, pmax, flag);
-  RP_LAUNCH(ce_chunk_sum_kernel, dim3((T + 255) / 256), dim3(256), 0, st, (const float2*)pmax, nblk, T, l);
-  return hipGetLastError();
-}
-
-hipError_t k_ce_ref_init(hipStream_t st, const float2* pmax, int nparts, int T, float* m, float* l, float* alpha) {
-  if (T == 0) return hipSuccess;
-  RP_LAUNCH(ce_chunk_ref_kernel, dim3((T + 255) / 256), dim3(256), 0, st, pmax, nparts, T, 1, m, l, alpha, (const int*)nullptr);
-  return hipGetLastError();
-}
-
-hipError_t k_ce_chunk_check(hipStream_t st, const float2* pmax, int nparts, int T, const float* m, int* flag) {
-  if (T == 0) return hipSuccess;
-  RP_LAUNCH(ce_chunk_check_kernel, dim3((T + 255) / 256, (nparts + 7) / 8), dim3(256), 0, st, pmax, nparts, T, m, flag);
-  return hipGetLastError();
-}
-
-hipError_t k_ce_rescale_rows(hipStream_t st, float* acc, const float* alpha, int T, int h, const int* flag) {
-  if (T == 0) return hipSuccess;
-  if (h % 4) return hipErrorInvalidValue;
-  RP_LAUNCH(ce_rescale_rows_kernel, dim3((T + 3) / 4), dim3(256), 0, st, acc, alpha, T, h, flag);
-  return hipGetLastError();
-}
-
-hipError_t k_ce_rescale_p(hipStream_t st, void* p, long rows, int T, const float* alpha, const int* flag) {
-  if (T == 0 || rows == 0) return hipSuccess;
-  if (T % 8) return hipErrorInvalidValue;
-  RP_LAUNCH(ce_rescale_p_kernel, dim3(2048), dim3(256), 0, st, (bf16*)p, rows, T, alpha, flag);
+  if (T % 8 || h % 4 || nblk > nparts) return hipErrorInvalidValue;   // one partial row per CE_PROB_ROWS vocabulary rows
+  const int bx = (T / 4 + 255) / 256, nr = (T + 3) / 4 < 256 ? (T + 3) / 4 : 256, nq = p_all && rows > 0 ? 512 : 0;
+  RP_LAUNCH(ce_chunk_ref_kernel, dim3((T + 255) / 256), dim3(256), 0, st, (const float2*)pmax, nparts, T, m, l_in, l_out, alpha, flag);
+  RP_LAUNCH(ce_chunk_apply_kernel, dim3(bx * nblk + nr + nq), dim3(256), 0, st, z, vc, T, (const float*)m, (bf16*)p, pmax, (const float*)alpha,
+            acc, h, (bf16*)p_all, rows, bx, bx * nblk, nr, flag);
+  RP_LAUNCH(ce_chunk_sum_kernel, dim3((T + 255) / 256), dim3(256), 0, st, (const float2*)pmax, nblk, T, l_out, flag);
   return hipGetLastError();
 }
 

@@ -797,7 +797,6 @@ rp_status rp_lmhead_ce_fwd_bwd(rp_ctx* ctx, int slot_id, const void* x, const in
 
   const double Td = (double)T;
   RUN(X, "rmsnorm_fwd", 0, 4.0 * Td * D.h, k_rmsnorm_fwd(X.st, x, W.t(RP_T_GF), X.at<void>(P.h_xf), X.at<float>(P.h_rstd), T, D.h, ctx->cfg.rms_eps));
-  RUN(X, "fill", 0, 4.0 * Td, k_fill_u32(X.st, X.at<void>(P.h_zlab), T, 0u));
   if (!ctx->cfg.head_two_sweeps && (!ctx->cfg.train_base || P.head_keep_p)) {
     // One sweep over the vocabulary: the softmax normaliser is only needed at the very end.  Per chunk: logits -> p =
     // exp(z - m_t) against a per-token reference exponent that moves (and rescales what has been accumulated) only when
@@ -810,25 +809,28 @@ rp_status rp_lmhead_ce_fwd_bwd(rp_ctx* ctx, int slot_id, const void* x, const in
     bf16_t* const pall = keep_p ? X.at<bf16_t>(P.h_pall) : nullptr;
     float* const zc = X.at<float>(P.h_z);
     float* const acc = X.at<float>(P.h_dxacc);
-    int* const flag = X.at<int>(P.h_flag);
-    RUN(X, "fill", 0, 4.0 * Td * D.h, k_fill_u32(X.st, acc, (long)T * D.h, 0u));
-    RUN(X, "fill", 0, 4.0, k_fill_u32(X.st, flag, 1, 0u));
+    constexpr int NFLAG = 64;                            // flags in the 256 bytes of P.h_flag: one per chunk
+    const int nchunk = (D.V + P.head_chunk - 1) / P.head_chunk;
+    RUN(X, "ce_init", 0, 4.0 * Td * D.h, k_ce_init(X.st, X.at<float>(P.h_zlab), T, acc, (long)T * D.h, X.at<int>(P.h_flag), NFLAG));
+    // a chunk reads the normalisers from one buffer and writes them to the other; the last one writes P.h_l
+    float* const lbuf[2] = {X.at<float>(P.h_l), X.at<float>(P.h_lse)};
     {
       // The reference exponents the sweep starts from: every token's largest logit over the first 256 vocabulary rows.
       // Any reference within e^60 of the row's true maximum serves (bf16 keeps its relative precision over that range),
-      // so this small product lets every chunk, the first one included, take the path without fp32 logits.
+      // so this small product lets every chunk, the first one included, take the path without fp32 logits.  It is an
+      // ordinary product on small tiles (2040 tokens, h = 5120: 113 us on eight 256x256 tiles with a column-maximum epilogue, 30 us).
       const int r0 = D.V < 256 ? D.V : 256;
-      GemmArgs g; gemm_zero_args(g);
-      g.A = Wv; g.lda = D.h; g.B = X.at<void>(P.h_xf); g.ldb = D.h; g.M = r0; g.N = T; g.K = D.h; g.epi = EPI_F32_COLMAX;
-      g.C = zc; g.ldc = T; g.labels = labels; g.zlab = X.at<float>(P.h_zlab); g.part = X.at<float2>(P.h_part); g.part_ld = T;
-      X.mark_gemm(GEMM_NT, g);
-      X.chk(gemm_launch(X.st, GEMM_NT, g), "lm head reference");
-      RUN(X, "ce_ref_init", 0, 28.0 * Td,
-          k_ce_ref_init(X.st, X.at<float2>(P.h_part), gemm_ce_stats_partials(r0), T, X.at<float>(P.h_m), X.at<float>(P.h_l), X.at<float>(P.h_alpha)));
+      X.gemm_f32_nt(Wv, D.h, X.at<void>(P.h_xf), D.h, zc, T, r0, T, D.h);
+      RUN(X, "ce_ref_init", 0, 4.0 * r0 * Td + 12.0 * Td,
+          k_ce_ref_init(X.st, zc, r0, T, X.at<float>(P.h_m), lbuf[nchunk & 1], X.at<float>(P.h_alpha)));
     }
-    for (int v0 = 0; v0 < D.V; v0 += P.head_chunk) {
+    for (int v0 = 0, ci = 0; v0 < D.V; v0 += P.head_chunk, ++ci) {
       const int vc = (D.V - v0 < P.head_chunk) ? (D.V - v0) : P.head_chunk;
       const int nparts = gemm_ce_stats_partials(vc);
+      int* const flag = X.at<int>(P.h_flag) + ci % NFLAG;
+      if (ci >= NFLAG) RUN(X, "fill", 0, 4.0, k_fill_u32(X.st, flag, 1, 0u));
+      const float* const l_in = lbuf[(nchunk - ci) & 1];
+      float* const l_out = lbuf[(nchunk - ci - 1) & 1];
       const bf16_t* Wc = Wv + (size_t)v0 * D.h;
       void* const pc = keep_p ? static_cast<void*>(pall + (size_t)v0 * T) : X.at<void>(P.h_dzt);   // this chunk's p [vc, T]
       GemmArgs g; gemm_zero_args(g);
@@ -842,18 +844,16 @@ rp_status rp_lmhead_ce_fwd_bwd(rp_ctx* ctx, int slot_id, const void* x, const in
         f.epi = EPI_CE_P; f.C = pc; f.lse = X.at<float>(P.h_m);
         X.mark_gemm(GEMM_NT, f);
         X.chk(gemm_launch(X.st, GEMM_NT, f), "lm head probabilities");
-        RUN(X, "ce_chunk_check", 0, 8.0 * nparts * Td, k_ce_chunk_check(X.st, X.at<float2>(P.h_part), nparts, T, X.at<float>(P.h_m), flag));
+        RUN(X, "ce_chunk_stats", 0, 8.0 * nparts * Td,
+            k_ce_chunk_stats(X.st, X.at<float2>(P.h_part), nparts, T, X.at<float>(P.h_m), l_in, l_out, flag));
       }
       // the slow path, behind the flag: fp32 logits, reference move with rescale of what has been accumulated, p again
       g.run_flag = flag; g.epi = EPI_F32_COLMAX; g.C = zc;
       X.mark("ce_slow_path", 0, 0);
       X.chk(gemm_launch(X.st, GEMM_NT, g), "lm head logits");
-      RUN(X, "ce_slow_path", 0, 8.0 * nparts * Td,
-          k_ce_chunk_update(X.st, zc, vc, T, X.at<float2>(P.h_part), nparts, 0, X.at<float>(P.h_m), X.at<float>(P.h_l),
-                            X.at<float>(P.h_alpha), pc, flag));
-      RUN(X, "ce_slow_path", 0, 0, k_ce_rescale_rows(X.st, acc, X.at<float>(P.h_alpha), T, D.h, flag));
-      if (keep_p && v0 > 0) RUN(X, "ce_slow_path", 0, 0, k_ce_rescale_p(X.st, pall, v0, T, X.at<float>(P.h_alpha), flag));
-      RUN(X, "fill", 0, 4.0, k_fill_u32(X.st, flag, 1, 0u));   // every reader of the flag is behind it in the stream
+      RUN(X, "ce_slow_path", 0, 0,
+          k_ce_chunk_redo(X.st, zc, vc, T, X.at<float2>(P.h_part), nparts, X.at<float>(P.h_m), l_in, l_out, X.at<float>(P.h_alpha), pc, acc,
+                          D.h, keep_p ? pall : nullptr, v0, flag));
       GemmArgs d; gemm_zero_args(d);   // acc[T, h] += p^T^T . W_c
       d.A = pc; d.lda = T; d.B = Wc; d.ldb = D.h; d.M = T; d.N = D.h; d.K = vc; d.C = acc;
       d.ldc = D.h; d.beta = 1; d.epi = EPI_F32;
@@ -885,6 +885,7 @@ rp_status rp_lmhead_ce_fwd_bwd(rp_ctx* ctx, int slot_id, const void* x, const in
                       X.at<float>(P.h_partials), T, D.h));
     return finish_call(ctx, sl, X);
   }
+  RUN(X, "fill", 0, 4.0 * Td, k_fill_u32(X.st, X.at<void>(P.h_zlab), T, 0u));
   {  // sweep 1: logits tile by tile, reduced to per-token (max, sum exp) partials; nothing of size T x V is stored
     GemmArgs g; gemm_zero_args(g);
     g.A = Wv; g.lda = D.h; g.B = X.at<void>(P.h_xf); g.ldb = D.h; g.M = D.V; g.N = T; g.K = D.h; g.epi = EPI_CE_STATS;
