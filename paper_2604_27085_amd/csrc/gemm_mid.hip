@@ -441,23 +441,31 @@ __global__ void __launch_bounds__(64 * WGM * WGN * KG * KI)
 // filling its pipeline; the adapters' products of one projection and the weight gradients of short sequences are four to seven
 // of them.  Measured (one stream): fused toy step of 128 tokens 479 -> 395 us, backward stage of 2 x 508 tokens at h = 4096
 // with seven adapters 1264 -> 1195 us, of 176 tokens at h = 5120 1080 -> 964 us, of 8192 tokens at h = 4096 8525 -> 8407 us.
-struct MultiArgs {
-  int n;
-  int layout[GEMM_GROUP_MAX], first[GEMM_GROUP_MAX], tiles[GEMM_GROUP_MAX];
-  GemmArgs g[GEMM_GROUP_MAX];
+// (the fields a product of a group has: the kernel arguments are copied at every launch)
+struct MultiOne {
+  const void *A, *B, *A2, *B2, *R;
+  void* C;
+  long lda, ldb, lda2, ldb2, ldr, ldc, c_slice_stride;
+  unsigned bytesA, bytesB, bytesA2, bytesB2;
+  int M, N, K, K2, beta, epi, splits, layout, first, tiles;
+  float alpha;
 };
-static_assert(sizeof(MultiArgs) <= 4096, "kernel arguments");
+struct MultiArgs { int n; MultiOne g[GEMM_GROUP_MAX]; };
 
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) gemm_multi_kernel(const MultiArgs a) {
   int i = 0;
-  while (i + 1 < a.n && (int)blockIdx.x >= a.first[i + 1]) ++i;
-  i = __builtin_amdgcn_readfirstlane(i);
-  const int local = (int)blockIdx.x - a.first[i], tiles = a.tiles[i];
-  const int slice = local / tiles, blk = local - slice * tiles;
-  const GemmArgs& g = a.g[i];
-  if (a.layout[i] == GEMM_NT) mid_block<1, 1, 4, 1, 2, false, false>(g, blk, slice, g.splits);
-  else if (a.layout[i] == GEMM_NN) mid_block<1, 1, 4, 1, 2, false, true>(g, blk, slice, g.splits);
-  else mid_block<1, 1, 4, 1, 2, true, true>(g, blk, slice, g.splits);
+  while (i + 1 < a.n && (int)blockIdx.x >= a.g[i + 1].first) ++i;
+  const MultiOne& q = a.g[__builtin_amdgcn_readfirstlane(i)];
+  const int local = (int)blockIdx.x - q.first;
+  const int slice = local / q.tiles, blk = local - slice * q.tiles;
+  GemmArgs g{};
+  g.A = q.A; g.B = q.B; g.A2 = q.A2; g.B2 = q.B2; g.R = q.R; g.C = q.C;
+  g.lda = q.lda; g.ldb = q.ldb; g.lda2 = q.lda2; g.ldb2 = q.ldb2; g.ldr = q.ldr; g.ldc = q.ldc; g.c_slice_stride = q.c_slice_stride;
+  g.bytesA = q.bytesA; g.bytesB = q.bytesB; g.bytesA2 = q.bytesA2; g.bytesB2 = q.bytesB2;
+  g.M = q.M; g.N = q.N; g.K = q.K; g.K2 = q.K2; g.beta = q.beta; g.epi = q.epi; g.alpha = q.alpha;
+  if (q.layout == GEMM_NT) mid_block<1, 1, 4, 1, 2, false, false>(g, blk, slice, q.splits);
+  else if (q.layout == GEMM_NN) mid_block<1, 1, 4, 1, 2, false, true>(g, blk, slice, q.splits);
+  else mid_block<1, 1, 4, 1, 2, true, true>(g, blk, slice, q.splits);
 }
 
 template <int WGM, int WGN, int KG, int KI, int NST, bool TA, bool TB>
@@ -510,11 +518,11 @@ hipError_t gemm_multi_run(hipStream_t st, int n, const int* layouts, const GemmA
   a.n = n;
   int blocks = 0;
   for (int i = 0; i < n; ++i) {
-    a.layout[i] = layouts[i];
-    a.g[i] = g[i];
-    a.first[i] = blocks;
-    a.tiles[i] = ((g[i].M + 63) / 64) * ((g[i].N + 63) / 64);
-    blocks += a.tiles[i] * g[i].splits;
+    const GemmArgs& p = g[i];
+    const int tiles = ((p.M + 63) / 64) * ((p.N + 63) / 64);
+    a.g[i] = {p.A, p.B, p.A2, p.B2, p.R, p.C, p.lda, p.ldb, p.lda2, p.ldb2, p.ldr, p.ldc, p.c_slice_stride, p.bytesA, p.bytesB, p.bytesA2,
+              p.bytesB2, p.M, p.N, p.K, p.K2, p.beta, p.epi, p.splits, layouts[i], blocks, tiles, p.alpha};
+    blocks += tiles * p.splits;
   }
   RP_LAUNCH(gemm_multi_kernel, dim3(blocks), dim3(256), SMEM, st, a);
   return hipGetLastError();

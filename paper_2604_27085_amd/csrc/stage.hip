@@ -735,7 +735,6 @@ rp_status rp_stage_backward(rp_ctx* ctx, int slot_id, int phases, const void* x_
   Exec X{ctx, ctx->compute, dims_of(ctx->cfg), batch, seq, (long)batch * seq, static_cast<char*>(workspace), P};
   X.split_off = P.split_bwd; X.has_split = true;
   const int L = ctx->cfg.n_layers;
-  const size_t act_bytes = (size_t)X.T * X.D.h * 2;
   if (do_fwd) RUN(X, "rope_table", 0, 4.0 * seq * X.D.d, k_rope_table(X.st, X.at<float2>(P.rope), seq, X.D.d, ctx->cfg.rope_base));
   auto set_of = [&](int l) { return X.ws + P.layer0 + P.layer_stride * (size_t)l; };
   if (do_fwd) {
@@ -747,12 +746,12 @@ rp_status rp_stage_backward(rp_ctx* ctx, int slot_id, int phases, const void* x_
       if (s != RP_OK) return s;
       const LayerW W{static_cast<const char*>(sl.dev) + ctx->wl.layer_bytes * (size_t)l, &ctx->wl,
                      static_cast<const char*>(sl.dev) + ctx->wl.total + ctx->dl.layer_bytes * (size_t)l};
-      void* z = set_of(l) + P.lb.z;
+      // the stage output goes straight to x_out: the backward needs the layer outputs below the last one only
+      void* z = (l == L - 1 && x_out) ? x_out : set_of(l) + P.lb.z;
       if (router_logits) X.router = router_logits + (size_t)l * X.T * X.D.E;
       layer_forward(X, W, set_of(l), x, z, P.moe_f_bwd);
       x = z;
     }
-    if (x_out) RUN(X, "copy", 0, 2.0 * act_bytes, k_copy16(X.st, x, x_out, (long)act_bytes));
   }
   // backward in reverse layer order
   const void* dz = dy;
