@@ -486,8 +486,10 @@ constexpr TileModel TILE_MODEL[9] = {{},                          // by tile num
                                      {256, 256, 0.95, 0.60, 6.0}, {256, 128, 0.60, 0.35, 4.0}, {128, 128, 0.55, 0.0, 3.5},
                                      {128, 64, 0.36, 0.0, 3.5},   {256, 128, 0.53, 0.40, 5.0}, {}, {}, {64, 64, 0.31, 0.0, 3.5}};
 
-double tile_cost(int tile, int splits, int M, int N, int k_tiles, bool out_f32) {
-  const TileModel& t = TILE_MODEL[tile];
+double tile_cost(int tile, int splits, int M, int N, int k_tiles, int epi) {
+  TileModel t = TILE_MODEL[tile];
+  // SwiGLU epilogues: what they read and write beside the product, per 256x256 tile on a full chip
+  t.epi += (epi == EPI_SWIGLU_BWD ? 18.0 : epi == EPI_SWIGLU_FWD ? 6.0 : 0.0) * (t.bm * t.bn) / 65536.0;
   const long wg = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * splits;
   const double rounds = (double)((wg + 255) / 256), fill = wg < 256 ? wg / 256.0 : 1.0;
   double tau = t.tau + t.tau_fill * fill;
@@ -497,7 +499,7 @@ double tile_cost(int tile, int splits, int M, int N, int k_tiles, bool out_f32) 
   }
   const int per = (k_tiles + splits - 1) / splits;
   double us = 3.0 + rounds * (per * tau + t.epi) + CHIP_WEIGHT * wg / 256.0 * (per * (tau + t.tau_fill * (1.0 - fill)) + t.epi);
-  if (splits > 1) us += 4.0 + (double)M * N * (8.0 * splits + (out_f32 ? 8.0 : 2.0)) / 4.0e6;
+  if (splits > 1) us += 4.0 + (double)M * N * (8.0 * splits + (epi != EPI_BF16 ? 8.0 : 2.0)) / 4.0e6;
   return us;
 }
 
@@ -543,14 +545,15 @@ static Choice choose(const GemmArgs& a, int tile_hint) {
   const bool skinny = a.N <= 64 || a.M <= 64;
   Choice best{1, 1};
   double best_cost = 1e300;
-  static const int order[5] = {1, 5, 3, 4, 8};
+  // (the eight-wave 256x128 tile of gemm_mid.hip stands in for the two-group one under a SwiGLU epilogue: 1000 x 6144 x 2048
+  // backward 57 us on 256x256, 37)
+  const int order[5] = {1, swiglu ? 2 : 5, 3, 4, 8};
   for (int i = 0; i < 5; ++i) {
     const int t = tile_hint ? (tile_hint == 7 ? 1 : tile_hint) : order[i];
-    if (!tile_hint && swiglu && t == 5) continue;
     const int min_per = (t == 1 || t == 5) && !skinny ? 16 : 4;
     for (int sp = 1; sp <= (may_split ? 16 : 1); ++sp) {
       if (sp > 1 && (k_tiles / sp < min_per || (size_t)sp * a.M * a.N * 4 > a.split_ws_bytes)) break;
-      const double c = tile_cost(t, sp, a.M, a.N, k_tiles, a.epi != EPI_BF16);
+      const double c = tile_cost(t, sp, a.M, a.N, k_tiles, a.epi);
       if (c < best_cost) { best_cost = c; best = {t, sp}; }
     }
     if (tile_hint) break;
