@@ -16,13 +16,13 @@
 //   forward : workgroup = NW waves x 32*QT queries of one head, loop over 64-key tiles up to the diagonal; NW = 8 (one
 //             workgroup per CU, two sets of K/V tiles, one barrier per tile) when the grid is large enough, else 4
 //   dQ      : same decomposition; recomputes S^T and dP^T, accumulates dQ^T
-//   dK, dV  : workgroup = 128 keys against ONE query head, loops over 64-query tiles from the diagonal on and
-//             accumulates dK^T, dV^T in registers.  d = 128: eight waves, pairs of waves share 32 keys, split the
-//             accumulators over the head dimension and the score recomputation over the queries
-//             (attn_bwd_dkv_pair_kernel); d = 64: four waves x 32 keys (attn_bwd_dkv_fused_kernel).  With grouped queries
-//             every query head of a group writes an fp32 partial and a small kernel adds the group's partials in head
-//             order (no atomics, fixed order); one workgroup per query head rather than per kv head multiplies the
-//             workgroup count, which is what lets the triangular work balance over the CUs.
+//   dK, dV  : workgroup = 128 keys against one query head, or two or four of a group one after the other
+//             (heads_per_workgroup); loops over 64-query tiles from the diagonal on and accumulates dK^T, dV^T in
+//             registers.  d = 128: eight waves, pairs of waves share 32 keys, split the accumulators over the head
+//             dimension and the score recomputation over the queries (attn_bwd_dkv_pair_kernel); d = 64: four waves x 32
+//             keys (attn_bwd_dkv_fused_kernel).  A workgroup that has a whole group stores its result; else each writes an
+//             fp32 partial and a small kernel adds the group's partials in head order (no atomics, fixed order).  Several
+//             workgroups per kv head is what lets the triangular work balance over the CUs.
 // Launch orders keep an XCD (eight of them, each with its own L2) on few heads: see xcd_head() and the dK/dV kernels.
 #include "common.hpp"
 #include "kernels.hpp"
@@ -43,6 +43,7 @@ struct AttnArgs {
   int batch, seq, a, kh;
   float scale_log2e, scale;
   int fold;   // see heavy_rank()
+  int hpw;    // dK/dV kernel: query heads of one group that a workgroup takes one after the other (a divisor of a / kh)
   int kblock; // dK/dV kernel: key tiles per run of one head in an XCD's launch order (0: key-tile-major order over all heads)
 };
 
@@ -595,20 +596,19 @@ __global__ void __launch_bounds__(NW * 64, (QT == 1 && NW <= 4) ? 2 : 1) attn_bw
 // the two 32-query halves so that one half's exponentials sit in the slots of the other half's MFMAs was 12-20 % slower
 // (a wave issues in order: the dependent multiply-exp-multiply chains hold back the next MFMA).  Two sets of LDS tiles
 // at d = 128 (the next query tile stored during the updates, one barrier per tile instead of two) changed nothing.
-template <int D>
+template <int D, bool MULTI>
 __global__ void __launch_bounds__(256) attn_bwd_dkv_fused_kernel(const AttnArgs p) {
-  constexpr int LDK = D + 8, LDT = D + 32, KS = D / 16, DT = D / 32;
+  const int hpw = MULTI ? p.hpw : 1;
+  constexpr int LDK = D + 24, KS = D / 16, DT = D / 32;
   using T64 = Tile64<D, 256>;
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn_smem[];
-  bf16* const smem = reinterpret_cast<bf16*>(dyn_smem);             // 2*64*LDK + 2*64*LDT elements
+  bf16* const smem = reinterpret_cast<bf16*>(dyn_smem);             // 2*64*LDK elements; one layout for both kinds of reads, see the pair kernel
   bf16* const Qs = smem;
   bf16* const dOs = smem + 64 * LDK;
-  bf16* const Qt = smem + 2 * 64 * LDK;
-  bf16* const dOt = Qt + 64 * LDT;
 
   const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lk = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nhb = p.a * p.batch;
+  const int ah = p.a / hpw, nhb = ah * p.batch;     // workgroups per key tile
   // Workgroups of one query head stream the same Q and dO tiles, a few tiles apart (key tile j starts at query tile 2j
   // and all advance at the same pace).  Consecutive workgroups go to consecutive XCDs, so XCD x (launch positions x,
   // x + 8, ...) takes nhb/8 neighbouring heads and walks them in runs of `kblock` key tiles: its 32 resident workgroups
@@ -625,9 +625,9 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_fused_kernel(const AttnArgs 
     kvt = (int)blockIdx.x / nhb;             // key tile 0 sees every query: heaviest first, for every head
     hb = (int)blockIdx.x % nhb;
   }
-  const int hq = hb % p.a, b = hb / p.a;
+  const int hg = hb % ah, b = hb / ah;                 // heads hg * hpw ..
   const int grp = p.a / p.kh;
-  const int g = hq / grp;
+  const int g = hg * hpw / grp;
   const int kv0 = kvt * 128, kw0 = kv0 + 32 * w;
   const long tok0 = (long)b * p.seq;
   const bf16* kb = p.k + tok0 * p.ldk + g * D;
@@ -657,8 +657,8 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_fused_kernel(const AttnArgs 
 
   const bf16* qfrag = Qs + lr * LDK + 8 * lk;
   const bf16* dofrag = dOs + lr * LDK + 8 * lk;
-  const bf16* qtfrag = Qt + tr_base<LDT>(lane);
-  const bf16* dotfrag = dOt + tr_base<LDT>(lane);
+  const bf16* qtfrag = Qs + tr_base<LDK>(lane);
+  const bf16* dotfrag = dOs + tr_base<LDK>(lane);
   // The per-query terms of the softmax recomputation ride along in the products: the pad chunk of a Q row holds
   // -lse/scale split into three bf16 numbers, that of a dO row -delta, and one extra MFMA step against ones3() adds
   // them, so the score tile comes out as q.k - lse/scale and the dP tile as dO.v - delta.  (Rows of the score tile are
@@ -669,31 +669,43 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_fused_kernel(const AttnArgs 
 
   uint4 qreg[T64::NREG], doreg[T64::NREG];
   float st_reg = 0.f;
-  const rsrc_t rq = seq_rsrc(p.q + tok0 * p.ldq + hq * D, p.ldq, p.seq, D);
-  const rsrc_t rdo = seq_rsrc(p.dout + tok0 * p.lddo + hq * D, p.lddo, p.seq, D);
-  auto prefetch = [&](int it) {
-    const int q0 = (qt0 + it) * 64;
+  int pf_h = hg * hpw;                   // head and (with several) query tile that are fetched next
+  [[maybe_unused]] int pf_it = 0;
+  rsrc_t rq = seq_rsrc(p.q + tok0 * p.ldq + pf_h * D, p.ldq, p.seq, D);
+  rsrc_t rdo = seq_rsrc(p.dout + tok0 * p.lddo + pf_h * D, p.lddo, p.seq, D);
+  auto prefetch = [&](int nxt) {
+    const int q0 = (qt0 + (MULTI ? pf_it : nxt)) * 64;
     T64::load(qreg, rq, p.ldq, q0, tid);
     T64::load(doreg, rdo, p.lddo, q0, tid);
     if (tid < 128) {
       const int qi = q0 + (tid & 63);
-      const long sidx = ((long)b * p.a + hq) * p.seq + (qi < p.seq ? qi : 0);
+      const long sidx = ((long)b * p.a + pf_h) * p.seq + (qi < p.seq ? qi : 0);
       const float v = tid < 64 ? -p.lse_in[sidx] / p.scale : -p.delta[sidx];
       st_reg = qi < p.seq ? v : (tid < 64 ? -3.0e4f : 0.f);   // padded query rows get P = exp(-3e4 scale) = 0
     }
+    if constexpr (MULTI) {
+      if (++pf_it == niter) {
+        pf_it = 0;
+        ++pf_h;
+        rq = seq_rsrc(p.q + tok0 * p.ldq + pf_h * D, p.ldq, p.seq, D);      // (past the last head: never loaded from)
+        rdo = seq_rsrc(p.dout + tok0 * p.lddo + pf_h * D, p.lddo, p.seq, D);
+      }
+    }
   };
-  if (niter > 0) prefetch(0);
+  const int total = niter * hpw;       // query tiles of all the workgroup's heads
+  if (total > 0) prefetch(0);
 
-  for (int it = 0; it < niter; ++it) {
+  int it_cur = 0;                        // query tile of the current head
+  for (int ia = 0; ia < total; ++ia) {
+    const int it = MULTI ? it_cur : ia;
+    if constexpr (MULTI) it_cur = it_cur + 1 == niter ? 0 : it_cur + 1;
     __syncthreads();
     T64::template store<LDK>(qreg, Qs, tid);
-    T64::template store<LDT>(qreg, Qt, tid);
     T64::template store<LDK>(doreg, dOs, tid);
-    T64::template store<LDT>(doreg, dOt, tid);
     if (tid < 64) *reinterpret_cast<uint4*>(Qs + tid * LDK + D) = split3(st_reg);
     else if (tid < 128) *reinterpret_cast<uint4*>(dOs + (tid - 64) * LDK + D) = split3(st_reg);
     __syncthreads();
-    if (it + 1 < niter) prefetch(it + 1);
+    if (ia + 1 < total) prefetch(ia + 1);
     const int q0 = (qt0 + it) * 64;
     {   // a wave whose keys all follow this tile's queries runs it fully masked (see the forward kernel)
       const bool need_mask = (q0 < kw0 + 31) || (kw0 + 32 > p.seq);   // wave-uniform
@@ -729,7 +741,7 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_fused_kernel(const AttnArgs 
         // the first fragments of the update phase are requested now, under the exponentials
         constexpr int NU = 4 * DT;
         auto ufrag_at = [&](int n) {   // n = (g2 * DT + dt) * 2 + which
-          return read_frag_tr<LDT>((n & 1) ? qtfrag : dotfrag, 2 * t2 + n / (2 * DT), 32 * ((n >> 1) % DT));
+          return read_frag_tr<LDK>((n & 1) ? qtfrag : dotfrag, 2 * t2 + n / (2 * DT), 32 * ((n >> 1) % DT));
         };
         uint4 uring[AHEAD];
 #pragma unroll
@@ -772,14 +784,14 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_fused_kernel(const AttnArgs 
     }
   }
   __syncthreads();
-  if (grp == 1) {
-    store_acc_T<D>(dkacc, p.scale, smem + w * 32 * LDK, p.dk + tok0 * p.lddk + g * D, p.lddk, kw0, p.seq, lane);
-    store_acc_T<D>(dvacc, 1.f, smem + w * 32 * LDK, p.dv + tok0 * p.lddv + g * D, p.lddv, kw0, p.seq, lane);
+  if (grp == hpw) {
+    store_acc_T<D>(dkacc, p.scale, smem + w * 32 * (D + 8), p.dk + tok0 * p.lddk + g * D, p.lddk, kw0, p.seq, lane);
+    store_acc_T<D>(dvacc, 1.f, smem + w * 32 * (D + 8), p.dv + tok0 * p.lddv + g * D, p.lddv, kw0, p.seq, lane);
   } else {
     float* const stage = reinterpret_cast<float*>(smem) + w * 32 * (D + 4);
-    const long ldp = (long)p.a * D;
-    store_acc_T_f32<D>(dkacc, p.scale, stage, p.dk_part + tok0 * ldp + hq * D, ldp, kw0, p.seq, lane);
-    store_acc_T_f32<D>(dvacc, 1.f, stage, p.dv_part + tok0 * ldp + hq * D, ldp, kw0, p.seq, lane);
+    const long ldp = (long)ah * D;
+    store_acc_T_f32<D>(dkacc, p.scale, stage, p.dk_part + tok0 * ldp + hg * D, ldp, kw0, p.seq, lane);
+    store_acc_T_f32<D>(dvacc, 1.f, stage, p.dv_part + tok0 * ldp + hg * D, ldp, kw0, p.seq, lane);
   }
 }
 
@@ -791,8 +803,9 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_fused_kernel(const AttnArgs 
 // keys) to its partner through LDS.  Every wave then updates its half of the accumulators with its own 32 queries --
 // before the workgroup barrier that publishes the exchange -- and with the partner's 32 queries after it.  Same number of
 // MFMAs per workgroup as the one-wave-per-SIMD kernel, same LDS fragment traffic per CU, 8 KB of exchange per pair and tile.
-template <int D>
+template <int D, bool MULTI>
 __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p) {
+  const int hpw = MULTI ? p.hpw : 1;
   // One LDS layout serves both kinds of fragment reads, so that every Q and dO tile is stored once: a row stride of
   // D + 24 elements is 12 banks past a multiple of 64, which keeps the 16 rows of a plain 16-byte read phase on distinct
   // banks; the transposing 8-byte reads (32 lanes a phase: 4 rows x 64 bytes) overlap on a quarter of their banks
@@ -811,7 +824,7 @@ __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p
   const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lk = lane >> 5;
   const int w8 = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int w = w8 >> 1, h = w8 & 1;
-  const int nhb = p.a * p.batch;
+  const int ah = p.a / hpw, nhb = ah * p.batch;
   int kvt, hb;                                 // launch order: see attn_bwd_dkv_fused_kernel
   if (p.kblock) {
     const int hp = nhb >> 3, per = hp * p.kblock;
@@ -823,9 +836,9 @@ __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p
     kvt = (int)blockIdx.x / nhb;
     hb = (int)blockIdx.x % nhb;
   }
-  const int hq = hb % p.a, b = hb / p.a;
+  const int hg = hb % ah, b = hb / ah;
   const int grp = p.a / p.kh;
-  const int g = hq / grp;
+  const int g = hg * hpw / grp;
   const int kv0 = kvt * 128, kw0 = kv0 + 32 * w;
   const long tok0 = (long)b * p.seq;
   const bf16* kb = p.k + tok0 * p.ldk + g * D;
@@ -867,20 +880,31 @@ __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p
 
   uint4 qreg[T64::NREG], doreg[T64::NREG];
   float st_reg = 0.f;
-  const rsrc_t rq = seq_rsrc(p.q + tok0 * p.ldq + hq * D, p.ldq, p.seq, D);
-  const rsrc_t rdo = seq_rsrc(p.dout + tok0 * p.lddo + hq * D, p.lddo, p.seq, D);
-  auto prefetch = [&](int it) {
-    const int q0 = (qt0 + it) * 64;
+  int pf_h = hg * hpw;                   // head and (with several) query tile that are fetched next
+  [[maybe_unused]] int pf_it = 0;
+  rsrc_t rq = seq_rsrc(p.q + tok0 * p.ldq + pf_h * D, p.ldq, p.seq, D);
+  rsrc_t rdo = seq_rsrc(p.dout + tok0 * p.lddo + pf_h * D, p.lddo, p.seq, D);
+  auto prefetch = [&](int nxt) {
+    const int q0 = (qt0 + (MULTI ? pf_it : nxt)) * 64;
     T64::load(qreg, rq, p.ldq, q0, tid);
     T64::load(doreg, rdo, p.lddo, q0, tid);
     if (tid < 128) {
       const int qi = q0 + (tid & 63);
-      const long sidx = ((long)b * p.a + hq) * p.seq + (qi < p.seq ? qi : 0);
+      const long sidx = ((long)b * p.a + pf_h) * p.seq + (qi < p.seq ? qi : 0);
       const float v = tid < 64 ? -p.lse_in[sidx] / p.scale : -p.delta[sidx];
       st_reg = qi < p.seq ? v : (tid < 64 ? -3.0e4f : 0.f);
     }
+    if constexpr (MULTI) {
+      if (++pf_it == niter) {
+        pf_it = 0;
+        ++pf_h;
+        rq = seq_rsrc(p.q + tok0 * p.ldq + pf_h * D, p.ldq, p.seq, D);      // (past the last head: never loaded from)
+        rdo = seq_rsrc(p.dout + tok0 * p.lddo + pf_h * D, p.lddo, p.seq, D);
+      }
+    }
   };
-  if (niter > 0) prefetch(0);
+  const int total = niter * hpw;       // query tiles of all the workgroup's heads
+  if (total > 0) prefetch(0);
 
   constexpr int AHEAD = 2;     // two waves per SIMD cover each other's LDS latency: a short ring is enough
   // the update products of one 32-query half t2 with the fragments pf (P) and df (dS): 4 * DH MFMAs
@@ -913,16 +937,19 @@ __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p
     const uint4 pdf[2] = {ex_theirs[128], ex_theirs[192]};
     update_half(it_prev & 1, h ^ 1, ppf, pdf);
   };
-  for (int it = 0; it < niter; ++it) {
+  int it_cur = 0;                        // query tile of the current head
+  for (int ia = 0; ia < total; ++ia) {
+    const int it = MULTI ? it_cur : ia;
+    if constexpr (MULTI) it_cur = it_cur + 1 == niter ? 0 : it_cur + 1;
     __syncthreads();
-    bf16* const q_set = smem + (it & 1) * TSET;
+    bf16* const q_set = smem + (ia & 1) * TSET;
     T64::template store<LDU>(qreg, q_set, tid);
     T64::template store<LDU>(doreg, q_set + 64 * LDU, tid);
     if (tid < 64) *reinterpret_cast<uint4*>(q_set + tid * LDU + D) = split3(st_reg);
     else if (tid < 128) *reinterpret_cast<uint4*>(q_set + 64 * LDU + (tid - 64) * LDU + D) = split3(st_reg);
-    if (it > 0) partner_update(it - 1);
+    if (ia > 0) partner_update(ia - 1);
     __syncthreads();
-    if (it + 1 < niter) prefetch(it + 1);
+    if (ia + 1 < total) prefetch(ia + 1);
     const int q0 = (qt0 + it) * 64;
     const int qh0 = q0 + 32 * h;                                            // first query of this wave's half
     const bool need_mask = (qh0 < kw0 + 31) || (kw0 + 32 > p.seq);          // wave-uniform
@@ -933,7 +960,7 @@ __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p
       auto sfrag_at = [&](int n) {
         const int ks = n >> 1;
         const bf16* src = ks < KS ? ((n & 1) ? dofrag : qfrag) + 16 * ks : ((n & 1) ? dox : qx);
-        return *reinterpret_cast<const uint4*>(src + (it & 1) * TSET);
+        return *reinterpret_cast<const uint4*>(src + (ia & 1) * TSET);
       };
       uint4 ring[AHEAD];
 #pragma unroll
@@ -972,24 +999,24 @@ __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p
     const uint4 dfg[2] = {pack_frag(dp, 0), pack_frag(dp, 8)};
     // the partner read last tile's fragments before the barrier above: the slots are free
     ex_mine[0] = pfg[0]; ex_mine[64] = pfg[1]; ex_mine[128] = dfg[0]; ex_mine[192] = dfg[1];
-    update_half(it & 1, h, pfg, dfg);
+    update_half(ia & 1, h, pfg, dfg);
   }
   __syncthreads();
-  if (niter > 0) partner_update(niter - 1);
+  if (total > 0) partner_update(total - 1);
   __syncthreads();
-  if (grp == 1) {
+  if (grp == hpw) {
     bf16* const stage = smem + w8 * 32 * (D / 2 + 8);
     store_acc_T<D / 2>(dkacc, p.scale, stage, p.dk + tok0 * p.lddk + g * D + h * (D / 2), p.lddk, kw0, p.seq, lane);
     store_acc_T<D / 2>(dvacc, 1.f, stage, p.dv + tok0 * p.lddv + g * D + h * (D / 2), p.lddv, kw0, p.seq, lane);
   } else {
     float* const stage = reinterpret_cast<float*>(smem) + w8 * 32 * (D / 2 + 4);
-    const long ldp = (long)p.a * D;
-    store_acc_T_f32<D / 2>(dkacc, p.scale, stage, p.dk_part + tok0 * ldp + hq * D + h * (D / 2), ldp, kw0, p.seq, lane);
-    store_acc_T_f32<D / 2>(dvacc, 1.f, stage, p.dv_part + tok0 * ldp + hq * D + h * (D / 2), ldp, kw0, p.seq, lane);
+    const long ldp = (long)ah * D;
+    store_acc_T_f32<D / 2>(dkacc, p.scale, stage, p.dk_part + tok0 * ldp + hg * D + h * (D / 2), ldp, kw0, p.seq, lane);
+    store_acc_T_f32<D / 2>(dvacc, 1.f, stage, p.dv_part + tok0 * ldp + hg * D + h * (D / 2), ldp, kw0, p.seq, lane);
   }
 }
 
-// dk[t, g, :] = sum over the query heads of group g of the fp32 partials, in head order; same for dv.
+// dk[t, g, :] = sum of the fp32 partials of group g (a of them per token, one for hpw query heads), in head order; same for dv.
 template <int D>
 __global__ void __launch_bounds__(256) attn_dkv_reduce_kernel(const float* __restrict__ dk_part, const float* __restrict__ dv_part,
                                                               bf16* __restrict__ dk, bf16* __restrict__ dv, long lddk,
@@ -1021,7 +1048,7 @@ __global__ void __launch_bounds__(256) attn_dkv_reduce_kernel(const float* __res
 constexpr int max_i(int a, int b) { return a > b ? a : b; }
 constexpr int fwd_smem_bytes(int d, int nw) { return max_i((nw >= 8 ? 2 : 1) * (64 * (d + 8) + 64 * (d + 32)), nw * 32 * (d + 8)) * 2; }
 constexpr int dq_smem_bytes(int d, int nw) { return max_i((nw >= 8 ? 2 : 1) * (64 * (d + 24) + 64 * (d + 8)), nw * 32 * (d + 8)) * 2; }
-constexpr int dkv_fused_smem_bytes(int d) { return (2 * 64 * (d + 8) + 2 * 64 * (d + 32)) * 2; }
+constexpr int dkv_fused_smem_bytes(int d) { return max_i(2 * 64 * (d + 24) * 2, 4 * 32 * (d + 4) * 4); }
 constexpr int dkv_pair_smem_bytes(int d) { return 2 * (2 * 64 * (d + 24)) * 2 + 8 * 4 * 64 * 16; }
 void fill_common(AttnArgs& p, int batch, int seq, int a, int kh, int d) {
   p.batch = batch; p.seq = seq; p.a = a; p.kh = kh;
@@ -1050,22 +1077,30 @@ hipError_t launch_fwd(hipStream_t st, const AttnArgs& p) {
   return hipGetLastError();
 }
 
-template <int D>
-hipError_t launch_dkv_fused(hipStream_t st, const AttnArgs& p, int grid) {
+template <int D, bool MULTI>
+hipError_t launch_dkv_fused_one(hipStream_t st, const AttnArgs& p, int grid) {
   static bool done = false;
-  hipError_t e = set_smem(attn_bwd_dkv_fused_kernel<D>, dkv_fused_smem_bytes(D), done);
+  hipError_t e = set_smem(attn_bwd_dkv_fused_kernel<D, MULTI>, dkv_fused_smem_bytes(D), done);
   if (e != hipSuccess) return e;
-  RP_LAUNCH((attn_bwd_dkv_fused_kernel<D>), dim3(grid), dim3(256), dkv_fused_smem_bytes(D), st, p);
+  RP_LAUNCH((attn_bwd_dkv_fused_kernel<D, MULTI>), dim3(grid), dim3(256), dkv_fused_smem_bytes(D), st, p);
   return hipGetLastError();
 }
+template <int D>
+hipError_t launch_dkv_fused(hipStream_t st, const AttnArgs& p, int grid) {
+  return p.hpw > 1 ? launch_dkv_fused_one<D, true>(st, p, grid) : launch_dkv_fused_one<D, false>(st, p, grid);
+}
 
+template <int D, bool MULTI>
+hipError_t launch_dkv_pair_one(hipStream_t st, const AttnArgs& p, int grid) {
+  static bool done = false;
+  hipError_t e = set_smem(attn_bwd_dkv_pair_kernel<D, MULTI>, dkv_pair_smem_bytes(D), done);
+  if (e != hipSuccess) return e;
+  RP_LAUNCH((attn_bwd_dkv_pair_kernel<D, MULTI>), dim3(grid), dim3(512), dkv_pair_smem_bytes(D), st, p);
+  return hipGetLastError();
+}
 template <int D>
 hipError_t launch_dkv_pair(hipStream_t st, const AttnArgs& p, int grid) {
-  static bool done = false;
-  hipError_t e = set_smem(attn_bwd_dkv_pair_kernel<D>, dkv_pair_smem_bytes(D), done);
-  if (e != hipSuccess) return e;
-  RP_LAUNCH((attn_bwd_dkv_pair_kernel<D>), dim3(grid), dim3(512), dkv_pair_smem_bytes(D), st, p);
-  return hipGetLastError();
+  return p.hpw > 1 ? launch_dkv_pair_one<D, true>(st, p, grid) : launch_dkv_pair_one<D, false>(st, p, grid);
 }
 
 template <int D, int QT, int NW>
@@ -1079,6 +1114,23 @@ hipError_t launch_dq(hipStream_t st, const AttnArgs& p) {
   pf.fold = NW <= 4 && grid > 256 && grid <= 512;
   RP_LAUNCH((attn_bwd_dq_kernel<D, QT, NW>), dim3(grid), dim3(NW * 64), dq_smem_bytes(D, NW), st, pf);
   return hipGetLastError();
+}
+
+// Query heads of a group that a dK/dV workgroup takes one after the other, summing them in its accumulators: every doubling halves
+// the fp32 partials that are written and read back (147 MB each way at 3 x 1500 tokens, 64 heads of 64) and the workgroups'
+// start and end, and doubles the longest chain (key tile 0 sees every query tile).  It pays while that chain is short against
+// the work per CU.  Measured, backward in us, one head | two | four, with chain / work per CU of the last two in brackets:
+//   d = 128: 8192 x 32 heads 1837 | 1808 (.49) | 1802 (.98);  4096 x 64: 1016 | 970 (.48) | 970 (.97);  2 x 2048 x 64:
+//            621 | 562 (.47) | 537 (.94);  4096 x 32: 529 | 516 (.97)
+//   d = 64 (two workgroups share a CU, a chain runs at half the pace): 3 x 1500 x 64: 306 | 285 (.41) | 297 (.82);
+//            8192 x 64: 1959 | - | 2018 (.49);  2048 x 64: 170 | 180 (.94)
+// Orders by runs of key tiles (from 96 tiles on, see k_attn_bwd) keep one head: 16384 x 64 at four heads is 3 % slower.
+int heads_per_workgroup(int seq, int batch, int a, int kh, int d) {
+  const long nkv = (seq + 127) / 128;
+  const double per_cu = (double)a * batch * nkv * (nkv + 1) / 256.0, most = d == 128 ? 1.0 : 0.45;
+  int hpw = 1;
+  while (nkv < 96 && hpw < 4 && (a / kh) % (2 * hpw) == 0 && 2.0 * hpw * 2.0 * nkv <= most * per_cu) hpw *= 2;
+  return hpw;
 }
 
 }  // namespace
@@ -1125,20 +1177,22 @@ hipError_t k_attn_bwd(hipStream_t st, int part, const void* q, const void* k, co
   if (d != 128 && d != 64) return hipErrorInvalidValue;
   if (a != kh && !scratch) return hipErrorInvalidValue;
   const long T = (long)batch * seq;
+  p.hpw = heads_per_workgroup(seq, batch, a, kh, d);
+  const int ah = a / p.hpw;     // partials per token
   p.dk_part = scratch;
   p.dv_part = scratch ? scratch + T * a * d : nullptr;
   hipError_t e = hipSuccess;
   if (part == 2) {   // sum of the group's partials
-    if (a == kh) return hipSuccess;
+    if (ah == kh) return hipSuccess;
     const long items = 2 * T * kh * (d / 8);
     const int grid = (int)((items + 255) / 256);
-    if (d == 128) RP_LAUNCH(attn_dkv_reduce_kernel<128>, dim3(grid), dim3(256), 0, st, p.dk_part, p.dv_part, p.dk, p.dv, lddk, lddv, T, a, kh);
-    else RP_LAUNCH(attn_dkv_reduce_kernel<64>, dim3(grid), dim3(256), 0, st, p.dk_part, p.dv_part, p.dk, p.dv, lddk, lddv, T, a, kh);
+    if (d == 128) RP_LAUNCH(attn_dkv_reduce_kernel<128>, dim3(grid), dim3(256), 0, st, p.dk_part, p.dv_part, p.dk, p.dv, lddk, lddv, T, ah, kh);
+    else RP_LAUNCH(attn_dkv_reduce_kernel<64>, dim3(grid), dim3(256), 0, st, p.dk_part, p.dv_part, p.dk, p.dv, lddk, lddv, T, ah, kh);
     return hipGetLastError();
   }
   if (part == 0) {
-    const int nkv = (seq + 127) / 128, nhb = a * batch;
-    int nk = nkv * nhb;                               // one workgroup per 128 keys and query head
+    const int nkv = (seq + 127) / 128, nhb = ah * batch;
+    int nk = nkv * nhb;                               // one workgroup per 128 keys and hpw query heads
     // XCD-aware order (see the kernel) from 96 key tiles on: 5-7 % at 16-32 k tokens; below that the re-fetches it saves
     // do not matter and the plain order balances the few rounds of workgroups better (4096 tokens: 10 % slower with it)
     if (nhb % 8 == 0 && nkv >= 96) {
