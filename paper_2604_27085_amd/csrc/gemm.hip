@@ -479,7 +479,8 @@ __global__ void __launch_bounds__(256) gemm_arrange_kernel(const bf16* __restric
 // one stream | three streams at once, against choosing by elapsed time alone: a backward stage of 928 tokens at h = 2048
 // takes 730 | 507 us at weight 1, 786 | 478 at 2; one of 4096 tokens 1959 | 1764 and 2083 | 1632 (the larger tile on half of
 // the chip); one of 2 x 508 tokens at h = 4096 1288 | 968 and 1307 | 962.  1.3 is the last value at which no call on one
-// stream loses.
+// stream loses.  What it costs: a forward stage of 1000 tokens at h = 2048 is 229 -> 180 us on one stream against the 256x128
+// tiles alone, but 127 -> 143 when three such calls really run at once.
 constexpr double CHIP_WEIGHT = 1.3;
 struct TileModel { int bm, bn; double tau, tau_fill, epi; };
 constexpr TileModel TILE_MODEL[9] = {{},                          // by tile number
