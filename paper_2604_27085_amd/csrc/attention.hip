@@ -1164,6 +1164,11 @@ hipError_t k_attn_delta(hipStream_t st, const void* o, const void* dout, float* 
   return hipGetLastError();
 }
 
+int k_attn_dkv_partials(int batch, int seq, int a, int kh, int d) {
+  const int ah = a / heads_per_workgroup(seq, batch, a, kh, d);
+  return ah == kh ? 0 : ah;
+}
+
 hipError_t k_attn_bwd(hipStream_t st, int part, const void* q, const void* k, const void* v, const void* dout,
                       const float* lse, const float* delta, void* dq, void* dk, void* dv, float* scratch, long ldq,
                       long ldk, long ldv, long lddo, long lddq, long lddk, long lddv, int batch, int seq, int a, int kh,

@@ -39,11 +39,14 @@ hipError_t k_attn_fwd(hipStream_t st, const void* q, const void* k, const void* 
 // delta[batch, a, seq] = rowsum(dO * O)
 hipError_t k_attn_delta(hipStream_t st, const void* o, const void* dout, float* delta, long ldo, long lddo, int batch,
                         int seq, int a, int d);
-// part 0: dk, dv [T, kh, d] (lddk, lddv) when a == kh, else per-query-head fp32 partials into scratch (2*T*a*d
-// floats);  part 2: sum of each group's partials into dk, dv (nothing to do when a == kh);  part 1: dq [T, a, d].
+// part 0: dk, dv [T, kh, d] (lddk, lddv) when k_attn_dkv_partials is 0, else fp32 partials into scratch (at most 2*T*a*d
+// floats);  part 2: sum of each group's partials into dk, dv (nothing to do without any);  part 1: dq [T, a, d].
 hipError_t k_attn_bwd(hipStream_t st, int part, const void* q, const void* k, const void* v, const void* dout, const float* lse,
                       const float* delta, void* dq, void* dk, void* dv, float* scratch, long ldq, long ldk, long ldv,
                       long lddo, long lddq, long lddk, long lddv, int batch, int seq, int a, int kh, int d);
+// Partials of dk (and of dv) per token that part 0 leaves for part 2: one per workgroup's share of a group, 0 when a workgroup
+// takes a whole group and part 2 launches nothing.
+int k_attn_dkv_partials(int batch, int seq, int a, int kh, int d);
 
 // Mixture-of-experts FFN, everything but the grouped GEMMs.  Entries are (token, choice) pairs, i = t*top_k + j; slots
 // are the same entries sorted by expert (stable).

@@ -477,11 +477,12 @@ void layer_backward(Exec& X, const LayerW& W, const LayerG& G, char* set, const 
   // useful FLOPs per kernel: dK/dV kernel runs S, dP, dV, dK (4 half-masked products), dQ kernel S, dP, dQ (3)
   static const int parts[3] = {0, 2, 1};
   static const char* const part_name[3] = {"attn_bwd_dkv", "attn_bwd_dq", "attn_dkv_reduce"};
+  const int n_part = k_attn_dkv_partials(X.batch, X.seq, D.a, D.kh, D.d);
   for (int i = 0; i < 3; ++i) {
     const int part = parts[i];
-    if (part == 2 && D.a == D.kh) continue;
+    if (part == 2 && n_part == 0) continue;
     const double fl = part == 0 ? 4.0 * s2qd : part == 1 ? 3.0 * s2qd : 0.0;
-    const double by = part == 2 ? Td * (8.0 * D.qd + 4.0 * D.kd) : 2.0 * Td * (3 * D.qd + 4 * D.kd);
+    const double by = part == 2 ? Td * (8.0 * n_part * D.d + 4.0 * D.kd) : 2.0 * Td * (3 * D.qd + 4 * D.kd);
     RUN(X, part_name[part], fl, by,
         k_attn_bwd(X.st, part, S(b.qr), S(b.kr), qkv + D.qd + D.kd, X.at<void>(X.P.dout), (const float*)S(b.lse),
                    X.at<float>(X.P.delta), X.at<void>(X.P.dqr), X.at<void>(X.P.dkr), dqkv + D.qd + D.kd,

@@ -1,0 +1,35 @@
+"""The per-kernel timeline of a stage call: what it records is what was launched, with the bytes that the launch moves."""
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+# (batch, seq, query heads, kv heads, head dimension) -> partials per token that the dK/dV workgroups leave (0: none)
+@pytest.mark.parametrize("batch,seq,a,kh,d,partials", [
+    (32, 300, 16, 4, 128, 0),     # a workgroup takes a whole group of four
+    (16, 300, 64, 8, 64, 32),     # two heads of eight
+    (24, 300, 64, 8, 64, 16),     # four heads of eight
+    (1, 264, 8, 2, 128, 8),       # one head
+    (1, 264, 4, 4, 128, 0),       # no groups
+])
+def test_reduction_of_dkv_partials_is_recorded_as_launched(batch, seq, a, kh, d, partials):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_27085_amd import binding as B, harness as H
+    c = synth.shrink(synth.CONFIGS["C1"], n_layers=1, hidden=256, ffn=256, n_q_heads=a, n_kv_heads=kh, head_dim=d, vocab=0, seq=seq, batch=batch)
+    r = H.StageRunner(H.cfg_from_dict(c), batch, seq)
+    r.slots[0].view(torch.bfloat16).normal_(0.0, 0.02)
+    x = torch.empty((batch * seq, 256), dtype=torch.bfloat16, device="cuda:0").normal_()
+    dy, dx = torch.empty_like(x).normal_(), torch.empty_like(x)
+    torch.cuda.synchronize()
+    r.bind()
+    B.rp_trace_start(r.ctx, 256)
+    B.rp_stage_backward(r.ctx, 0, B.PHASE_BOTH, x, dy, dx, None, r.grads, None, None, batch, seq, r.ws, r.wsbytes)
+    rec = [t for t in B.rp_trace_stop(r.ctx, 256) if t[0] == "attn_dkv_reduce"]
+    r.close()
+    # fp32 partials of dk and dv read, bf16 sums written
+    want = [batch * seq * (2 * 4.0 * partials * d + 2 * 2.0 * kh * d)] if partials else []
+    assert [t[2] for t in rec] == want
