@@ -538,9 +538,10 @@ hipError_t gemm_arrange(hipStream_t st, const void* B, long ldb, int N, int K, i
 // plain outputs can be summed from slices.  A slice keeps at least four K tiles of a small tile, sixteen of a large one (four
 // for a skinny output, which is bound by reading the other operand).
 static Choice choose(const GemmArgs& a, int tile_hint) {
+  if (a.grp_tab) return {1, 1};      // the table's entries are rows of 256-row tiles
   if (a.b_direct || a.epi == EPI_CE_STATS || a.epi == EPI_CE_DZ || a.epi == EPI_F32_COLMAX || a.epi == EPI_CE_P) return {1, 1};
   const bool swiglu = a.epi == EPI_SWIGLU_FWD || a.epi == EPI_SWIGLU_BWD;
-  const bool may_split = a.split_ws && !a.grp_tab && a.run_flag == nullptr &&
+  const bool may_split = a.split_ws && a.run_flag == nullptr &&
                          ((a.epi == EPI_BF16 && (long)((a.M + 255) / 256) * ((a.N + 127) / 128) < 256) || (a.epi == EPI_F32 && a.beta));
   const int k_tiles = (a.K + 63) / 64 + (a.K2 + 63) / 64;
   const bool skinny = a.N <= 64 || a.M <= 64;
@@ -609,10 +610,9 @@ hipError_t gemm_launch(hipStream_t st, int layout, const GemmArgs& a_in, int til
   hipError_t e = prepare(layout, a);
   if (e != hipSuccess) return e;
   const Choice ch = choose(a, tile_hint);
-  int tile = ch.tile;
+  const int tile = ch.tile;
   if (a.grp_tab) {   // grouped: 256-row tiles as in the table, rows of A are tile rows, one operand pair
     if (ta || a.K2 || !a.grp_ntiles || a.grp_max_tiles <= 0 || (a.epi != EPI_BF16 && a.epi != EPI_F32 && a.epi != EPI_SWIGLU_FWD)) return hipErrorInvalidValue;
-    tile = 1;
     if (a.row_map) {
       a.bytesA = extent_bytes(a.row_map_rows, a.K, a.lda);
       if (a.bytesA == ~0u || a.row_map_rows <= 0) return hipErrorInvalidValue;

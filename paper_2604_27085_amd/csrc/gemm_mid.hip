@@ -119,27 +119,9 @@ RP_DEV void mid_block(const GemmArgs& p, int blk, int slice, int nslices) {
   const int ki = wg / (WGM * WGN), wm = wg % (WGM * WGN) / WGN, wn = wg % WGN;
   const int lr = lane & 31, lk = lane >> 5;
 
-  int tile_n, m0, Mlim = p.M;
-  const bf16* Bbase = static_cast<const bf16*>(p.B);
-  if (p.grp_tab) {   // uniform: a table entry is up to 256 rows of one group, cut into BM-row tiles
-    constexpr int PER = 256 / BM;
-    const int tiles_n = (p.N + BN - 1) / BN, nblk = *p.grp_ntiles * tiles_n * PER;
-    if (blk >= nblk) return;
-    // the row tiles of one entry and weight column are neighbours, so that one XCD's L2 fetches the weights for both
-    const int pid = xcd_remap(blk, nblk);
-    const int rest = pid / PER;
-    tile_n = rest % tiles_n;
-    const int4 g = p.grp_tab[rest / tiles_n];
-    m0 = g.y + pid % PER * BM;
-    Mlim = g.y + g.z;
-    if (m0 >= Mlim) return;
-    Bbase += (long)g.x * p.grp_strideB;
-  } else {
-    int tile_m;
-    tile_of_block(p.M, p.N, BM, BN, tile_m, tile_n, 8, blk);
-    m0 = tile_m * BM;
-  }
-  const int n0 = tile_n * BN;
+  int tile_m, tile_n;
+  tile_of_block(p.M, p.N, BM, BN, tile_m, tile_n, 8, blk);
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
   const int nk1 = (p.K + BK - 1) / BK;
   const int nk_all = nk1 + (p.K2 + BK - 1) / BK;
   const int per_split = (nk_all + nslices - 1) / nslices;
@@ -152,22 +134,15 @@ RP_DEV void mid_block(const GemmArgs& p, int blk, int slice, int nslices) {
   UA ua;
   UB ub;
   uint32_t va[UA::NL], vb[UB::NL];
-  auto a_row = [&](bool first) {
-    return [&, first](int r) -> long {
-      const int gm = m0 + r;
-      if (gm >= Mlim) return -1;
-      if constexpr (!TA) { if (first && p.row_map) return p.row_map[gm]; }
-      return gm;
-    };
-  };
+  auto a_row = [&](int r) -> long { return m0 + r < p.M ? m0 + r : -1; };
   auto b_row = [&](int r) -> long {
     if (!fold) return n0 + r < p.N ? n0 + r : -1;
     const int gl = (n0 >> 1) + (r < BN / 2 ? r : r - BN / 2);
     return gl < fold ? (r < BN / 2 ? gl : fold + gl) : -1;
   };
-  ua.offsets(va, wg, lane, p.lda, a_row(true));
+  ua.offsets(va, wg, lane, p.lda, a_row);
   ub.offsets(vb, wg, lane, p.ldb, b_row);
-  i32x4 rsA = raw_rsrc(p.A, p.bytesA), rsB = raw_rsrc(Bbase, p.bytesB);
+  i32x4 rsA = raw_rsrc(p.A, p.bytesA), rsB = raw_rsrc(p.B, p.bytesB);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem + (uint32_t)kg * C::SUB;
 
   // the stage being loaded: reduction indices left from its K tile on (0 or less: past the end), byte offsets of the tile,
@@ -189,7 +164,7 @@ RP_DEV void mid_block(const GemmArgs& p, int blk, int slice, int nslices) {
     if (lim <= 0 && !second && kt >= nk1 && kt < kt_end) {       // uniform over the wave, once: on to the second operand pair
       asm volatile("" ::: "memory");
       second = true;
-      ua.offsets(va, wg, lane, p.lda2, a_row(false));
+      ua.offsets(va, wg, lane, p.lda2, a_row);
       ub.offsets(vb, wg, lane, p.ldb2, b_row);
       rsA = raw_rsrc(p.A2, p.bytesA2);
       rsB = raw_rsrc(p.B2, p.bytesB2);
@@ -350,7 +325,7 @@ RP_DEV void mid_block(const GemmArgs& p, int blk, int slice, int nslices) {
       float g[8], u[8], a[8];
       take(row, col, g);
       take(row, col + BN / 2, u);
-      if (grow < Mlim && gcol < fold) {
+      if (grow < p.M && gcol < fold) {
         const uint4 gp = pack(g), up = pack(u);
         *reinterpret_cast<uint4*>(Cp + (long)grow * p.ldc + gcol) = gp;
         *reinterpret_cast<uint4*>(Cp + (long)grow * p.ldc + fold + gcol) = up;
@@ -376,7 +351,7 @@ RP_DEV void mid_block(const GemmArgs& p, int blk, int slice, int nslices) {
       const int c = (t0 + u) * NTH + tid, row = c / CW, col = c % CW * 8, grow = m0 + row, gcol = n0 + col;
       r0[u] = make_uint4(0u, 0u, 0u, 0u);
       r1[u] = r0[u];
-      if (grow < Mlim && gcol < p.N) {
+      if (grow < p.M && gcol < p.N) {
         if (p.epi == EPI_SWIGLU_BWD) {
           r0[u] = *reinterpret_cast<const uint4*>(Rp + (long)grow * p.ldr + gcol);
           r1[u] = *reinterpret_cast<const uint4*>(Rp + (long)grow * p.ldr + p.N + gcol);
@@ -396,7 +371,7 @@ RP_DEV void mid_block(const GemmArgs& p, int blk, int slice, int nslices) {
       const int c = (t0 + u) * NTH + tid, row = c / CW, col = c % CW * 8, grow = m0 + row, gcol = n0 + col;
       float o[8];
       take(row, col, o);
-      if (grow >= Mlim || gcol >= p.N) continue;
+      if (grow >= p.M || gcol >= p.N) continue;
       if (p.epi == EPI_SWIGLU_BWD) {
         float d[8], g[8], up[8], dg[8], du[8];
         unpack(pack(o), d);      // the product is rounded as if it had been stored
@@ -478,8 +453,7 @@ hipError_t mid_launch_one(hipStream_t st, const GemmArgs& a) {
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  const int tiles_n = (a.N + C::BN - 1) / C::BN;
-  const int tiles = (a.grp_tab ? a.grp_max_tiles * (256 / C::BM) : (a.M + C::BM - 1) / C::BM) * tiles_n;
+  const int tiles = ((a.M + C::BM - 1) / C::BM) * ((a.N + C::BN - 1) / C::BN);
   RP_LAUNCH(kern, dim3(tiles, a.splits > 0 ? a.splits : 1), dim3(64 * C::NW), C::SMEM, st, a);
   return hipGetLastError();
 }
