@@ -71,7 +71,9 @@ hipError_t k_moe_dlogits(hipStream_t st, const int* idx, const float* w, const i
 
 // Cross-entropy helpers.  part [P, T] (max, sumexp) partials -> lse[T]; then loss / coef from lse, label logits, labels.
 hipError_t k_ce_lse(hipStream_t st, const float2* part, int P, long part_ld, float* lse, int T);
-// One sweep over the vocabulary.  zlab [T], acc [n] (n a multiple of 4) and flags [nflags <= 256] become zero.
+// One sweep over the vocabulary: a flag per chunk; a sweep of more chunks uses them again in turn, cleared by a fill.
+#define RP_CE_FLAGS 64
+// zlab [T], acc [n] (n a multiple of 4) and flags [nflags <= 256] become zero.
 hipError_t k_ce_init(hipStream_t st, float* zlab, int T, float* acc, long n, int* flags, int nflags);
 // m[t] = max over the rows of z [rows, T] fp32, l[t] = 0, alpha[t] = 1: the reference exponents a sweep starts from.
 hipError_t k_ce_ref_init(hipStream_t st, const float* z, int rows, int T, float* m, float* l, float* alpha);

@@ -4,7 +4,7 @@
 #include <stdint.h>
 #include <stdlib.h>
 #include "../../include/rp.h"
-#include "kernels.hpp"   // RP_PARTIAL_BLOCKS
+#include "kernels.hpp"   // RP_PARTIAL_BLOCKS, RP_CE_FLAGS
 #include "gemm.hpp"      // RP_SPLITK_WS_BYTES
 
 namespace rp {
@@ -210,7 +210,7 @@ inline Plan make_plan(const rp_stage_cfg& c, int batch, int seq) {
     P.h_split = take(RP_SPLITK_WS_BYTES);
     if (!c.train_base || keep_p) {
       P.h_z = take((size_t)P.head_chunk * T * 4);
-      P.h_m = take(T * 4); P.h_l = take(T * 4); P.h_alpha = take(T * 4); P.h_flag = take(4);
+      P.h_m = take(T * 4); P.h_l = take(T * 4); P.h_alpha = take(T * 4); P.h_flag = take(RP_CE_FLAGS * 4);
     }
     if (keep_p) { P.h_pall = take((size_t)D.V * T * 2); P.h_xs = take(T * D.h * 2); }
   }

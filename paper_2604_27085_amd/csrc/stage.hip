@@ -809,9 +809,8 @@ rp_status rp_lmhead_ce_fwd_bwd(rp_ctx* ctx, int slot_id, const void* x, const in
     bf16_t* const pall = keep_p ? X.at<bf16_t>(P.h_pall) : nullptr;
     float* const zc = X.at<float>(P.h_z);
     float* const acc = X.at<float>(P.h_dxacc);
-    constexpr int NFLAG = 64;                            // flags in the 256 bytes of P.h_flag: one per chunk
     const int nchunk = (D.V + P.head_chunk - 1) / P.head_chunk;
-    RUN(X, "ce_init", 0, 4.0 * Td * D.h, k_ce_init(X.st, X.at<float>(P.h_zlab), T, acc, (long)T * D.h, X.at<int>(P.h_flag), NFLAG));
+    RUN(X, "ce_init", 0, 4.0 * Td * D.h, k_ce_init(X.st, X.at<float>(P.h_zlab), T, acc, (long)T * D.h, X.at<int>(P.h_flag), RP_CE_FLAGS));
     // a chunk reads the normalisers from one buffer and writes them to the other; the last one writes P.h_l
     float* const lbuf[2] = {X.at<float>(P.h_l), X.at<float>(P.h_lse)};
     {
@@ -827,8 +826,8 @@ rp_status rp_lmhead_ce_fwd_bwd(rp_ctx* ctx, int slot_id, const void* x, const in
     for (int v0 = 0, ci = 0; v0 < D.V; v0 += P.head_chunk, ++ci) {
       const int vc = (D.V - v0 < P.head_chunk) ? (D.V - v0) : P.head_chunk;
       const int nparts = gemm_ce_stats_partials(vc);
-      int* const flag = X.at<int>(P.h_flag) + ci % NFLAG;
-      if (ci >= NFLAG) RUN(X, "fill", 0, 4.0, k_fill_u32(X.st, flag, 1, 0u));
+      int* const flag = X.at<int>(P.h_flag) + ci % RP_CE_FLAGS;
+      if (ci >= RP_CE_FLAGS) RUN(X, "fill", 0, 4.0, k_fill_u32(X.st, flag, 1, 0u));
       const float* const l_in = lbuf[(nchunk - ci) & 1];
       float* const l_out = lbuf[(nchunk - ci - 1) & 1];
       const bf16_t* Wc = Wv + (size_t)v0 * D.h;
