@@ -32,6 +32,20 @@ RP_API rp_status rp_op_gemm(void* stream, int layout, int out_f32, const void* A
                      long lda, long ldb, long ldc, float alpha, int beta, const void* A2, const void* B2, int K2, long lda2,
                      long ldb2, const void* R, long ldr, int tile, void* split_ws, size_t split_ws_bytes);
 
+/* Products that do not depend on each other, in as few launches as the layers use for them (the adapters' products of one
+ * projection, App. B.2 and C.3): those with at most 64 rows or columns, or at most 128 tiles of 64x64, share one launch on 64x64
+ * tiles -- and one merge launch when any of them is cut along the reduction, their partial products side by side in split_ws --,
+ * the others run one by one before it.  n <= 8 products; the fields of rp_gemm_desc are the arguments of rp_op_gemm (out_f32 0 or
+ * 1, tile automatic).  split_ws as there; without it, or where it is too small, fewer slices. */
+typedef struct {
+  const void *A, *B, *A2, *B2, *R;
+  void* C;
+  long lda, ldb, lda2, ldb2, ldr, ldc;
+  int layout, out_f32, M, N, K, K2, beta;
+  float alpha;
+} rp_gemm_desc;
+RP_API rp_status rp_op_gemm_group(void* stream, const rp_gemm_desc* g, int n, void* split_ws, size_t split_ws_bytes);
+
 /* The B operand of rp_op_gemm in the fragment order of the matrix instruction, for tile 6: B is [N, K] row-major
  * (transposed 0: the operand of layout 0) or [K, N] row-major (transposed 1: layout 1), bf16, row stride ldb.
  * out [dev, out_bytes]: ceil(N/64) * ceil(K/64) * 8192 bytes, columns and reduction indices past the end zero.

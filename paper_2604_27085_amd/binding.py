@@ -45,6 +45,12 @@ class TraceRecord(C.Structure):
     _fields_ = [("name", C.c_char * 40), ("flops", C.c_double), ("bytes", C.c_double), ("ms", C.c_float)]
 
 
+class GemmDesc(C.Structure):
+    _fields_ = [(n, C.c_void_p) for n in ("A", "B", "A2", "B2", "R", "C")] + \
+               [(n, C.c_long) for n in ("lda", "ldb", "lda2", "ldb2", "ldr", "ldc")] + \
+               [(n, C.c_int) for n in ("layout", "out_f32", "M", "N", "K", "K2", "beta")] + [("alpha", C.c_float)]
+
+
 class RpError(RuntimeError):
     def __init__(self, code, msg):
         super().__init__("rp status %d: %s" % (code, msg))
@@ -94,6 +100,7 @@ _SIGS = {
     "rp_trace_start": [_vp, _i],
     "rp_trace_stop": [_vp, C.POINTER(TraceRecord), _i, C.POINTER(_i)],
     "rp_op_gemm": [_vp, _i, _i, _vp, _vp, _vp, _i, _i, _i, _l, _l, _l, _f, _i, _vp, _vp, _i, _l, _l, _vp, _l, _i, _vp, _sz],
+    "rp_op_gemm_group": [_vp, C.POINTER(GemmDesc), _i, _vp, _sz],
     "rp_op_gemm_arrange": [_vp, _vp, _l, _i, _i, _i, _vp, _sz],
     "rp_op_rmsnorm_fwd": [_vp, _vp, _vp, _vp, _vp, _i, _i, _f],
     "rp_op_rmsnorm_bwd": [_vp, _vp, _i, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _i, _i],
@@ -298,6 +305,17 @@ def rp_op_gemm(stream, layout, out_f32, A, B, Cm, M, N, K, lda, ldb, ldc, alpha=
     _check(lib.rp_op_gemm(stream, layout, out_f32, _ptr(A), _ptr(B), _ptr(Cm), M, N, K, lda, ldb, ldc, alpha, beta,
                           _ptr(A2), _ptr(B2), K2, lda2, ldb2, _ptr(R), ldr, tile, _ptr(split_ws),
                           split_ws.numel() * split_ws.element_size() if split_ws is not None else 0))
+
+
+def rp_op_gemm_group(stream, products, split_ws=None):
+    """products: dicts of GemmDesc's fields (tensors or addresses; what is left out is 0, alpha 1)."""
+    arr = (GemmDesc * max(len(products), 1))()
+    for d, p in zip(arr, products):
+        d.alpha = 1.0
+        for k, v in p.items():
+            setattr(d, k, _ptr(v) if k in ("A", "B", "A2", "B2", "R", "C") else v)
+    _check(lib.rp_op_gemm_group(stream, arr, len(products), _ptr(split_ws),
+                                split_ws.numel() * split_ws.element_size() if split_ws is not None else 0))
 
 
 def rp_op_gemm_arrange(stream, Bm, ldb, N, K, transposed, out):

@@ -988,6 +988,30 @@ rp_status rp_op_gemm(void* stream, int layout, int out_f32, const void* A, const
   OP_RET(e);
 }
 
+rp_status rp_op_gemm_group(void* stream, const rp_gemm_desc* d, int n, void* split_ws, size_t split_ws_bytes) {
+  if (n < 0 || n > GEMM_GROUP_MAX || (n && !d) || (split_ws && reinterpret_cast<uintptr_t>(split_ws) % 16))
+    return fail(nullptr, RP_EINVAL, "rp_op_gemm_group: bad count / split_ws");
+  int layouts[GEMM_GROUP_MAX];
+  GemmArgs q[GEMM_GROUP_MAX];
+  for (int i = 0; i < n; ++i) {
+    const rp_gemm_desc& p = d[i];
+    if (!p.A || !p.B || !p.C || p.M < 0 || p.N < 0 || p.K < 0 || p.K % 8 || p.K2 < 0 || p.K2 % 8 || p.lda % 8 || p.ldb % 8 || p.lda2 % 8 ||
+        p.ldb2 % 8 || p.layout < 0 || p.layout > 2 || p.out_f32 < 0 || p.out_f32 > 1)
+      return fail(nullptr, RP_EINVAL, "rp_op_gemm_group: bad arguments of product %d", i);
+    if (p.layout != GEMM_NT && (p.N % 8 || (p.layout == GEMM_TN && p.M % 8)))
+      return fail(nullptr, RP_EINVAL, "rp_op_gemm_group: transposed operands need multiples of 8 (product %d)", i);
+    GemmArgs& g = q[i];
+    gemm_zero_args(g);
+    layouts[i] = p.layout;
+    g.A = p.A; g.B = p.B; g.C = p.C; g.M = p.M; g.N = p.N; g.K = p.K; g.lda = p.lda; g.ldb = p.ldb; g.ldc = p.ldc; g.alpha = p.alpha; g.beta = p.beta;
+    g.A2 = p.A2; g.B2 = p.B2; g.K2 = (p.A2 && p.B2) ? p.K2 : 0; g.lda2 = p.lda2; g.ldb2 = p.ldb2; g.R = p.R; g.ldr = p.ldr;
+    g.epi = p.out_f32 ? EPI_F32 : EPI_BF16;
+    g.split_ws = static_cast<float*>(split_ws); g.split_ws_bytes = split_ws ? split_ws_bytes : 0;
+  }
+  hipError_t e = gemm_group_launch(reinterpret_cast<hipStream_t>(stream), n, layouts, q);
+  OP_RET(e);
+}
+
 rp_status rp_op_gemm_arrange(void* stream, const void* B, long ldb, int N, int K, int transposed, void* out, size_t out_bytes) {
   if (!B || !out || N < 0 || K < 0 || K % 8 || ldb % 8 || (transposed && N % 8)) return fail(nullptr, RP_EINVAL, "rp_op_gemm_arrange: bad arguments");
   if (out_bytes < gemm_arranged_bytes(N, K)) return fail(nullptr, RP_EINVAL, "rp_op_gemm_arrange: out holds %zu bytes, %zu needed", out_bytes, gemm_arranged_bytes(N, K));

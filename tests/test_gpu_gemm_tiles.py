@@ -1,6 +1,7 @@
 """Small-tile GEMMs (operands loaded straight into LDS, waves of 64x64) at the edges of their tiles, and the stage calls whose
-products they serve.  bf16 results: one rounding of an fp32 sum, relative error 2^-9 = 2e-3, bound 4e-3; fp32 results: sums of
-at most 1300 products of bf16 values in fp32, bound 1e-5."""
+products they serve.  bf16 results: one rounding of an fp32 sum, relative error 2^-9 = 2e-3, bound 4e-3; fp32 results: a
+sum of n products in fp32 is off by at most about sqrt(n) 2^-24 of its size when the errors are independent, 7e-6 for the longest
+reduction here (12320), bound 1e-5."""
 import numpy as np
 import pytest
 
@@ -71,3 +72,113 @@ def test_short_stage_with_swiglu_epilogues(rp, seq, batch, ffn, hidden):
     wl = synth.make_workload(c, 4242 + seq, gains_random=True)
     errs = pu.compare_chain(pu.oracle_chain(c, wl, dtype=np.float32), pu.gpu_chain(c, wl, rp[1]), c)
     assert max(errs.values()) <= 2e-2
+
+
+def operand(rng, rows, cols, std=1.0):
+    """bf16 [rows, cols] on the GPU, drawn there."""
+    return torch.empty((rows, cols), dtype=torch.bfloat16, device="cuda:0").normal_(0.0, std, generator=rng)
+
+
+def product(rng, layout, M, N, K, K2):
+    """Operands of one product as the layout stores them, their leading dimensions, and the product in 64 bits."""
+    kw, ref = {}, 0.0
+    for x, y, k, sfx in ((("A", "B", K, ""), ("A2", "B2", K2, "2")) if K2 else (("A", "B", K, ""),)):
+        a, b = operand(rng, M, k), operand(rng, N, k, 0.05)
+        ref = ref + a.double() @ b.double().t().contiguous()
+        kw[x], kw["lda" + sfx] = (a.t().contiguous(), M) if layout == 2 else (a, k)
+        kw[y], kw["ldb" + sfx] = (b.t().contiguous(), N) if layout else (b, k)
+    return kw, ref
+
+
+def err(got, ref):
+    return float((got.double() - ref).norm() / ref.norm())
+
+
+# (M, N, K, K2) that the cost model cuts along the reduction, with the tile it takes: 256x256 (four waves), 256x128 by two groups,
+# 128x128 (ragged and with eight rows), 128x64, 64x64 (three)
+SPLIT_SHAPES = [(1032, 2056, 12296, 24), (1016, 1032, 8200, 24), (520, 1032, 4104, 24), (8, 2056, 4104, 16), (72, 72, 1288, 24),
+                (1032, 136, 2312, 24), (136, 56, 1288, 0), (8, 264, 4104, 8), (8, 8, 12296, 0)]
+
+
+@pytest.mark.parametrize("shape", SPLIT_SHAPES)
+@pytest.mark.parametrize("layout", [0, 1, 2])
+def test_automatic_splits_of_the_reduction(rp, layout, shape):
+    """The product really is cut (the slices' partial products, and nothing behind them, replace what the scratch held), the merge
+    takes the residual or the old value, and the sum does not depend on the run; scratch that holds one slice is left alone."""
+    B, _ = rp
+    M, N, K, K2 = shape
+    rng = torch.Generator(device="cuda:0").manual_seed(M + N + K + layout)
+    kw, ref = product(rng, layout, M, N, K, K2)
+    A, Bm, lda, ldb = (kw.pop(k) for k in ("A", "B", "lda", "ldb"))
+    if K2:
+        kw["K2"] = K2
+    R = operand(rng, M, N)
+    for f32, want, bound in ((0, -0.5 * ref + R.double(), 4e-3), (1, 0.5 * ref + 2.0, 1e-5)):
+        outs = []
+        for ws in (torch.full((16 * M * N + 64,), float("nan"), device="cuda:0"), torch.full((16 * M * N + 64,), float("nan"), device="cuda:0"),
+                   torch.full((M * N,), float("nan"), device="cuda:0")):
+            C = torch.full((M, N), 2.0, dtype=torch.float32 if f32 else torch.bfloat16, device="cuda:0")
+            if f32:
+                B.rp_op_gemm(stream(), layout, 1, A, Bm, C, M, N, K, lda, ldb, N, alpha=0.5, beta=1, split_ws=ws, **kw)
+            else:
+                B.rp_op_gemm(stream(), layout, 0, A, Bm, C, M, N, K, lda, ldb, N, alpha=-0.5, R=R, ldr=N, split_ws=ws, **kw)
+            torch.cuda.synchronize()
+            assert err(C, want) < bound
+            outs.append(C)
+            written = int((~torch.isnan(ws)).sum())
+            if ws.numel() == M * N:
+                assert written == 0
+            else:
+                assert written % (M * N) == 0 and 2 <= written // (M * N) <= 16 and not torch.isnan(ws[:written]).any()
+        assert torch.equal(outs[0], outs[1])
+
+
+# (layout, fp32 output, accumulate, M, N, K, K2, residual): what the adapters of a projection are made of; long and short reductions;
+# one that does not share the launch (561 tiles of 64x64)
+GROUP = [(1, 0, 0, 1016, 16, 4104, 0, 0), (2, 1, 1, 4104, 16, 1016, 0, 0), (2, 1, 1, 72, 520, 1016, 0, 0), (0, 0, 0, 264, 136, 2568, 24, 1),
+         (1, 0, 0, 1032, 2056, 264, 0, 0), (0, 1, 0, 8, 8, 8, 0, 0), (2, 1, 1, 136, 56, 12296, 0, 0), (1, 0, 0, 48, 1032, 328, 40, 1)]
+
+
+@pytest.mark.parametrize("scratch", ["none", "one product's three slices", "all"])
+@pytest.mark.parametrize("members", [(0, 1, 2, 3, 4, 5, 6, 7), (6, 3), (4, 5), (4,), (0, 1, 2)])
+def test_products_that_share_a_launch(rp, members, scratch):
+    B, _ = rp
+    floats = {"none": 0, "one product's three slices": 3 * 1016 * 16 + 8, "all": sum(16 * GROUP[i][3] * GROUP[i][4] for i in members)}[scratch]
+    runs = []
+    for _ in range(2):
+        rng = torch.Generator(device="cuda:0").manual_seed(77)
+        descs, checks = [], []
+        for i in members:
+            layout, f32, beta, M, N, K, K2, res = GROUP[i]
+            d, ref = product(rng, layout, M, N, K, K2)
+            C = torch.full((M, N + 8), 3.0, dtype=torch.float32 if f32 else torch.bfloat16, device="cuda:0")    # rows with room behind them
+            R = operand(rng, M, N) if res else None
+            d.update(C=C, ldc=N + 8, layout=layout, out_f32=f32, M=M, N=N, K=K, K2=K2, beta=beta, alpha=0.5)
+            if res:
+                d.update(R=R, ldr=N)
+            descs.append(d)
+            checks.append((i, C, 0.5 * ref + (R.double() if res else 0.0) + (3.0 if beta else 0.0), 1e-5 if f32 else 4e-3))
+        ws = torch.full((floats,), float("nan"), device="cuda:0") if floats else None
+        torch.cuda.synchronize()
+        B.rp_op_gemm_group(stream(), descs, split_ws=ws)
+        torch.cuda.synchronize()
+        for i, C, want, bound in checks:
+            N = GROUP[i][4]
+            assert err(C[:, :N], want) < bound, GROUP[i]
+            assert bool((C[:, N:] == 3.0).all()), GROUP[i]
+        runs.append([C for _, C, _, _ in checks])
+        if ws is not None and members in ((0, 1, 2, 3, 4, 5, 6, 7), (0, 1, 2)):      # the first product is cut, into slices of [1016, 16]
+            assert not torch.isnan(ws[:2 * 1016 * 16]).any()
+    assert all(torch.equal(a, b) for a, b in zip(*runs))
+
+
+def test_a_group_refuses_what_a_single_product_refuses(rp):
+    B, _ = rp
+    a = torch.zeros((64, 64), dtype=torch.bfloat16, device="cuda:0")
+    ok = dict(A=a, B=a, C=a, lda=64, ldb=64, ldc=64, layout=0, M=64, N=64, K=64)
+    for bad in (dict(A=None), dict(K=12), dict(lda=60), dict(layout=3), dict(out_f32=2), dict(M=-1)):
+        with pytest.raises(B.RpError) as e:
+            B.rp_op_gemm_group(stream(), [ok, dict(ok, **bad)])
+        assert e.value.code == B.RP_EINVAL
+    with pytest.raises(B.RpError):
+        B.rp_op_gemm_group(stream(), [ok] * 9)
