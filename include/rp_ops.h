@@ -102,8 +102,8 @@ RP_API rp_status rp_op_moe_route_plan(void* stream, const float* logits, int T, 
 RP_API rp_status rp_op_attn_fwd(void* stream, const void* q, const void* k, const void* v, void* o, float* lse, long ldq, long ldk,
                          long ldv, long ldo, int batch, int seq, int a, int kh, int d);
 /* delta fp32 [batch, a, seq] is scratch (rowsum(dO*O)); dq [T,a,d], dk, dv [T,kh,d] overwritten.  scratch: device
- * fp32 [2, T, a, d], needed when a > kh (per-query-head partials of dk, dv, summed in head order); may be NULL when
- * a == kh. */
+ * fp32 [2, T, a, d], needed when a > kh (partials of dk, dv, one per query head or per two or four heads of a group, summed in
+ * head order); may be NULL when a == kh. */
 RP_API rp_status rp_op_attn_bwd(void* stream, const void* q, const void* k, const void* v, const void* o, const void* dout,
                          const float* lse, float* delta, void* dq, void* dk, void* dv, float* scratch, long ldq, long ldk,
                          long ldv, long ldo, long lddo, long lddq, long lddk, long lddv, int batch, int seq, int a, int kh,

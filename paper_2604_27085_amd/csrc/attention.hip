@@ -9,8 +9,8 @@
 // score products of the dK/dV kernel) is read with plain 16-byte LDS loads from a [rows][D + 8] tile; an operand
 // whose reduction index is the row index of the tile (V for P.V, K for dS.K, Q and dO for dK/dV) is read with the
 // transposing LDS load from a [rows][D + 32] tile.  A tile needed both ways (K in the dQ kernel, Q and dO in the dK/dV
-// kernel at d = 128) has the row stride D + 24, which serves both kinds of reads (the transposing ones with some bank
-// conflicts), and is stored once; nothing is transposed in registers.  Global loads are 16-byte buffer loads whose descriptor ends with the
+// kernels) has the row stride D + 24, which serves both kinds of reads (the transposing ones with some bank conflicts), and is
+// stored once; nothing is transposed in registers.  Global loads are 16-byte buffer loads whose descriptor ends with the
 // sequence, so rows past the end read as zero without a branch.
 //
 //   forward : workgroup = NW waves x 32*QT queries of one head, loop over 64-key tiles up to the diagonal; NW = 8 (one
@@ -38,7 +38,7 @@ struct AttnArgs {
   float* lse;
   const float* lse_in;
   const float* delta;
-  float *dk_part, *dv_part;   // fp32 [T, a*d] partials of the dK/dV kernel when a > kh
+  float *dk_part, *dv_part;   // fp32 [T, a / hpw * d] partials of the dK/dV kernel unless a workgroup takes a whole group
   long ldq, ldk, ldv, ldo, lddo, lddq, lddk, lddv;
   int batch, seq, a, kh;
   float scale_log2e, scale;
@@ -1123,7 +1123,7 @@ hipError_t launch_dq(hipStream_t st, const AttnArgs& p) {
 //   d = 128: 8192 x 32 heads 1837 | 1808 (.49) | 1802 (.98);  4096 x 64: 1016 | 970 (.48) | 970 (.97);  2 x 2048 x 64:
 //            621 | 562 (.47) | 537 (.94);  4096 x 32: 529 | 516 (.97)
 //   d = 64 (two workgroups share a CU, a chain runs at half the pace): 3 x 1500 x 64: 306 | 285 (.41) | 297 (.82);
-//            8192 x 64: 1959 | - | 2018 (.49);  2048 x 64: 170 | 180 (.94)
+//            8192 x 64: 1996 | 1937 (.25) | 2014 (.49);  2048 x 64: 170 | 180 (.94)
 // Orders by runs of key tiles (from 96 tiles on, see k_attn_bwd) keep one head: 16384 x 64 at four heads is 3 % slower.
 int heads_per_workgroup(int seq, int batch, int a, int kh, int d) {
   const long nkv = (seq + 127) / 128;

@@ -534,9 +534,13 @@ hipError_t gemm_arrange(hipStream_t st, const void* B, long ldb, int N, int K, i
 }
 
 // Tile and reduction slices of a product, the cheapest by the model above.  Cross-entropy epilogues are written for the
-// 256x256 tile (their partial rows are numbered by it), SwiGLU epilogues are not part of the 256x128 two-group tile, and only
-// plain outputs can be summed from slices.  A slice keeps at least four K tiles of a small tile, sixteen of a large one (four
-// for a skinny output, which is bound by reading the other operand).
+// 256x256 tile: the partial rows of three of them are numbered by it, and EPI_CE_DZ, which has none, is faster there even where
+// tokens fill a corner of it (second sweep over 32768 vocabulary rows of 2048 for 8 | 64 tokens: 128x64 tiles 84 | 87 us,
+// 256x256 47 | 49; 32000 rows of 5120: 191 | 205 and 103 | 107).  SwiGLU epilogues are not part of the 256x128 two-group tile.
+// Only plain outputs can be summed from slices, a bf16 one only while its 256x128 tiles leave CUs idle: from 256 of them on a
+// split gains nothing (4096 x 2048 x 12288 NN in two slices 187 -> 180 us with its merge, but the product behind it 217 -> 224
+// and the backward stage of 4096 tokens 1864 -> 1873).  A slice keeps at least four K tiles of a small tile, sixteen of a large
+// one (four for a skinny output, which is bound by reading the other operand).
 static Choice choose(const GemmArgs& a, int tile_hint) {
   if (a.grp_tab) return {1, 1};      // the table's entries are rows of 256-row tiles
   if (a.b_direct || a.epi == EPI_CE_STATS || a.epi == EPI_CE_DZ || a.epi == EPI_F32_COLMAX || a.epi == EPI_CE_P) return {1, 1};

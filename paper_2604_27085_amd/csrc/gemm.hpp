@@ -25,10 +25,10 @@ enum {
   // exponent (p.lse holds ref), plus per-column partials (maximum of acc in .x, fp32 sum of the exponentials in .y, one
   // per 128 rows) and the label logit.  The frozen head's later vocabulary chunks: no logits go to memory.
   EPI_CE_P = 7,
-  // NT, 256x256 tile, the N = 2m columns are gate | up of a SwiGLU MLP: an output tile takes 128 gate columns and the 128
-  // up columns that belong to them (B rows t*128.. and m + t*128..), C [M, 2m] bf16 is written as by EPI_BF16 (no
-  // residual) and C2 [M, m] bf16 = silu(gate) * up from the rounded values, as the separate SwiGLU kernel would compute
-  // it from C.  m is a multiple of 8.
+  // NT, the N = 2m columns are gate | up of a SwiGLU MLP: an output tile BN columns wide takes BN/2 gate columns and the BN/2 up
+  // columns that belong to them (B rows t*BN/2.. and m + t*BN/2..), C [M, 2m] bf16 is written as by EPI_BF16 (no residual) and
+  // C2 [M, m] bf16 = silu(gate) * up from the rounded values, as the separate SwiGLU kernel would compute it from C.  m is a
+  // multiple of 8.
   EPI_SWIGLU_FWD = 8
 };
 // exp argument beyond which EPI_CE_P saturates; a chunk whose maximum exceeds ref + CE_P_LIMIT is redone the slow way
@@ -74,7 +74,8 @@ struct GemmArgs {
   long c_slice_stride;         // set by gemm_launch: elements between the partial outputs of consecutive slices
 };
 
-// Scratch that lets every reduction split gemm_launch would choose go ahead: splits * tiles <= 256 tiles of 256 x 256.
+// Scratch a stage call keeps for reduction splits.  splits * M * N floats are needed; a split that does not fit is not chosen (16
+// slices of 1000 x 1048 fit, two of 4096 x 2048).
 #define RP_SPLITK_WS_BYTES ((size_t)64 << 20)
 
 // Enqueues one GEMM.  Returns hipSuccess or the launch error.  tile_hint: 0 = choose automatically.

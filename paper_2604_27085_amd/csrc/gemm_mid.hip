@@ -1,17 +1,18 @@
 // bf16 GEMM for outputs that leave the chip idle on 256x256 tiles: small tiles, operands loaded straight into LDS, every
 // wave a 64x64 block of C (2x2 tiles of v_mfma_f32_32x32x16_bf16, 64 accumulator registers).
 //
-// A workgroup is KG wave groups of WGM x WGN waves.  The groups work on the same output tile and take the K tiles of the
-// reduction in turn (group g: tiles g, g + KG, ...), each from operand tiles of its own in LDS, so a small tile still keeps
-// four or eight waves busy and every wave has sixteen MFMAs between two barriers whatever the tile; the groups' sums are
-// added through LDS in group order before the epilogue.
+// A workgroup is KG wave groups of WGM x WGN blocks of 64x64.  The groups work on the same output tile and take the K tiles of
+// the reduction in turn (group g: tiles g, g + KG, ...), each from operand tiles of its own in LDS, so a small tile still keeps
+// four or eight waves busy.  Inside a group KI waves (one, or two in the 128x128 tile) share a block and take 4 / KI of the four
+// 16-deep steps of every K tile.  A wave has 16 / KI MFMAs between two barriers: sixteen, or eight in the 128x128 tile.  The sums
+// of the groups and of the waves of a block are added through LDS in a fixed order before the epilogue.
 //
 //   LDS       a ring of NST stages; a stage holds, per group, one K tile (64 deep) of A and of B in the layout of
 //             gemm_dtl.hip: [rows][128 bytes] with the 16-byte chunk c of row r at c ^ ((r >> 1) & 7) for an operand whose
 //             reduction index is contiguous; [64 reduction rows][columns] with 64-byte segments swizzled by the row for a
 //             strided one, read with the transposing LDS load.
-//   loop      one stage per trip, sixteen slots of one MFMA each.  Slots 0..11 issue the loads of the stage NST - 1 ahead into
-//             the ring slot that the barrier of the previous trip freed; at slot 12 the wave has all its fragments, waits
+//   loop      one stage per trip, S = 16 / KI slots of one MFMA each.  Slots 0..S-5 issue the loads of the stage NST - 1 ahead
+//             into the ring slot that the barrier of the previous trip freed; at slot S-4 the wave has all its fragments, waits
 //             for its loads of the next stage, and after the barrier reads that stage's first fragments under the last step.
 //             Stages past the end are loaded through offsets outside the descriptor: the number of loads in flight, and
 //             with it every s_waitcnt immediate, is the same in every trip.

@@ -174,7 +174,9 @@ inline Plan make_plan(const rp_stage_cfg& c, int batch, int seq) {
     f = align_up(f + T * D.h * 2, 256);
     if (D.E > 0) { P.moe_f_fwd = f; f = align_up(f + Tk * D.h * 2, 256); }
     P.split_fwd = f;
-    if (D.r > 0) f = align_up(f + RP_SPLITK_WS_BYTES, 256);   // only the skinny LoRA products split in a forward stage
+    // every bf16 product may split; the smallest workspace a stage without adapters accepts ends here all the same, and its
+    // products then run unsplit (rp_query_sizes reports more: the backward plan holds its own scratch)
+    if (D.r > 0) f = align_up(f + RP_SPLITK_WS_BYTES, 256);
     P.fwd_bytes = f;
   }
   o += set * (size_t)(D.L > 0 ? D.L : 0);

@@ -693,7 +693,8 @@ rp_status rp_stage_forward(rp_ctx* ctx, int slot_id, const void* x_in, void* x_o
   Slot& sl = ctx->slots[slot_id];
   Exec X{ctx, ctx->compute, dims_of(ctx->cfg), batch, seq, (long)batch * seq, static_cast<char*>(workspace), P};
   X.fwd_only = true;
-  // (a workspace of rp_query_sizes always holds the scratch behind the forward plan, whose own size counts it with adapters only)
+  // a workspace of rp_query_sizes holds the scratch behind the forward plan, and the products are cut as in the recomputation of
+  // rp_stage_backward (same bits); in a smaller one they run unsplit
   X.split_off = P.split_fwd; X.has_split = workspace_bytes_in >= P.split_fwd + RP_SPLITK_WS_BYTES;
   const int L = ctx->cfg.n_layers;
   const size_t act_bytes = (size_t)X.T * X.D.h * 2;
