@@ -126,7 +126,7 @@ struct Plan {
   size_t moe_dlog, moe_dlog16;   // router in the stage: gradient of the logits fp32 [T, E] and its bf16 copy
   int moe_max_tiles;             // capacity of the tile table
   size_t split_fwd, split_bwd, h_split;   // partial products of a GEMM reduction split (RP_SPLITK_WS_BYTES each), per plan
-  size_t dkvp;   // per-query-head dK/dV partials of grouped attention; shares memory with dact|dgu, dead by then
+  size_t dkvp;   // dK/dV partials of grouped attention (at most one per query head); shares memory with dact|dgu, dead by then
   size_t fwd_bytes, bwd_bytes;
   // head
   size_t h_xf, h_rstd, h_part, h_zlab, h_lse, h_coef, h_dzt, h_dxacc, h_partials, head_bytes;

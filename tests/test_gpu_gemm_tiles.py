@@ -182,3 +182,27 @@ def test_a_group_refuses_what_a_single_product_refuses(rp):
         assert e.value.code == B.RP_EINVAL
     with pytest.raises(B.RpError):
         B.rp_op_gemm_group(stream(), [ok] * 9)
+
+
+@pytest.mark.parametrize("tile", [0, 2, 3, 4])
+@pytest.mark.parametrize("layout", [0, 1, 2])
+@pytest.mark.parametrize("K2", [0, 24, 136])
+def test_small_tiles_with_an_empty_first_pair(rp, layout, tile, K2):
+    """K = 0: the reduction is the second operand pair alone, or nothing (then the result is the residual, or the old value)."""
+    B, _ = rp
+    M, N = 136, 72
+    rng = torch.Generator(device="cuda:0").manual_seed(K2)
+    kw, ref = product(rng, layout, M, N, max(K2, 8), 0)
+    ref = ref if K2 else torch.zeros_like(ref)
+    X, Y, ldx, ldy = (kw.pop(k) for k in ("A", "B", "lda", "ldb"))
+    pair = dict(A2=X, B2=Y, K2=K2, lda2=ldx, ldb2=ldy) if K2 else {}
+    R = operand(rng, M, N)
+    for split in (None, torch.full((16 * M * N,), float("nan"), device="cuda:0")):
+        C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+        B.rp_op_gemm(stream(), layout, 0, X, Y, C, M, N, 0, ldx, ldy, N, R=R, ldr=N, tile=tile, split_ws=split, **pair)
+        C32 = torch.full((M, N), 2.0, device="cuda:0")
+        B.rp_op_gemm(stream(), layout, 1, X, Y, C32, M, N, 0, ldx, ldy, N, beta=1, tile=tile, split_ws=split, **pair)
+        torch.cuda.synchronize()
+        assert err(C, ref + R.double()) < 4e-3 and err(C32, ref + 2.0) < 1e-5
+        if not K2:
+            assert torch.equal(C, R) and bool((C32 == 2.0).all())
