@@ -80,11 +80,13 @@ typedef struct {
   int32_t moe_router;  /* MoE only.  1: the layer chunk holds the router Wr [E, h] and the stage computes the router
                           logits n2 Wr^T itself (fp32);  0: the caller supplies the logits */
   int32_t head_chunk;  /* vocabulary rows per pass of the LM head (the logits of one pass are the largest buffer of its
-                          workspace); 0 = automatic (32768, or 16384 for more than 4096 tokens), else a multiple of 256.
+                          workspace); 0 = automatic (16384 for more than 4096 tokens, else as many times 32768 as keep
+                          rows * tokens within 2^27), else a multiple of 256.
                           Enters rp_query_sizes like every other field. */
-  int32_t head_two_sweeps; /* 0: the LM head makes one sweep over the vocabulary (a trainable head then keeps the
-                          bf16 probabilities of the whole vocabulary, 2 * vocab * tokens bytes, in its workspace and
-                          forms dW from them afterwards -- only while that is at most 4 GiB, else as 1);  1: the
+  int32_t head_two_sweeps; /* 0: the LM head makes one sweep over the vocabulary and keeps the bf16 probabilities of the
+                          whole vocabulary, 2 * vocab * tokens bytes, in its workspace while that is at most 4 GiB (above
+                          it a trainable head runs as 1, a frozen one keeps one pass's; a frozen head also does so in a
+                          workspace too small for all of them);  1: the
                           two-sweep schedule (softmax statistics, then the logits
                           again for the gradients): no vocabulary-sized buffer, one more logit-sized product -- same
                           results within bf16 noise */

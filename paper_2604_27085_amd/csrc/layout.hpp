@@ -130,15 +130,17 @@ struct Plan {
   size_t fwd_bytes, bwd_bytes;
   // head
   size_t h_xf, h_rstd, h_part, h_zlab, h_lse, h_coef, h_dzt, h_dxacc, h_partials, head_bytes;
-  bool head_keep_p;      // trainable head in one sweep (see make_plan)
-  size_t h_pall, h_xs;   // then: the probabilities of the whole vocabulary [V, T] bf16, the scaled input
-  size_t h_z, h_m, h_l, h_alpha, h_flag;   // frozen head: fp32 logits of one chunk, reference exponent, normaliser, rescale
+  bool head_keep_p;      // one sweep that keeps all probabilities (see make_plan)
+  size_t h_pall, h_xs;   // then: the probabilities of the whole vocabulary [V, T] bf16, the scaled input (trainable)
+  size_t h_z, h_m, h_l, h_alpha, h_flag;   // one sweep: fp32 logits of one chunk, reference exponent, normaliser, rescale
                                            // factor, the flag that switches a chunk's slow path on
   int head_chunk, head_parts;
   LayerBuf lb;                                    // offsets relative to a layer set
 };
 
-inline Plan make_plan(const rp_stage_cfg& c, int batch, int seq) {
+// compact: the smallest plan that a call accepts, for a workspace that does not hold the full one.  (The head's chunks are then at
+// most 32768 vocabulary rows and a frozen head keeps the probabilities of one of them only.)
+inline Plan make_plan(const rp_stage_cfg& c, int batch, int seq, bool compact = false) {
   const Dims D = dims_of(c);
   const size_t T = (size_t)batch * seq;
   Plan P{};
@@ -194,17 +196,23 @@ inline Plan make_plan(const rp_stage_cfg& c, int batch, int seq) {
   // head
   o = 0;
   if (D.V > 0) {
-    // vocabulary rows per pass: 32768 while the transposed dZ chunk stays within 2^27 elements, else 16384, unless the
-    // configuration fixes it (the tests use that to put several chunks into a small vocabulary)
+    // vocabulary rows per pass: as many times 32768 as keep a [chunk, T] array within 2^27 elements and the chunk's weights within
+    // 2 GiB (at least one, 16384 for more than 4096 tokens), unless the configuration fixes it (the tests use that to put several
+    // chunks into a small vocabulary).  A pass costs six launches beside its products: a frozen head of 64
+    // tokens at 151936 x 5120 takes 983 us in five passes, 785 in one
     P.head_chunk = (T * 32768 <= ((size_t)1 << 27)) ? 32768 : 16384;
+    if (!compact)
+      while (P.head_chunk < D.V && ((size_t)P.head_chunk + 32768) * T <= ((size_t)1 << 27) && ((size_t)P.head_chunk + 32768) * D.h < ((size_t)1 << 30))
+        P.head_chunk += 32768;
     if (c.head_chunk > 0) P.head_chunk = c.head_chunk;
     if (P.head_chunk > D.V) P.head_chunk = (int)align_up(D.V, 8);
     P.head_parts = 2 * ((D.V + 255) / 256);
     P.h_xf = take(T * D.h * 2); P.h_rstd = take(T * 4); P.h_part = take((size_t)P.head_parts * T * 8);
     P.h_zlab = take(T * 4); P.h_lse = take(T * 4); P.h_coef = take(T * 4);
-    // a trainable head in one sweep keeps every chunk's probabilities (h_pall, bf16 [V, T]) instead of one chunk's dZ^T:
-    // taken when that buffer stays within 4 GiB (1.2 GB at 151936 x 4096), else the two-sweep schedule
-    const bool keep_p = c.train_base && !c.head_two_sweeps && (size_t)D.V * T * 2 <= ((size_t)4 << 30);
+    // a head in one sweep keeps every chunk's probabilities (h_pall, bf16 [V, T]) instead of one chunk's when that buffer stays
+    // within 4 GiB (1.2 GB at 151936 x 4096): a trainable head, which takes the two-sweep schedule otherwise, needs them for its
+    // weight gradient; a frozen one forms the gradient of its input from them in one product of the whole vocabulary's length
+    const bool keep_p = !c.head_two_sweeps && (c.train_base || !compact) && (size_t)D.V * T * 2 <= ((size_t)4 << 30);
     P.head_keep_p = keep_p;
     P.h_dzt = keep_p ? 0 : take((size_t)P.head_chunk * T * 2);
     P.h_dxacc = take(T * D.h * 4);
@@ -214,7 +222,8 @@ inline Plan make_plan(const rp_stage_cfg& c, int batch, int seq) {
       P.h_z = take((size_t)P.head_chunk * T * 4);
       P.h_m = take(T * 4); P.h_l = take(T * 4); P.h_alpha = take(T * 4); P.h_flag = take(RP_CE_FLAGS * 4);
     }
-    if (keep_p) { P.h_pall = take((size_t)D.V * T * 2); P.h_xs = take(T * D.h * 2); }
+    if (keep_p) P.h_pall = take((size_t)D.V * T * 2);
+    if (keep_p && c.train_base) P.h_xs = take(T * D.h * 2);
   }
   P.head_bytes = o;
   return P;

@@ -778,7 +778,8 @@ rp_status rp_lmhead_ce_fwd_bwd(rp_ctx* ctx, int slot_id, const void* x, const in
                                void* grads, float grad_scale, int batch, int seq, void* workspace, size_t workspace_bytes_in) {
   if (!ctx) return fail(nullptr, RP_EINVAL, "ctx is NULL");
   if (ctx->cfg.vocab == 0) return fail(ctx, RP_EINVAL, "stage has no LM head");
-  const Plan P = make_plan(ctx->cfg, batch > 0 ? batch : 1, seq > 0 ? seq : 8);
+  Plan P = make_plan(ctx->cfg, batch > 0 ? batch : 1, seq > 0 ? seq : 8);
+  if (workspace_bytes_in < P.head_bytes) P = make_plan(ctx->cfg, batch > 0 ? batch : 1, seq > 0 ? seq : 8, true);
   rp_status s = check_call(ctx, slot_id, batch, seq, workspace, workspace_bytes_in, P.head_bytes);
   if (s != RP_OK) return s;
   if (!x || !labels || !loss_out || !dx) return fail(ctx, RP_EINVAL, "x, labels, loss_out and dx must be non-NULL");
@@ -801,11 +802,16 @@ rp_status rp_lmhead_ce_fwd_bwd(rp_ctx* ctx, int slot_id, const void* x, const in
   if (!ctx->cfg.head_two_sweeps && (!ctx->cfg.train_base || P.head_keep_p)) {
     // One sweep over the vocabulary: the softmax normaliser is only needed at the very end.  Per chunk: logits -> p =
     // exp(z - m_t) against a per-token reference exponent that moves (and rescales what has been accumulated) only when
-    // a chunk outgrows it -> acc_t += p W_c;  finally lse_t = m_t + log l_t and dx_t = coef_t (acc_t / l_t - W[y_t]).
-    // Frozen head: two logit-sized products instead of three, one chunk of p in memory at a time.  Trainable head
-    // (keep_p): the p of every chunk stay in memory ([V, T] bf16) and the weight gradient follows from them afterwards,
-    // dW = P'^T^T xs with P'[v, t] = p[v, t] - l_t [v = y_t], xs_t = (coef_t / l_t) xf_t: three products instead of the
-    // four of the two-sweep schedule, which has to compute the logits twice.
+    // a chunk outgrows it;  acc_t = sum_v p_tv W_v;  finally lse_t = m_t + log l_t and dx_t = coef_t (acc_t / l_t - W[y_t]).
+    // keep_p: the p of every chunk stay in memory ([V, T] bf16) and acc is one product over the whole vocabulary behind the
+    // sweep; without it (compact workspace, or more than 4 GiB of p) every chunk adds its share to acc, one chunk of p in
+    // memory at a time.  The long reduction is what a short batch needs: the 160 tiles of 2040 x 5120 fill 62 % of the chip, and
+    // cutting the reduction so that they fill it costs one merge instead of one per chunk.
+    // Vocabulary 151936, one product against one per chunk: frozen, h = 5120, 256 | 2040 | 4096 tokens 1401 -> 1129 | 6145 -> 5720 |
+    // 12475 -> 10978 us; trainable, h = 2048, 4096 tokens 7684 -> 7356.
+    // Trainable head: the weight gradient follows from the p as well, dW = P'^T^T xs with P'[v, t] = p[v, t] - l_t [v = y_t],
+    // xs_t = (coef_t / l_t) xf_t: three products instead of the four of the two-sweep schedule, which has to compute the
+    // logits twice.
     const bool keep_p = P.head_keep_p;
     bf16_t* const pall = keep_p ? X.at<bf16_t>(P.h_pall) : nullptr;
     float* const zc = X.at<float>(P.h_z);
@@ -824,6 +830,21 @@ rp_status rp_lmhead_ce_fwd_bwd(rp_ctx* ctx, int slot_id, const void* x, const in
       RUN(X, "ce_ref_init", 0, 4.0 * r0 * Td + 12.0 * Td,
           k_ce_ref_init(X.st, zc, r0, T, X.at<float>(P.h_m), lbuf[nchunk & 1], X.at<float>(P.h_alpha)));
     }
+    // acc[T, h] += p^T^T . W over `rows` vocabulary rows.  The fp32 logits' buffer is free by then (the slow path of the chunk
+    // before is done) and serves as scratch of the split
+    auto add_dx = [&](const void* p, const bf16_t* Wr, int rows) {
+      GemmArgs d; gemm_zero_args(d);
+      d.A = p; d.lda = T; d.B = Wr; d.ldb = D.h; d.M = T; d.N = D.h; d.K = rows; d.C = acc;
+      d.ldc = D.h; d.beta = 1; d.epi = EPI_F32;
+      X.give_split_ws(d);
+      const size_t zbytes = (size_t)P.head_chunk * T * 4;
+      if (zbytes > d.split_ws_bytes) { d.split_ws = zc; d.split_ws_bytes = zbytes; }
+      X.mark_gemm(GEMM_TN, d);
+      X.chk(gemm_launch(X.st, GEMM_TN, d), "lm head dX");
+    };
+    // vocabulary rows of one product over the kept p: operands are addressed with 31-bit byte offsets
+    const long widest = T > D.h ? T : D.h;
+    const int piece = (int)((((1L << 31) - 1) / 2 / widest) / 256 * 256);
     for (int v0 = 0, ci = 0; v0 < D.V; v0 += P.head_chunk, ++ci) {
       const int vc = (D.V - v0 < P.head_chunk) ? (D.V - v0) : P.head_chunk;
       const int nparts = gemm_ce_stats_partials(vc);
@@ -854,13 +875,9 @@ rp_status rp_lmhead_ce_fwd_bwd(rp_ctx* ctx, int slot_id, const void* x, const in
       RUN(X, "ce_slow_path", 0, 0,
           k_ce_chunk_redo(X.st, zc, vc, T, X.at<float2>(P.h_part), nparts, X.at<float>(P.h_m), l_in, l_out, X.at<float>(P.h_alpha), pc, acc,
                           D.h, keep_p ? pall : nullptr, v0, flag));
-      GemmArgs d; gemm_zero_args(d);   // acc[T, h] += p^T^T . W_c
-      d.A = pc; d.lda = T; d.B = Wc; d.ldb = D.h; d.M = T; d.N = D.h; d.K = vc; d.C = acc;
-      d.ldc = D.h; d.beta = 1; d.epi = EPI_F32;
-      X.give_split_ws(d);
-      X.mark_gemm(GEMM_TN, d);
-      X.chk(gemm_launch(X.st, GEMM_TN, d), "lm head dX");
+      if (!keep_p) add_dx(pc, Wc, vc);
     }
+    if (keep_p) for (int v0 = 0; v0 < D.V; v0 += piece) add_dx(pall + (size_t)v0 * T, Wv + (size_t)v0 * D.h, D.V - v0 < piece ? D.V - v0 : piece);
     RUN(X, "ce_lse", 0, 12.0 * Td, k_ce_lse_from_ref(X.st, X.at<float>(P.h_m), X.at<float>(P.h_l), X.at<float>(P.h_lse), T));
     RUN(X, "ce_finalize", 0, 16.0 * Td,
         k_ce_finalize(X.st, X.at<float>(P.h_lse), X.at<float>(P.h_zlab), labels, grad_scale, X.at<float>(P.h_coef), loss_out, T));
@@ -868,8 +885,8 @@ rp_status rp_lmhead_ce_fwd_bwd(rp_ctx* ctx, int slot_id, const void* x, const in
       RUN(X, "ce_patch_label", 0, 16.0 * Td, k_ce_patch_label(X.st, pall, T, D.V, labels, X.at<float>(P.h_l), X.at<float>(P.h_coef)));
       RUN(X, "ce_scale_x", 0, 4.0 * Td * D.h,
           k_ce_scale_x(X.st, X.at<void>(P.h_xf), X.at<float>(P.h_coef), X.at<float>(P.h_l), X.at<void>(P.h_xs), T, D.h));
-      for (int v0 = 0; v0 < D.V; v0 += P.head_chunk) {
-        const int vc = (D.V - v0 < P.head_chunk) ? (D.V - v0) : P.head_chunk;
+      for (int v0 = 0; v0 < D.V; v0 += piece) {
+        const int vc = (D.V - v0 < piece) ? (D.V - v0) : piece;
         GemmArgs w; gemm_zero_args(w);  // dW_c[vc, h] += P'_c . xs
         w.A = pall + (size_t)v0 * T; w.lda = T; w.B = X.at<void>(P.h_xs); w.ldb = D.h; w.M = vc; w.N = D.h; w.K = T;
         w.C = G.t(RP_T_WV) + (size_t)v0 * D.h; w.ldc = D.h; w.beta = 1; w.epi = EPI_F32;
