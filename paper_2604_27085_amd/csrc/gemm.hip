@@ -49,10 +49,9 @@ struct TileLoader {
   uint32_t kstep;
   int row0, ch;
 
-  // row_map (only for operands whose rows are the tile rows): row gx is read from row row_map[gx] of the buffer.
   // fold_half (only !TR): the tile's rows are the two halves of a folded index range -- rows [0, BX/2) are x0/2 + row,
   // rows [BX/2, BX) are fold_half + x0/2 + row - BX/2 (the gate and up rows of one SwiGLU column block).
-  RP_DEV void init(long ld, int x0, int Xdim, int tid, const int* row_map = nullptr, int fold_half = 0) {
+  RP_DEV void init(long ld, int x0, int Xdim, int tid, int fold_half = 0) {
     row0 = tid / S::CH;
     ch = tid % S::CH;
     kstep = TR ? (uint32_t)ld * 2u : 2u;
@@ -63,8 +62,7 @@ struct TileLoader {
         const int gl = fold_half ? (x0 >> 1) + (row < BX / 2 ? row : row - BX / 2) : x0 + row;
         const int gx = fold_half && row >= BX / 2 ? fold_half + gl : gl;
         const bool in = gl < (fold_half ? fold_half : Xdim);
-        const long src = (row_map && in) ? row_map[gx] : gx;
-        voff[it] = in ? (uint32_t)(src * ld + ch * 8) * 2u : OOB;
+        voff[it] = in ? (uint32_t)((long)gx * ld + ch * 8) * 2u : OOB;
       } else {
         const int gx = x0 + ch * 8;
         voff[it] = gx < Xdim ? (uint32_t)((long)row * ld + gx) * 2u : OOB;
@@ -147,21 +145,9 @@ __global__ void __launch_bounds__(WGM* WGN* KG * 64)
   const int wm = wmn / WGN, wn = wmn % WGN;
   const int ks0 = kg * KSL;
 
-  int tile_m, tile_n, m0, Mlim = p.M;
-  const bf16* Bbase = static_cast<const bf16*>(p.B);
-  if (p.grp_tab) {   // uniform over the grid
-    const int tiles_n = (p.N + BN - 1) / BN;
-    tile_m = (int)blockIdx.x / tiles_n;
-    tile_n = (int)blockIdx.x % tiles_n;
-    if (tile_m >= *p.grp_ntiles) return;
-    const int4 g = p.grp_tab[tile_m];
-    m0 = g.y;
-    Mlim = g.y + g.z;
-    Bbase += (long)g.x * p.grp_strideB;
-  } else {
-    tile_of_block(p.M, p.N, BM, BN, tile_m, tile_n);
-    m0 = tile_m * BM;
-  }
+  int tile_m, tile_n;
+  tile_of_block(p.M, p.N, BM, BN, tile_m, tile_n);
+  const int m0 = tile_m * BM;
   const int n0 = tile_n * BN;
   const int nk1 = (p.K + BK - 1) / BK;
   const int nk_all = nk1 + (p.K2 + BK - 1) / BK;
@@ -172,16 +158,16 @@ __global__ void __launch_bounds__(WGM* WGN* KG * 64)
 
   LA la, la2;
   LB lb, lb2;
-  la.init(p.lda, m0, Mlim, tid, TA ? nullptr : p.row_map);
+  la.init(p.lda, m0, p.M, tid);
   const int fold = (!TB && p.epi == EPI_SWIGLU_FWD) ? p.N >> 1 : 0;   // uniform
-  lb.init(p.ldb, n0, p.N, tid, nullptr, fold);
-  const rsrc_t rsA = make_rsrc(p.A, p.bytesA), rsB = make_rsrc(Bbase, p.bytesB);
+  lb.init(p.ldb, n0, p.N, tid, fold);
+  const rsrc_t rsA = make_rsrc(p.A, p.bytesA), rsB = make_rsrc(p.B, p.bytesB);
   rsrc_t rsA2 = rsA, rsB2 = rsB;
   la2 = la;
   lb2 = lb;
   if (p.K2 > 0) {
     la2.init(p.lda2, m0, p.M, tid);
-    lb2.init(p.ldb2, n0, p.N, tid, nullptr, fold);
+    lb2.init(p.ldb2, n0, p.N, tid, fold);
     rsA2 = make_rsrc(p.A2, p.bytesA2);
     rsB2 = make_rsrc(p.B2, p.bytesB2);
   }
@@ -335,12 +321,12 @@ __global__ void __launch_bounds__(WGM* WGN* KG * 64)
         for (int v = 0; v < 16; ++v) acc[i][j][v] += theirs[(i * 16 + v) * 64];
     }
     __syncthreads();   // the staging of the epilogue overwrites the exchange area
-    epilogue(p, Mlim, acc, smem, wave, lane, m0 + wm * WAVE_M, n0 + wn * WAVE_N, p.part_row0 + tile_m * WGM + wm, kg, kg + 1);
+    epilogue(p, p.M, acc, smem, wave, lane, m0 + wm * WAVE_M, n0 + wn * WAVE_N, p.part_row0 + tile_m * WGM + wm, kg, kg + 1);
     return;
   }
   // a folded tile's wave columns: waves 0, 1 of a row hold gate columns, waves 2, 3 the up columns that go with them
   const int wcol = fold ? (n0 >> 1) + (wn & 1) * WAVE_N + (wn >> 1) * fold : n0 + wn * WAVE_N;
-  epilogue(p, Mlim, acc, smem, wmn, lane, m0 + wm * WAVE_M, wcol, p.part_row0 + tile_m * WGM + wm);
+  epilogue(p, p.M, acc, smem, wmn, lane, m0 + wm * WAVE_M, wcol, p.part_row0 + tile_m * WGM + wm);
 }
 
 template <int WGM, int WGN, int BK, bool TA, bool TB, int KG = 1, bool GATED = false, bool BD = false>
@@ -353,8 +339,7 @@ hipError_t launch_one(hipStream_t st, const GemmArgs& a) {
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  int tiles = ((a.M + C::BM - 1) / C::BM) * ((a.N + C::BN - 1) / C::BN);
-  if (a.grp_tab) tiles = a.grp_max_tiles * ((a.N + C::BN - 1) / C::BN);
+  const int tiles = ((a.M + C::BM - 1) / C::BM) * ((a.N + C::BN - 1) / C::BN);
   RP_LAUNCH(kern, dim3(tiles, a.splits > 0 ? a.splits : 1), dim3(C::NTHR), C::SMEM, st, a);
   return hipGetLastError();
 }
@@ -641,7 +626,8 @@ hipError_t gemm_launch(hipStream_t st, int layout, const GemmArgs& a_in, int til
   // faster -- unless a kernel is asked for by name (hint 1: eight waves, hint 7: four) or the variant has no
   // counterpart there.
   // Skinny outputs (the LoRA products, bound by reading the other operand once) stay on the eight-wave kernel too: +14 %.
-  const bool dtl = tile == 1 && tile_hint != 1 && !a.run_flag && !a.b_direct && (tile_hint == 7 || (a.K + a.K2 >= 2560 && a.M > 64 && a.N > 64));
+  // Grouped products always take it: it is the kernel that knows their tile table.
+  const bool dtl = a.grp_tab || (tile == 1 && tile_hint != 1 && !a.run_flag && !a.b_direct && (tile_hint == 7 || (a.K + a.K2 >= 2560 && a.M > 64 && a.N > 64)));
   if (dtl) {
     e = gemm_dtl_launch(st, a, layout);
   } else {

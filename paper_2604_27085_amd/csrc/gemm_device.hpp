@@ -127,13 +127,16 @@ RP_DEV bool label_logit(const f32x16 (&acc)[TM][TN], int j, int lab_local, float
 // barrier inside.
 // part_row: row of the cross-entropy partial array this wave writes (EPI_CE_STATS).
 // M: rows of C that exist (the end of the group's rows in grouped mode).
+// IS: rows of C between the 32-row MFMA tiles of the wave's block (32: the block is 128 consecutive rows).
 // j0, j1 (wave-uniform): the 32-column halves [j0, j1) of the block this wave writes -- both, except in the plain
 // epilogues of the two-group tile, where the groups take one half each.
+template <int IS = 32>
 RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsigned char* smem, int wave, int lane,
                      int wrow0, int wcol0, int part_row, int j0 = 0, int j1 = TN) {
   const int lr = lane & 31, lk = lane >> 5;
   unsigned char* const stg = smem + wave * STG_BYTES;
   const int rr = lane >> 3, cc = lane & 7;   // read-back: 8 rows per pass, 8 chunks of 16 bytes per row
+  auto out_row = [&](int t) __attribute__((always_inline)) { return wrow0 + (t >> 2) * IS + (t & 3) * 8 + rr; };   // row of C of local row 8 t + rr
 
   if ((p.epi == EPI_BF16 && !p.R) || p.epi == EPI_CE_DZ || p.epi == EPI_SWIGLU_BWD || p.epi == EPI_CE_P || p.epi == EPI_SWIGLU_FWD) {
     bf16* s16 = reinterpret_cast<bf16*>(stg);
@@ -258,7 +261,7 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
         uint4 gv[NB], uv[NB];
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
-          const int grow = wrow0 + (t0 + u) * 8 + rr;
+          const int grow = out_row(t0 + u);
           gv[u] = make_uint4(0u, 0u, 0u, 0u);
           uv[u] = gv[u];
           if (grow < M && gcol < p.N) {
@@ -268,7 +271,7 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
         }
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
-          const int row = (t0 + u) * 8 + rr, grow = wrow0 + row;
+          const int row = (t0 + u) * 8 + rr, grow = out_row(t0 + u);
           const uint4 dv = *reinterpret_cast<const uint4*>(s16 + row * STG_LD + cc * 8);
           const uint32_t dw[4] = {dv.x, dv.y, dv.z, dv.w}, gw[4] = {gv[u].x, gv[u].y, gv[u].z, gv[u].w},
                          uw[4] = {uv[u].x, uv[u].y, uv[u].z, uv[u].w};
@@ -299,7 +302,7 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
       const int nlim = p.epi == EPI_SWIGLU_FWD && (wave & 3) < 2 ? p.N >> 1 : p.N;
 #pragma unroll
       for (int t = 0; t < WAVE_M / 8; ++t) {
-        const int row = t * 8 + rr, grow = wrow0 + row;
+        const int row = t * 8 + rr, grow = out_row(t);
         if (grow < M && gcol < nlim)
           *reinterpret_cast<uint4*>(Cp + (long)grow * p.ldc + gcol) = *reinterpret_cast<const uint4*>(s16 + row * STG_LD + cc * 8);
       }
@@ -307,7 +310,7 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
       const int lcol = j0 * 32 + (lane & 3) * 8, gcol = wcol0 + lcol;
 #pragma unroll
       for (int t = 0; t < WAVE_M / 16; ++t) {
-        const int row = t * 16 + (lane >> 2), grow = wrow0 + row;
+        const int row = t * 16 + (lane >> 2), grow = wrow0 + (t >> 1) * IS + (t & 1) * 16 + (lane >> 2);
         if (grow < M && gcol < p.N)
           *reinterpret_cast<uint4*>(Cp + (long)grow * p.ldc + gcol) = *reinterpret_cast<const uint4*>(s16 + row * STG_LD + lcol);
       }
@@ -402,7 +405,7 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
           if (p.beta) {
 #pragma unroll
             for (int u = 0; u < NB; ++u) {
-              const int grow = wrow0 + (t0 + u) * 8 + rr;
+              const int grow = out_row(t0 + u);
               o[u] = (grow < M && colok) ? *reinterpret_cast<const float4*>(Cf + (long)grow * p.ldc + gcol) : make_float4(0.f, 0.f, 0.f, 0.f);
             }
           } else {
@@ -411,7 +414,7 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
           }
 #pragma unroll
           for (int u = 0; u < NB; ++u) {
-            const int row = (t0 + u) * 8 + rr, grow = wrow0 + row;
+            const int row = (t0 + u) * 8 + rr, grow = out_row(t0 + u);
             float4 x = *reinterpret_cast<const float4*>(s32 + row * (STG_LD / 2) + cc * 4);
             x.x += o[u].x; x.y += o[u].y; x.z += o[u].z; x.w += o[u].w;
             if (grow < M && colok) *reinterpret_cast<float4*>(Cf + (long)grow * p.ldc + gcol) = x;
@@ -420,13 +423,13 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
           uint2 r2[NB];
 #pragma unroll
           for (int u = 0; u < NB; ++u) {
-            const int grow = wrow0 + (t0 + u) * 8 + rr;
+            const int grow = out_row(t0 + u);
             r2[u] = (grow < M && colok) ? *reinterpret_cast<const uint2*>(reinterpret_cast<const bf16*>(p.R) + (long)grow * p.ldr + gcol)
                                         : make_uint2(0u, 0u);
           }
 #pragma unroll
           for (int u = 0; u < NB; ++u) {
-            const int row = (t0 + u) * 8 + rr, grow = wrow0 + row;
+            const int row = (t0 + u) * 8 + rr, grow = out_row(t0 + u);
             float4 x = *reinterpret_cast<const float4*>(s32 + row * (STG_LD / 2) + cc * 4);
             x.x += bf16_lo(r2[u].x); x.y += bf16_hi(r2[u].x); x.z += bf16_lo(r2[u].y); x.w += bf16_hi(r2[u].y);
             if (grow < M && colok)

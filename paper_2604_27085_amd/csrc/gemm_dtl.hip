@@ -83,9 +83,15 @@ RP_DEV i32x4 raw_rsrc(const void* base, uint32_t bytes) {
 
 // TB: the B operand is [K, N] (reduction index strided, the NN product); its units keep that layout and its fragments
 // are read with the transposing LDS load.  TA (with TB: the TN product): the same for A, which is [K, M].
-template <bool TA, bool TB>
+// GRP: grouped mode.  A group's last tile of 256 rows is rarely full (2048 tokens on 8 of 128 experts: 128 rows per expert on
+// average), and what its empty rows cost is the matrix pipe's time and power.  The two wave rows take alternate blocks of 32 rows,
+// and the K loop exists for one to four blocks per wave (NI): a tile of `rows` rows runs ceil(rows / 64) / 4 of the MFMAs.  Measured
+// with that and the tile order of the plain products, us: h = 4096, 128 experts of 1536, backward stage of 256 | 2048 | 8192 tokens
+// 2326 -> 2250 | 3664 -> 3510 | 13270 -> 12950;  h = 2880, 32 experts of 2880, forward of 1000 | 8192 tokens 659 -> 636 |
+// 2995 -> 2876.  What bounds the 128-row tiles then is the experts' weights (gate/up 3.5 GB in 706 us, matrix pipe 31 % busy).
+template <bool TA, bool TB, bool GRP>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) gemm_dtl_kernel(const GemmArgs p) {
-  static_assert(!TA || TB, "A transposed alone is not a layout of this library");
+  static_assert((!TA || TB) && !(GRP && TA), "not a layout of this library");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -94,14 +100,16 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
 
   int tile_m, tile_n, m0, Mlim = p.M;
   const bf16* Bbase = static_cast<const bf16*>(p.B);
-  if (p.grp_tab) {   // uniform over the grid
-    const int tiles_n = (p.N + 255) / 256;
-    tile_m = (int)blockIdx.x / tiles_n;
-    tile_n = (int)blockIdx.x % tiles_n;
-    if (tile_m >= *p.grp_ntiles) return;
+  int NI = 4;                                  // 32-row blocks of a wave that hold rows
+  if constexpr (GRP) {
+    // the table's length is known on the device only: surplus workgroups leave
+    const int ntiles = *p.grp_ntiles, tiles_n = (p.N + 255) / 256;
+    if ((int)blockIdx.x >= ntiles * tiles_n) return;
+    tile_of_block(ntiles * 256, p.N, 256, 256, tile_m, tile_n, 4);
     const int4 g = p.grp_tab[tile_m];
     m0 = g.y;
     Mlim = g.y + g.z;
+    NI = __builtin_amdgcn_readfirstlane((g.z + 63) >> 6);
     Bbase += (long)g.x * p.grp_strideB;
   } else {
     // narrow outputs (up to 24 tile columns) sweep their columns in groups of 4 tile rows, wide ones of 8: measured
@@ -266,11 +274,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
   uint32_t fkA[4], fkB[4];
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
-    fkA[ks] = (uint32_t)((wm * 128 + lr) * 128 + ((2 * ks + lk) ^ s7) * 16);
+    fkA[ks] = (uint32_t)((wm * (GRP ? 32 : 128) + lr) * 128 + ((2 * ks + lk) ^ s7) * 16);
     fkB[ks] = (uint32_t)((wn * 128 + lr) * 128 + ((2 * ks + lk) ^ s7) * 16);
   }
   uint4 af[2][4], bfr[2][4];
-  auto read_a = [&](int set, uint32_t off, int i) { af[set][i] = *reinterpret_cast<const uint4*>(smem + off + i * 4096); };
+  auto read_a = [&](int set, uint32_t off, int i) { af[set][i] = *reinterpret_cast<const uint4*>(smem + off + i * (GRP ? 8192 : 4096)); };
   auto read_b = [&](int set, uint32_t off, int j) { bfr[set][j] = *reinterpret_cast<const uint4*>(smem + off + j * 4096); };
   // TB: a fragment of B is two transposing reads (reduction rows +0..3 and +4..7 of the lane's half of the 16-deep step).
   // fkBt[j]: byte offset of the lane's first read of step 0 for MFMA tile column j of the wave: reduction row
@@ -340,8 +348,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
   //   slots 45..47, 56..60 the loads of A of tile t+2, into the slot of B of this tile
   //   slots 61, 62         the state of the loads of tile t+3
   constexpr int BAR = 44;
-  auto main_loop = [&](auto wtag) __attribute__((always_inline)) {
-    constexpr int W = decltype(wtag)::value;
+  auto main_loop = [&](auto wtag, auto nitag) __attribute__((always_inline)) {
+    constexpr int W = decltype(wtag)::value, NB = decltype(nitag)::value;   // NB: blocks of 32 rows
     uint32_t ring = 0;                 // ring slot of B of the current tile; A follows
     uint32_t curA = UNIT_BYTES, curB = 0, nA = 0;
     uint32_t fa = curA + fkA[1], fb = curB + fkB[1];   // offsets of the reads of the coming step
@@ -355,8 +363,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
         }
         // one wait per step for all of its fragments (read eight slots or more ago) instead of one per fragment
         if constexpr (I == 0 && ks < 3) __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-        acc[jj >> 1][i][jj & 1] = mfma32(af[set][i], bfr[set][jj], acc[jj >> 1][i][jj & 1]);
-        if constexpr (I < 4) read_a(set ^ 1, fa, I);
+        if constexpr (i < NB) acc[jj >> 1][i][jj & 1] = mfma32(af[set][i], bfr[set][jj], acc[jj >> 1][i][jj & 1]);
+        if constexpr (I < NB) read_a(set ^ 1, fa, I);
         if constexpr (I >= 4 && I < 8) read_b(set ^ 1, fb, I - 4);
         // address arithmetic for the reads of the coming step, in slots without a memory instruction
         if constexpr (sl == 8 + (W & 1)) fa = curA + fkA[2];
@@ -387,8 +395,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
   //   slots 12..15, 28..31       the loads of B of tile t+2
   //   slot  46                   vmcnt(8); barrier
   //   slots 47, 53, 55, 57, 60..63  the loads of A of tile t+2
-  [[maybe_unused]] auto main_loop_tb = [&]() __attribute__((always_inline)) {
-    constexpr int BARB = 46;
+  [[maybe_unused]] auto main_loop_tb = [&](auto nitag) __attribute__((always_inline)) {
+    constexpr int BARB = 46, NB = decltype(nitag)::value;
     uint32_t ring = 0;
     uint32_t curA = UNIT_BYTES, nA = 0;
     uint32_t fa = curA + fkA[1];
@@ -404,8 +412,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
           __syncthreads();
         }
         if constexpr (I == 0 && ks < 3) __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-        acc[jj >> 1][i][jj & 1] = mfma32(af[set][i], bfr[set][jj], acc[jj >> 1][i][jj & 1]);
-        if constexpr (I < 4) read_a(set ^ 1, fa, I);
+        if constexpr (i < NB) acc[jj >> 1][i][jj & 1] = mfma32(af[set][i], bfr[set][jj], acc[jj >> 1][i][jj & 1]);
+        if constexpr (I < NB) read_a(set ^ 1, fa, I);
         if constexpr (I >= 4 && I < 12) {
           constexpr int j = (I - 4) >> 1, half = (I - 4) & 1;
           if constexpr (ks < 3) read_bt(set ^ 1, fbj[j] + (ks + 1) * 8192, j, half);
@@ -494,11 +502,22 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
   };
   if constexpr (TA) {
     main_loop_tn();
-  } else if constexpr (TB) {
-    main_loop_tb();
   } else {
-  // (one plan for all four waves: staggering the waves' load slots against each other measured 0.5-1.5 % slower)
-  main_loop(std::integral_constant<int, 1>{});
+    // (one plan for all four waves: staggering the waves' load slots against each other measured 0.5-1.5 % slower)
+    auto run = [&](auto nitag) __attribute__((always_inline)) {
+      if constexpr (TB) main_loop_tb(nitag);
+      else main_loop(IC<1>{}, nitag);
+    };
+    if constexpr (GRP) {
+      switch (NI) {
+        case 1: run(IC<1>{}); break;
+        case 2: run(IC<2>{}); break;
+        case 3: run(IC<3>{}); break;
+        default: run(IC<4>{});
+      }
+    } else {
+      run(IC<4>{});
+    }
   }
   __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): the empty loads past the end write LDS too
   __syncthreads();                      // every wave is done with the operand stages: the epilogue reuses the LDS
@@ -516,7 +535,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
         for (int v = 0; v < 16; ++v) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(half[i][j][v]) : "a"(acc[h][i][j][v]));
   };
   asm volatile("s_nop 7\n\ts_nop 7");   // the last MFMA has long retired (a barrier ago); the copies are invisible to the hazard checks
-  const int wrow = m0 + wm * 128;
+  constexpr int IS = GRP ? 64 : 32;      // a wave's blocks of 32 rows: every other one, or consecutive
+  const int wrow = m0 + wm * (GRP ? 32 : 128);
   const int part_row = p.part_row0 + tile_m * 2 + wm;
   if (fold) {
     // gate | up as by EPI_BF16, then silu(gate) * up from the rounded values (what the SwiGLU kernel would read back)
@@ -524,10 +544,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
     q.epi = EPI_BF16;
     const int gcol = (n0 >> 1) + wn * 64;
     fetch(1);
-    epilogue(q, Mlim, half, smem, wave, lane, wrow, gcol + fold, part_row);
+    epilogue<IS>(q, Mlim, half, smem, wave, lane, wrow, gcol + fold, part_row);
     q.N = fold;     // the last tile's gate columns end where the up columns begin
     fetch(0);
-    epilogue(q, Mlim, half, smem, wave, lane, wrow, gcol, part_row);
+    epilogue<IS>(q, Mlim, half, smem, wave, lane, wrow, gcol, part_row);
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -541,33 +561,34 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
         }
     q.C = p.C2;
     q.ldc = p.ldc2;
-    epilogue(q, Mlim, half, smem, wave, lane, wrow, gcol, part_row);
+    epilogue<IS>(q, Mlim, half, smem, wave, lane, wrow, gcol, part_row);
     return;
   }
   fetch(0);
-  epilogue(p, Mlim, half, smem, wave, lane, wrow, n0 + wn * 128, part_row);
+  epilogue<IS>(p, Mlim, half, smem, wave, lane, wrow, n0 + wn * 128, part_row);
   fetch(1);
-  epilogue(p, Mlim, half, smem, wave, lane, wrow, n0 + wn * 128 + 64, part_row);
+  epilogue<IS>(p, Mlim, half, smem, wave, lane, wrow, n0 + wn * 128 + 64, part_row);
 }
 
 }  // namespace
 
-template <bool TA, bool TB>
+template <bool TA, bool TB, bool GRP = false>
 static hipError_t dtl_launch_one(hipStream_t st, const GemmArgs& a) {
   static bool attr_done = false;
-  auto kern = gemm_dtl_kernel<TA, TB>;
+  auto kern = gemm_dtl_kernel<TA, TB, GRP>;
   if (!attr_done) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, DTL_SMEM);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
   int tiles = ((a.M + 255) / 256) * ((a.N + 255) / 256);
-  if (a.grp_tab) tiles = a.grp_max_tiles * ((a.N + 255) / 256);
+  if (GRP) tiles = a.grp_max_tiles * ((a.N + 255) / 256);
   RP_LAUNCH(kern, dim3(tiles, a.splits > 0 ? a.splits : 1), dim3(256), DTL_SMEM, st, a);
   return hipGetLastError();
 }
 
 hipError_t gemm_dtl_launch(hipStream_t st, const GemmArgs& a, int layout) {
+  if (a.grp_tab) return layout == GEMM_NT ? dtl_launch_one<false, false, true>(st, a) : layout == GEMM_NN ? dtl_launch_one<false, true, true>(st, a) : hipErrorInvalidValue;
   switch (layout) {
     case GEMM_NT: return dtl_launch_one<false, false>(st, a);
     case GEMM_NN: return dtl_launch_one<false, true>(st, a);
