@@ -71,6 +71,15 @@ RP_DEV uint4 buf_load16(rsrc_t r, uint32_t voff) {
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+// Softmax statistics of a 64-query tile for the dK/dV kernels, one per lane: wave 0 fetches lse, wave 1 delta.  The load is only
+// issued here; what the score products take is worked out when the tile is stored to LDS (stat_chunk), a tile later.  (Worked out
+// where it is loaded, it makes the two waves wait for memory in every tile and the others for them: dK/dV of 8192 tokens, 32 heads
+// of 128: 1252 -> 1109 us; 4096 x 16 heads 172 -> 162; 2048 x 64 188 -> 169.)
+RP_DEV rsrc_t stat_rsrc(const float* lse, const float* delta, int wave, long head, int seq) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(wave == 0 ? lse : delta) + head * seq, 0, seq * 4, 0x00020000);
+}
+RP_DEV float stat_load(rsrc_t r, int q) { return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, q * 4, 0, 0)); }
+
 // ---- 64 x D tile: global -> registers -> LDS -----------------------------------------------------------------
 template <int D, int NT>
 struct Tile64 {
@@ -118,6 +127,14 @@ RP_DEV uint4 pack_frag(const f32x16& s, int off) {
                     pack_bf16x2(s[off + 4], s[off + 5]), pack_bf16x2(s[off + 6], s[off + 7]));
 }
 
+// max over lanes l and l ^ 32, in the vector unit: the exchange through LDS is a round trip of the wave in every key tile.  Forward of
+// 8192 tokens, 64 heads of 64: 702 -> 673 us (with the mask test on one limit per lane); the eight-wave kernel, whose waves pair up
+// around that wait, is 4 % slower with it (521 -> 542) and keeps the exchange
+RP_DEV float half_max(float x) {
+  const uint32_t u = __float_as_uint(x);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
 RP_DEV float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Two waves share a SIMD in the forward kernel.  Left alone they fall into step: both issue their matrix products at
@@ -138,6 +155,10 @@ RP_DEV uint4 split3(float x) {
   const uint32_t m = f32_to_bf16_bits(r1);
   const uint32_t l = f32_to_bf16_bits(r1 - bf16_bits_to_f32(m));
   return make_uint4(h | (m << 16), l, 0u, 0u);
+}
+// The pad chunk of a Q row (wave 0: -lse / scale) or dO row (wave 1: -delta); padded query rows get P = exp(-3e4 scale) = 0.
+RP_DEV uint4 stat_chunk(float raw, int wave, bool in, float scale) {
+  return split3(wave == 0 ? (in ? -raw / scale : -3.0e4f) : (in ? -raw : 0.f));
 }
 // The other operand of that step: ones in the same three slots for the lanes that hold reduction indices 0..7.
 RP_DEV uint4 ones3(int lk) { return lk == 0 ? make_uint4(0x3F803F80u, 0x00003F80u, 0u, 0u) : make_uint4(0u, 0u, 0u, 0u); }
@@ -319,22 +340,20 @@ __global__ void __launch_bounds__(NW * 64, (QT == 1 && NW <= 4) ? 2 : 1) attn_fw
       const bool need_mask = (kv0 + 63 > qw0) || (kv0 + 64 > p.seq);   // wave-uniform
 #pragma unroll
       for (int t = 0; t < QT; ++t) {
-        const int qpos = qw0 + 32 * t + lr;
         if (need_mask) {
+          const int qpos = qw0 + 32 * t + lr;
+          const int klim = (qpos < p.seq - 1 ? qpos : p.seq - 1) - (kv0 + 4 * lk);   // keys up to klim past the lane's first
 #pragma unroll
           for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              const int kpos = kv0 + 32 * kt + 8 * (v >> 2) + 4 * lk + (v & 3);
-              sT[t][kt][v] = (kpos > qpos || kpos >= p.seq) ? -INFINITY : sT[t][kt][v];
-            }
+            for (int v = 0; v < 16; ++v) sT[t][kt][v] = (32 * kt + 8 * (v >> 2) + (v & 3) > klim) ? -INFINITY : sT[t][kt][v];
         }
         float mx = -INFINITY;
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
           for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sT[t][kt][v]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * p.scale_log2e;
+        mx = (NW < 8 ? half_max(mx) : fmaxf(mx, __shfl_xor(mx, 32, 64))) * p.scale_log2e;
         // The accumulator is rescaled on every key tile, without a branch: a conditional rescale (only when the
         // maximum grows) makes the compiler carry a second copy of the accumulator through the loop, which costs more
         // than the multiplies.  The first key tile contains key 0 <= qpos, so m_run is finite from then on.
@@ -673,22 +692,19 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_fused_kernel(const AttnArgs 
   [[maybe_unused]] int pf_it = 0;
   rsrc_t rq = seq_rsrc(p.q + tok0 * p.ldq + pf_h * D, p.ldq, p.seq, D);
   rsrc_t rdo = seq_rsrc(p.dout + tok0 * p.lddo + pf_h * D, p.lddo, p.seq, D);
+  rsrc_t rst = stat_rsrc(p.lse_in, p.delta, w, (long)b * p.a + pf_h, p.seq);
   auto prefetch = [&](int nxt) {
     const int q0 = (qt0 + (MULTI ? pf_it : nxt)) * 64;
     T64::load(qreg, rq, p.ldq, q0, tid);
     T64::load(doreg, rdo, p.lddo, q0, tid);
-    if (tid < 128) {
-      const int qi = q0 + (tid & 63);
-      const long sidx = ((long)b * p.a + pf_h) * p.seq + (qi < p.seq ? qi : 0);
-      const float v = tid < 64 ? -p.lse_in[sidx] / p.scale : -p.delta[sidx];
-      st_reg = qi < p.seq ? v : (tid < 64 ? -3.0e4f : 0.f);   // padded query rows get P = exp(-3e4 scale) = 0
-    }
+    if (w < 2) st_reg = stat_load(rst, q0 + lane);
     if constexpr (MULTI) {
       if (++pf_it == niter) {
         pf_it = 0;
         ++pf_h;
         rq = seq_rsrc(p.q + tok0 * p.ldq + pf_h * D, p.ldq, p.seq, D);      // (past the last head: never loaded from)
         rdo = seq_rsrc(p.dout + tok0 * p.lddo + pf_h * D, p.lddo, p.seq, D);
+        rst = stat_rsrc(p.lse_in, p.delta, w, (long)b * p.a + pf_h, p.seq);
       }
     }
   };
@@ -702,8 +718,7 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_fused_kernel(const AttnArgs 
     __syncthreads();
     T64::template store<LDK>(qreg, Qs, tid);
     T64::template store<LDK>(doreg, dOs, tid);
-    if (tid < 64) *reinterpret_cast<uint4*>(Qs + tid * LDK + D) = split3(st_reg);
-    else if (tid < 128) *reinterpret_cast<uint4*>(dOs + (tid - 64) * LDK + D) = split3(st_reg);
+    if (w < 2) *reinterpret_cast<uint4*>((w == 0 ? Qs : dOs) + lane * LDK + D) = stat_chunk(st_reg, w, (qt0 + it) * 64 + lane < p.seq, p.scale);
     __syncthreads();
     if (ia + 1 < total) prefetch(ia + 1);
     const int q0 = (qt0 + it) * 64;
@@ -884,22 +899,19 @@ __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p
   [[maybe_unused]] int pf_it = 0;
   rsrc_t rq = seq_rsrc(p.q + tok0 * p.ldq + pf_h * D, p.ldq, p.seq, D);
   rsrc_t rdo = seq_rsrc(p.dout + tok0 * p.lddo + pf_h * D, p.lddo, p.seq, D);
+  rsrc_t rst = stat_rsrc(p.lse_in, p.delta, w8, (long)b * p.a + pf_h, p.seq);
   auto prefetch = [&](int nxt) {
     const int q0 = (qt0 + (MULTI ? pf_it : nxt)) * 64;
     T64::load(qreg, rq, p.ldq, q0, tid);
     T64::load(doreg, rdo, p.lddo, q0, tid);
-    if (tid < 128) {
-      const int qi = q0 + (tid & 63);
-      const long sidx = ((long)b * p.a + pf_h) * p.seq + (qi < p.seq ? qi : 0);
-      const float v = tid < 64 ? -p.lse_in[sidx] / p.scale : -p.delta[sidx];
-      st_reg = qi < p.seq ? v : (tid < 64 ? -3.0e4f : 0.f);
-    }
+    if (w8 < 2) st_reg = stat_load(rst, q0 + lane);
     if constexpr (MULTI) {
       if (++pf_it == niter) {
         pf_it = 0;
         ++pf_h;
         rq = seq_rsrc(p.q + tok0 * p.ldq + pf_h * D, p.ldq, p.seq, D);      // (past the last head: never loaded from)
         rdo = seq_rsrc(p.dout + tok0 * p.lddo + pf_h * D, p.lddo, p.seq, D);
+        rst = stat_rsrc(p.lse_in, p.delta, w8, (long)b * p.a + pf_h, p.seq);
       }
     }
   };
@@ -945,8 +957,7 @@ __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p
     bf16* const q_set = smem + (ia & 1) * TSET;
     T64::template store<LDU>(qreg, q_set, tid);
     T64::template store<LDU>(doreg, q_set + 64 * LDU, tid);
-    if (tid < 64) *reinterpret_cast<uint4*>(q_set + tid * LDU + D) = split3(st_reg);
-    else if (tid < 128) *reinterpret_cast<uint4*>(q_set + 64 * LDU + (tid - 64) * LDU + D) = split3(st_reg);
+    if (w8 < 2) *reinterpret_cast<uint4*>(q_set + (64 * w8 + lane) * LDU + D) = stat_chunk(st_reg, w8, (qt0 + it) * 64 + lane < p.seq, p.scale);
     if (ia > 0) partner_update(ia - 1);
     __syncthreads();
     if (ia + 1 < total) prefetch(ia + 1);
