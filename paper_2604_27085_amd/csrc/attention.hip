@@ -26,6 +26,7 @@
 // Launch orders keep an XCD (eight of them, each with its own L2) on few heads: see xcd_head() and the dK/dV kernels.
 #include "common.hpp"
 #include "kernels.hpp"
+#include "gemm.hpp"
 #include <stdlib.h>
 
 namespace {
@@ -45,7 +46,15 @@ struct AttnArgs {
   int fold;   // see heavy_rank()
   int hpw;    // dK/dV kernel: query heads of one group that a workgroup takes one after the other (a divisor of a / kh)
   int kblock; // dK/dV kernel: key tiles per run of one head in an XCD's launch order (0: key-tile-major order over all heads)
+  bf16* ds;   // dK/dV kernel with kept dS: [batch * a] heads of attn_ds_head_bytes each (see attn_ds_block)
 };
+
+// The dK/dV kernel can leave dS (bf16, as its products take it) in memory, from which dQ = dS K is one product instead of the three
+// of the dQ kernel.  A head's dS is a triangle of 64-key x 128-query blocks of 16 KB: a 128-query tile t sees the keys of blocks
+// 0 .. 2t + 1, which lie one after the other.  Inside a block the sixteen 1 KB pieces are what a wave stores at once (32 keys x 16
+// queries: lane l holds eight queries from 8 (l / 32) on of key l % 32), piece (key / 32) * 8 + query / 16.  Block of 64-key tile kt
+// and query tile t:
+RP_DEV int attn_ds_block(int t, int kt) { return t * (t + 1) + kt; }
 
 // Launch position -> rank in the order "heaviest workgroup first".  A kernel that keeps two workgroups per CU and whose
 // grid fits on the chip at once (at most 2 x 256 workgroups) has all of them resident from the start, CU c holding
@@ -818,7 +827,11 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_fused_kernel(const AttnArgs 
 // keys) to its partner through LDS.  Every wave then updates its half of the accumulators with its own 32 queries --
 // before the workgroup barrier that publishes the exchange -- and with the partner's 32 queries after it.  Same number of
 // MFMAs per workgroup as the one-wave-per-SIMD kernel, same LDS fragment traffic per CU, 8 KB of exchange per pair and tile.
-template <int D, bool MULTI>
+// DS: dS is kept as well (see attn_ds_block): a wave stores its 32 keys x 32 queries of every tile, 16 bytes of a key's row per lane
+// after one exchange between the half-waves.  The stores are older than the next tile's loads and overlap the updates: 
+// 8192 tokens, 32 heads 1109 -> 1201 us, 4096 x 16 heads 162 -> 171 (stored past the L2: with ordinary stores, which push the Q and dO
+// tiles out of it, 1215), and dQ 726 -> 506 and 137 -> 80.
+template <int D, bool MULTI, bool DS>
 __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p) {
   const int hpw = MULTI ? p.hpw : 1;
   // One LDS layout serves both kinds of fragment reads, so that every Q and dO tile is stored once: a row stride of
@@ -950,6 +963,9 @@ __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p
     update_half(it_prev & 1, h ^ 1, ppf, pdf);
   };
   int it_cur = 0;                        // query tile of the current head
+  [[maybe_unused]] const uint32_t ds_lane = (uint32_t)((w & 1) * 8192 + h * 2048 + lane * 16);    // where the lane stores in a block
+  [[maybe_unused]] const uint32_t ds_bytes = (uint32_t)attn_ds_block((nQ + 1) / 2, 0) * 16384u;
+  [[maybe_unused]] int ds_h = b * p.a + hg * hpw;
   for (int ia = 0; ia < total; ++ia) {
     const int it = MULTI ? it_cur : ia;
     if constexpr (MULTI) it_cur = it_cur + 1 == niter ? 0 : it_cur + 1;
@@ -1010,6 +1026,21 @@ __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p
     const uint4 dfg[2] = {pack_frag(dp, 0), pack_frag(dp, 8)};
     // the partner read last tile's fragments before the barrier above: the slots are free
     ex_mine[0] = pfg[0]; ex_mine[64] = pfg[1]; ex_mine[128] = dfg[0]; ex_mine[192] = dfg[1];
+    if constexpr (DS) {
+      // a fragment holds, for lane half lk, queries {4lk..4lk+3, 8+4lk..8+4lk+3} of 16: after the exchange 8lk..8lk+7
+      const rsrc_t rds = __builtin_amdgcn_make_buffer_rsrc(p.ds + (size_t)ds_h * (ds_bytes / 2), 0, (int)ds_bytes, 0x00020000);
+      const int j = qt0 + it;
+      const uint32_t at = (uint32_t)attn_ds_block(j >> 1, 2 * kvt + (w >> 1)) * 16384u + (uint32_t)((j & 1) * 4096);
+#pragma unroll
+      for (int f = 0; f < 2; ++f) {
+        typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+        const auto p0 = __builtin_amdgcn_permlane32_swap(dfg[f].x, dfg[f].z, false, false);
+        const auto p1 = __builtin_amdgcn_permlane32_swap(dfg[f].y, dfg[f].w, false, false);
+        const u32x4 o = {p0[0], p1[0], p0[1], p1[1]};
+        __builtin_amdgcn_raw_buffer_store_b128(o, rds, (int)(ds_lane + 1024 * f), (int)at, 2);
+      }
+      if (MULTI && it + 1 == niter) ++ds_h;
+    }
     update_half(ia & 1, h, pfg, dfg);
   }
   __syncthreads();
@@ -1101,17 +1132,18 @@ hipError_t launch_dkv_fused(hipStream_t st, const AttnArgs& p, int grid) {
   return p.hpw > 1 ? launch_dkv_fused_one<D, true>(st, p, grid) : launch_dkv_fused_one<D, false>(st, p, grid);
 }
 
-template <int D, bool MULTI>
+template <int D, bool MULTI, bool DS>
 hipError_t launch_dkv_pair_one(hipStream_t st, const AttnArgs& p, int grid) {
   static bool done = false;
-  hipError_t e = set_smem(attn_bwd_dkv_pair_kernel<D, MULTI>, dkv_pair_smem_bytes(D), done);
+  hipError_t e = set_smem(attn_bwd_dkv_pair_kernel<D, MULTI, DS>, dkv_pair_smem_bytes(D), done);
   if (e != hipSuccess) return e;
-  RP_LAUNCH((attn_bwd_dkv_pair_kernel<D, MULTI>), dim3(grid), dim3(512), dkv_pair_smem_bytes(D), st, p);
+  RP_LAUNCH((attn_bwd_dkv_pair_kernel<D, MULTI, DS>), dim3(grid), dim3(512), dkv_pair_smem_bytes(D), st, p);
   return hipGetLastError();
 }
 template <int D>
 hipError_t launch_dkv_pair(hipStream_t st, const AttnArgs& p, int grid) {
-  return p.hpw > 1 ? launch_dkv_pair_one<D, true>(st, p, grid) : launch_dkv_pair_one<D, false>(st, p, grid);
+  if (p.ds) return p.hpw > 1 ? launch_dkv_pair_one<D, true, true>(st, p, grid) : launch_dkv_pair_one<D, false, true>(st, p, grid);
+  return p.hpw > 1 ? launch_dkv_pair_one<D, true, false>(st, p, grid) : launch_dkv_pair_one<D, false, false>(st, p, grid);
 }
 
 template <int D, int QT, int NW>
@@ -1180,12 +1212,19 @@ int k_attn_dkv_partials(int batch, int seq, int a, int kh, int d) {
   return ah == kh ? 0 : ah;
 }
 
+size_t k_attn_ds_bytes(int seq, int d) {
+  const size_t n = ((size_t)seq + 127) / 128, bytes = n * (n + 1) * 16384;
+  return d == 128 && bytes < ((size_t)1 << 31) ? bytes : 0;     // addressed with 31-bit offsets
+}
+
 hipError_t k_attn_bwd(hipStream_t st, int part, const void* q, const void* k, const void* v, const void* dout,
                       const float* lse, const float* delta, void* dq, void* dk, void* dv, float* scratch, long ldq,
                       long ldk, long ldv, long lddo, long lddq, long lddk, long lddv, int batch, int seq, int a, int kh,
-                      int d) {
+                      int d, void* ds) {
   if (batch * seq == 0) return hipSuccess;
+  if (ds && k_attn_ds_bytes(seq, d) == 0) return hipErrorInvalidValue;
   AttnArgs p = {};
+  p.ds = (bf16*)ds;
   p.q = (const bf16*)q; p.k = (const bf16*)k; p.v = (const bf16*)v; p.dout = (const bf16*)dout;
   p.lse_in = lse; p.delta = delta; p.dq = (bf16*)dq; p.dk = (bf16*)dk; p.dv = (bf16*)dv;
   p.ldq = ldq; p.ldk = ldk; p.ldv = ldv; p.lddo = lddo; p.lddq = lddq; p.lddk = lddk; p.lddv = lddv;
@@ -1217,6 +1256,8 @@ hipError_t k_attn_bwd(hipStream_t st, int part, const void* q, const void* k, co
     }
     if (d == 128) return launch_dkv_pair<128>(st, p, nk);
     return launch_dkv_fused<64>(st, p, nk);   // d = 64: its registers already allow two waves per SIMD
+  } else if (ds) {
+    return gemm_attn_dq(st, ds, k_attn_ds_bytes(seq, d), k, ldk, dq, lddq, batch, seq, a, kh, d, p.scale);
   } else {
     const bool big = (long)((seq + 255) / 256) * a * batch >= 1024;
     if (d == 128 && big) return launch_dq<128, 1, 8>(st, p);

@@ -96,6 +96,9 @@ bool gemm_groupable(const GemmArgs& a);
 hipError_t gemm_group_launch(hipStream_t st, int n, const int* layouts, const GemmArgs* g);
 // The shared launch itself (gemm_mid.hip): arguments prepared, g[i].splits slices each.
 hipError_t gemm_multi_run(hipStream_t st, int n, const int* layouts, const GemmArgs* g);
+// dq [T, a * d] = scale * dS^T k per head, from the blocks of dS that the dK/dV kernel left (attention.hip; head_bytes each, d = 128).
+hipError_t gemm_attn_dq(hipStream_t st, const void* ds, size_t head_bytes, const void* k, long ldk, void* dq, long lddq, int batch, int seq,
+                        int a, int kh, int d, float scale);
 // Tile gemm_launch picks for these arguments: 1..4 = 256x256, 256x128, 128x128, 128x64, 5 = 256x128 with eight waves in two
 // groups that split every K tile, 8 = 64x64.  (A product on tile 1 with a long enough reduction and an output that is not
 // skinny runs gemm_dtl_launch unless tile_hint is 1; hint 7 asks for it by name.)

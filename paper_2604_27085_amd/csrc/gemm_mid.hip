@@ -91,6 +91,17 @@ struct Unit {
       }
     }
   }
+  // the same for a unit that is one 16 KB block of dS (128 columns, see attention.hip)
+  RP_DEV void offsets_ds(uint32_t (&vo)[NL], int w, int lane) {
+    static_assert(TR && X == 128, "the layout of dS");
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int row = (w * NL + i) * RPI + lane / CPR, pos = lane % CPR;
+      const int q = ((pos >> 2) ^ seg_swz(row)) * 32 + (pos & 3) * 8;
+      kidx[i] = row;
+      vo[i] = (uint32_t)(((row >> 5) * 8 + (q >> 4)) * 1024 + ((q >> 3) & 1) * 512 + (row & 31) * 16);
+    }
+  }
   RP_DEV int k_of(int i) const { return kidx[TR ? i : (i & 1)]; }
 };
 
@@ -107,7 +118,8 @@ struct MidCfg {
 };
 
 // One workgroup's tile of one product: tile number `blk` of the product's `tiles`, reduction slice `slice` of `nslices`.
-template <int WGM, int WGN, int KG, int KI, int NST, bool TA, bool TB>
+// ADS: A is a row of blocks of dS.
+template <int WGM, int WGN, int KG, int KI, int NST, bool TA, bool TB, bool ADS = false>
 RP_DEV void mid_block(const GemmArgs& p, int blk, int slice, int nslices) {
   using C = MidCfg<WGM, WGN, KG, KI, NST, TA, TB>;
   using UA = typename C::UA;
@@ -141,7 +153,8 @@ RP_DEV void mid_block(const GemmArgs& p, int blk, int slice, int nslices) {
     const int gl = (n0 >> 1) + (r < BN / 2 ? r : r - BN / 2);
     return gl < fold ? (r < BN / 2 ? gl : fold + gl) : -1;
   };
-  ua.offsets(va, wg, lane, p.lda, a_row);
+  if constexpr (ADS) ua.offsets_ds(va, wg, lane);
+  else ua.offsets(va, wg, lane, p.lda, a_row);
   ub.offsets(vb, wg, lane, p.ldb, b_row);
   i32x4 rsA = raw_rsrc(p.A, p.bytesA), rsB = raw_rsrc(p.B, p.bytesB);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem + (uint32_t)kg * C::SUB;
@@ -444,6 +457,34 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
   else mid_block<1, 1, 4, 1, 2, true, true>(g, blk, slice, q.splits);
 }
 
+// dQ of causal attention from the dS that the dK/dV kernel left: per head and 128-query tile t a product of a [64 (2t + 2), 128]
+// matrix (blocks of dS) with the head's K, reduction over the keys up to the tile's last query.  Heaviest
+// tiles first; an XCD works on neighbouring heads, i.e. on few K/V heads.  Bound by reading dS:
+// 8192 tokens, 32 heads 2.2 GB in 506 us (4.3 TB/s), where the kernel that recomputes the scores takes 726.
+struct AttnDqArgs { const bf16 *ds, *k; bf16* dq; size_t head; long ldk, lddq; int batch, seq, a, kh; float scale; };
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) attn_dq_from_ds_kernel(const AttnDqArgs p) {
+  const int nt = (p.seq + 127) / 128, nhb = p.a * p.batch;
+  const int t = nt - 1 - (int)blockIdx.x / nhb, i = (int)blockIdx.x % nhb;
+  const int hb = (nhb & 7) ? i : (i & 7) * (nhb >> 3) + (i >> 3);
+  const int hq = hb % p.a, b = hb / p.a;
+  const long tok0 = (long)b * p.seq;
+  GemmArgs g{};
+  g.M = p.seq - 128 * t < 128 ? p.seq - 128 * t : 128;
+  g.N = 128;
+  g.K = 128 * t + g.M;                       // the keys up to the tile's last query
+  g.A = p.ds + (size_t)hb * p.head + (size_t)(t * (t + 1)) * 8192;
+  g.lda = 128;
+  g.bytesA = (unsigned)(2 * t + 2) * 16384u;
+  g.B = p.k + tok0 * p.ldk + hq / (p.a / p.kh) * 128;
+  g.ldb = p.ldk;
+  g.bytesB = (unsigned)(((long)(g.K - 1) * p.ldk + 128) * 2);
+  g.C = p.dq + (tok0 + 128 * t) * p.lddq + hq * 128;
+  g.ldc = p.lddq;
+  g.alpha = p.scale;
+  g.epi = EPI_BF16;
+  mid_block<2, 2, 1, 2, 4, true, true, true>(g, 0, 0, 1);
+}
+
 template <int WGM, int WGN, int KG, int KI, int NST, bool TA, bool TB>
 hipError_t mid_launch_one(hipStream_t st, const GemmArgs& a) {
   using C = MidCfg<WGM, WGN, KG, KI, NST, TA, TB>;
@@ -478,6 +519,21 @@ hipError_t gemm_mid_launch(hipStream_t st, const GemmArgs& a, int layout, int ti
     case 8: return mid_launch_layout<1, 1, 4, 1, 2>(st, a, layout);   // 64x64, four waves in four groups
     default: return hipErrorInvalidValue;
   }
+}
+
+hipError_t gemm_attn_dq(hipStream_t st, const void* ds, size_t head_bytes, const void* k, long ldk, void* dq, long lddq, int batch, int seq,
+                        int a, int kh, int d, float scale) {
+  constexpr int SMEM = MidCfg<2, 2, 1, 2, 4, true, true>::SMEM;
+  static bool attr_done = false;
+  if (!attr_done) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_dq_from_ds_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
+    if (e != hipSuccess) return e;
+    attr_done = true;
+  }
+  if (d != 128 || ldk % 8 || lddq % 8 || (long)seq * ldk >= (1L << 30)) return hipErrorInvalidValue;
+  const AttnDqArgs p{(const bf16*)ds, (const bf16*)k, (bf16*)dq, head_bytes / 2, ldk, lddq, batch, seq, a, kh, scale};
+  RP_LAUNCH(attn_dq_from_ds_kernel, dim3((unsigned)((seq + 127) / 128 * a * batch)), dim3(512), SMEM, st, p);
+  return hipGetLastError();
 }
 
 hipError_t gemm_multi_run(hipStream_t st, int n, const int* layouts, const GemmArgs* g) {

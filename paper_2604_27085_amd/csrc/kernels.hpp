@@ -43,7 +43,10 @@ hipError_t k_attn_delta(hipStream_t st, const void* o, const void* dout, float* 
 // floats);  part 2: sum of each group's partials into dk, dv (nothing to do without any);  part 1: dq [T, a, d].
 hipError_t k_attn_bwd(hipStream_t st, int part, const void* q, const void* k, const void* v, const void* dout, const float* lse,
                       const float* delta, void* dq, void* dk, void* dv, float* scratch, long ldq, long ldk, long ldv,
-                      long lddo, long lddq, long lddk, long lddv, int batch, int seq, int a, int kh, int d);
+                      long lddo, long lddq, long lddk, long lddv, int batch, int seq, int a, int kh, int d, void* ds = nullptr);
+// Scratch per query head for parts 0 and 1 with ds: part 0 leaves dS there, from which part 1 makes dq in one product instead of
+// recomputing the scores.  0: not available for this shape (head dimension 64, or a head's dS of 2 GiB and more).
+size_t k_attn_ds_bytes(int seq, int d);
 // Partials of dk (and of dv) per token that part 0 leaves for part 2: one per workgroup's share of a group, 0 when a workgroup
 // takes a whole group and part 2 launches nothing.
 int k_attn_dkv_partials(int batch, int seq, int a, int kh, int d);

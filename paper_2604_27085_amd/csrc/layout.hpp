@@ -127,7 +127,8 @@ struct Plan {
   int moe_max_tiles;             // capacity of the tile table
   size_t split_fwd, split_bwd, h_split;   // partial products of a GEMM reduction split (RP_SPLITK_WS_BYTES each), per plan
   size_t dkvp;   // dK/dV partials of grouped attention (at most one per query head); shares memory with dact|dgu, dead by then
-  size_t fwd_bytes, bwd_bytes;
+  size_t ds;                                      // dS of the attention backward, at the end of the backward plan
+  size_t fwd_bytes, bwd_min, bwd_bytes;           // bwd_min: the plan without dS
   // head
   size_t h_xf, h_rstd, h_part, h_zlab, h_lse, h_coef, h_dzt, h_dxacc, h_partials, head_bytes;
   bool head_keep_p;      // one sweep that keeps all probabilities (see make_plan)
@@ -137,6 +138,17 @@ struct Plan {
   int head_chunk, head_parts;
   LayerBuf lb;                                    // offsets relative to a layer set
 };
+
+// Query heads (over all sequences) of one pass of the attention backward whose dS fits into `bytes`: whole sequences, else within a
+// sequence whole groups of query heads, eight heads at least; 0: none.
+inline int attn_ds_heads(size_t bytes, int batch, int seq, int a, int kh, int d) {
+  const size_t per = k_attn_ds_bytes(seq, d);
+  if (per == 0 || (size_t)seq * kh * d >= ((size_t)1 << 30)) return 0;     // K is addressed with 31-bit offsets too
+  const size_t fit = bytes / per;
+  if (fit >= (size_t)a) return a * (int)(fit / a < (size_t)batch ? fit / a : batch);
+  const int grp = a / kh, unit = grp >= 8 ? grp : (8 + grp - 1) / grp * grp;
+  return (int)(fit / unit) * unit;
+}
 
 // compact: the smallest plan that a call accepts, for a workspace that does not hold the full one.  (The head's chunks are then at
 // most 32768 vocabulary rows and a frozen head keeps the probabilities of one of them only.)
@@ -192,6 +204,11 @@ inline Plan make_plan(const rp_stage_cfg& c, int batch, int seq, bool compact = 
   P.ud = take(T * (size_t)(3 * D.r) * 2);
   P.split_bwd = take(RP_SPLITK_WS_BYTES);
   P.partials = take((size_t)RP_PARTIAL_BLOCKS * (size_t)(D.h > 2 * D.d ? D.h : 2 * D.d) * 4);
+  P.bwd_min = o;
+  // dS of the attention backward (see k_attn_ds_bytes), as many query heads as 4 GiB hold; a workspace that ends before it runs the
+  // dQ kernel that recomputes the scores
+  P.ds = o;
+  if (D.L > 0) take(k_attn_ds_bytes(seq, D.d) * (size_t)attn_ds_heads((size_t)4 << 30, batch, seq, D.a, D.kh, D.d));
   P.bwd_bytes = o;
   // head
   o = 0;

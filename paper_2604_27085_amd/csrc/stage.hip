@@ -171,6 +171,7 @@ struct Exec {
   bool fwd_only = false;           // the forward-stage plan of the workspace is in use (rp_stage_forward)
   size_t split_off = 0;            // scratch for the partial products of a GEMM reduction split, in the plan in use
   bool has_split = false;
+  int ds_heads = 0;                // query heads whose dS the workspace holds (0: the attention backward recomputes the scores for dQ)
   float* router = nullptr;         // router logits of the layer being run, fp32 [T, E] (mixture of experts): read, or
                                    // written first when the stage holds the router weights
   float* d_router = nullptr;       // their gradient (optional)
@@ -473,21 +474,36 @@ void layer_backward(Exec& X, const LayerW& W, const LayerG& G, char* set, const 
              X.at<void>(X.P.dout), S(b.u2));
   RUN(X, "attn_delta", 0, 4.0 * Td * D.qd,
       k_attn_delta(X.st, S(b.o), X.at<void>(X.P.dout), X.at<float>(X.P.delta), D.qd, D.qd, X.batch, X.seq, D.a, D.d));
-  const double s2qd = (double)X.batch * X.seq * (double)X.seq * D.qd;
-  // useful FLOPs per kernel: dK/dV kernel runs S, dP, dV, dK (4 half-masked products), dQ kernel S, dP, dQ (3)
-  static const int parts[3] = {0, 2, 1};
-  static const char* const part_name[3] = {"attn_bwd_dkv", "attn_bwd_dq", "attn_dkv_reduce"};
-  const int n_part = k_attn_dkv_partials(X.batch, X.seq, D.a, D.kh, D.d);
-  for (int i = 0; i < 3; ++i) {
-    const int part = parts[i];
-    if (part == 2 && n_part == 0) continue;
-    const double fl = part == 0 ? 4.0 * s2qd : part == 1 ? 3.0 * s2qd : 0.0;
-    const double by = part == 2 ? Td * (8.0 * n_part * D.d + 4.0 * D.kd) : 2.0 * Td * (3 * D.qd + 4 * D.kd);
-    RUN(X, part_name[part], fl, by,
-        k_attn_bwd(X.st, part, S(b.qr), S(b.kr), qkv + D.qd + D.kd, X.at<void>(X.P.dout), (const float*)S(b.lse),
-                   X.at<float>(X.P.delta), X.at<void>(X.P.dqr), X.at<void>(X.P.dkr), dqkv + D.qd + D.kd,
-                   X.at<float>(X.P.dkvp), D.qd, D.kd, D.n1, D.qd, D.qd, D.kd, D.n1, X.batch, X.seq, D.a, D.kh, D.d));
-  }
+  // In passes over heads (one, unless the dS of all heads exceeds its share of the workspace): sequences [b0, b0 + nb), query heads
+  // [h0, h0 + nh) of them; more than one sequence only with all heads.
+  const int heads = X.ds_heads > 0 ? X.ds_heads : D.a * X.batch;
+  void* const ds = X.ds_heads > 0 ? X.at<void>(X.P.ds) : nullptr;
+  const int nb_all = heads >= D.a ? heads / D.a : 1, nh_all = heads >= D.a ? D.a : heads;
+  for (int b0 = 0; b0 < X.batch; b0 += nb_all)
+    for (int h0 = 0; h0 < D.a; h0 += nh_all) {
+      const int nb = X.batch - b0 < nb_all ? X.batch - b0 : nb_all, nh = D.a - h0 < nh_all ? D.a - h0 : nh_all;
+      const int g0 = h0 / (D.a / D.kh), nkh = nh / (D.a / D.kh);
+      const long t0 = (long)b0 * X.seq, stat = ((long)b0 * D.a + h0) * X.seq;
+      const long qo = t0 * D.qd + (long)h0 * D.d, ko = t0 * D.kd + (long)g0 * D.d, vo = t0 * D.n1 + D.qd + D.kd + (long)g0 * D.d;
+      auto P16 = [](void* p, long o) { return reinterpret_cast<bf16_t*>(p) + o; };
+      const double Tp = (double)nb * X.seq, s2 = Tp * X.seq * (double)(nh * D.d), qdp = nh * D.d, kdp = nkh * D.d;
+      // useful FLOPs per kernel: dK/dV kernel S, dP, dV, dK (4 half-masked products), dQ kernel S, dP, dQ (3), or dQ alone (1) from
+      // the dS that the dK/dV kernel left
+      static const int parts[3] = {0, 2, 1};
+      static const char* const part_name[3] = {"attn_bwd_dkv", "attn_bwd_dq", "attn_dkv_reduce"};
+      const int n_part = k_attn_dkv_partials(nb, X.seq, nh, nkh, D.d);
+      for (int i = 0; i < 3; ++i) {
+        const int part = parts[i];
+        if (part == 2 && n_part == 0) continue;
+        const double fl = part == 0 ? 4.0 * s2 : part == 1 ? (ds ? 1.0 : 3.0) * s2 : 0.0;
+        const double by = part == 2 ? Tp * (8.0 * n_part * D.d + 4.0 * kdp)
+                                    : (ds && part == 1 ? 2.0 * Tp * (qdp + kdp) : 2.0 * Tp * (3 * qdp + 4 * kdp)) + (ds ? Tp * X.seq * nh : 0.0);
+        RUN(X, part_name[part], fl, by,
+            k_attn_bwd(X.st, part, P16(S(b.qr), qo), P16(S(b.kr), ko), qkv + vo, P16(X.at<void>(X.P.dout), qo), (const float*)S(b.lse) + stat,
+                       X.at<float>(X.P.delta) + stat, P16(X.at<void>(X.P.dqr), qo), P16(X.at<void>(X.P.dkr), ko), dqkv + vo,
+                       X.at<float>(X.P.dkvp), D.qd, D.kd, D.n1, D.qd, D.qd, D.kd, D.n1, nb, X.seq, nh, nkh, D.d, ds));
+      }
+    }
   RUN(X, "qknorm_rope_bwd", 0, 6.0 * Td * (D.qd + D.kd),
       k_qknorm_rope(X.st, 1, D.d, X.at<void>(X.P.dqr), X.at<void>(X.P.dkr), D.qd, D.kd, dqkv, dqkv + D.qd, D.n1, D.n1,
                     W.t(RP_T_GQ), W.t(RP_T_GK), (float*)S(b.rstd_q), (float*)S(b.rstd_k), qkv, qkv + D.qd, D.n1,
@@ -723,7 +739,7 @@ rp_status rp_stage_backward(rp_ctx* ctx, int slot_id, int phases, const void* x_
   if (ctx->cfg.n_layers == 0) return fail(ctx, RP_EINVAL, "stage has no decoder layers");
   if (ctx->cfg.n_experts > 0 && !router_logits) return fail(ctx, RP_EINVAL, "MoE stage needs router_logits");
   const Plan P = make_plan(ctx->cfg, batch > 0 ? batch : 1, seq > 0 ? seq : 8);
-  rp_status s = check_call(ctx, slot_id, batch, seq, workspace, workspace_bytes_in, P.bwd_bytes);
+  rp_status s = check_call(ctx, slot_id, batch, seq, workspace, workspace_bytes_in, P.bwd_min);
   if (s != RP_OK) return s;
   if (phases < 1 || phases > 3) return fail(ctx, RP_EINVAL, "phases must be RP_PHASE_RECOMPUTE, RP_PHASE_BACKWARD or both");
   const bool do_fwd = phases & RP_PHASE_RECOMPUTE, do_bwd = phases & RP_PHASE_BACKWARD;
@@ -736,6 +752,7 @@ rp_status rp_stage_backward(rp_ctx* ctx, int slot_id, int phases, const void* x_
   Slot& sl = ctx->slots[slot_id];
   Exec X{ctx, ctx->compute, dims_of(ctx->cfg), batch, seq, (long)batch * seq, static_cast<char*>(workspace), P};
   X.split_off = P.split_bwd; X.has_split = true;
+  X.ds_heads = attn_ds_heads((workspace_bytes_in < P.bwd_bytes ? workspace_bytes_in : P.bwd_bytes) - P.ds, batch, seq, X.D.a, X.D.kh, X.D.d);
   const int L = ctx->cfg.n_layers;
   if (do_fwd) RUN(X, "rope_table", 0, 4.0 * seq * X.D.d, k_rope_table(X.st, X.at<float2>(P.rope), seq, X.D.d, ctx->cfg.rope_base));
   auto set_of = [&](int l) { return X.ws + P.layer0 + P.layer_stride * (size_t)l; };
@@ -1178,7 +1195,7 @@ rp_status round_run(rp_ctx* ctx, int slot_id, const rp_round_io* io, bool backwa
   const int M = io->n_micro;
   if (M < 1 || M > 256) return fail(ctx, RP_EINVAL, "n_micro must be in [1, 256]");
   const Plan P = make_plan(ctx->cfg, batch > 0 ? batch : 1, seq > 0 ? seq : 8);
-  rp_status s = check_call(ctx, slot_id, batch, seq, workspace, workspace_bytes_in, backward ? P.bwd_bytes : P.fwd_bytes);
+  rp_status s = check_call(ctx, slot_id, batch, seq, workspace, workspace_bytes_in, backward ? P.bwd_min : P.fwd_bytes);
   if (s != RP_OK) return s;
   if (!io->x_host || !io->out_host || (backward && !io->dy_host)) return fail(ctx, RP_EINVAL, "host activation arrays must be non-NULL");
   for (int j = 0; j < M; ++j)
