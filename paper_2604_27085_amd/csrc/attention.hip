@@ -38,7 +38,8 @@ struct AttnArgs {
   bf16 *o, *dq, *dk, *dv;
   float* lse;
   const float* lse_in;
-  const float* delta;
+  float* delta;               // read, or (dQ kernel with o_in) worked out and written first
+  const bf16* o_in;           // dQ kernel: the forward's output, delta = rowsum(dO * O) comes from it; or NULL
   float *dk_part, *dv_part;   // fp32 [T, a / hpw * d] partials of the dK/dV kernel unless a workgroup takes a whole group
   long ldq, ldk, ldv, ldo, lddo, lddq, lddk, lddv;
   int batch, seq, a, kh;
@@ -500,7 +501,22 @@ __global__ void __launch_bounds__(NW * 64, (QT == 1 && NW <= 4) ? 2 : 1) attn_bw
     }
     const long stat = ((long)b * p.a + hq) * p.seq + qpos;
     lse2[t] = qok ? p.lse_in[stat] * 1.4426950408889634f : INFINITY;   // padded rows get P = 0
-    dl[t] = qok ? p.delta[stat] : 0.f;
+    if (p.o_in) {   // uniform: this wave is the only one that holds the row's dO, so delta costs one read of O and no kernel
+      float s = 0.f;
+      if (qok) {
+        const bf16* orow = p.o_in + (tok0 + qpos) * p.ldo + hq * D + 8 * lk;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          const uint4 u = *reinterpret_cast<const uint4*>(orow + 16 * ks), d = dof[t][ks];
+          s += bf16_lo(u.x) * bf16_lo(d.x) + bf16_hi(u.x) * bf16_hi(d.x) + bf16_lo(u.y) * bf16_lo(d.y) + bf16_hi(u.y) * bf16_hi(d.y) +
+               bf16_lo(u.z) * bf16_lo(d.z) + bf16_hi(u.z) * bf16_hi(d.z) + bf16_lo(u.w) * bf16_lo(d.w) + bf16_hi(u.w) * bf16_hi(d.w);
+        }
+      }
+      dl[t] = s + __shfl_xor(s, 32, 64);
+      if (qok && lk == 0) p.delta[stat] = dl[t];
+    } else {
+      dl[t] = qok ? p.delta[stat] : 0.f;
+    }
   }
 
   const int kv_end = (q0 + BQ < p.seq) ? (q0 + BQ) : p.seq;
@@ -1218,13 +1234,13 @@ size_t k_attn_ds_bytes(int seq, int d) {
 }
 
 hipError_t k_attn_bwd(hipStream_t st, int part, const void* q, const void* k, const void* v, const void* dout,
-                      const float* lse, const float* delta, void* dq, void* dk, void* dv, float* scratch, long ldq,
+                      const float* lse, float* delta, void* dq, void* dk, void* dv, float* scratch, long ldq,
                       long ldk, long ldv, long lddo, long lddq, long lddk, long lddv, int batch, int seq, int a, int kh,
-                      int d, void* ds) {
+                      int d, void* ds, const void* o, long ldo) {
   if (batch * seq == 0) return hipSuccess;
   if (ds && k_attn_ds_bytes(seq, d) == 0) return hipErrorInvalidValue;
   AttnArgs p = {};
-  p.ds = (bf16*)ds;
+  p.ds = (bf16*)ds; p.o_in = (const bf16*)o; p.ldo = ldo;
   p.q = (const bf16*)q; p.k = (const bf16*)k; p.v = (const bf16*)v; p.dout = (const bf16*)dout;
   p.lse_in = lse; p.delta = delta; p.dq = (bf16*)dq; p.dk = (bf16*)dk; p.dv = (bf16*)dv;
   p.ldq = ldq; p.ldk = ldk; p.ldv = ldv; p.lddo = lddo; p.lddq = lddq; p.lddk = lddk; p.lddv = lddv;

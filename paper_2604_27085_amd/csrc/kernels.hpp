@@ -41,9 +41,11 @@ hipError_t k_attn_delta(hipStream_t st, const void* o, const void* dout, float* 
                         int seq, int a, int d);
 // part 0: dk, dv [T, kh, d] (lddk, lddv) when k_attn_dkv_partials is 0, else fp32 partials into scratch (at most 2*T*a*d
 // floats);  part 2: sum of each group's partials into dk, dv (nothing to do without any);  part 1: dq [T, a, d].
+// o (without ds): part 1 works out delta = rowsum(dO * O) itself and writes it; it then comes before part 0.  Else delta is read.
 hipError_t k_attn_bwd(hipStream_t st, int part, const void* q, const void* k, const void* v, const void* dout, const float* lse,
-                      const float* delta, void* dq, void* dk, void* dv, float* scratch, long ldq, long ldk, long ldv,
-                      long lddo, long lddq, long lddk, long lddv, int batch, int seq, int a, int kh, int d, void* ds = nullptr);
+                      float* delta, void* dq, void* dk, void* dv, float* scratch, long ldq, long ldk, long ldv,
+                      long lddo, long lddq, long lddk, long lddv, int batch, int seq, int a, int kh, int d, void* ds = nullptr,
+                      const void* o = nullptr, long ldo = 0);
 // Scratch per query head for parts 0 and 1 with ds: part 0 leaves dS there, from which part 1 makes dq in one product instead of
 // recomputing the scores.  0: not available for this shape (head dimension 64, or a head's dS of 2 GiB and more).
 size_t k_attn_ds_bytes(int seq, int d);

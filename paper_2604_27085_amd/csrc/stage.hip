@@ -472,12 +472,14 @@ void layer_backward(Exec& X, const LayerW& W, const LayerG& G, char* set, const 
   // y = x + o_proj(o)
   linear_bwd(X, W, G, RP_T_WO, fused_single(D.lora[3], RP_T_LA_O, RP_T_LB_O, D.h), 0, dy, D.h, S(b.o), D.qd,
              X.at<void>(X.P.dout), S(b.u2));
-  RUN(X, "attn_delta", 0, 4.0 * Td * D.qd,
-      k_attn_delta(X.st, S(b.o), X.at<void>(X.P.dout), X.at<float>(X.P.delta), D.qd, D.qd, X.batch, X.seq, D.a, D.d));
   // In passes over heads (one, unless the dS of all heads exceeds its share of the workspace): sequences [b0, b0 + nb), query heads
   // [h0, h0 + nh) of them; more than one sequence only with all heads.
   const int heads = X.ds_heads > 0 ? X.ds_heads : D.a * X.batch;
   void* const ds = X.ds_heads > 0 ? X.at<void>(X.P.ds) : nullptr;
+  // (without dS the dQ kernel comes first and works delta out)
+  if (ds)
+    RUN(X, "attn_delta", 0, 4.0 * Td * D.qd,
+        k_attn_delta(X.st, S(b.o), X.at<void>(X.P.dout), X.at<float>(X.P.delta), D.qd, D.qd, X.batch, X.seq, D.a, D.d));
   const int nb_all = heads >= D.a ? heads / D.a : 1, nh_all = heads >= D.a ? D.a : heads;
   for (int b0 = 0; b0 < X.batch; b0 += nb_all)
     for (int h0 = 0; h0 < D.a; h0 += nh_all) {
@@ -489,7 +491,8 @@ void layer_backward(Exec& X, const LayerW& W, const LayerG& G, char* set, const 
       const double Tp = (double)nb * X.seq, s2 = Tp * X.seq * (double)(nh * D.d), qdp = nh * D.d, kdp = nkh * D.d;
       // useful FLOPs per kernel: dK/dV kernel S, dP, dV, dK (4 half-masked products), dQ kernel S, dP, dQ (3), or dQ alone (1) from
       // the dS that the dK/dV kernel left
-      static const int parts[3] = {0, 2, 1};
+      static const int order[2][3] = {{1, 0, 2}, {0, 2, 1}};
+      const int* const parts = order[ds ? 1 : 0];
       static const char* const part_name[3] = {"attn_bwd_dkv", "attn_bwd_dq", "attn_dkv_reduce"};
       const int n_part = k_attn_dkv_partials(nb, X.seq, nh, nkh, D.d);
       for (int i = 0; i < 3; ++i) {
@@ -497,11 +500,11 @@ void layer_backward(Exec& X, const LayerW& W, const LayerG& G, char* set, const 
         if (part == 2 && n_part == 0) continue;
         const double fl = part == 0 ? 4.0 * s2 : part == 1 ? (ds ? 1.0 : 3.0) * s2 : 0.0;
         const double by = part == 2 ? Tp * (8.0 * n_part * D.d + 4.0 * kdp)
-                                    : (ds && part == 1 ? 2.0 * Tp * (qdp + kdp) : 2.0 * Tp * (3 * qdp + 4 * kdp)) + (ds ? Tp * X.seq * nh : 0.0);
+                                    : (ds && part == 1 ? 2.0 * Tp * (qdp + kdp) : 2.0 * Tp * ((ds || part == 0 ? 3 : 4) * qdp + 4 * kdp)) + (ds ? Tp * X.seq * nh : 0.0);
         RUN(X, part_name[part], fl, by,
             k_attn_bwd(X.st, part, P16(S(b.qr), qo), P16(S(b.kr), ko), qkv + vo, P16(X.at<void>(X.P.dout), qo), (const float*)S(b.lse) + stat,
                        X.at<float>(X.P.delta) + stat, P16(X.at<void>(X.P.dqr), qo), P16(X.at<void>(X.P.dkr), ko), dqkv + vo,
-                       X.at<float>(X.P.dkvp), D.qd, D.kd, D.n1, D.qd, D.qd, D.kd, D.n1, nb, X.seq, nh, nkh, D.d, ds));
+                       X.at<float>(X.P.dkvp), D.qd, D.kd, D.n1, D.qd, D.qd, D.kd, D.n1, nb, X.seq, nh, nkh, D.d, ds, ds ? nullptr : P16(S(b.o), qo), D.qd));
       }
     }
   RUN(X, "qknorm_rope_bwd", 0, 6.0 * Td * (D.qd + D.kd),
@@ -1139,11 +1142,13 @@ rp_status rp_op_attn_bwd(void* stream, const void* q, const void* k, const void*
   if (a != kh && !scratch) return fail(nullptr, RP_EINVAL, "rp_op_attn_bwd: grouped queries need the scratch buffer");
   if (ldq % 8 || ldk % 8 || ldv % 8 || ldo % 8 || lddo % 8 || lddq % 8 || lddk % 8 || lddv % 8) return fail(nullptr, RP_EINVAL, "rp_op_attn_bwd: strides must be multiples of 8");
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  hipError_t e = k_attn_delta(st, o, dout, delta, ldo, lddo, batch, seq, a, d);
-  static const int parts[3] = {0, 2, 1};
+  // dQ first, with delta in passing, unless dq takes the place of something that the dK/dV kernel still reads
+  const bool in_place = dq == q || dq == dout || dq == o;
+  hipError_t e = in_place ? k_attn_delta(st, o, dout, delta, ldo, lddo, batch, seq, a, d) : hipSuccess;
+  static const int order[2][3] = {{1, 0, 2}, {0, 2, 1}};
   for (int i = 0; i < 3 && e == hipSuccess; ++i)
-    e = k_attn_bwd(st, parts[i], q, k, v, dout, lse, delta, dq, dk, dv, scratch, ldq, ldk, ldv, lddo, lddq, lddk, lddv, batch, seq,
-                   a, kh, d);
+    e = k_attn_bwd(st, order[in_place][i], q, k, v, dout, lse, delta, dq, dk, dv, scratch, ldq, ldk, ldv, lddo, lddq, lddk, lddv, batch, seq,
+                   a, kh, d, nullptr, in_place ? nullptr : o, ldo);
   OP_RET(e);
 }
 

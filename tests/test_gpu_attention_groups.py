@@ -63,3 +63,34 @@ def test_heads_per_workgroup(batch, seq, a, kh, d):
                 nrm[n] += float(y.square().sum())
     for n, name in enumerate(("o", "dq", "dk", "dv")):
         assert math.sqrt(err[n] / nrm[n]) < 5e-3, name
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_backward_in_place(d):
+    """dq in the place of q or of the output's gradient: delta comes from a kernel of its own and dQ last, with the same result but
+    for the rounding of delta's sum (2^-24 of each term, far below the bf16 step of dS)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_27085_amd import binding as B
+    b, n, a, kh = 2, 200, 4, 2
+    g = torch.Generator(device="cuda:0").manual_seed(5)
+    mk = lambda k: torch.empty((b * n, k, d), dtype=torch.bfloat16, device="cuda:0").normal_(0.0, 1.0, generator=g)  # noqa: E731
+    q, k, v, do = mk(a), mk(kh), mk(kh), mk(a)
+    o, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
+    lse = torch.empty((b, a, n), dtype=torch.float32, device="cuda:0")
+    scratch = torch.empty((2, b * n, a, d), dtype=torch.float32, device="cuda:0")
+    st = torch.cuda.current_stream().cuda_stream
+    B.rp_op_attn_fwd(st, q, k, v, o, lse, a * d, kh * d, kh * d, a * d, b, n, a, kh, d)
+    want = None
+    for place in ("own", "q", "do"):
+        q1, do1, delta = q.clone(), do.clone(), torch.full_like(lse, float("nan"))
+        dq = dict(own=torch.empty_like(q), q=q1, do=do1)[place]
+        B.rp_op_attn_bwd(st, q1, k, v, o, do1, lse, delta, dq, dk, dv, scratch, a * d, kh * d, kh * d, a * d, a * d, a * d, kh * d, kh * d,
+                         b, n, a, kh, d)
+        torch.cuda.synchronize()
+        got = [t.double().clone() for t in (dq, dk, dv, delta)]
+        ref = (do.double() * o.double()).sum(-1).view(b, n, a).transpose(1, 2)
+        assert float((got[3] - ref).norm() / ref.norm()) < 1e-6
+        want = want or got
+        for x, y in zip(got[:3], want):
+            assert float((x - y).norm() / y.norm()) < 1e-3
