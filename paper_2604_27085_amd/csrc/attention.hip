@@ -1183,10 +1183,12 @@ hipError_t launch_dq(hipStream_t st, const AttnArgs& p) {
 //            621 | 562 (.47) | 537 (.94);  4096 x 32: 529 | 516 (.97)
 //   d = 64 (two workgroups share a CU, a chain runs at half the pace): 3 x 1500 x 64: 306 | 285 (.41) | 297 (.82);
 //            8192 x 64: 1996 | 1937 (.25) | 2014 (.49);  2048 x 64: 170 | 180 (.94)
+// A few tokens of two-head groups take both heads as well (128 tokens: 3 us more of chain, 7 us less of partials and their launch).
 // Orders by runs of key tiles (from 96 tiles on, see k_attn_bwd) keep one head: 16384 x 64 at four heads is 3 % slower.
 int heads_per_workgroup(int seq, int batch, int a, int kh, int d) {
   const long nkv = (seq + 127) / 128;
   const double per_cu = (double)a * batch * nkv * (nkv + 1) / 256.0, most = d == 128 ? 1.0 : 0.45;
+  if (a == 2 * kh && nkv <= 2) return 2;
   int hpw = 1;
   while (nkv < 96 && hpw < 4 && (a / kh) % (2 * hpw) == 0 && 2.0 * hpw * 2.0 * nkv <= most * per_cu) hpw *= 2;
   return hpw;

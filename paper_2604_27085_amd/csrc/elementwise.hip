@@ -13,13 +13,36 @@ RP_DEV uint4 pack8(const float (&f)[8]) {
   return make_uint4(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7]));
 }
 
+// ------------------------------------------------------------------------------------------------ RoPE table
+// cs[p][i] = (cos, sin)(p * base^(-2i/d)), evaluated in double so that long sequences keep full fp32 accuracy.
+struct RopeTable { float2* cs; int seq, half; double log2_base; };
+RP_DEV void rope_entry(const RopeTable& r, long idx) {
+  if (idx >= (long)r.seq * r.half) return;
+  const int p = (int)(idx / r.half), i = (int)(idx - (long)p * r.half);
+  const double theta = exp2(-(double)i / (double)r.half * r.log2_base);
+  const double phi = (double)p * theta;
+  double s, c;
+  sincos(phi, &s, &c);
+  r.cs[idx] = make_float2((float)c, (float)s);
+}
+__global__ void __launch_bounds__(256) rope_table_kernel(const RopeTable r) { rope_entry(r, (long)blockIdx.x * 256 + threadIdx.x); }
+
 // ------------------------------------------------------------------------------------------------ RMSNorm forward
 // One wave per row, the row lives in registers between the sum of squares and the scaling.  MAXC = 16-byte chunks
 // per lane (h <= 512*MAXC).
-template <int MAXC>
+// ROPE: the blocks past the rows fill the stage's RoPE table, which the kernel after next reads: one launch less per stage (4 of the
+// 165 us of a forward stage of 1000 tokens at h = 2048).
+template <int MAXC, bool ROPE>
 __global__ void __launch_bounds__(256) rmsnorm_fwd_kernel(const bf16* __restrict__ x, const bf16* __restrict__ g,
                                                           bf16* __restrict__ y, float* __restrict__ rstd_out, int T,
-                                                          int h, float eps) {
+                                                          int h, float eps, const RopeTable rope) {
+  if constexpr (ROPE) {
+    const int row_blocks = (T + 3) / 4;
+    if ((int)blockIdx.x >= row_blocks) {
+      rope_entry(rope, (long)((int)blockIdx.x - row_blocks) * 256 + threadIdx.x);
+      return;
+    }
+  }
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= T) return;
@@ -65,11 +88,13 @@ __global__ void __launch_bounds__(256) rmsnorm_fwd_kernel(const bf16* __restrict
 // One BLOCK per row: the four waves split the row's columns (chunk (4i + wave)*64 + lane, i < MAXC, so
 // h <= 2048*MAXC), the row's dot product crosses the waves through LDS (one barrier per row), and every lane owns its
 // columns for all the rows of the block, so the gain-gradient partial is written straight from registers.
-template <int MAXC, int NR, typename DyT>
+// CE (fp32 dy): the head's norm.  dy holds acc_t = sum_v p_tv W_v, and what arrives at the norm is coef_t (acc_t / l_t - W[label_t])
+// (zero where coef_t is; a label outside the vocabulary has no logit to subtract).
+template <int MAXC, int NR, typename DyT, bool CE>
 __global__ void __launch_bounds__(256) rmsnorm_bwd_kernel(const DyT* __restrict__ dy, const bf16* __restrict__ x,
                                                                const bf16* __restrict__ g, const float* __restrict__ rstd_in,
                                                                const bf16* __restrict__ dres, bf16* __restrict__ dx,
-                                                               float* __restrict__ part, int T, int h) {
+                                                               float* __restrict__ part, int T, int h, const CeRows ce) {
   // NR rows per trip (rows r, r + gridDim.x, ...): NR times the loads in flight per thread and one barrier for all of
   // them, against NR times the registers (measured: two rows win at h = 5120, 145 against 181 us for 16384 rows, and
   // lose at h = 4096, where they halve the waves per SIMD).
@@ -95,6 +120,16 @@ __global__ void __launch_bounds__(256) rmsnorm_bwd_kernel(const DyT* __restrict_
       const bool rok = row < T;
       rstd[r] = rok ? rstd_in[row] : 0.f;
       dot[r] = 0.f;
+      [[maybe_unused]] float ce_c = 0.f, ce_il = 0.f;
+      [[maybe_unused]] const uint4* ce_w = nullptr;
+      if constexpr (CE) {
+        if (rok) {
+          ce_c = ce.coef[row];
+          ce_il = ce_c / ce.l[row];
+          const int lab = ce.labels[row];
+          if (lab >= 0 && lab < ce.V) ce_w = reinterpret_cast<const uint4*>(static_cast<const bf16*>(ce.W) + (long)lab * h);
+        }
+      }
 #pragma unroll
       for (int i = 0; i < MAXC; ++i) {
         const int c = (4 * i + wave) * 64 + lane;
@@ -108,6 +143,12 @@ __global__ void __launch_bounds__(256) rmsnorm_bwd_kernel(const DyT* __restrict_
             const float4 a = dr[0], b = dr[1];
             dyv[r][i][0] = a.x; dyv[r][i][1] = a.y; dyv[r][i][2] = a.z; dyv[r][i][3] = a.w;
             dyv[r][i][4] = b.x; dyv[r][i][5] = b.y; dyv[r][i][6] = b.z; dyv[r][i][7] = b.w;
+            if constexpr (CE) {
+              float wv[8];
+              unpack8(ce_w ? ce_w[c] : make_uint4(0u, 0u, 0u, 0u), wv);
+#pragma unroll
+              for (int e = 0; e < 8; ++e) dyv[r][i][e] = ce_c == 0.f ? 0.f : dyv[r][i][e] * ce_il - ce_c * wv[e];
+            }
           } else {
             unpack8(reinterpret_cast<const uint4*>(dy + (long)row * h)[c], dyv[r][i]);
           }
@@ -165,14 +206,19 @@ __global__ void __launch_bounds__(256) rmsnorm_bwd_kernel(const DyT* __restrict_
   }
 }
 
-// dst[c] += sum_r part[r][c], r = 0..rows-1 (columns from cols1 on go to dst2).  A block owns 64 columns; its sixteen
+// dst[c] += sum_r part[r][c], r = 0..rows-1 (columns from cols1 on go to dst2), for up to three arrays of partials: a layer's three
+// gain gradients take one launch (its 2.5 us is mostly the launch).  A block owns 64 columns of one array; its sixteen
 // waves each sum every sixteenth row (four independent loads in flight per thread) and the slices are merged in LDS in
 // a fixed order.
-__global__ void __launch_bounds__(1024) colsum_add_kernel(const float* __restrict__ part, int rows, int ld, int cols,
-                                                          float* __restrict__ dst, int cols1, float* __restrict__ dst2) {
+__global__ void __launch_bounds__(1024) colsum_add_kernel(const ColSums q) {
+  int k = 0;
+  while (k + 1 < q.n && (int)blockIdx.x >= q.s[k + 1].first) ++k;
+  const ColSum& m = q.s[__builtin_amdgcn_readfirstlane(k)];
+  const float* const part = m.part;
+  const int rows = m.rows, cols = m.cols, ld = m.cols, cols1 = m.cols1;
   __shared__ float red[16][64];
   const int cl = threadIdx.x & 63, sl = threadIdx.x >> 6;
-  const int c = blockIdx.x * 64 + cl;
+  const int c = ((int)blockIdx.x - m.first) * 64 + cl;
   float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
   if (c < cols) {
     int r = sl;
@@ -190,21 +236,8 @@ __global__ void __launch_bounds__(1024) colsum_add_kernel(const float* __restric
     float t = 0.f;
 #pragma unroll
     for (int k = 0; k < 16; ++k) t += red[k][cl];
-    if (c < cols1) dst[c] += t; else dst2[c - cols1] += t;
+    if (c < cols1) m.dst[c] += t; else m.dst2[c - cols1] += t;
   }
-}
-
-// ------------------------------------------------------------------------------------------------ RoPE table
-// cs[p][i] = (cos, sin)(p * base^(-2i/d)), evaluated in double so that long sequences keep full fp32 accuracy.
-__global__ void rope_table_kernel(float2* __restrict__ cs, int seq, int half, double log2_base) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= seq * half) return;
-  const int p = idx / half, i = idx - p * half;
-  const double theta = exp2(-(double)i / (double)half * log2_base);
-  const double phi = (double)p * theta;
-  double s, c;
-  sincos(phi, &s, &c);
-  cs[idx] = make_float2((float)c, (float)s);
 }
 
 // ------------------------------------------------------------------------------------------------ QK-norm + RoPE
@@ -446,48 +479,75 @@ int grid_for(long n, int block = 256, int cap = 256 * 16) {
 }  // namespace
 
 // ------------------------------------------------------------------------------------------------ launchers
-hipError_t k_rmsnorm_fwd(hipStream_t st, const void* x, const void* g, void* y, float* rstd, int T, int h, float eps) {
+hipError_t k_rmsnorm_fwd(hipStream_t st, const void* x, const void* g, void* y, float* rstd, int T, int h, float eps, float2* cs, int seq,
+                         int d, float base) {
   const int grid = (T + 3) / 4;
   if (grid == 0) return hipSuccess;
-  if (h <= 2048)
-    RP_LAUNCH((rmsnorm_fwd_kernel<4>), dim3(grid), dim3(256), 0, st, (const bf16*)x, (const bf16*)g, (bf16*)y, rstd, T, h, eps);
-  else
-    RP_LAUNCH((rmsnorm_fwd_kernel<16>), dim3(grid), dim3(256), 0, st, (const bf16*)x, (const bf16*)g, (bf16*)y, rstd, T, h, eps);
+  const RopeTable rope{cs, seq, d / 2, cs ? log2((double)base) : 0.0};
+  const int more = cs ? (int)(((long)seq * (d / 2) + 255) / 256) : 0;
+#define RP_LAUNCH_RF(MAXC, ROPE) \
+  RP_LAUNCH((rmsnorm_fwd_kernel<MAXC, ROPE>), dim3(grid + more), dim3(256), 0, st, (const bf16*)x, (const bf16*)g, (bf16*)y, rstd, T, h, eps, rope)
+  if (h <= 2048) { if (cs) RP_LAUNCH_RF(4, true); else RP_LAUNCH_RF(4, false); }
+  else { if (cs) RP_LAUNCH_RF(16, true); else RP_LAUNCH_RF(16, false); }
+#undef RP_LAUNCH_RF
   return hipGetLastError();
 }
 
+hipError_t k_colsum_add(hipStream_t st, const ColSums& q) {
+  int blocks = 0;
+  ColSums a = q;
+  for (int i = 0; i < a.n; ++i) { a.s[i].first = blocks; blocks += (a.s[i].cols + 63) / 64; }
+  if (blocks == 0) return hipSuccess;
+  RP_LAUNCH(colsum_add_kernel, dim3(blocks), dim3(1024), 0, st, a);
+  return hipGetLastError();
+}
+
+// Adds the partials now, or leaves them to a later k_colsum_add.
+static hipError_t colsum_or_defer(hipStream_t st, ColSums* defer, const ColSum& c) {
+  if (defer) {
+    if (defer->n >= ColSums::MAX) return hipErrorInvalidValue;
+    defer->s[defer->n++] = c;
+    return hipSuccess;
+  }
+  ColSums q{};
+  q.n = 1;
+  q.s[0] = c;
+  return k_colsum_add(st, q);
+}
+
 hipError_t k_rmsnorm_bwd(hipStream_t st, const void* dy, int dy_is_f32, const void* x, const void* g, const float* rstd,
-                         const void* dres, void* dx, float* dg, float* scratch, int T, int h) {
+                         const void* dres, void* dx, float* dg, float* scratch, int T, int h, ColSums* defer, const CeRows* ce) {
   if (T == 0) return hipSuccess;
-  if (dg && !scratch) return hipErrorInvalidValue;
+  if ((dg && !scratch) || (ce && !dy_is_f32)) return hipErrorInvalidValue;
   const int grid = T < RP_PARTIAL_BLOCKS ? T : RP_PARTIAL_BLOCKS;
   float* part = dg ? scratch : nullptr;
-#define RP_LAUNCH_RR(MAXC, NR, DT) \
-  RP_LAUNCH((rmsnorm_bwd_kernel<MAXC, NR, DT>), dim3(grid), dim3(256), 0, st, (const DT*)dy, (const bf16*)x, \
-                     (const bf16*)g, rstd, (const bf16*)dres, (bf16*)dx, part, T, h)
-  if (h <= 2048) { if (dy_is_f32) RP_LAUNCH_RR(1, 2, float); else RP_LAUNCH_RR(1, 2, bf16); }
-  else if (h <= 4096) { if (dy_is_f32) RP_LAUNCH_RR(2, 1, float); else RP_LAUNCH_RR(2, 1, bf16); }
-  else { if (dy_is_f32) RP_LAUNCH_RR(4, 2, float); else RP_LAUNCH_RR(4, 2, bf16); }
+  const CeRows cr = ce ? *ce : CeRows{};
+#define RP_LAUNCH_RR(MAXC, NR, DT, CE) \
+  RP_LAUNCH((rmsnorm_bwd_kernel<MAXC, NR, DT, CE>), dim3(grid), dim3(256), 0, st, (const DT*)dy, (const bf16*)x, \
+                     (const bf16*)g, rstd, (const bf16*)dres, (bf16*)dx, part, T, h, cr)
+#define RP_LAUNCH_RD(MAXC, NR) \
+  do { if (ce) RP_LAUNCH_RR(MAXC, NR, float, true); else if (dy_is_f32) RP_LAUNCH_RR(MAXC, NR, float, false); else RP_LAUNCH_RR(MAXC, NR, bf16, false); } while (0)
+  if (h <= 2048) RP_LAUNCH_RD(1, 2);
+  else if (h <= 4096) RP_LAUNCH_RD(2, 1);
+  else RP_LAUNCH_RD(4, 2);
+#undef RP_LAUNCH_RD
 #undef RP_LAUNCH_RR
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess && dg) {
-    RP_LAUNCH(colsum_add_kernel, dim3((h + 63) / 64), dim3(1024), 0, st, part, grid, h, h, dg, h, (float*)nullptr);
-    e = hipGetLastError();
-  }
-  return e;
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !dg) return e;
+  return colsum_or_defer(st, defer, ColSum{part, dg, nullptr, grid, h, h, 0});
 }
 
 hipError_t k_rope_table(hipStream_t st, float2* cs, int seq, int d, float base) {
   const int n = seq * (d / 2);
   if (n == 0) return hipSuccess;
-  RP_LAUNCH(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, st, cs, seq, d / 2, log2((double)base));
+  RP_LAUNCH(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, st, RopeTable{cs, seq, d / 2, log2((double)base)});
   return hipGetLastError();
 }
 
 hipError_t k_qknorm_rope(hipStream_t st, int bwd, int d, const void* in_q, const void* in_k, long ld_in_q, long ld_in_k,
                          void* out_q, void* out_k, long ld_out_q, long ld_out_k, const void* gq, const void* gk,
                          float* rstd_q, float* rstd_k, const void* raw_q, const void* raw_k, long ld_raw, float* dgq,
-                         float* dgk, float* scratch, const float2* cs, int T, int seq, int a, int k, int use_norm, float eps) {
+                         float* dgk, float* scratch, const float2* cs, int T, int seq, int a, int k, int use_norm, float eps, ColSums* defer) {
   if (T == 0) return hipSuccess;
   const int nthr = 256;
   int grid = (T + nthr / 64 - 1) / (nthr / 64);
@@ -503,12 +563,9 @@ hipError_t k_qknorm_rope(hipStream_t st, int bwd, int d, const void* in_q, const
   else if (d == 64) { if (bwd) RP_LAUNCH_QR(64, true); else RP_LAUNCH_QR(64, false); }
   else return hipErrorInvalidValue;
 #undef RP_LAUNCH_QR
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess && want_dg) {
-    RP_LAUNCH(colsum_add_kernel, dim3((2 * d + 63) / 64), dim3(1024), 0, st, part, grid, 2 * d, 2 * d, dgq, d, dgk);
-    e = hipGetLastError();
-  }
-  return e;
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !want_dg) return e;
+  return colsum_or_defer(st, defer, ColSum{part, dgq, dgk, grid, 2 * d, d, 0});
 }
 
 hipError_t k_swiglu_fwd(hipStream_t st, const void* gu, void* act, long T, int m) {

@@ -458,8 +458,8 @@ __global__ void __launch_bounds__(256) gemm_arrange_kernel(const bf16* __restric
 //     of the chip is busy;
 //   - the small tiles are bound by what a CU can fetch -- 50 bytes/ns of data that comes from HBM, however many loads are
 //     in flight (80 from the Infinity Cache, 150 from L2) -- so their K tile costs its operand bytes.
-// A split into `splits` slices adds the merge kernel and its traffic, which for accumulating outputs (the large ones) is chip time as
-// well: 2040 x 5120 x 151936 TN in eight slices or three, frozen head on one stream 5175 | 5150 us, on three 5385 | 5310; the bf16
+// A split into `splits` slices adds the merge kernel and its traffic, which for accumulating outputs is chip time as well from 64 MB
+// on, what the caches do not hold: 2040 x 5120 x 151936 TN in eight slices or three, frozen head on one stream 5175 | 5150 us, on three 5385 | 5310; the bf16
 // results of short batches are 2-3 % slower with fewer slices.  Added to the elapsed time is the chip time the
 // workgroups use up (their summed time over 256 CUs): what is left over belongs to other streams, so a small tile has to buy
 // enough latency for the extra operand traffic it causes.  The weight of that term, both ends measured on whole stage calls,
@@ -487,7 +487,10 @@ double tile_cost(int tile, int splits, int M, int N, int k_tiles, int epi) {
   }
   const int per = (k_tiles + splits - 1) / splits;
   double us = 3.0 + rounds * (per * tau + t.epi) + CHIP_WEIGHT * wg / 256.0 * (per * (tau + t.tau_fill * (1.0 - fill)) + t.epi);
-  if (splits > 1) us += 4.0 + (epi != EPI_BF16 ? 1.0 + CHIP_WEIGHT : 1.0) * (double)M * N * (8.0 * splits + (epi != EPI_BF16 ? 8.0 : 2.0)) / 4.0e6;
+  if (splits > 1) {
+    const double bytes = (double)M * N * (8.0 * splits + (epi != EPI_BF16 ? 8.0 : 2.0)), beyond = bytes > 64.0e6 ? bytes - 64.0e6 : 0.0;
+    us += 4.0 + (bytes + (epi != EPI_BF16 ? CHIP_WEIGHT * beyond : 0.0)) / 4.0e6;
+  }
   return us;
 }
 
@@ -533,7 +536,7 @@ static Choice choose(const GemmArgs& a, int tile_hint) {
   if (a.b_direct || a.epi == EPI_CE_STATS || a.epi == EPI_CE_DZ || a.epi == EPI_F32_COLMAX || a.epi == EPI_CE_P) return {1, 1};
   const bool swiglu = a.epi == EPI_SWIGLU_FWD || a.epi == EPI_SWIGLU_BWD;
   const bool may_split = a.split_ws && a.run_flag == nullptr &&
-                         ((a.epi == EPI_BF16 && (long)((a.M + 255) / 256) * ((a.N + 127) / 128) < 256) || (a.epi == EPI_F32 && a.beta));
+                         ((a.epi == EPI_BF16 && (long)((a.M + 255) / 256) * ((a.N + 127) / 128) < 256) || a.epi == EPI_F32);
   const int k_tiles = (a.K + 63) / 64 + (a.K2 + 63) / 64;
   const bool skinny = a.N <= 64 || a.M <= 64;
   Choice best{1, 1};

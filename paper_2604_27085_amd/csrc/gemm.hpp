@@ -66,7 +66,7 @@ struct GemmArgs {
   int b_direct;
   int splits;                  // reduction slices (grid.y), chosen by gemm_launch
   int part_row0;               // first partial row this launch writes (2 per M tile)
-  // Reduction split (EPI_F32 with beta, EPI_BF16): with a scratch buffer of at least splits * M * N floats the slices write
+  // Reduction split (EPI_F32, EPI_BF16): with a scratch buffer of at least splits * M * N floats the slices write
   // their partial products there ([slice][M][N]) and a second kernel adds them to C (or writes their sum plus the residual
   // as bf16) in slice order, so the result does not depend on scheduling.  Without the buffer the GEMM is not split.
   // split_out_bf16: with EPI_F32, asks for the bf16 result.

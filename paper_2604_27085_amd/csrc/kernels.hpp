@@ -8,14 +8,24 @@ struct LoraSegs {           // up to three row segments of a fused projection, e
   int row0[3], row1[3], col0[3];
 };
 
-// y = x * rstd * g, rstd[T] saved (may be NULL).  x, y bf16 [T, h]; g bf16 [h].
-hipError_t k_rmsnorm_fwd(hipStream_t st, const void* x, const void* g, void* y, float* rstd, int T, int h, float eps);
+// y = x * rstd * g, rstd[T] saved (may be NULL).  x, y bf16 [T, h]; g bf16 [h].  cs (optional): the launch also fills the RoPE table
+// (see k_rope_table).
+hipError_t k_rmsnorm_fwd(hipStream_t st, const void* x, const void* g, void* y, float* rstd, int T, int h, float eps, float2* cs = nullptr,
+                         int seq = 0, int d = 0, float base = 0.f);
 // Gain gradients are reduced block by block into `scratch` and then added to their destination in a fixed order.
 #define RP_PARTIAL_BLOCKS 1024
+// part [rows, cols] fp32: the sum over the rows of column c is added to dst[c], from cols1 on to dst2[c - cols1].
+struct ColSum { const float* part; float *dst, *dst2; int rows, cols, cols1, first; };
+struct ColSums { static constexpr int MAX = 3; int n; ColSum s[MAX]; };
+hipError_t k_colsum_add(hipStream_t st, const ColSums& q);
+// A row's gradient in the head: coef (dy / l - W[label]), see k_rmsnorm_bwd.
+struct CeRows { const float *l, *coef; const int* labels; const void* W; int V; };
 // dx = rmsnorm backward (+ dres if non-NULL); dg (fp32 [h], may be NULL) += its gradient, using scratch
-// [RP_PARTIAL_BLOCKS * h] floats.  dy bf16 or fp32.
+// [RP_PARTIAL_BLOCKS * h] floats.  dy bf16 or fp32.  defer: the partials are left in scratch and noted there, to be added by
+// k_colsum_add.  ce (fp32 dy): the gradient of row t is coef[t] (dy_t / l[t] - W[labels[t]]), zero where coef[t] is.
 hipError_t k_rmsnorm_bwd(hipStream_t st, const void* dy, int dy_is_f32, const void* x, const void* g, const float* rstd,
-                         const void* dres, void* dx, float* dg, float* scratch, int T, int h);
+                         const void* dres, void* dx, float* dg, float* scratch, int T, int h, ColSums* defer = nullptr,
+                         const CeRows* ce = nullptr);
 // cs[seq][d/2] = (cos, sin)(pos * base^(-2i/d))
 hipError_t k_rope_table(hipStream_t st, float2* cs, int seq, int d, float base);
 // forward: (optional per-head RMSNorm) then RoPE on q heads and k heads.  backward: the transpose.
@@ -23,7 +33,7 @@ hipError_t k_qknorm_rope(hipStream_t st, int bwd, int d, const void* in_q, const
                          void* out_q, void* out_k, long ld_out_q, long ld_out_k, const void* gq, const void* gk,
                          float* rstd_q, float* rstd_k, const void* raw_q, const void* raw_k, long ld_raw, float* dgq,
                          float* dgk, float* scratch /* [RP_PARTIAL_BLOCKS * 2 * d] floats, backward with gains */,
-                         const float2* cs, int T, int seq, int a, int k, int use_norm, float eps);
+                         const float2* cs, int T, int seq, int a, int k, int use_norm, float eps, ColSums* defer = nullptr);
 // act[T, m] = silu(gu[:, :m]) * gu[:, m:]
 hipError_t k_swiglu_fwd(hipStream_t st, const void* gu, void* act, long T, int m);
 hipError_t k_swiglu_bwd(hipStream_t st, const void* dact, const void* gu, void* dgu, long T, int m);
@@ -78,27 +88,22 @@ hipError_t k_moe_dlogits(hipStream_t st, const int* idx, const float* w, const i
 hipError_t k_ce_lse(hipStream_t st, const float2* part, int P, long part_ld, float* lse, int T);
 // One sweep over the vocabulary: a flag per chunk; a sweep of more chunks uses them again in turn, cleared by a fill.
 #define RP_CE_FLAGS 64
-// zlab [T], acc [n] (n a multiple of 4) and flags [nflags <= 256] become zero.
-hipError_t k_ce_init(hipStream_t st, float* zlab, int T, float* acc, long n, int* flags, int nflags);
-// m[t] = max over the rows of z [rows, T] fp32, l[t] = 0, alpha[t] = 1: the reference exponents a sweep starts from.
-hipError_t k_ce_ref_init(hipStream_t st, const float* z, int rows, int T, float* m, float* l, float* alpha);
+// m[t] = max over the rows of z [rows, T] fp32, l[t] = 0, alpha[t] = 1: the reference exponents a sweep starts from; zlab [T] and
+// flags [nflags <= 1024] become zero.
+hipError_t k_ce_ref_init(hipStream_t st, const float* z, int rows, int T, float* m, float* l, float* alpha, float* zlab, int* flags, int nflags);
 // part [nparts][T]: what EPI_CE_P left, maxima in .x and sums of exponentials in .y.  l_out = l_in + the sums in a fixed order;
 // *flag = 1 when some token's maximum lies more than RP_CE_P_LIMIT above its reference m.
 hipError_t k_ce_chunk_stats(hipStream_t st, const float2* part, int nparts, int T, const float* m, const float* l_in, float* l_out, int* flag);
-// Nothing unless *flag: the chunk again from its fp32 logits z [vc, T].  The reference m moves where the chunk outgrows it by more
+// Nothing unless *flag (which counts up then): the chunk again from its fp32 logits z [vc, T].  The reference m moves where the chunk outgrows it by more
 // than e^8 (alpha = the factor), p = exp(z - m_t) [vc, T] bf16, l_out = alpha l_in + row sums (through the .y halves of pmax,
 // whose .x halves hold the column maxima, one row per 128 vocabulary rows), acc [T, h] and the probabilities stored before
 // the chunk (p_all, `rows` rows, or NULL) times alpha.
 hipError_t k_ce_chunk_redo(hipStream_t st, const float* z, int vc, int T, float2* pmax, int nparts, float* m, const float* l_in, float* l_out,
-                           float* alpha, void* p, float* acc, int h, void* p_all, long rows, const int* flag);
-hipError_t k_ce_lse_from_ref(hipStream_t st, const float* m, const float* l, float* lse, int T);
+                           float* alpha, void* p, float* acc, int h, void* p_all, long rows, int* flag);
 // One sweep with a trainable head (the probabilities of all chunks stay in memory, [V, T] bf16):
-// p[labels[t], t] -= l[t] for tokens with coef != 0 and a label inside the vocabulary;
-hipError_t k_ce_patch_label(hipStream_t st, void* p, int T, int V, const int* labels, const float* l, const float* coef);
-// xs[t, :] = xf[t, :] * coef[t] / l[t] (bf16).
-hipError_t k_ce_scale_x(hipStream_t st, const void* xf, const float* coef, const float* l, void* xs, int T, int h);
-// acc[t, :] = coef[t] * (acc[t, :] / l[t] - W[labels[t], :]) (zero where coef is zero).
-hipError_t k_ce_frozen_dx(hipStream_t st, float* acc, const float* l, const float* coef, const int* labels, const void* W, int T, int h,
-                          int V);
-hipError_t k_ce_finalize(hipStream_t st, const float* lse, const float* zlab, const int* labels, float grad_scale,
+// p[labels[t], t] -= l[t] for tokens with coef != 0 and a label inside the vocabulary;  xs[t, :] = xf[t, :] * coef[t] / l[t] (bf16).
+hipError_t k_ce_patch_scale(hipStream_t st, void* p, int T, int V, const int* labels, const float* l, const float* coef, const void* xf,
+                            void* xs, int h);
+// lse[t], or with l the log-sum-exp lse[t] + log l[t].
+hipError_t k_ce_finalize(hipStream_t st, const float* lse, const float* l, const float* zlab, const int* labels, float grad_scale,
                          float* coef, float* loss_out, int T);

@@ -127,8 +127,8 @@ struct Plan {
   int moe_max_tiles;             // capacity of the tile table
   size_t split_fwd, split_bwd, h_split;   // partial products of a GEMM reduction split (RP_SPLITK_WS_BYTES each), per plan
   size_t dkvp;   // dK/dV partials of grouped attention (at most one per query head); shares memory with dact|dgu, dead by then
-  size_t ds;                                      // dS of the attention backward, at the end of the backward plan
-  size_t fwd_bytes, bwd_min, bwd_bytes;           // bwd_min: the plan without dS
+  size_t gain_parts, ds;                          // optional: gain gradient partials, dS of the attention backward
+  size_t fwd_bytes, bwd_min, bwd_bytes;           // bwd_min: the backward plan without the optional regions
   // head
   size_t h_xf, h_rstd, h_part, h_zlab, h_lse, h_coef, h_dzt, h_dxacc, h_partials, head_bytes;
   bool head_keep_p;      // one sweep that keeps all probabilities (see make_plan)
@@ -205,6 +205,10 @@ inline Plan make_plan(const rp_stage_cfg& c, int batch, int seq, bool compact = 
   P.split_bwd = take(RP_SPLITK_WS_BYTES);
   P.partials = take((size_t)RP_PARTIAL_BLOCKS * (size_t)(D.h > 2 * D.d ? D.h : 2 * D.d) * 4);
   P.bwd_min = o;
+  // behind what every accepted workspace holds:
+  // the partials of two more gain gradients of a layer, so that all three are added by one launch at its end
+  P.gain_parts = o;
+  if (D.L > 0 && c.train_base) take(((size_t)RP_PARTIAL_BLOCKS * D.h + (size_t)RP_PARTIAL_BLOCKS * 2 * D.d) * 4);
   // dS of the attention backward (see k_attn_ds_bytes), as many query heads as 4 GiB hold; a workspace that ends before it runs the
   // dQ kernel that recomputes the scores
   P.ds = o;

@@ -39,7 +39,8 @@ __global__ void __launch_bounds__(1024) ce_lse_kernel(const float2* __restrict__
 }
 
 // One block: counts the valid tokens, loss = sum(lse - z_label) / n_valid, coef[t] = grad_scale / n_valid or 0.
-__global__ void __launch_bounds__(1024) ce_finalize_kernel(const float* __restrict__ lse, const float* __restrict__ zlab,
+// lse[t] is lse[t] + log l[t] where l is given (the reference exponents and normalisers of the one-sweep schedule).
+__global__ void __launch_bounds__(1024) ce_finalize_kernel(const float* __restrict__ lse, const float* __restrict__ l, const float* __restrict__ zlab,
                                                            const int* __restrict__ labels, float grad_scale,
                                                            float* __restrict__ coef, float* __restrict__ loss_out, int T) {
   __shared__ float red[16];
@@ -49,7 +50,7 @@ __global__ void __launch_bounds__(1024) ce_finalize_kernel(const float* __restri
   int cnt = 0;
   float sum = 0.f;
   for (int t = tid; t < T; t += 1024) {
-    if (labels[t] != -100) { ++cnt; sum += lse[t] - zlab[t]; }
+    if (labels[t] != -100) { ++cnt; sum += (l ? lse[t] + logf(l[t]) : lse[t]) - zlab[t]; }
   }
   sum = wave_sum(sum);
   float fc = wave_sum((float)cnt);
@@ -79,20 +80,15 @@ __global__ void __launch_bounds__(1024) ce_finalize_kernel(const float* __restri
 
 constexpr int CE_PROB_ROWS = 128;
 
-// Zeroes what a sweep accumulates into: the label logits [T], acc [n], the chunks' flags.
-__global__ void __launch_bounds__(256) ce_init_kernel(float* __restrict__ zlab, int T, float4* __restrict__ acc, long n4, int* __restrict__ flags, int nflags) {
-  const long i0 = (long)blockIdx.x * 256 + threadIdx.x;
-  for (long i = i0; i < n4; i += (long)gridDim.x * 256) acc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (long i = i0; i < T; i += (long)gridDim.x * 256) zlab[i] = 0.f;
-  if (i0 < nflags) flags[i0] = 0;
-}
-
 // Sixteen waves share 64 tokens (lane = token) and split the rows of a [rows][T] array; red[wave][token] is theirs to merge.
 constexpr int CE_SLICES = 16;
 
-// m[t] = max over the rows of z [rows][T], l[t] = 0, alpha[t] = 1: the reference exponents a sweep starts from.
+// m[t] = max over the rows of z [rows][T], l[t] = 0, alpha[t] = 1: the reference exponents a sweep starts from; and zeroes the label
+// logits and the chunks' flags.
 __global__ void __launch_bounds__(1024) ce_ref_init_kernel(const float* __restrict__ z, int rows, int T, float* __restrict__ m,
-                                                           float* __restrict__ l, float* __restrict__ alpha) {
+                                                           float* __restrict__ l, float* __restrict__ alpha, float* __restrict__ zlab,
+                                                           int* __restrict__ flags, int nflags) {
+  if (blockIdx.x == 0 && (int)threadIdx.x < nflags) flags[threadIdx.x] = 0;
   __shared__ float red[CE_SLICES][64];
   const int lane = threadIdx.x & 63, sl = threadIdx.x >> 6, t = blockIdx.x * 64 + lane;
   float mx = -INFINITY;
@@ -102,7 +98,7 @@ __global__ void __launch_bounds__(1024) ce_ref_init_kernel(const float* __restri
   __syncthreads();
   if (sl == 0 && t < T) {
     for (int k = 1; k < CE_SLICES; ++k) mx = fmaxf(mx, red[k][lane]);
-    m[t] = mx; l[t] = 0.f; alpha[t] = 1.f;
+    m[t] = mx; l[t] = 0.f; alpha[t] = 1.f; zlab[t] = 0.f;
   }
 }
 
@@ -175,20 +171,18 @@ RP_DEV void chunk_prob(int bx, int by, const float* __restrict__ z, int vc, int 
   row[0].y = s.x; row[1].y = s.y; row[2].y = s.z; row[3].y = s.w;
 }
 
-// l[t] += sum over the chunk's partial rows of part[i][t].y, in row order.
-__global__ void __launch_bounds__(256) ce_chunk_sum_kernel(const float2* __restrict__ part, int nslab, int T, float* __restrict__ l,
-                                                           const int* __restrict__ run_flag) {
-  if (*run_flag == 0) return;
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t >= T) return;
-  float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;   // four chains, merged in a fixed order
-  int i = 0;
-  for (; i + 4 <= nslab; i += 4) {
-    s0 += part[(long)i * T + t].y; s1 += part[(long)(i + 1) * T + t].y;
-    s2 += part[(long)(i + 2) * T + t].y; s3 += part[(long)(i + 3) * T + t].y;
+// l[t] += sum over the chunk's partial rows of part[i][t].y, in a fixed order; one block takes all tokens.
+RP_DEV void chunk_sum(const float2* part, int nslab, int T, float* l) {
+  for (int t = threadIdx.x; t < T; t += 256) {
+    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;   // four chains, merged in a fixed order
+    int i = 0;
+    for (; i + 4 <= nslab; i += 4) {
+      s0 += part[(long)i * T + t].y; s1 += part[(long)(i + 1) * T + t].y;
+      s2 += part[(long)(i + 2) * T + t].y; s3 += part[(long)(i + 3) * T + t].y;
+    }
+    for (; i < nslab; ++i) s0 += part[(long)i * T + t].y;
+    l[t] += (s0 + s1) + (s2 + s3);
   }
-  for (; i < nslab; ++i) s0 += part[(long)i * T + t].y;
-  l[t] += (s0 + s1) + (s2 + s3);
 }
 
 // acc[t, :] *= alpha[t] for the rows whose reference moved.  One wave per row, blocks bx of nb.
@@ -222,36 +216,42 @@ RP_DEV void rescale_p(int bx, int nb, bf16* __restrict__ p, long rows, int T, co
 }
 
 // Behind the flag, in one launch: the chunk's probabilities from its fp32 logits, and the rescale of the rows of acc and of the
-// probabilities stored before the chunk (p_all, `rows` of them).  Blocks [0, np) probabilities, [np, np + nr) acc, then p_all.
+// probabilities stored before the chunk (p_all, `rows` of them).  Blocks [0, np) probabilities, [np, np + nr) acc, then p_all.  Every
+// block counts itself off on the flag (1 when it starts, and nobody reads it afterwards); the last one, which sees all the partial
+// sums, adds them to the normalisers.
 __global__ void __launch_bounds__(256) ce_chunk_apply_kernel(const float* __restrict__ z, int vc, int T, const float* __restrict__ m,
-                                                             bf16* p, float2* __restrict__ part, const float* __restrict__ alpha,
+                                                             bf16* p, float2* part, const float* __restrict__ alpha,
                                                              float* __restrict__ acc, int h, bf16* p_all, long rows, int bx_prob, int np,
-                                                             int nr, const int* __restrict__ run_flag) {
+                                                             int nr, float* __restrict__ l, int nslab, int* run_flag) {
   if (*run_flag == 0) return;
+  __shared__ int s_last;
   const int b = (int)blockIdx.x;
   if (b < np) chunk_prob(b % bx_prob, b / bx_prob, z, vc, T, m, p, part);
   else if (b < np + nr) rescale_rows(b - np, nr, acc, alpha, T, h);
   else rescale_p(b - np - nr, (int)gridDim.x - np - nr, p_all, rows, T, alpha);
+  __threadfence();
+  __syncthreads();
+  if (threadIdx.x == 0) s_last = atomicAdd(run_flag, 1) == (int)gridDim.x;
+  __syncthreads();
+  if (!s_last) return;
+  __threadfence();
+  chunk_sum(part, nslab, T, l);
 }
 
-// p[y_t, t] -= l_t for every token whose label takes part in the loss (coef != 0) and lies inside the vocabulary.  One
-// element per token, all in different columns: no two threads touch the same one.
-__global__ void __launch_bounds__(256) ce_patch_label_kernel(bf16* __restrict__ p, int T, int V, const int* __restrict__ labels,
-                                                             const float* __restrict__ l, const float* __restrict__ coef) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t >= T) return;
-  const int y = labels[t];
-  if (coef[t] == 0.f || y < 0 || y >= V) return;
-  bf16* const e = p + (long)y * T + t;
-  *e = (bf16)((float)*e - l[t]);
-}
-
-// xs[t, :] = xf[t, :] * coef[t] / l[t]  (bf16; zero rows for ignored tokens)
-__global__ void __launch_bounds__(256) ce_scale_x_kernel(const bf16* __restrict__ xf, const float* __restrict__ coef,
-                                                         const float* __restrict__ l, bf16* __restrict__ xs, int T, int h) {
+// p[y_t, t] -= l_t for every token whose label takes part in the loss (coef != 0) and lies inside the vocabulary (one
+// element per token, all in different columns: no two threads touch the same one), and
+// xs[t, :] = xf[t, :] * coef[t] / l[t]  (bf16; zero rows for ignored tokens).  One wave per token.
+__global__ void __launch_bounds__(256) ce_patch_scale_kernel(bf16* __restrict__ p, int T, int V, const int* __restrict__ labels,
+                                                             const float* __restrict__ l, const float* __restrict__ coef,
+                                                             const bf16* __restrict__ xf, bf16* __restrict__ xs, int h) {
   const int t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (t >= T) return;
-  const float s = coef[t] == 0.f ? 0.f : coef[t] / l[t];
+  const float lt = l[t], s = coef[t] == 0.f ? 0.f : coef[t] / lt;
+  const int y = labels[t];
+  if (lane == 0 && coef[t] != 0.f && y >= 0 && y < V) {
+    bf16* const e = p + (long)y * T + t;
+    *e = (bf16)((float)*e - lt);
+  }
   const uint4* src = reinterpret_cast<const uint4*>(xf + (long)t * h);
   uint4* dst = reinterpret_cast<uint4*>(xs + (long)t * h);
   for (int c = lane; c < h / 8; c += 64) {
@@ -261,51 +261,12 @@ __global__ void __launch_bounds__(256) ce_scale_x_kernel(const bf16* __restrict_
   }
 }
 
-__global__ void __launch_bounds__(256) ce_lse_from_ref_kernel(const float* __restrict__ m, const float* __restrict__ l,
-                                                              float* __restrict__ lse, int T) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t < T) lse[t] = m[t] + logf(l[t]);
-}
-
-// acc[t, :] = coef[t] * (acc[t, :] / l[t] - W[label_t, :]); rows with coef 0 (ignored labels) become zero.
-__global__ void __launch_bounds__(256) ce_frozen_dx_kernel(float* __restrict__ acc, const float* __restrict__ l,
-                                                           const float* __restrict__ coef, const int* __restrict__ labels,
-                                                           const bf16* __restrict__ W, int T, int h, int V) {
-  const int t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (t >= T) return;
-  const float c = coef[t];
-  float4* row = reinterpret_cast<float4*>(acc + (long)t * h);
-  if (c == 0.f) {
-    for (int q = lane; q < h / 4; q += 64) row[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-    return;
-  }
-  const float il = c / l[t];
-  const int lab = labels[t];
-  const bool has = lab >= 0 && lab < V;          // a label outside the vocabulary has no logit to subtract
-  const uint2* wr = reinterpret_cast<const uint2*>(W + (long)(has ? lab : 0) * h);
-  for (int q = lane; q < h / 4; q += 64) {
-    float4 v = row[q];
-    const uint2 w2 = has ? wr[q] : make_uint2(0u, 0u);
-    v.x = v.x * il - c * bf16_lo(w2.x); v.y = v.y * il - c * bf16_hi(w2.x);
-    v.z = v.z * il - c * bf16_lo(w2.y); v.w = v.w * il - c * bf16_hi(w2.y);
-    row[q] = v;
-  }
-}
-
 }  // namespace
 
-hipError_t k_ce_init(hipStream_t st, float* zlab, int T, float* acc, long n, int* flags, int nflags) {
+hipError_t k_ce_ref_init(hipStream_t st, const float* z, int rows, int T, float* m, float* l, float* alpha, float* zlab, int* flags, int nflags) {
   if (T == 0) return hipSuccess;
-  if (n % 4 || nflags > 256) return hipErrorInvalidValue;
-  const long blocks = (n / 4 + 255) / 256;
-  RP_LAUNCH(ce_init_kernel, dim3((unsigned)(blocks < 1 ? 1 : blocks > 4096 ? 4096 : blocks)), dim3(256), 0, st, zlab, T, reinterpret_cast<float4*>(acc),
-            n / 4, flags, nflags);
-  return hipGetLastError();
-}
-
-hipError_t k_ce_ref_init(hipStream_t st, const float* z, int rows, int T, float* m, float* l, float* alpha) {
-  if (T == 0) return hipSuccess;
-  RP_LAUNCH(ce_ref_init_kernel, dim3((T + 63) / 64), dim3(1024), 0, st, z, rows, T, m, l, alpha);
+  if (nflags > 1024) return hipErrorInvalidValue;
+  RP_LAUNCH(ce_ref_init_kernel, dim3((T + 63) / 64), dim3(1024), 0, st, z, rows, T, m, l, alpha, zlab, flags, nflags);
   return hipGetLastError();
 }
 
@@ -316,42 +277,22 @@ hipError_t k_ce_chunk_stats(hipStream_t st, const float2* part, int nparts, int 
 }
 
 hipError_t k_ce_chunk_redo(hipStream_t st, const float* z, int vc, int T, float2* pmax, int nparts, float* m, const float* l_in, float* l_out,
-                           float* alpha, void* p, float* acc, int h, void* p_all, long rows, const int* flag) {
+                           float* alpha, void* p, float* acc, int h, void* p_all, long rows, int* flag) {
   if (T == 0 || vc == 0) return hipSuccess;
   const int nblk = (vc + CE_PROB_ROWS - 1) / CE_PROB_ROWS;
   if (T % 8 || h % 4 || nblk > nparts) return hipErrorInvalidValue;   // one partial row per CE_PROB_ROWS vocabulary rows
   const int bx = (T / 4 + 255) / 256, nr = (T + 3) / 4 < 256 ? (T + 3) / 4 : 256, nq = p_all && rows > 0 ? 512 : 0;
-  RP_LAUNCH(ce_chunk_ref_kernel, dim3((T + 255) / 256), dim3(256), 0, st, (const float2*)pmax, nparts, T, m, l_in, l_out, alpha, flag);
+  RP_LAUNCH(ce_chunk_ref_kernel, dim3((T + 255) / 256), dim3(256), 0, st, (const float2*)pmax, nparts, T, m, l_in, l_out, alpha, (const int*)flag);
   RP_LAUNCH(ce_chunk_apply_kernel, dim3(bx * nblk + nr + nq), dim3(256), 0, st, z, vc, T, (const float*)m, (bf16*)p, pmax, (const float*)alpha,
-            acc, h, (bf16*)p_all, rows, bx, bx * nblk, nr, flag);
-  RP_LAUNCH(ce_chunk_sum_kernel, dim3((T + 255) / 256), dim3(256), 0, st, (const float2*)pmax, nblk, T, l_out, flag);
+            acc, h, (bf16*)p_all, rows, bx, bx * nblk, nr, l_out, nblk, flag);
   return hipGetLastError();
 }
 
-hipError_t k_ce_patch_label(hipStream_t st, void* p, int T, int V, const int* labels, const float* l, const float* coef) {
-  if (T == 0) return hipSuccess;
-  RP_LAUNCH(ce_patch_label_kernel, dim3((T + 255) / 256), dim3(256), 0, st, (bf16*)p, T, V, labels, l, coef);
-  return hipGetLastError();
-}
-
-hipError_t k_ce_scale_x(hipStream_t st, const void* xf, const float* coef, const float* l, void* xs, int T, int h) {
+hipError_t k_ce_patch_scale(hipStream_t st, void* p, int T, int V, const int* labels, const float* l, const float* coef, const void* xf,
+                            void* xs, int h) {
   if (T == 0) return hipSuccess;
   if (h % 8) return hipErrorInvalidValue;
-  RP_LAUNCH(ce_scale_x_kernel, dim3((T + 3) / 4), dim3(256), 0, st, (const bf16*)xf, coef, l, (bf16*)xs, T, h);
-  return hipGetLastError();
-}
-
-hipError_t k_ce_lse_from_ref(hipStream_t st, const float* m, const float* l, float* lse, int T) {
-  if (T == 0) return hipSuccess;
-  RP_LAUNCH(ce_lse_from_ref_kernel, dim3((T + 255) / 256), dim3(256), 0, st, m, l, lse, T);
-  return hipGetLastError();
-}
-
-hipError_t k_ce_frozen_dx(hipStream_t st, float* acc, const float* l, const float* coef, const int* labels, const void* W, int T, int h,
-                          int V) {
-  if (T == 0) return hipSuccess;
-  if (h % 4) return hipErrorInvalidValue;
-  RP_LAUNCH(ce_frozen_dx_kernel, dim3((T + 3) / 4), dim3(256), 0, st, acc, l, coef, labels, (const bf16*)W, T, h, V);
+  RP_LAUNCH(ce_patch_scale_kernel, dim3((T + 3) / 4), dim3(256), 0, st, (bf16*)p, T, V, labels, l, coef, (const bf16*)xf, (bf16*)xs, h);
   return hipGetLastError();
 }
 
@@ -361,8 +302,8 @@ hipError_t k_ce_lse(hipStream_t st, const float2* part, int P, long part_ld, flo
   return hipGetLastError();
 }
 
-hipError_t k_ce_finalize(hipStream_t st, const float* lse, const float* zlab, const int* labels, float grad_scale,
+hipError_t k_ce_finalize(hipStream_t st, const float* lse, const float* l, const float* zlab, const int* labels, float grad_scale,
                          float* coef, float* loss_out, int T) {
-  RP_LAUNCH(ce_finalize_kernel, dim3(1), dim3(1024), 0, st, lse, zlab, labels, grad_scale, coef, loss_out, T);
+  RP_LAUNCH(ce_finalize_kernel, dim3(1), dim3(1024), 0, st, lse, l, zlab, labels, grad_scale, coef, loss_out, T);
   return hipGetLastError();
 }

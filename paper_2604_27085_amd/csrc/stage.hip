@@ -158,6 +158,9 @@ struct LayerG {
   float* t(int id) const { return (base && L->elems[id]) ? reinterpret_cast<float*>(base + L->off[id]) : nullptr; }
 };
 
+// Set until the RoPE table has been filled.
+struct RopeArgs { float2* cs = nullptr; int seq = 0, d = 0; float base = 0.f; };
+
 struct Exec {
   rp_ctx* ctx;
   hipStream_t st;
@@ -171,6 +174,8 @@ struct Exec {
   bool fwd_only = false;           // the forward-stage plan of the workspace is in use (rp_stage_forward)
   size_t split_off = 0;            // scratch for the partial products of a GEMM reduction split, in the plan in use
   bool has_split = false;
+  bool gain_parts = false;         // a layer's three gain gradients are summed by one launch (scratch for two more of them)
+  RopeArgs rope;                   // the RoPE table is filled by the first norm of the stage
   int ds_heads = 0;                // query heads whose dS the workspace holds (0: the attention backward recomputes the scores for dQ)
   float* router = nullptr;         // router logits of the layer being run, fp32 [T, E] (mixture of experts): read, or
                                    // written first when the stage holds the router weights
@@ -381,7 +386,10 @@ void layer_forward(Exec& X, const LayerW& W, char* set, const void* x, void* z, 
   bf16_t* qkv = reinterpret_cast<bf16_t*>(S(b.qkv));
 
   const double Td = (double)T;
-  RUN(X, "rmsnorm_fwd", 0, 4.0 * Td * D.h, k_rmsnorm_fwd(X.st, x, W.t(RP_T_G1), S(b.n1), (float*)S(b.rstd1), T, D.h, c.rms_eps));
+  const RopeArgs ra = X.rope;
+  X.rope = RopeArgs{};
+  RUN(X, "rmsnorm_fwd", 0, 4.0 * Td * D.h + (ra.cs ? 4.0 * ra.seq * ra.d : 0.0),
+      k_rmsnorm_fwd(X.st, x, W.t(RP_T_G1), S(b.n1), (float*)S(b.rstd1), T, D.h, c.rms_eps, ra.cs, ra.seq, ra.d, ra.base));
   linear_fwd(X, W, RP_T_WQKV, fused_qkv(D), X.ctx->dl.bd1, S(b.n1), D.h, qkv, D.n1, S(b.u1), nullptr);
   RUN(X, "qknorm_rope_fwd", 0, 4.0 * Td * (D.qd + D.kd),
       k_qknorm_rope(X.st, 0, D.d, qkv, qkv + D.qd, D.n1, D.n1, S(b.qr), S(b.kr), D.qd, D.kd, W.t(RP_T_GQ), W.t(RP_T_GK),
@@ -467,8 +475,14 @@ void layer_backward(Exec& X, const LayerW& W, const LayerG& G, char* set, const 
                nullptr, S(b.u4), S(b.gu), X.at<void>(X.P.dgu));
     linear_bwd(X, W, G, RP_T_WGU, fused_gu(D), X.ctx->dl.bd3, X.at<void>(X.P.dgu), 2 * D.m, S(b.n2), D.h, X.at<void>(X.P.dn), S(b.u3));
   }
+  // gain gradients: partials of each norm in a region of its own, added together at the layer's end (or one by one through `partials`)
+  ColSums gains{};
+  ColSums* const defer = X.gain_parts ? &gains : nullptr;
+  float* const partials = X.at<float>(X.P.partials);
+  float* const gp_h = defer ? X.at<float>(X.P.gain_parts) : partials;
+  float* const gp_qk = defer ? gp_h + (size_t)RP_PARTIAL_BLOCKS * D.h : partials;
   RUN(X, "rmsnorm_bwd", 0, 8.0 * Td * D.h,
-      k_rmsnorm_bwd(X.st, X.at<void>(X.P.dn), 0, S(b.y), W.t(RP_T_G2), (const float*)S(b.rstd2), dz, dy, G.t(RP_T_G2), X.at<float>(X.P.partials), T, D.h));
+      k_rmsnorm_bwd(X.st, X.at<void>(X.P.dn), 0, S(b.y), W.t(RP_T_G2), (const float*)S(b.rstd2), dz, dy, G.t(RP_T_G2), gp_h, T, D.h, defer));
   // y = x + o_proj(o)
   linear_bwd(X, W, G, RP_T_WO, fused_single(D.lora[3], RP_T_LA_O, RP_T_LB_O, D.h), 0, dy, D.h, S(b.o), D.qd,
              X.at<void>(X.P.dout), S(b.u2));
@@ -510,10 +524,11 @@ void layer_backward(Exec& X, const LayerW& W, const LayerG& G, char* set, const 
   RUN(X, "qknorm_rope_bwd", 0, 6.0 * Td * (D.qd + D.kd),
       k_qknorm_rope(X.st, 1, D.d, X.at<void>(X.P.dqr), X.at<void>(X.P.dkr), D.qd, D.kd, dqkv, dqkv + D.qd, D.n1, D.n1,
                     W.t(RP_T_GQ), W.t(RP_T_GK), (float*)S(b.rstd_q), (float*)S(b.rstd_k), qkv, qkv + D.qd, D.n1,
-                    G.t(RP_T_GQ), G.t(RP_T_GK), X.at<float>(X.P.partials), X.at<float2>(X.P.rope), T, X.seq, D.a, D.kh, c.qk_norm, c.rms_eps));
+                    G.t(RP_T_GQ), G.t(RP_T_GK), gp_qk, X.at<float2>(X.P.rope), T, X.seq, D.a, D.kh, c.qk_norm, c.rms_eps, defer));
   linear_bwd(X, W, G, RP_T_WQKV, fused_qkv(D), X.ctx->dl.bd1, dqkv, D.n1, S(b.n1), D.h, X.at<void>(X.P.dn), S(b.u1));
   RUN(X, "rmsnorm_bwd", 0, 8.0 * Td * D.h,
-      k_rmsnorm_bwd(X.st, X.at<void>(X.P.dn), 0, x, W.t(RP_T_G1), (const float*)S(b.rstd1), dy, dx_out, G.t(RP_T_G1), X.at<float>(X.P.partials), T, D.h));
+      k_rmsnorm_bwd(X.st, X.at<void>(X.P.dn), 0, x, W.t(RP_T_G1), (const float*)S(b.rstd1), dy, dx_out, G.t(RP_T_G1), partials, T, D.h, defer));
+  if (gains.n) RUN(X, "gain_grads", 0, 4.0 * (T < RP_PARTIAL_BLOCKS ? T : RP_PARTIAL_BLOCKS) * (2.0 * D.h + 2.0 * D.d), k_colsum_add(X.st, gains));
 }
 
 hipError_t build_derived(const rp_ctx* ctx, hipStream_t st, char* slot, int l) {
@@ -717,7 +732,7 @@ rp_status rp_stage_forward(rp_ctx* ctx, int slot_id, const void* x_in, void* x_o
   X.split_off = P.split_fwd; X.has_split = workspace_bytes_in >= P.split_fwd + RP_SPLITK_WS_BYTES;
   const int L = ctx->cfg.n_layers;
   const size_t act_bytes = (size_t)X.T * X.D.h * 2;
-  RUN(X, "rope_table", 0, 4.0 * seq * X.D.d, k_rope_table(X.st, X.at<float2>(P.rope), seq, X.D.d, ctx->cfg.rope_base));
+  X.rope = RopeArgs{X.at<float2>(P.rope), seq, X.D.d, ctx->cfg.rope_base};
   char* set = X.ws + P.layer0;
   void* pp[2] = {set + P.lb.z, X.ws + P.layer0 + P.layer_stride};
   const void* x = x_in;
@@ -755,9 +770,10 @@ rp_status rp_stage_backward(rp_ctx* ctx, int slot_id, int phases, const void* x_
   Slot& sl = ctx->slots[slot_id];
   Exec X{ctx, ctx->compute, dims_of(ctx->cfg), batch, seq, (long)batch * seq, static_cast<char*>(workspace), P};
   X.split_off = P.split_bwd; X.has_split = true;
-  X.ds_heads = attn_ds_heads((workspace_bytes_in < P.bwd_bytes ? workspace_bytes_in : P.bwd_bytes) - P.ds, batch, seq, X.D.a, X.D.kh, X.D.d);
+  X.gain_parts = ctx->cfg.train_base && workspace_bytes_in >= P.ds;
+  if (workspace_bytes_in > P.ds) X.ds_heads = attn_ds_heads((workspace_bytes_in < P.bwd_bytes ? workspace_bytes_in : P.bwd_bytes) - P.ds, batch, seq, X.D.a, X.D.kh, X.D.d);
   const int L = ctx->cfg.n_layers;
-  if (do_fwd) RUN(X, "rope_table", 0, 4.0 * seq * X.D.d, k_rope_table(X.st, X.at<float2>(P.rope), seq, X.D.d, ctx->cfg.rope_base));
+  if (do_fwd) X.rope = RopeArgs{X.at<float2>(P.rope), seq, X.D.d, ctx->cfg.rope_base};
   auto set_of = [&](int l) { return X.ws + P.layer0 + P.layer_stride * (size_t)l; };
   if (do_fwd) {
     // recomputation: forward over the stage keeping every layer's internals; layer l starts as soon as its own chunk
@@ -837,7 +853,6 @@ rp_status rp_lmhead_ce_fwd_bwd(rp_ctx* ctx, int slot_id, const void* x, const in
     float* const zc = X.at<float>(P.h_z);
     float* const acc = X.at<float>(P.h_dxacc);
     const int nchunk = (D.V + P.head_chunk - 1) / P.head_chunk;
-    RUN(X, "ce_init", 0, 4.0 * Td * D.h, k_ce_init(X.st, X.at<float>(P.h_zlab), T, acc, (long)T * D.h, X.at<int>(P.h_flag), RP_CE_FLAGS));
     // a chunk reads the normalisers from one buffer and writes them to the other; the last one writes P.h_l
     float* const lbuf[2] = {X.at<float>(P.h_l), X.at<float>(P.h_lse)};
     {
@@ -848,14 +863,15 @@ rp_status rp_lmhead_ce_fwd_bwd(rp_ctx* ctx, int slot_id, const void* x, const in
       const int r0 = D.V < 256 ? D.V : 256;
       X.gemm_f32_nt(Wv, D.h, X.at<void>(P.h_xf), D.h, zc, T, r0, T, D.h);
       RUN(X, "ce_ref_init", 0, 4.0 * r0 * Td + 12.0 * Td,
-          k_ce_ref_init(X.st, zc, r0, T, X.at<float>(P.h_m), lbuf[nchunk & 1], X.at<float>(P.h_alpha)));
+          k_ce_ref_init(X.st, zc, r0, T, X.at<float>(P.h_m), lbuf[nchunk & 1], X.at<float>(P.h_alpha), X.at<float>(P.h_zlab), X.at<int>(P.h_flag),
+                        RP_CE_FLAGS));
     }
     // acc[T, h] += p^T^T . W over `rows` vocabulary rows.  The fp32 logits' buffer is free by then (the slow path of the chunk
     // before is done) and serves as scratch of the split
-    auto add_dx = [&](const void* p, const bf16_t* Wr, int rows) {
+    auto add_dx = [&](const void* p, const bf16_t* Wr, int rows, bool first) {
       GemmArgs d; gemm_zero_args(d);
       d.A = p; d.lda = T; d.B = Wr; d.ldb = D.h; d.M = T; d.N = D.h; d.K = rows; d.C = acc;
-      d.ldc = D.h; d.beta = 1; d.epi = EPI_F32;
+      d.ldc = D.h; d.beta = !first; d.epi = EPI_F32;       // (the first product writes acc, so nothing has to clear it)
       X.give_split_ws(d);
       const size_t zbytes = (size_t)P.head_chunk * T * 4;
       if (zbytes > d.split_ws_bytes) { d.split_ws = zc; d.split_ws_bytes = zbytes; }
@@ -895,16 +911,14 @@ rp_status rp_lmhead_ce_fwd_bwd(rp_ctx* ctx, int slot_id, const void* x, const in
       RUN(X, "ce_slow_path", 0, 0,
           k_ce_chunk_redo(X.st, zc, vc, T, X.at<float2>(P.h_part), nparts, X.at<float>(P.h_m), l_in, l_out, X.at<float>(P.h_alpha), pc, acc,
                           D.h, keep_p ? pall : nullptr, v0, flag));
-      if (!keep_p) add_dx(pc, Wc, vc);
+      if (!keep_p) add_dx(pc, Wc, vc, v0 == 0);
     }
-    if (keep_p) for (int v0 = 0; v0 < D.V; v0 += piece) add_dx(pall + (size_t)v0 * T, Wv + (size_t)v0 * D.h, D.V - v0 < piece ? D.V - v0 : piece);
-    RUN(X, "ce_lse", 0, 12.0 * Td, k_ce_lse_from_ref(X.st, X.at<float>(P.h_m), X.at<float>(P.h_l), X.at<float>(P.h_lse), T));
+    if (keep_p) for (int v0 = 0; v0 < D.V; v0 += piece) add_dx(pall + (size_t)v0 * T, Wv + (size_t)v0 * D.h, D.V - v0 < piece ? D.V - v0 : piece, v0 == 0);
     RUN(X, "ce_finalize", 0, 16.0 * Td,
-        k_ce_finalize(X.st, X.at<float>(P.h_lse), X.at<float>(P.h_zlab), labels, grad_scale, X.at<float>(P.h_coef), loss_out, T));
+        k_ce_finalize(X.st, X.at<float>(P.h_m), X.at<float>(P.h_l), X.at<float>(P.h_zlab), labels, grad_scale, X.at<float>(P.h_coef), loss_out, T));
     if (train && G.t(RP_T_WV)) {
-      RUN(X, "ce_patch_label", 0, 16.0 * Td, k_ce_patch_label(X.st, pall, T, D.V, labels, X.at<float>(P.h_l), X.at<float>(P.h_coef)));
-      RUN(X, "ce_scale_x", 0, 4.0 * Td * D.h,
-          k_ce_scale_x(X.st, X.at<void>(P.h_xf), X.at<float>(P.h_coef), X.at<float>(P.h_l), X.at<void>(P.h_xs), T, D.h));
+      RUN(X, "ce_patch_scale", 0, 16.0 * Td + 4.0 * Td * D.h,
+          k_ce_patch_scale(X.st, pall, T, D.V, labels, X.at<float>(P.h_l), X.at<float>(P.h_coef), X.at<void>(P.h_xf), X.at<void>(P.h_xs), D.h));
       for (int v0 = 0; v0 < D.V; v0 += piece) {
         const int vc = (D.V - v0 < piece) ? (D.V - v0) : piece;
         GemmArgs w; gemm_zero_args(w);  // dW_c[vc, h] += P'_c . xs
@@ -915,11 +929,10 @@ rp_status rp_lmhead_ce_fwd_bwd(rp_ctx* ctx, int slot_id, const void* x, const in
         X.chk(gemm_launch(X.st, GEMM_NN, w), "lm head dW");
       }
     }
-    RUN(X, "ce_frozen_dx", 0, 8.0 * Td * D.h + 2.0 * Td * D.h,
-        k_ce_frozen_dx(X.st, acc, X.at<float>(P.h_l), X.at<float>(P.h_coef), labels, Wv, T, D.h, D.V));
-    RUN(X, "rmsnorm_bwd", 0, 8.0 * Td * D.h,
+    const CeRows ce{X.at<float>(P.h_l), X.at<float>(P.h_coef), labels, Wv, D.V};
+    RUN(X, "rmsnorm_bwd", 0, 10.0 * Td * D.h,
         k_rmsnorm_bwd(X.st, acc, 1, x, W.t(RP_T_GF), X.at<float>(P.h_rstd), nullptr, dx, train ? G.t(RP_T_GF) : nullptr,
-                      X.at<float>(P.h_partials), T, D.h));
+                      X.at<float>(P.h_partials), T, D.h, nullptr, &ce));
     return finish_call(ctx, sl, X);
   }
   RUN(X, "fill", 0, 4.0 * Td, k_fill_u32(X.st, X.at<void>(P.h_zlab), T, 0u));
@@ -932,7 +945,7 @@ rp_status rp_lmhead_ce_fwd_bwd(rp_ctx* ctx, int slot_id, const void* x, const in
   }
   RUN(X, "ce_lse", 0, 8.0 * P.head_parts * Td, k_ce_lse(X.st, X.at<float2>(P.h_part), P.head_parts, T, X.at<float>(P.h_lse), T));
   RUN(X, "ce_finalize", 0, 16.0 * Td,
-      k_ce_finalize(X.st, X.at<float>(P.h_lse), X.at<float>(P.h_zlab), labels, grad_scale, X.at<float>(P.h_coef), loss_out, T));
+      k_ce_finalize(X.st, X.at<float>(P.h_lse), nullptr, X.at<float>(P.h_zlab), labels, grad_scale, X.at<float>(P.h_coef), loss_out, T));
   RUN(X, "fill", 0, 4.0 * Td * D.h, k_fill_u32(X.st, X.at<void>(P.h_dxacc), (long)T * D.h, 0u));
   // sweep 2: per vocabulary chunk recompute the logits, turn them into dZ^T (bf16), and feed dX and dW
   for (int v0 = 0, ci = 0; v0 < D.V; v0 += P.head_chunk, ++ci) {
@@ -1020,7 +1033,8 @@ rp_status rp_op_gemm(void* stream, int layout, int out_f32, const void* A, const
   g.A = A; g.B = B; g.C = C; g.M = M; g.N = N; g.K = K; g.lda = lda; g.ldb = ldb; g.ldc = ldc; g.alpha = alpha; g.beta = beta;
   g.A2 = A2; g.B2 = B2; g.K2 = (A2 && B2) ? K2 : 0; g.lda2 = lda2; g.ldb2 = ldb2; g.R = R; g.ldr = ldr;
   g.epi = out_f32 == 2 ? EPI_F32_ATOMIC : (out_f32 ? EPI_F32 : EPI_BF16);
-  g.split_ws = static_cast<float*>(split_ws); g.split_ws_bytes = split_ws ? split_ws_bytes : 0; g.split_out_bf16 = out_f32 == 3;
+  if (out_f32 != 1 || beta) { g.split_ws = static_cast<float*>(split_ws); g.split_ws_bytes = split_ws ? split_ws_bytes : 0; }   // (1 without beta: one pass)
+  g.split_out_bf16 = out_f32 == 3;
   if (tile == 6) { g.b_direct = 1; tile = 0; }   // B and B2 in fragment order (rp_op_gemm_arrange)
   hipError_t e = gemm_launch(reinterpret_cast<hipStream_t>(stream), layout, g, tile);
   OP_RET(e);
