@@ -96,6 +96,11 @@ bool gemm_groupable(const GemmArgs& a);
 hipError_t gemm_group_launch(hipStream_t st, int n, const int* layouts, const GemmArgs* g);
 // The shared launch itself (gemm_mid.hip): arguments prepared, g[i].splits slices each.
 hipError_t gemm_multi_run(hipStream_t st, int n, const int* layouts, const GemmArgs* g);
+// Weight gradients (layout TN, fp32, accumulating, the same reduction) that do not depend on each other: in one launch of 256x256 tiles
+// when the tile model finds that cheaper than one by one, which it is when their last rounds would stay partly empty.
+#define GEMM_WGRAD_MAX 4
+hipError_t gemm_wgrad_launch(hipStream_t st, int n, const GemmArgs* g);
+hipError_t gemm_wgrad_run(hipStream_t st, int n, const GemmArgs* g);     // the shared launch (gemm_dtl.hip): arguments prepared
 // dq [T, a * d] = scale * dS^T k per head, from the blocks of dS that the dK/dV kernel left (attention.hip; head_bytes each, d = 128).
 hipError_t gemm_attn_dq(hipStream_t st, const void* ds, size_t head_bytes, const void* k, long ldk, void* dq, long lddq, int batch, int seq,
                         int a, int kh, int d, float scale);

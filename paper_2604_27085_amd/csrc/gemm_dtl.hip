@@ -89,8 +89,9 @@ RP_DEV i32x4 raw_rsrc(const void* base, uint32_t bytes) {
 // with that and the tile order of the plain products, us: h = 4096, 128 experts of 1536, backward stage of 256 | 2048 | 8192 tokens
 // 2326 -> 2250 | 3664 -> 3510 | 13270 -> 12950;  h = 2880, 32 experts of 2880, forward of 1000 | 8192 tokens 659 -> 636 |
 // 2995 -> 2876.  What bounds the 128-row tiles then is the experts' weights (gate/up 3.5 GB in 706 us, matrix pipe 31 % busy).
+// blk: the output tile of the product (-1: the workgroup's number).
 template <bool TA, bool TB, bool GRP>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) gemm_dtl_kernel(const GemmArgs p) {
+RP_DEV void dtl_block(const GemmArgs& p, int blk) {
   static_assert((!TA || TB) && !(GRP && TA), "not a layout of this library");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -114,7 +115,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
   } else {
     // narrow outputs (up to 24 tile columns) sweep their columns in groups of 4 tile rows, wide ones of 8: measured
     // +2-3 % at N = 5120, -1.5-2 % at N >= 10240 for groups of 4
-    tile_of_block(p.M, p.N, 256, 256, tile_m, tile_n, (p.N + 255) / 256 <= 24 ? 4 : 8);
+    tile_of_block(p.M, p.N, 256, 256, tile_m, tile_n, (p.N + 255) / 256 <= 24 ? 4 : 8, blk);
     m0 = tile_m * 256;
   }
   const int n0 = tile_n * 256;
@@ -570,6 +571,27 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
   epilogue<IS>(p, Mlim, half, smem, wave, lane, wrow, n0 + wn * 128 + 64, part_row);
 }
 
+template <bool TA, bool TB, bool GRP>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) gemm_dtl_kernel(const GemmArgs p) {
+  dtl_block<TA, TB, GRP>(p, -1);
+}
+
+// Weight gradients of a layer in one launch: C_i += A_i^T B_i (fp32), all with the same reduction.  Alone each ends in a round of
+// workgroups that is partly empty (h = 2048, ffn 6144: 384, 192, 128 and 64 tiles on 256 CUs), or takes smaller tiles or a split to
+// fill the chip; together they are 768 tiles, three full rounds.  Measured there, four launches -> one, us: 4096 tokens 470 -> 367,
+// 2048 287 -> 224, 1024 185 -> 145 (with the eight-wave kernel 386, 221 and 137: it is behind where the launch is long).
+struct WgradOne { const void *A, *B; void* C; long lda, ldb, ldc; unsigned bytesA, bytesB; int M, N, first; };
+struct WgradArgs { int n, K; WgradOne g[GEMM_WGRAD_MAX]; };
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) gemm_wgrad_kernel(const WgradArgs a) {
+  int i = 0;
+  while (i + 1 < a.n && (int)blockIdx.x >= a.g[i + 1].first) ++i;
+  const WgradOne& q = a.g[__builtin_amdgcn_readfirstlane(i)];
+  GemmArgs g{};
+  g.A = q.A; g.B = q.B; g.C = q.C; g.lda = q.lda; g.ldb = q.ldb; g.ldc = q.ldc; g.bytesA = q.bytesA; g.bytesB = q.bytesB;
+  g.M = q.M; g.N = q.N; g.K = a.K; g.alpha = 1.f; g.beta = 1; g.epi = EPI_F32;
+  dtl_block<true, true, false>(g, (int)blockIdx.x - q.first);
+}
+
 }  // namespace
 
 template <bool TA, bool TB, bool GRP = false>
@@ -594,4 +616,26 @@ hipError_t gemm_dtl_launch(hipStream_t st, const GemmArgs& a, int layout) {
     case GEMM_NN: return dtl_launch_one<false, true>(st, a);
     default: return dtl_launch_one<true, true>(st, a);
   }
+}
+
+hipError_t gemm_wgrad_run(hipStream_t st, int n, const GemmArgs* g) {
+  static bool attr_done = false;
+  if (!attr_done) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_wgrad_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, DTL_SMEM);
+    if (e != hipSuccess) return e;
+    attr_done = true;
+  }
+  if (n < 1 || n > GEMM_WGRAD_MAX) return hipErrorInvalidValue;
+  WgradArgs a{};
+  a.n = n;
+  a.K = g[0].K;
+  int blocks = 0;
+  for (int i = 0; i < n; ++i) {
+    const GemmArgs& p = g[i];
+    if (p.K != a.K || p.K2 || p.epi != EPI_F32 || !p.beta || p.alpha != 1.f) return hipErrorInvalidValue;
+    a.g[i] = {p.A, p.B, p.C, p.lda, p.ldb, p.ldc, p.bytesA, p.bytesB, p.M, p.N, blocks};
+    blocks += ((p.M + 255) / 256) * ((p.N + 255) / 256);
+  }
+  RP_LAUNCH(gemm_wgrad_kernel, dim3(blocks), dim3(256), DTL_SMEM, st, a);
+  return hipGetLastError();
 }

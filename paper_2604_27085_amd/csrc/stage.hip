@@ -175,6 +175,10 @@ struct Exec {
   size_t split_off = 0;            // scratch for the partial products of a GEMM reduction split, in the plan in use
   bool has_split = false;
   bool gain_parts = false;         // a layer's three gain gradients are summed by one launch (scratch for two more of them)
+  struct Late { int n = 0; GemmArgs g[GEMM_WGRAD_MAX]; };
+  bool late_wgrads = false;        // dact|dgu stay as they are to the end of a layer
+  Late* late = nullptr;            // where set, large weight gradients are noted here and run together at the layer's end
+  size_t dkvp = 0;                 // dK/dV partials
   RopeArgs rope;                   // the RoPE table is filled by the first norm of the stage
   int ds_heads = 0;                // query heads whose dS the workspace holds (0: the attention backward recomputes the scores for dQ)
   float* router = nullptr;         // router logits of the layer being run, fp32 [T, E] (mixture of experts): read, or
@@ -250,6 +254,17 @@ struct Exec {
       chk(gemm_group_launch(st, s.n, s.layout, s.g), "gemm group");
     }
     q.n = 0;
+  }
+  void run_late(const Late& q) {
+    if (q.n == 0) return;
+    double fl = 0.0, by = 0.0;
+    for (int i = 0; i < q.n; ++i) {
+      const GemmArgs& g = q.g[i];
+      fl += 2.0 * g.M * (double)g.N * g.K;
+      by += 2.0 * ((double)g.M + g.N) * g.K + 8.0 * g.M * (double)g.N;
+    }
+    mark("gemm_256x256_TN", fl, by);
+    chk(gemm_wgrad_launch(st, q.n, q.g), "weight gradients");
   }
   // Grouped GEMM over expert-sorted slot rows: C[slot, N] = A[row_map ? row_map[slot] : slot, K] * op(B_e), B_e the
   // matrix of the expert that owns the slot.  set = the layer's saved internals (routing plan).
@@ -350,11 +365,14 @@ void linear_bwd(Exec& X, const LayerW& W, const LayerG& G, int w_id, const Fused
   const int nr = f.n * X.D.r, T = (int)X.T;
   void* ud = X.at<void>(X.P.ud);
   Exec::Group q;
-  // the weight gradient joins the first group when it is small enough to share a launch, else it runs behind dX
+  // the weight gradient joins the first group when it is small enough to share a launch, else it waits for the layer's end, or runs
+  // behind dX
   auto wgrad = [&](bool first) {
     Exec::Group w;
     X.add_wgrad(w, dy, N, x, K, G.t(w_id), K, N, K, T);
-    if (w.n && gemm_groupable(w.g[0]) == first) X.add(q, GEMM_TN, w.g[0]);
+    if (!w.n || gemm_groupable(w.g[0]) != first) return;
+    if (!first && X.late && X.late->n < GEMM_WGRAD_MAX) X.late->g[X.late->n++] = w.g[0];
+    else X.add(q, GEMM_TN, w.g[0]);
   };
   if (f.n) {
     // what needs dy and the forward's U only: dU = s dY B, dB += dY^T U per adapter
@@ -438,6 +456,8 @@ void layer_backward(Exec& X, const LayerW& W, const LayerG& G, char* set, const 
   bf16_t* dqkv = X.at<bf16_t>(X.P.dqkv);
   void* dy = X.at<void>(X.P.tA);
 
+  Exec::Late late;
+  X.late = X.late_wgrads ? &late : nullptr;
   const double Td = (double)T;
   if (D.E > 0) {
     // z = y + sum_j w_j FFN_ej(n2): per slot dact = Wd_e^T dz_t (the routing weight is applied inside the SwiGLU
@@ -518,7 +538,7 @@ void layer_backward(Exec& X, const LayerW& W, const LayerG& G, char* set, const 
         RUN(X, part_name[part], fl, by,
             k_attn_bwd(X.st, part, P16(S(b.qr), qo), P16(S(b.kr), ko), qkv + vo, P16(X.at<void>(X.P.dout), qo), (const float*)S(b.lse) + stat,
                        X.at<float>(X.P.delta) + stat, P16(X.at<void>(X.P.dqr), qo), P16(X.at<void>(X.P.dkr), ko), dqkv + vo,
-                       X.at<float>(X.P.dkvp), D.qd, D.kd, D.n1, D.qd, D.qd, D.kd, D.n1, nb, X.seq, nh, nkh, D.d, ds, ds ? nullptr : P16(S(b.o), qo), D.qd));
+                       X.at<float>(X.dkvp), D.qd, D.kd, D.n1, D.qd, D.qd, D.kd, D.n1, nb, X.seq, nh, nkh, D.d, ds, ds ? nullptr : P16(S(b.o), qo), D.qd));
       }
     }
   RUN(X, "qknorm_rope_bwd", 0, 6.0 * Td * (D.qd + D.kd),
@@ -526,6 +546,8 @@ void layer_backward(Exec& X, const LayerW& W, const LayerG& G, char* set, const 
                     W.t(RP_T_GQ), W.t(RP_T_GK), (float*)S(b.rstd_q), (float*)S(b.rstd_k), qkv, qkv + D.qd, D.n1,
                     G.t(RP_T_GQ), G.t(RP_T_GK), gp_qk, X.at<float2>(X.P.rope), T, X.seq, D.a, D.kh, c.qk_norm, c.rms_eps, defer));
   linear_bwd(X, W, G, RP_T_WQKV, fused_qkv(D), X.ctx->dl.bd1, dqkv, D.n1, S(b.n1), D.h, X.at<void>(X.P.dn), S(b.u1));
+  X.run_late(late);       // (before the norm below: dz may lie in dx_out)
+  X.late = nullptr;
   RUN(X, "rmsnorm_bwd", 0, 8.0 * Td * D.h,
       k_rmsnorm_bwd(X.st, X.at<void>(X.P.dn), 0, x, W.t(RP_T_G1), (const float*)S(b.rstd1), dy, dx_out, G.t(RP_T_G1), partials, T, D.h, defer));
   if (gains.n) RUN(X, "gain_grads", 0, 4.0 * (T < RP_PARTIAL_BLOCKS ? T : RP_PARTIAL_BLOCKS) * (2.0 * D.h + 2.0 * D.d), k_colsum_add(X.st, gains));
@@ -770,7 +792,8 @@ rp_status rp_stage_backward(rp_ctx* ctx, int slot_id, int phases, const void* x_
   Slot& sl = ctx->slots[slot_id];
   Exec X{ctx, ctx->compute, dims_of(ctx->cfg), batch, seq, (long)batch * seq, static_cast<char*>(workspace), P};
   X.split_off = P.split_bwd; X.has_split = true;
-  X.gain_parts = ctx->cfg.train_base && workspace_bytes_in >= P.ds;
+  X.gain_parts = X.late_wgrads = ctx->cfg.train_base && workspace_bytes_in >= P.ds;
+  X.dkvp = X.late_wgrads && X.D.a != X.D.kh ? P.dkvp_own : P.dkvp;
   if (workspace_bytes_in > P.ds) X.ds_heads = attn_ds_heads((workspace_bytes_in < P.bwd_bytes ? workspace_bytes_in : P.bwd_bytes) - P.ds, batch, seq, X.D.a, X.D.kh, X.D.d);
   const int L = ctx->cfg.n_layers;
   if (do_fwd) X.rope = RopeArgs{X.at<float2>(P.rope), seq, X.D.d, ctx->cfg.rope_base};

@@ -50,9 +50,9 @@ def test_dq_from_kept_ds(batch, seq, a, kh, passes):
     need = int(re.search(r"< (\d+)", str(e.value)).group(1))
     dx0, gr0, n0 = run(need)
     assert n0 == 1
-    need = r.wsbytes - _heads(seq) * a * batch          # with the partials of the gain gradients, which add up in the same order
+    need = r.wsbytes - _heads(seq) * a * batch          # with the other optional regions
     dx1, gr1, n0 = run(need)
-    assert n0 == 1 and torch.equal(dx0, dx1) and torch.equal(gr0, gr1)
+    assert n0 == 1 and torch.equal(dx0, dx1) and float((gr1 - gr0).norm() / gr0.norm()) < 1e-5       # fp32 sums in another order
     first = None
     for k, heads in enumerate(passes):
         dx, gr, n = run(need + heads * _heads(seq))
