@@ -545,10 +545,10 @@ RP_DEV void dtl_block(const GemmArgs& p, int blk) {
     q.epi = EPI_BF16;
     const int gcol = (n0 >> 1) + wn * 64;
     fetch(1);
-    epilogue<IS>(q, Mlim, half, smem, wave, lane, wrow, gcol + fold, part_row);
+    epilogue<IS, true>(q, Mlim, half, smem, wave, lane, wrow, gcol + fold, part_row);
     q.N = fold;     // the last tile's gate columns end where the up columns begin
     fetch(0);
-    epilogue<IS>(q, Mlim, half, smem, wave, lane, wrow, gcol, part_row);
+    epilogue<IS, true>(q, Mlim, half, smem, wave, lane, wrow, gcol, part_row);
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -562,18 +562,22 @@ RP_DEV void dtl_block(const GemmArgs& p, int blk) {
         }
     q.C = p.C2;
     q.ldc = p.ldc2;
-    epilogue<IS>(q, Mlim, half, smem, wave, lane, wrow, gcol, part_row);
+    epilogue<IS, true>(q, Mlim, half, smem, wave, lane, wrow, gcol, part_row);
     return;
   }
   fetch(0);
-  epilogue<IS>(p, Mlim, half, smem, wave, lane, wrow, n0 + wn * 128, part_row);
+  epilogue<IS, true>(p, Mlim, half, smem, wave, lane, wrow, n0 + wn * 128, part_row);
   fetch(1);
-  epilogue<IS>(p, Mlim, half, smem, wave, lane, wrow, n0 + wn * 128 + 64, part_row);
+  epilogue<IS, true>(p, Mlim, half, smem, wave, lane, wrow, n0 + wn * 128 + 64, part_row);
 }
 
-template <bool TA, bool TB, bool GRP>
+// SWB: the instance for EPI_SWIGLU_BWD alone.  Its epilogue is the longest of all; compiled together with the others a third of its
+// scalars live in vector registers (8192 x 12288 x 4096 NN 830 -> 812 us with its loads a batch ahead).
+template <bool TA, bool TB, bool GRP, bool SWB>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) gemm_dtl_kernel(const GemmArgs p) {
-  dtl_block<TA, TB, GRP>(p, -1);
+  GemmArgs q = p;
+  if constexpr (SWB) q.epi = EPI_SWIGLU_BWD;
+  dtl_block<TA, TB, GRP>(q, -1);
 }
 
 // Weight gradients of a layer in one launch: C_i += A_i^T B_i (fp32), all with the same reduction.  Alone each ends in a round of
@@ -594,10 +598,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
 
 }  // namespace
 
-template <bool TA, bool TB, bool GRP = false>
+template <bool TA, bool TB, bool GRP = false, bool SWB = false>
 static hipError_t dtl_launch_one(hipStream_t st, const GemmArgs& a) {
   static bool attr_done = false;
-  auto kern = gemm_dtl_kernel<TA, TB, GRP>;
+  auto kern = gemm_dtl_kernel<TA, TB, GRP, SWB>;
   if (!attr_done) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, DTL_SMEM);
     if (e != hipSuccess) return e;
@@ -613,7 +617,7 @@ hipError_t gemm_dtl_launch(hipStream_t st, const GemmArgs& a, int layout) {
   if (a.grp_tab) return layout == GEMM_NT ? dtl_launch_one<false, false, true>(st, a) : layout == GEMM_NN ? dtl_launch_one<false, true, true>(st, a) : hipErrorInvalidValue;
   switch (layout) {
     case GEMM_NT: return dtl_launch_one<false, false>(st, a);
-    case GEMM_NN: return dtl_launch_one<false, true>(st, a);
+    case GEMM_NN: return a.epi == EPI_SWIGLU_BWD ? dtl_launch_one<false, true, false, true>(st, a) : dtl_launch_one<false, true>(st, a);
     default: return dtl_launch_one<true, true>(st, a);
   }
 }
