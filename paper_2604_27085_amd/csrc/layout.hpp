@@ -127,7 +127,7 @@ struct Plan {
   int moe_max_tiles;             // capacity of the tile table
   size_t split_fwd, split_bwd, h_split;   // partial products of a GEMM reduction split (RP_SPLITK_WS_BYTES each), per plan
   size_t dkvp;   // dK/dV partials of grouped attention (at most one per query head); shares memory with dact|dgu, dead by then
-  size_t gain_parts, dkvp_own, ds;                // optional: gain gradient partials, dK/dV partials of their own, dS of the attention backward
+  size_t gain_parts, dkvp_own, ud2, ds;                // optional: gain gradient partials, dK/dV partials of their own, dS of the attention backward
   size_t fwd_bytes, bwd_min, bwd_bytes;           // bwd_min: the backward plan without the optional regions
   // head
   size_t h_xf, h_rstd, h_part, h_zlab, h_lse, h_coef, h_dzt, h_dxacc, h_partials, head_bytes;
@@ -212,6 +212,8 @@ inline Plan make_plan(const rp_stage_cfg& c, int batch, int seq, bool compact = 
   // dK/dV partials that leave dact|dgu alone: the weight gradients then wait for each other until the layer's end and share a launch
   P.dkvp_own = o;
   if (D.L > 0 && c.train_base && D.a != D.kh) take(2 * T * D.qd * 4);
+  P.ud2 = o;   // a second dU buffer
+  if (D.L > 0) take(T * (size_t)(3 * D.r) * 2);
   // dS of the attention backward (see k_attn_ds_bytes), as many query heads as 4 GiB hold; a workspace that ends before it runs the
   // dQ kernel that recomputes the scores
   P.ds = o;
