@@ -596,21 +596,27 @@ static hipError_t prepare(int layout, GemmArgs& a) {
   return hipSuccess;
 }
 
+// Grouped: 256-row tiles as in the table, rows of A are tile rows, one operand pair.
+static hipError_t prepare_grouped(int layout, GemmArgs& a) {
+  if (layout == GEMM_TN || a.K2 || !a.grp_ntiles || a.grp_max_tiles <= 0 || (a.epi != EPI_BF16 && a.epi != EPI_F32 && a.epi != EPI_SWIGLU_FWD)) return hipErrorInvalidValue;
+  if (a.row_map) {
+    a.bytesA = extent_bytes(a.row_map_rows, a.K, a.lda);
+    if (a.bytesA == ~0u || a.row_map_rows <= 0) return hipErrorInvalidValue;
+  }
+  return hipSuccess;
+}
+
 hipError_t gemm_launch(hipStream_t st, int layout, const GemmArgs& a_in, int tile_hint) {
   if (a_in.M <= 0 || a_in.N <= 0) return hipSuccess;
   if (layout < GEMM_NT || layout > GEMM_TN) return hipErrorInvalidValue;
   GemmArgs a = a_in;
-  const bool ta = layout == GEMM_TN;
   hipError_t e = prepare(layout, a);
   if (e != hipSuccess) return e;
   const Choice ch = choose(a, tile_hint);
   const int tile = ch.tile;
-  if (a.grp_tab) {   // grouped: 256-row tiles as in the table, rows of A are tile rows, one operand pair
-    if (ta || a.K2 || !a.grp_ntiles || a.grp_max_tiles <= 0 || (a.epi != EPI_BF16 && a.epi != EPI_F32 && a.epi != EPI_SWIGLU_FWD)) return hipErrorInvalidValue;
-    if (a.row_map) {
-      a.bytesA = extent_bytes(a.row_map_rows, a.K, a.lda);
-      if (a.bytesA == ~0u || a.row_map_rows <= 0) return hipErrorInvalidValue;
-    }
+  if (a.grp_tab) {
+    e = prepare_grouped(layout, a);
+    if (e != hipSuccess) return e;
   }
   // Reduction split: the slices' partial products go to scratch memory and a second kernel adds them in a fixed order, so
   // results are reproducible run to run.
@@ -733,4 +739,17 @@ hipError_t gemm_wgrad_launch(hipStream_t st, int n, const GemmArgs* g) {
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+hipError_t gemm_pair_launch(hipStream_t st, const GemmArgs& nt, const GemmArgs& nn) {
+  GemmArgs a = nt, b = nn;
+  if (a.M <= 0 || a.N <= 0 || b.N <= 0) return hipErrorInvalidValue;
+  if (!a.grp_tab || a.grp_tab != b.grp_tab || a.grp_ntiles != b.grp_ntiles || a.grp_max_tiles != b.grp_max_tiles || a.epi != EPI_BF16 || b.epi != EPI_BF16 ||
+      a.R || b.R || a.alpha != 1.f || b.alpha != 1.f)
+    return hipErrorInvalidValue;
+  hipError_t e = prepare(GEMM_NT, a);
+  if (e == hipSuccess) e = prepare_grouped(GEMM_NT, a);
+  if (e == hipSuccess) e = prepare(GEMM_NN, b);
+  if (e == hipSuccess) e = prepare_grouped(GEMM_NN, b);
+  return e == hipSuccess ? gemm_pair_run(st, a, b) : e;
 }

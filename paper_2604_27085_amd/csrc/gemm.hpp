@@ -96,6 +96,9 @@ bool gemm_groupable(const GemmArgs& a);
 hipError_t gemm_group_launch(hipStream_t st, int n, const int* layouts, const GemmArgs* g);
 // The shared launch itself (gemm_mid.hip): arguments prepared, g[i].splits slices each.
 hipError_t gemm_multi_run(hipStream_t st, int n, const int* layouts, const GemmArgs* g);
+// Two grouped products over the same table in one launch, layouts NT and NN, bf16 results.
+hipError_t gemm_pair_launch(hipStream_t st, const GemmArgs& nt, const GemmArgs& nn);
+hipError_t gemm_pair_run(hipStream_t st, const GemmArgs& nt, const GemmArgs& nn);       // the launch itself (gemm_dtl.hip)
 // Weight gradients (layout TN, fp32, accumulating, the same reduction) that do not depend on each other: in one launch of 256x256 tiles
 // when the tile model finds that cheaper than one by one, which it is when their last rounds would stay partly empty.
 #define GEMM_WGRAD_MAX 4

@@ -89,9 +89,9 @@ RP_DEV i32x4 raw_rsrc(const void* base, uint32_t bytes) {
 // with that and the tile order of the plain products, us: h = 4096, 128 experts of 1536, backward stage of 256 | 2048 | 8192 tokens
 // 2326 -> 2250 | 3664 -> 3510 | 13270 -> 12950;  h = 2880, 32 experts of 2880, forward of 1000 | 8192 tokens 659 -> 636 |
 // 2995 -> 2876.  What bounds the 128-row tiles then is the experts' weights (gate/up 3.5 GB in 706 us, matrix pipe 31 % busy).
-// blk: the output tile of the product (-1: the workgroup's number).
+// blk: the output tile of the product (-1: the workgroup's number); grouped: the entry gm of the table and the tile column gn.
 template <bool TA, bool TB, bool GRP>
-RP_DEV void dtl_block(const GemmArgs& p, int blk) {
+RP_DEV void dtl_block(const GemmArgs& p, int blk, int gm = 0, int gn = 0) {
   static_assert((!TA || TB) && !(GRP && TA), "not a layout of this library");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -103,10 +103,8 @@ RP_DEV void dtl_block(const GemmArgs& p, int blk) {
   const bf16* Bbase = static_cast<const bf16*>(p.B);
   int NI = 4;                                  // 32-row blocks of a wave that hold rows
   if constexpr (GRP) {
-    // the table's length is known on the device only: surplus workgroups leave
-    const int ntiles = *p.grp_ntiles, tiles_n = (p.N + 255) / 256;
-    if ((int)blockIdx.x >= ntiles * tiles_n) return;
-    tile_of_block(ntiles * 256, p.N, 256, 256, tile_m, tile_n, 4);
+    tile_m = gm;
+    tile_n = gn;
     const int4 g = p.grp_tab[tile_m];
     m0 = g.y;
     Mlim = g.y + g.z;
@@ -577,7 +575,32 @@ template <bool TA, bool TB, bool GRP, bool SWB>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) gemm_dtl_kernel(const GemmArgs p) {
   GemmArgs q = p;
   if constexpr (SWB) q.epi = EPI_SWIGLU_BWD;
-  dtl_block<TA, TB, GRP>(q, -1);
+  int tile_m = 0, tile_n = 0;
+  if constexpr (GRP) {   // the table's length is known on the device only: surplus workgroups leave
+    const int ntiles = *p.grp_ntiles;
+    if ((int)blockIdx.x >= ntiles * ((p.N + 255) / 256)) return;
+    tile_of_block(ntiles * 256, p.N, 256, 256, tile_m, tile_n, 4);
+  }
+  dtl_block<TA, TB, GRP>(q, -1, tile_m, tile_n);
+}
+
+// Two grouped products that read the same weights, NT and NN, over the same table: the tiles of an entry follow each other, those of
+// the first product and then those of the second, on one XCD.  The second reading of a group's weights then comes out of the Infinity
+// Cache (the groups in flight have 150 MB) instead of HBM: h = 4096, 128 experts of 1536, 2048 tokens
+// 413 + 333 -> 638 us; backward stage of 256 | 2048 tokens 2178 -> 2110 | 3510 -> 3369.
+struct PairArgs { GemmArgs nt, nn; };
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) gemm_pair_kernel(const PairArgs a) {
+  GemmArgs p = a.nt, q = a.nn;       // (the plain epilogue only, known here: it needs none of the others' code or scalars)
+  p.epi = q.epi = EPI_BF16;
+  p.R = q.R = nullptr;
+  p.alpha = q.alpha = 1.f;
+  p.K2 = q.K2 = 0;
+  const int ntiles = *a.nt.grp_ntiles, c1 = (a.nt.N + 255) / 256, cols = c1 + (a.nn.N + 255) / 256;
+  if ((int)blockIdx.x >= ntiles * cols) return;
+  const int id = xcd_remap((int)blockIdx.x, ntiles * cols);
+  const int tile_m = id / cols, c = id - tile_m * cols;
+  if (c < c1) dtl_block<false, false, true>(p, -1, tile_m, c);
+  else dtl_block<false, true, true>(q, -1, tile_m, c - c1);
 }
 
 // Weight gradients of a layer in one launch: C_i += A_i^T B_i (fp32), all with the same reduction.  Alone each ends in a round of
@@ -641,5 +664,17 @@ hipError_t gemm_wgrad_run(hipStream_t st, int n, const GemmArgs* g) {
     blocks += ((p.M + 255) / 256) * ((p.N + 255) / 256);
   }
   RP_LAUNCH(gemm_wgrad_kernel, dim3(blocks), dim3(256), DTL_SMEM, st, a);
+  return hipGetLastError();
+}
+
+hipError_t gemm_pair_run(hipStream_t st, const GemmArgs& nt, const GemmArgs& nn) {
+  static bool attr_done = false;
+  if (!attr_done) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_pair_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, DTL_SMEM);
+    if (e != hipSuccess) return e;
+    attr_done = true;
+  }
+  const PairArgs a{nt, nn};
+  RP_LAUNCH(gemm_pair_kernel, dim3(nt.grp_max_tiles * ((nt.N + 255) / 256 + (nn.N + 255) / 256)), dim3(256), DTL_SMEM, st, a);
   return hipGetLastError();
 }

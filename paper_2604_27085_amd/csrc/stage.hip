@@ -176,6 +176,7 @@ struct Exec {
   bool has_split = false;
   bool gain_parts = false;         // a layer's three gain gradients are summed by one launch (scratch for two more of them)
   struct Late { int n = 0; GemmArgs g[GEMM_WGRAD_MAX]; };
+  const void* moe_dz = nullptr;    // mixture of experts: the output gradient of the layer being run, where the forward already has it
   bool late_wgrads = false;        // dact|dgu stay as they are to the end of a layer
   Late* late = nullptr;            // where set, large weight gradients are noted here and run together at the layer's end
   size_t dkvp = 0;                 // dK/dV partials
@@ -278,23 +279,25 @@ struct Exec {
   }
   // Grouped GEMM over expert-sorted slot rows: C[slot, N] = A[row_map ? row_map[slot] : slot, K] * op(B_e), B_e the
   // matrix of the expert that owns the slot.  set = the layer's saved internals (routing plan).
-  void gemm_grouped(int layout, const char* set, const void* A, long lda, int a_rows, bool gather, const void* B, long ldb,
-                    long strideB, void* C, long ldc, int N, int K, void* act = nullptr) {
+  GemmArgs grouped_args(const char* set, const void* A, long lda, int a_rows, bool gather, const void* B, long ldb, long strideB, void* C,
+                        long ldc, int N, int K, void* act = nullptr) const {
     GemmArgs g; gemm_zero_args(g);
-    const long Tk = T * D.topk;
-    g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc; g.M = (int)Tk; g.N = N; g.K = K; g.epi = EPI_BF16;
+    g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc; g.M = (int)(T * D.topk); g.N = N; g.K = K; g.epi = EPI_BF16;
     if (act) { g.epi = EPI_SWIGLU_FWD; g.C2 = act; g.ldc2 = N / 2; }   // gate | up columns: silu(gate) * up from the epilogue
     g.grp_tab = reinterpret_cast<const int4*>(set + P.lb.m_tab);
     g.grp_ntiles = reinterpret_cast<const int*>(set + P.lb.m_ntiles);
     g.grp_max_tiles = P.moe_max_tiles;
     g.grp_strideB = strideB;
     if (gather) { g.row_map = reinterpret_cast<const int*>(set + P.lb.m_tok); g.row_map_rows = a_rows; }
-    if (ctx->tracing) {
-      char nm[40];
-      snprintf(nm, sizeof(nm), "gemm_grouped_%s", layout == GEMM_NT ? "NT" : "NN");
-      // every expert's weights are read once; rows as in the dense case
-      mark(nm, 2.0 * Tk * (double)N * K, 2.0 * ((double)Tk * K + (double)D.E * N * K) + (act ? 3.0 : 2.0) * Tk * (double)N);
-    }
+    return g;
+  }
+  // every expert's weights are read once; rows as in the dense case
+  double grouped_flops(const GemmArgs& g) const { return 2.0 * g.M * (double)g.N * g.K; }
+  double grouped_bytes(const GemmArgs& g) const {
+    return 2.0 * ((double)g.M * g.K + (double)D.E * g.N * g.K) + (g.C2 ? 3.0 : 2.0) * g.M * (double)g.N;
+  }
+  void gemm_grouped(int layout, const GemmArgs& g) {
+    mark(layout == GEMM_NT ? "gemm_grouped_NT" : "gemm_grouped_NN", grouped_flops(g), grouped_bytes(g));
     chk(gemm_launch(st, layout, g), "gemm_grouped");
   }
   // C[M,N] (fp32) = A * B^T, overwritten; one pass, no reduction split, so the result does not depend on scheduling
@@ -411,6 +414,12 @@ void linear_bwd(Exec& X, const LayerW& W, const LayerG& G, int w_id, const Fused
   X.run(q);
 }
 
+// dact = Wd_e^T dz_t per slot.
+GemmArgs moe_dact(const Exec& X, const LayerW& W, const char* set, const void* dz) {
+  const Dims& D = X.D;
+  return X.grouped_args(set, dz, D.h, (int)X.T, true, W.t(RP_T_WD), D.m, (long)D.h * D.m, X.at<void>(X.P.dact), D.m, D.m, D.h);
+}
+
 // moe_f_off: workspace offset of the per-slot expert output buffer of the plan in use (forward or backward stage).
 void layer_forward(Exec& X, const LayerW& W, char* set, const void* x, void* z, size_t moe_f_off) {
   const Dims& D = X.D;
@@ -451,8 +460,15 @@ void layer_forward(Exec& X, const LayerW& W, char* set, const void* x, void* z, 
     RUN(X, "moe_plan", 0, 16.0 * Tkd, k_moe_plan(X.st, idx, T, D.E, D.topk, (int*)S(b.m_cnt), (int*)S(b.m_seg), S(b.m_tab),
                                                      (int*)S(b.m_ntiles), slot_of, (int*)S(b.m_tok), (int*)S(b.m_hist)));
     // SwiGLU in the epilogue, as in the dense layer
-    X.gemm_grouped(GEMM_NT, set, S(b.n2), D.h, T, true, W.t(RP_T_WGU), D.h, (long)2 * D.m * D.h, S(b.gu), 2 * D.m, 2 * D.m, D.h, S(b.act));
-    X.gemm_grouped(GEMM_NT, set, S(b.act), D.m, (int)Tk, false, W.t(RP_T_WD), D.m, (long)D.h * D.m, f, D.h, D.h, D.m);
+    X.gemm_grouped(GEMM_NT, X.grouped_args(set, S(b.n2), D.h, T, true, W.t(RP_T_WGU), D.h, (long)2 * D.m * D.h, S(b.gu), 2 * D.m, 2 * D.m, D.h, S(b.act)));
+    const GemmArgs down = X.grouped_args(set, S(b.act), D.m, (int)Tk, false, W.t(RP_T_WD), D.m, (long)D.h * D.m, f, D.h, D.h, D.m);
+    if (X.moe_dz) {   // the gradient of this layer's output is known: its product with the same weights rides along
+      const GemmArgs back = moe_dact(X, W, set, X.moe_dz);
+      X.mark("gemm_grouped_pair", X.grouped_flops(down) + X.grouped_flops(back), X.grouped_bytes(down) + X.grouped_bytes(back) - 2.0 * D.E * D.h * (double)D.m);
+      X.chk(gemm_pair_launch(X.st, down, back), "gemm_grouped_pair");
+    } else {
+      X.gemm_grouped(GEMM_NT, down);
+    }
     RUN(X, "moe_combine", 0, 2.0 * Tkd * D.h + 4.0 * Td * D.h, k_moe_combine(X.st, f, slot_of, w, S(b.y), z, T, D.h, D.topk));
     return;
   }
@@ -487,15 +503,16 @@ void layer_backward(Exec& X, const LayerW& W, const LayerG& G, char* set, const 
     float* w_slot = X.at<float>(X.P.moe_wslot);
     float* dw_slot = X.at<float>(X.P.moe_dw);
     void* dxp = X.at<void>(X.P.moe_f_bwd);
-    X.gemm_grouped(GEMM_NN, set, dz, D.h, T, true, W.t(RP_T_WD), D.m, (long)D.h * D.m, X.at<void>(X.P.dact), D.m, D.m, D.h);
+    if (!X.moe_dz) X.gemm_grouped(GEMM_NN, moe_dact(X, W, set, dz));
+    X.moe_dz = nullptr;
     RUN(X, "moe_scatter_w", 0, 12.0 * Tkd, k_moe_scatter_w(X.st, w, slot_of, w_slot, Tk));
     RUN(X, "moe_swiglu_bwd", 0, 10.0 * Tkd * D.m,
         k_moe_swiglu_bwd(X.st, X.at<void>(X.P.dact), S(b.gu), w_slot, X.at<void>(X.P.dgu), dw_slot, Tk, D.m));
     float* dlog = X.d_router ? X.d_router : (c.moe_router ? X.at<float>(X.P.moe_dlog) : nullptr);
     if (dlog)
       RUN(X, "moe_dlogits", 0, 4.0 * Td * D.E + 12.0 * Tkd, k_moe_dlogits(X.st, idx, w, slot_of, dw_slot, dlog, T, D.E, D.topk));
-    X.gemm_grouped(GEMM_NN, set, X.at<void>(X.P.dgu), 2 * D.m, (int)Tk, false, W.t(RP_T_WGU), D.h, (long)2 * D.m * D.h, dxp, D.h,
-                   D.h, 2 * D.m);
+    X.gemm_grouped(GEMM_NN, X.grouped_args(set, X.at<void>(X.P.dgu), 2 * D.m, (int)Tk, false, W.t(RP_T_WGU), D.h, (long)2 * D.m * D.h, dxp,
+                                           D.h, D.h, 2 * D.m));
     RUN(X, "moe_combine", 0, 2.0 * Tkd * D.h + 2.0 * Td * D.h,
         k_moe_combine(X.st, dxp, slot_of, nullptr, nullptr, X.at<void>(X.P.dn), T, D.h, D.topk));
     if (c.moe_router) {
@@ -828,6 +845,7 @@ rp_status rp_stage_backward(rp_ctx* ctx, int slot_id, int phases, const void* x_
       // the stage output goes straight to x_out: the backward needs the layer outputs below the last one only
       void* z = (l == L - 1 && x_out) ? x_out : set_of(l) + P.lb.z;
       if (router_logits) X.router = router_logits + (size_t)l * X.T * X.D.E;
+      X.moe_dz = l == L - 1 && do_bwd ? dy : nullptr;
       layer_forward(X, W, set_of(l), x, z, P.moe_f_bwd);
       x = z;
     }
