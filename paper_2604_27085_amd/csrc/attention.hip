@@ -1,4 +1,5 @@
-// Causal grouped-query attention on the gfx950 matrix cores, flash style (no s x s matrix ever leaves the CU).
+// Causal grouped-query attention on the gfx950 matrix cores, flash style: no s x s matrix leaves the CU, except
+// that a backward with room for it keeps dS in bf16 (see attn_ds_block).
 //
 // All three kernels use v_mfma_f32_32x32x16_bf16 with the score tile computed TRANSPOSED relative to the row that is
 // being normalised: the 32x32 accumulator layout gives every lane one column and 16 rows, so with queries (forward,
@@ -15,7 +16,8 @@
 //
 //   forward : workgroup = NW waves x 32*QT queries of one head, loop over 64-key tiles up to the diagonal; NW = 8 (one
 //             workgroup per CU, two sets of K/V tiles, one barrier per tile) when the grid is large enough, else 4
-//   dQ      : same decomposition; recomputes S^T and dP^T, accumulates dQ^T
+//   dQ      : same decomposition; recomputes S^T and dP^T, accumulates dQ^T, and works out delta = rowsum(dO * O) for itself and
+//             for dK/dV, which runs behind it; with kept dS it is a product of gemm_mid.hip behind dK/dV instead
 //   dK, dV  : workgroup = 128 keys against one query head, or two or four of a group one after the other
 //             (heads_per_workgroup); loops over 64-query tiles from the diagonal on and accumulates dK^T, dV^T in
 //             registers.  d = 128: eight waves, pairs of waves share 32 keys, split the accumulators over the head
@@ -47,7 +49,7 @@ struct AttnArgs {
   int fold;   // see heavy_rank()
   int hpw;    // dK/dV kernel: query heads of one group that a workgroup takes one after the other (a divisor of a / kh)
   int kblock; // dK/dV kernel: key tiles per run of one head in an XCD's launch order (0: key-tile-major order over all heads)
-  bf16* ds;   // dK/dV kernel with kept dS: [batch * a] heads of attn_ds_head_bytes each (see attn_ds_block)
+  bf16* ds;   // dK/dV kernel with kept dS: [batch * a] heads of k_attn_ds_bytes each (see attn_ds_block)
 };
 
 // The dK/dV kernel can leave dS (bf16, as its products take it) in memory, from which dQ = dS K is one product instead of the three

@@ -32,9 +32,9 @@
 //             s of row k at segment s ^ (k & 3)), its fragments are two transposing reads (ds_read_b64_tr_b16) each:
 //             twelve read instructions and four loads per 16-slot step, a slot plan of its own.
 //   TN        the same for A: sixteen reads per step, one per slot, the loads on top of them.
-// Second operand pair, row map, grouped mode, reduction slices and every epilogue of gemm_device.hpp (applied to the
-// two 128x64 halves of a wave's block in turn) as in gemm.hip; results are bit-identical to its 256x256 tile (same
-// MFMA, same order of the reduction).  gemm_launch picks this kernel for reductions of 40 K tiles or more and outputs
+// Second operand pair, row map, reduction slices and every epilogue of gemm_device.hpp (applied to the two 128x64 halves
+// of a wave's block in turn) as in gemm.hip; results are bit-identical to its 256x256 tile (same MFMA, same order of the
+// reduction).  Grouped products (GRP below) run here only.  gemm_launch picks this kernel for reductions of 40 K tiles or more and outputs
 // that are not skinny: its fixed cost per output tile is higher than the eight-wave kernel's.
 #include "gemm_device.hpp"
 #include <type_traits>

@@ -145,7 +145,7 @@ __global__ void __launch_bounds__(256) ce_chunk_ref_kernel(const float2* __restr
 
 // p[r][t] = exp(z[r][t] - m[t]) as bf16; the fp32 sum over the block's CE_PROB_ROWS rows goes to the .y half of the
 // block's row of the partial array (whose .x half holds the column maxima the logits GEMM left there, one row of
-// partials per CE_PROB_ROWS vocabulary rows): no atomics, ce_chunk_sum_kernel adds the rows in order.
+// partials per CE_PROB_ROWS vocabulary rows): no atomics, chunk_sum adds the rows in order.
 RP_DEV void chunk_prob(int bx, int by, const float* __restrict__ z, int vc, int T, const float* __restrict__ m, bf16* __restrict__ p,
                        float2* __restrict__ part) {
   const int t = (bx * 256 + threadIdx.x) * 4;      // four tokens per thread: 16-byte loads, 8-byte stores
