@@ -63,12 +63,19 @@ static_assert(DTL_SMEM >= 4 * STG_BYTES, "epilogue staging does not fit");
 // lds + IMM + 1024) of the workgroup, lane l at + 16 l.  Lanes whose offset lies outside the descriptor deliver zeros.
 // The LDS address travels in M0; a scalar write of M0 has to be one wait state old when the load reads it (the no-op costs
 // nothing: 8192^3 within 0.2 % on all layouts).
-template <int IMM>
+// NT: marked non-temporal, for what no other workgroup reads.
+template <int IMM, bool NT = false>
 RP_DEV void load_to_lds(uint32_t lds, uint32_t voff, i32x4 rs, uint32_t soff) {
-  asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %4 offen lds"
-               :
-               : "s"(lds), "v"(voff), "s"(rs), "n"(IMM), "s"(soff)
-               : "memory", "scc");
+  if constexpr (NT)
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %4 offen nt lds"
+                 :
+                 : "s"(lds), "v"(voff), "s"(rs), "n"(IMM), "s"(soff)
+                 : "memory", "scc");
+  else
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %4 offen lds"
+                 :
+                 : "s"(lds), "v"(voff), "s"(rs), "n"(IMM), "s"(soff)
+                 : "memory", "scc");
 }
 
 RP_DEV i32x4 raw_rsrc(const void* base, uint32_t bytes) {
@@ -90,7 +97,8 @@ RP_DEV i32x4 raw_rsrc(const void* base, uint32_t bytes) {
 // 2326 -> 2250 | 3664 -> 3510 | 13270 -> 12950;  h = 2880, 32 experts of 2880, forward of 1000 | 8192 tokens 659 -> 636 |
 // 2995 -> 2876.  What bounds the 128-row tiles then is the experts' weights (gate/up 3.5 GB in 706 us, matrix pipe 31 % busy).
 // blk: the output tile of the product (-1: the workgroup's number); grouped: the entry gm of the table and the tile column gn.
-template <bool TA, bool TB, bool GRP>
+// ONCE: B is loaded non-temporally (see gemm_once_kernel).
+template <bool TA, bool TB, bool GRP, bool ONCE = false>
 RP_DEV void dtl_block(const GemmArgs& p, int blk, int gm = 0, int gn = 0) {
   static_assert((!TA || TB) && !(GRP && TA), "not a layout of this library");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -249,7 +257,7 @@ RP_DEV void dtl_block(const GemmArgs& p, int blk, int gm = 0, int gn = 0) {
   auto tile_setup = [&](int s) { setup_pair(s); setup_mask(); setup_lds(); };
   auto issue_b = [&](auto itag) __attribute__((always_inline)) {
     constexpr int i = decltype(itag)::value;
-    load_to_lds<i * 1024>(ld_ldsB, vcB[i], rcB, ld_soffB);
+    load_to_lds<i * 1024, ONCE>(ld_ldsB, vcB[i], rcB, ld_soffB);
   };
   auto issue_a = [&](auto itag) __attribute__((always_inline)) {
     constexpr int i = decltype(itag)::value;
@@ -571,17 +579,39 @@ RP_DEV void dtl_block(const GemmArgs& p, int blk, int gm = 0, int gn = 0) {
 
 // SWB: the instance for EPI_SWIGLU_BWD alone.  Its epilogue is the longest of all; compiled together with the others a third of its
 // scalars live in vector registers (8192 x 12288 x 4096 NN 830 -> 812 us with its loads a batch ahead).
+// The entry of the table and the tile column of a workgroup of a grouped product (the table's length is known on the device only:
+// surplus workgroups leave).
+RP_DEV bool grouped_tile(const GemmArgs& p, int& tile_m, int& tile_n) {
+  const int ntiles = *p.grp_ntiles;
+  if ((int)blockIdx.x >= ntiles * ((p.N + 255) / 256)) return false;
+  tile_of_block(ntiles * 256, p.N, 256, 256, tile_m, tile_n, 4);
+  return true;
+}
+
 template <bool TA, bool TB, bool GRP, bool SWB>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) gemm_dtl_kernel(const GemmArgs p) {
   GemmArgs q = p;
   if constexpr (SWB) q.epi = EPI_SWIGLU_BWD;
   int tile_m = 0, tile_n = 0;
-  if constexpr (GRP) {   // the table's length is known on the device only: surplus workgroups leave
-    const int ntiles = *p.grp_ntiles;
-    if ((int)blockIdx.x >= ntiles * ((p.N + 255) / 256)) return;
-    tile_of_block(ntiles * 256, p.N, 256, 256, tile_m, tile_n, 4);
+  if constexpr (GRP) {
+    if (!grouped_tile(p, tile_m, tile_n)) return;
   }
   dtl_block<TA, TB, GRP>(q, -1, tile_m, tile_n);
+}
+
+// Grouped products whose groups have one tile each: a group's weights are then read once in the launch (every 256 columns by one
+// workgroup), and loads marked non-temporal spare them the way through the caches for reuse that does not come.  What bounds these
+// products is that reading alone: without any of its MFMAs gate/up of 2048 tokens on 8 of 128 experts (h = 4096, width 1536: 3.2 GB)
+// took 695 us of 713, as with another half tile in flight (723) or with reductions that start at different places (708); with this
+// 633, and 690 -> 675 for the gradient of the layer's input.  Stages, us (h = 4096, 128 experts | h = 2880, 32 experts of 2880):
+// forward of 512, 1024, 2048, 3072 | 512, 1000, 1504 tokens 1226 -> 1151, 1373 -> 1288, 1653 -> 1565, 1954 -> 1895 | 558 -> 515,
+// 614 -> 563, 700 -> 658.  With two tiles per group the second reading, which the Infinity Cache serves otherwise, comes from HBM:
+// 4096 | 2048 tokens (256 rows per group) 2585 -> 2620 | 908 -> 907, gemm_pair_kernel 620 -> 751.  grouped_once draws the line.
+template <bool TB>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) gemm_once_kernel(const GemmArgs p) {
+  int tile_m = 0, tile_n = 0;
+  if (!grouped_tile(p, tile_m, tile_n)) return;
+  dtl_block<false, TB, true, true>(p, -1, tile_m, tile_n);
 }
 
 // Two grouped products that read the same weights, NT and NN, over the same table: the tiles of an entry follow each other, those of
@@ -621,10 +651,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
 
 }  // namespace
 
-template <bool TA, bool TB, bool GRP = false, bool SWB = false>
+template <bool TA, bool TB, bool GRP = false, bool SWB = false, bool ONCE = false>
 static hipError_t dtl_launch_one(hipStream_t st, const GemmArgs& a) {
   static bool attr_done = false;
   auto kern = gemm_dtl_kernel<TA, TB, GRP, SWB>;
+  if constexpr (ONCE) kern = gemm_once_kernel<TB>;
   if (!attr_done) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, DTL_SMEM);
     if (e != hipSuccess) return e;
@@ -636,8 +667,17 @@ static hipError_t dtl_launch_one(hipStream_t st, const GemmArgs& a) {
   return hipGetLastError();
 }
 
+// Groups of one tile each, judged by what the host knows: with 256 rows or fewer in all groups the table has at most rows / 256 + groups
+// + 1 entries, and 112 rows per entry are 195 rows per group (of which 188 and 192 gain 3-6 %, 256 lose 1 %).
+static bool grouped_once(const GemmArgs& a) { return (long)a.M <= 112L * a.grp_max_tiles; }
+
 hipError_t gemm_dtl_launch(hipStream_t st, const GemmArgs& a, int layout) {
-  if (a.grp_tab) return layout == GEMM_NT ? dtl_launch_one<false, false, true>(st, a) : layout == GEMM_NN ? dtl_launch_one<false, true, true>(st, a) : hipErrorInvalidValue;
+  if (a.grp_tab) {
+    const bool once = grouped_once(a);
+    if (layout == GEMM_NT) return once ? dtl_launch_one<false, false, true, false, true>(st, a) : dtl_launch_one<false, false, true>(st, a);
+    if (layout == GEMM_NN) return once ? dtl_launch_one<false, true, true, false, true>(st, a) : dtl_launch_one<false, true, true>(st, a);
+    return hipErrorInvalidValue;
+  }
   switch (layout) {
     case GEMM_NT: return dtl_launch_one<false, false>(st, a);
     case GEMM_NN: return a.epi == EPI_SWIGLU_BWD ? dtl_launch_one<false, true, false, true>(st, a) : dtl_launch_one<false, true>(st, a);
