@@ -150,6 +150,14 @@ inline int attn_ds_heads(size_t bytes, int batch, int seq, int a, int kh, int d)
   return (int)(fit / unit) * unit;
 }
 
+// Vocabulary rows of one product over the kept probabilities [V, T] and the head's weights [V, h]: both are addressed with 31-bit byte
+// offsets.  Multiples of 256 rows (whole tiles) where that many fit, else of 8, what the products need; 2^24 tokens, the most a call
+// takes, leave 56.
+inline int head_rows_per_product(size_t T, int h) {
+  const size_t widest = T > (size_t)h ? T : (size_t)h, fit = (((size_t)1 << 30) - 1) / widest;
+  return (int)(fit >= 256 ? fit / 256 * 256 : fit / 8 * 8);
+}
+
 // compact: the smallest plan that a call accepts, for a workspace that does not hold the full one.  (The head's chunks are then at
 // most 32768 vocabulary rows and a frozen head keeps the probabilities of one of them only.)
 inline Plan make_plan(const rp_stage_cfg& c, int batch, int seq, bool compact = false) {

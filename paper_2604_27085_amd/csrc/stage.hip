@@ -942,9 +942,7 @@ rp_status rp_lmhead_ce_fwd_bwd(rp_ctx* ctx, int slot_id, const void* x, const in
       X.mark_gemm(GEMM_TN, d);
       X.chk(gemm_launch(X.st, GEMM_TN, d), "lm head dX");
     };
-    // vocabulary rows of one product over the kept p: operands are addressed with 31-bit byte offsets
-    const long widest = T > D.h ? T : D.h;
-    const int piece = (int)((((1L << 31) - 1) / 2 / widest) / 256 * 256);
+    const int piece = head_rows_per_product(T, D.h);   // of one product over the kept p
     for (int v0 = 0, ci = 0; v0 < D.V; v0 += P.head_chunk, ++ci) {
       const int vc = (D.V - v0 < P.head_chunk) ? (D.V - v0) : P.head_chunk;
       const int nparts = gemm_ce_stats_partials(vc);
