@@ -95,7 +95,7 @@ hipError_t k_ce_ref_init(hipStream_t st, const float* z, int rows, int T, float*
 // *flag = 1 when some token's maximum lies more than RP_CE_P_LIMIT above its reference m.
 hipError_t k_ce_chunk_stats(hipStream_t st, const float2* part, int nparts, int T, const float* m, const float* l_in, float* l_out, int* flag);
 // Nothing unless *flag (which counts up then): the chunk again from its fp32 logits z [vc, T].  The reference m moves where the chunk outgrows it by more
-// than e^8 (alpha = the factor), p = exp(z - m_t) [vc, T] bf16, l_out = alpha l_in + row sums (through the .y halves of pmax,
+// than e^8 (alpha = the factor, a power of two), p = exp(z - m_t) [vc, T] bf16, l_out = alpha l_in + row sums (through the .y halves of pmax,
 // whose .x halves hold the column maxima, one row per 128 vocabulary rows), acc [T, h] and the probabilities stored before
 // the chunk (p_all, `rows` rows, or NULL) times alpha.
 hipError_t k_ce_chunk_redo(hipStream_t st, const float* z, int vc, int T, float2* pmax, int nparts, float* m, const float* l_in, float* l_out,

@@ -71,7 +71,7 @@ __global__ void __launch_bounds__(1024) ce_finalize_kernel(const float* __restri
 // ---- frozen head: one sweep over the vocabulary (no dW, so the softmax normaliser is only needed at the end) ---------
 // Per vocabulary chunk the logits Z^T [vc, T] (fp32) are turned into p = exp(z - m_t) against a per-token reference
 // exponent m_t, and acc_t = sum_v p_tv W_v, l_t = sum_v p_tv are carried from chunk to chunk; when a chunk's maximum
-// outgrows the reference by more than 2^8 (in e-units: 8), the reference moves and acc_t, l_t are rescaled.  At the end
+// outgrows the reference by more than 8 (in e-units), the reference moves and acc_t, l_t (or the p kept so far) are rescaled.  At the end
 // lse_t = m_t + log l_t and dx_t = coef_t (acc_t / l_t - W[y_t]).
 //
 // After the first chunk the logits GEMM writes p itself (EPI_CE_P) against the reference as it stands, together with the
@@ -137,8 +137,16 @@ __global__ void __launch_bounds__(256) ce_chunk_ref_kernel(const float2* __restr
   float cm = -INFINITY;
   for (int i = 0; i < nslab; ++i) cm = fmaxf(cm, pmax[(long)i * T + t].x);
   const float mo = m[t];
-  const float a = cm > mo + 8.f ? __expf(mo - cm) : 1.f;
-  if (cm > mo + 8.f) m[t] = cm;
+  float a = 1.f;
+  if (cm > mo + 8.f) {
+    // by a whole number k of ln 2, to the first such value that is not below the chunk's maximum: the factor 2^-k then multiplies
+    // what is stored in 16 bits without rounding it again (rounded, 2^-9 of everything before the chunk, and the same way for equal
+    // probabilities: 3.1e-3 of dx where 2048 equal logits are outgrown by 9)
+    const float k = ceilf((cm - mo) * 1.44269504f);
+    const bool far = k > 300.f;            // nothing before the chunk is left (also where either maximum is infinite)
+    a = far ? 0.f : ldexpf(1.f, -(int)k);
+    m[t] = far ? cm : fmaf(k, 0.693147181f, mo);
+  }
   l_out[t] = l_in[t] * a;
   alpha[t] = a;
 }
