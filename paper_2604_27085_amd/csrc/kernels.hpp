@@ -91,19 +91,22 @@ hipError_t k_ce_lse(hipStream_t st, const float2* part, int P, long part_ld, flo
 // m[t] = max over the rows of z [rows, T] fp32, l[t] = 0, alpha[t] = 1: the reference exponents a sweep starts from; zlab [T] and
 // flags [nflags <= 1024] become zero.
 hipError_t k_ce_ref_init(hipStream_t st, const float* z, int rows, int T, float* m, float* l, float* alpha, float* zlab, int* flags, int nflags);
-// part [nparts][T]: what EPI_CE_P left, maxima in .x and sums of exponentials in .y.  l_out = l_in + the sums in a fixed order;
-// *flag = 1 when some token's maximum lies more than RP_CE_P_LIMIT above its reference m.
-hipError_t k_ce_chunk_stats(hipStream_t st, const float2* part, int nparts, int T, const float* m, const float* l_in, float* l_out, int* flag);
-// Nothing unless *flag (which counts up then): the chunk again from its fp32 logits z [vc, T].  The reference m moves where the chunk outgrows it by more
-// than e^8 (alpha = the factor, a power of two), p = exp(z - m_t) [vc, T] bf16, l_out = alpha l_in + row sums (through the .y halves of pmax,
-// whose .x halves hold the column maxima, one row per 128 vocabulary rows), acc [T, h] and the probabilities stored before
-// the chunk (p_all, `rows` rows, or NULL) times alpha.
+// What a chunk that was done again still owes its normalisers: where *flag, the sum of part[i][t].y over `rows` rows.  part NULL: nothing.
+struct CeSums { const float2* part; int rows; const int* flag; };
+// part [nparts][T]: what EPI_CE_P left, maxima in .x and sums of exponentials in .y.  l_in += what prev owes it, l_out = l_in + the sums,
+// in a fixed order;  *flag = 1 when some token's maximum lies more than RP_CE_P_LIMIT above its reference m.
+hipError_t k_ce_chunk_stats(hipStream_t st, const float2* part, int nparts, int T, const float* m, float* l_in, float* l_out, int* flag,
+                            const CeSums& prev);
+// Nothing unless *flag: the chunk again from its fp32 logits z [vc, T].  The reference m moves where the chunk outgrows it by more
+// than e^8 (alpha = the factor, a power of two), p = exp(z - m_t) [vc, T] bf16, l_out = alpha l_in, to which the row sums are still
+// owed (*sums; in the .y halves of pmax, whose .x halves hold the column maxima, one row per 128 vocabulary rows), acc [T, h] and the
+// probabilities stored before the chunk (p_all, `rows` rows, or NULL) times alpha.
 hipError_t k_ce_chunk_redo(hipStream_t st, const float* z, int vc, int T, float2* pmax, int nparts, float* m, const float* l_in, float* l_out,
-                           float* alpha, void* p, float* acc, int h, void* p_all, long rows, int* flag);
+                           float* alpha, void* p, float* acc, int h, void* p_all, long rows, const int* flag, CeSums* sums);
 // One sweep with a trainable head (the probabilities of all chunks stay in memory, [V, T] bf16):
 // p[labels[t], t] -= l[t] for tokens with coef != 0 and a label inside the vocabulary;  xs[t, :] = xf[t, :] * coef[t] / l[t] (bf16).
 hipError_t k_ce_patch_scale(hipStream_t st, void* p, int T, int V, const int* labels, const float* l, const float* coef, const void* xf,
                             void* xs, int h);
-// lse[t], or with l the log-sum-exp lse[t] + log l[t].
-hipError_t k_ce_finalize(hipStream_t st, const float* lse, const float* l, const float* zlab, const int* labels, float grad_scale,
-                         float* coef, float* loss_out, int T);
+// lse[t], or with l the log-sum-exp lse[t] + log l[t], l += what `last` owes it first.
+hipError_t k_ce_finalize(hipStream_t st, const float* lse, float* l, const float* zlab, const int* labels, float grad_scale,
+                         float* coef, float* loss_out, int T, const CeSums& last = CeSums{});

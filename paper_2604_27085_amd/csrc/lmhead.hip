@@ -40,13 +40,38 @@ __global__ void __launch_bounds__(1024) ce_lse_kernel(const float2* __restrict__
 
 // One block: counts the valid tokens, loss = sum(lse - z_label) / n_valid, coef[t] = grad_scale / n_valid or 0.
 // lse[t] is lse[t] + log l[t] where l is given (the reference exponents and normalisers of the one-sweep schedule).
-__global__ void __launch_bounds__(1024) ce_finalize_kernel(const float* __restrict__ lse, const float* __restrict__ l, const float* __restrict__ zlab,
+// last: the sums that the last chunk still owes l.
+__global__ void __launch_bounds__(1024) ce_finalize_kernel(const float* __restrict__ lse, float* __restrict__ l, const float* __restrict__ zlab,
                                                            const int* __restrict__ labels, float grad_scale,
-                                                           float* __restrict__ coef, float* __restrict__ loss_out, int T) {
+                                                           float* __restrict__ coef, float* __restrict__ loss_out, int T, const CeSums last) {
   __shared__ float red[16];
   __shared__ int redi[16];
   __shared__ float bc;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  if (last.part && *last.flag) {      // uniform.  All threads on min(T, 1024) tokens at a time, the rows split over what is left of them
+    __shared__ float part[1024];
+    const int width = T < 1024 ? (T + 63) / 64 * 64 : 1024, ns = 1024 / width, sl = tid / width, tl = tid - sl * width;
+    for (int t0 = 0; t0 < T; t0 += width) {
+      const int t = t0 + tl;
+      float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;   // four chains, merged in a fixed order
+      if (t < T && sl < ns) {
+        int i = sl;
+        for (; i + 3 * ns < last.rows; i += 4 * ns) {
+          s0 += last.part[(long)i * T + t].y; s1 += last.part[(long)(i + ns) * T + t].y;
+          s2 += last.part[(long)(i + 2 * ns) * T + t].y; s3 += last.part[(long)(i + 3 * ns) * T + t].y;
+        }
+        for (; i < last.rows; i += ns) s0 += last.part[(long)i * T + t].y;
+      }
+      part[tid] = (s0 + s1) + (s2 + s3);
+      __syncthreads();
+      if (sl == 0 && t < T) {
+        float s = part[tl];
+        for (int k = 1; k < ns; ++k) s += part[k * width + tl];
+        l[t] += s;
+      }
+      __syncthreads();      // (also makes l visible to the threads that read it below)
+    }
+  }
   int cnt = 0;
   float sum = 0.f;
   for (int t = tid; t < T; t += 1024) {
@@ -104,12 +129,28 @@ __global__ void __launch_bounds__(1024) ce_ref_init_kernel(const float* __restri
 
 // What EPI_CE_P left per token: l_out[t] = l_in[t] + the chunk's sum (.y of the partial rows, sixteen interleaved chains merged
 // in a fixed order), and *flag = 1 when some token's maximum (.x) lies more than RP_CE_P_LIMIT above its reference exponent:
-// the chunk is then done again by the kernels behind the flag.  Bound by reading the partials once: 10 + 5.6 us in two kernels
+// the chunk is then done again by the kernels behind the flag, which leave its sums to the next reader of l: here those of the chunk
+// before (prev) are added to l_in first, with no launch of their own (4 us in every chunk, flag or not) and without counting blocks off
+// (the fence that takes in every block of the apply kernel: 3.6 ms of 57 at 16384 tokens with eight chunks done again).  Bound by reading the partials once: 10 + 5.6 us in two kernels
 // before (one thread per token in the sum), 5 us, at 2040 tokens and 32768 vocabulary rows.
 __global__ void __launch_bounds__(1024) ce_chunk_stats_kernel(const float2* __restrict__ part, int nslab, int T, const float* __restrict__ m,
-                                                              const float* __restrict__ l_in, float* __restrict__ l_out, int* __restrict__ flag) {
+                                                              float* __restrict__ l_in, float* __restrict__ l_out, int* __restrict__ flag, const CeSums prev) {
   __shared__ float2 red[CE_SLICES][64];
   const int lane = threadIdx.x & 63, sl = threadIdx.x >> 6, t = blockIdx.x * 64 + lane;
+  float lin = sl == 0 && t < T ? l_in[t] : 0.f;
+  if (prev.part && *prev.flag) {      // uniform
+    float s = 0.f;
+    if (t < T)
+      for (int i = sl; i < prev.rows; i += CE_SLICES) s += prev.part[(long)i * T + t].y;
+    red[sl][lane].x = s;
+    __syncthreads();
+    if (sl == 0 && t < T) {
+      for (int k = 1; k < CE_SLICES; ++k) s += red[k][lane].x;
+      lin += s;
+      l_in[t] = lin;
+    }
+    __syncthreads();
+  }
   float mx = -INFINITY, sum = 0.f;
   if (t < T)
     for (int i = sl; i < nslab; i += CE_SLICES) {
@@ -121,7 +162,7 @@ __global__ void __launch_bounds__(1024) ce_chunk_stats_kernel(const float2* __re
   __syncthreads();
   if (sl == 0 && t < T) {
     for (int k = 1; k < CE_SLICES; ++k) { mx = fmaxf(mx, red[k][lane].x); sum += red[k][lane].y; }
-    l_out[t] = l_in[t] + sum;
+    l_out[t] = lin + sum;
     if (mx > m[t] + RP_CE_P_LIMIT) *flag = 1;   // every writer stores the same value
   }
 }
@@ -153,7 +194,7 @@ __global__ void __launch_bounds__(256) ce_chunk_ref_kernel(const float2* __restr
 
 // p[r][t] = exp(z[r][t] - m[t]) as bf16; the fp32 sum over the block's CE_PROB_ROWS rows goes to the .y half of the
 // block's row of the partial array (whose .x half holds the column maxima the logits GEMM left there, one row of
-// partials per CE_PROB_ROWS vocabulary rows): no atomics, chunk_sum adds the rows in order.
+// partials per CE_PROB_ROWS vocabulary rows): no atomics, whoever reads the normaliser next adds the rows (CeSums).
 RP_DEV void chunk_prob(int bx, int by, const float* __restrict__ z, int vc, int T, const float* __restrict__ m, bf16* __restrict__ p,
                        float2* __restrict__ part) {
   const int t = (bx * 256 + threadIdx.x) * 4;      // four tokens per thread: 16-byte loads, 8-byte stores
@@ -177,20 +218,6 @@ RP_DEV void chunk_prob(int bx, int by, const float* __restrict__ z, int vc, int 
   for (; r < r1; ++r) one(*reinterpret_cast<const float4*>(z + (long)r * T + t), r);
   float2* const row = part + (long)by * T + t;
   row[0].y = s.x; row[1].y = s.y; row[2].y = s.z; row[3].y = s.w;
-}
-
-// l[t] += sum over the chunk's partial rows of part[i][t].y, in a fixed order; one block takes all tokens.
-RP_DEV void chunk_sum(const float2* part, int nslab, int T, float* l) {
-  for (int t = threadIdx.x; t < T; t += 256) {
-    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;   // four chains, merged in a fixed order
-    int i = 0;
-    for (; i + 4 <= nslab; i += 4) {
-      s0 += part[(long)i * T + t].y; s1 += part[(long)(i + 1) * T + t].y;
-      s2 += part[(long)(i + 2) * T + t].y; s3 += part[(long)(i + 3) * T + t].y;
-    }
-    for (; i < nslab; ++i) s0 += part[(long)i * T + t].y;
-    l[t] += (s0 + s1) + (s2 + s3);
-  }
 }
 
 // acc[t, :] *= alpha[t] for the rows whose reference moved.  One wave per row, blocks bx of nb.
@@ -224,26 +251,16 @@ RP_DEV void rescale_p(int bx, int nb, bf16* __restrict__ p, long rows, int T, co
 }
 
 // Behind the flag, in one launch: the chunk's probabilities from its fp32 logits, and the rescale of the rows of acc and of the
-// probabilities stored before the chunk (p_all, `rows` of them).  Blocks [0, np) probabilities, [np, np + nr) acc, then p_all.  Every
-// block counts itself off on the flag (1 when it starts, and nobody reads it afterwards); the last one, which sees all the partial
-// sums, adds them to the normalisers.
+// probabilities stored before the chunk (p_all, `rows` of them).  Blocks [0, np) probabilities, [np, np + nr) acc, then p_all.
 __global__ void __launch_bounds__(256) ce_chunk_apply_kernel(const float* __restrict__ z, int vc, int T, const float* __restrict__ m,
-                                                             bf16* p, float2* part, const float* __restrict__ alpha,
+                                                             bf16* p, float2* __restrict__ part, const float* __restrict__ alpha,
                                                              float* __restrict__ acc, int h, bf16* p_all, long rows, int bx_prob, int np,
-                                                             int nr, float* __restrict__ l, int nslab, int* run_flag) {
+                                                             int nr, const int* __restrict__ run_flag) {
   if (*run_flag == 0) return;
-  __shared__ int s_last;
   const int b = (int)blockIdx.x;
   if (b < np) chunk_prob(b % bx_prob, b / bx_prob, z, vc, T, m, p, part);
   else if (b < np + nr) rescale_rows(b - np, nr, acc, alpha, T, h);
   else rescale_p(b - np - nr, (int)gridDim.x - np - nr, p_all, rows, T, alpha);
-  __threadfence();
-  __syncthreads();
-  if (threadIdx.x == 0) s_last = atomicAdd(run_flag, 1) == (int)gridDim.x;
-  __syncthreads();
-  if (!s_last) return;
-  __threadfence();
-  chunk_sum(part, nslab, T, l);
 }
 
 // p[y_t, t] -= l_t for every token whose label takes part in the loss (coef != 0) and lies inside the vocabulary (one
@@ -278,21 +295,23 @@ hipError_t k_ce_ref_init(hipStream_t st, const float* z, int rows, int T, float*
   return hipGetLastError();
 }
 
-hipError_t k_ce_chunk_stats(hipStream_t st, const float2* part, int nparts, int T, const float* m, const float* l_in, float* l_out, int* flag) {
+hipError_t k_ce_chunk_stats(hipStream_t st, const float2* part, int nparts, int T, const float* m, float* l_in, float* l_out, int* flag,
+                            const CeSums& prev) {
   if (T == 0) return hipSuccess;
-  RP_LAUNCH(ce_chunk_stats_kernel, dim3((T + 63) / 64), dim3(1024), 0, st, part, nparts, T, m, l_in, l_out, flag);
+  RP_LAUNCH(ce_chunk_stats_kernel, dim3((T + 63) / 64), dim3(1024), 0, st, part, nparts, T, m, l_in, l_out, flag, prev);
   return hipGetLastError();
 }
 
 hipError_t k_ce_chunk_redo(hipStream_t st, const float* z, int vc, int T, float2* pmax, int nparts, float* m, const float* l_in, float* l_out,
-                           float* alpha, void* p, float* acc, int h, void* p_all, long rows, int* flag) {
+                           float* alpha, void* p, float* acc, int h, void* p_all, long rows, const int* flag, CeSums* sums) {
+  *sums = CeSums{pmax, (vc + CE_PROB_ROWS - 1) / CE_PROB_ROWS, flag};
   if (T == 0 || vc == 0) return hipSuccess;
   const int nblk = (vc + CE_PROB_ROWS - 1) / CE_PROB_ROWS;
   if (T % 8 || h % 4 || nblk > nparts) return hipErrorInvalidValue;   // one partial row per CE_PROB_ROWS vocabulary rows
   const int bx = (T / 4 + 255) / 256, nr = (T + 3) / 4 < 256 ? (T + 3) / 4 : 256, nq = p_all && rows > 0 ? 512 : 0;
-  RP_LAUNCH(ce_chunk_ref_kernel, dim3((T + 255) / 256), dim3(256), 0, st, (const float2*)pmax, nparts, T, m, l_in, l_out, alpha, (const int*)flag);
+  RP_LAUNCH(ce_chunk_ref_kernel, dim3((T + 255) / 256), dim3(256), 0, st, (const float2*)pmax, nparts, T, m, l_in, l_out, alpha, flag);
   RP_LAUNCH(ce_chunk_apply_kernel, dim3(bx * nblk + nr + nq), dim3(256), 0, st, z, vc, T, (const float*)m, (bf16*)p, pmax, (const float*)alpha,
-            acc, h, (bf16*)p_all, rows, bx, bx * nblk, nr, l_out, nblk, flag);
+            acc, h, (bf16*)p_all, rows, bx, bx * nblk, nr, flag);
   return hipGetLastError();
 }
 
@@ -310,8 +329,8 @@ hipError_t k_ce_lse(hipStream_t st, const float2* part, int P, long part_ld, flo
   return hipGetLastError();
 }
 
-hipError_t k_ce_finalize(hipStream_t st, const float* lse, const float* l, const float* zlab, const int* labels, float grad_scale,
-                         float* coef, float* loss_out, int T) {
-  RP_LAUNCH(ce_finalize_kernel, dim3(1), dim3(1024), 0, st, lse, l, zlab, labels, grad_scale, coef, loss_out, T);
+hipError_t k_ce_finalize(hipStream_t st, const float* lse, float* l, const float* zlab, const int* labels, float grad_scale,
+                         float* coef, float* loss_out, int T, const CeSums& last) {
+  RP_LAUNCH(ce_finalize_kernel, dim3(1), dim3(1024), 0, st, lse, l, zlab, labels, grad_scale, coef, loss_out, T, last);
   return hipGetLastError();
 }

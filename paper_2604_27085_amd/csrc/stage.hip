@@ -943,18 +943,20 @@ rp_status rp_lmhead_ce_fwd_bwd(rp_ctx* ctx, int slot_id, const void* x, const in
       X.chk(gemm_launch(X.st, GEMM_TN, d), "lm head dX");
     };
     const int piece = head_rows_per_product(T, D.h);   // of one product over the kept p
+    CeSums owed{};                       // by the chunk before, if it was done again
     for (int v0 = 0, ci = 0; v0 < D.V; v0 += P.head_chunk, ++ci) {
       const int vc = (D.V - v0 < P.head_chunk) ? (D.V - v0) : P.head_chunk;
       const int nparts = gemm_ce_stats_partials(vc);
+      float2* const part = X.at<float2>(P.h_part) + (size_t)(v0 / 128) * T;      // rows of its own: the next chunk reads them
       int* const flag = X.at<int>(P.h_flag) + ci % RP_CE_FLAGS;
       if (ci >= RP_CE_FLAGS) RUN(X, "fill", 0, 4.0, k_fill_u32(X.st, flag, 1, 0u));
-      const float* const l_in = lbuf[(nchunk - ci) & 1];
+      float* const l_in = lbuf[(nchunk - ci) & 1];
       float* const l_out = lbuf[(nchunk - ci - 1) & 1];
       const bf16_t* Wc = Wv + (size_t)v0 * D.h;
       void* const pc = keep_p ? static_cast<void*>(pall + (size_t)v0 * T) : X.at<void>(P.h_dzt);   // this chunk's p [vc, T]
       GemmArgs g; gemm_zero_args(g);
       g.A = Wc; g.lda = D.h; g.B = X.at<void>(P.h_xf); g.ldb = D.h; g.M = vc; g.N = T; g.K = D.h;
-      g.ldc = T; g.labels = labels; g.zlab = X.at<float>(P.h_zlab); g.part = X.at<float2>(P.h_part); g.part_ld = T;
+      g.ldc = T; g.labels = labels; g.zlab = X.at<float>(P.h_zlab); g.part = part; g.part_ld = T;
       g.row_offset = v0;
       {
         // the probabilities straight from the accumulators, against the reference as it stands; the chunk is redone
@@ -964,20 +966,20 @@ rp_status rp_lmhead_ce_fwd_bwd(rp_ctx* ctx, int slot_id, const void* x, const in
         X.mark_gemm(GEMM_NT, f);
         X.chk(gemm_launch(X.st, GEMM_NT, f), "lm head probabilities");
         RUN(X, "ce_chunk_stats", 0, 8.0 * nparts * Td,
-            k_ce_chunk_stats(X.st, X.at<float2>(P.h_part), nparts, T, X.at<float>(P.h_m), l_in, l_out, flag));
+            k_ce_chunk_stats(X.st, part, nparts, T, X.at<float>(P.h_m), l_in, l_out, flag, owed));
       }
       // the slow path, behind the flag: fp32 logits, reference move with rescale of what has been accumulated, p again
       g.run_flag = flag; g.epi = EPI_F32_COLMAX; g.C = zc;
       X.mark("ce_slow_path", 0, 0);
       X.chk(gemm_launch(X.st, GEMM_NT, g), "lm head logits");
       RUN(X, "ce_slow_path", 0, 0,
-          k_ce_chunk_redo(X.st, zc, vc, T, X.at<float2>(P.h_part), nparts, X.at<float>(P.h_m), l_in, l_out, X.at<float>(P.h_alpha), pc, acc,
-                          D.h, keep_p ? pall : nullptr, v0, flag));
+          k_ce_chunk_redo(X.st, zc, vc, T, part, nparts, X.at<float>(P.h_m), l_in, l_out, X.at<float>(P.h_alpha), pc, acc,
+                          D.h, keep_p ? pall : nullptr, v0, flag, &owed));
       if (!keep_p) add_dx(pc, Wc, vc, v0 == 0);
     }
     if (keep_p) for (int v0 = 0; v0 < D.V; v0 += piece) add_dx(pall + (size_t)v0 * T, Wv + (size_t)v0 * D.h, D.V - v0 < piece ? D.V - v0 : piece, v0 == 0);
     RUN(X, "ce_finalize", 0, 16.0 * Td,
-        k_ce_finalize(X.st, X.at<float>(P.h_m), X.at<float>(P.h_l), X.at<float>(P.h_zlab), labels, grad_scale, X.at<float>(P.h_coef), loss_out, T));
+        k_ce_finalize(X.st, X.at<float>(P.h_m), X.at<float>(P.h_l), X.at<float>(P.h_zlab), labels, grad_scale, X.at<float>(P.h_coef), loss_out, T, owed));
     if (train && G.t(RP_T_WV)) {
       RUN(X, "ce_patch_scale", 0, 16.0 * Td + 4.0 * Td * D.h,
           k_ce_patch_scale(X.st, pall, T, D.V, labels, X.at<float>(P.h_l), X.at<float>(P.h_coef), X.at<void>(P.h_xf), X.at<void>(P.h_xs), D.h));
