@@ -99,8 +99,8 @@ hipError_t k_ce_chunk_stats(hipStream_t st, const float2* part, int nparts, int 
                             const CeSums& prev);
 // Nothing unless *flag: the chunk again from its fp32 logits z [vc, T].  The reference m moves where the chunk outgrows it by more
 // than e^8 (alpha = the factor, a power of two), p = exp(z - m_t) [vc, T] bf16, l_out = alpha l_in, to which the row sums are still
-// owed (*sums; in the .y halves of pmax, whose .x halves hold the column maxima, one row per 128 vocabulary rows), acc [T, h] and the
-// probabilities stored before the chunk (p_all, `rows` rows, or NULL) times alpha.
+// owed (*sums; in the .y halves of pmax, whose .x halves hold the column maxima, one row per 128 vocabulary rows), acc [T, h] (or
+// NULL) and the probabilities stored before the chunk (p_all, `rows` rows, or NULL) times alpha.
 hipError_t k_ce_chunk_redo(hipStream_t st, const float* z, int vc, int T, float2* pmax, int nparts, float* m, const float* l_in, float* l_out,
                            float* alpha, void* p, float* acc, int h, void* p_all, long rows, const int* flag, CeSums* sums);
 // One sweep with a trainable head (the probabilities of all chunks stay in memory, [V, T] bf16):

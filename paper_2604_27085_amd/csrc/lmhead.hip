@@ -307,8 +307,8 @@ hipError_t k_ce_chunk_redo(hipStream_t st, const float* z, int vc, int T, float2
   *sums = CeSums{pmax, (vc + CE_PROB_ROWS - 1) / CE_PROB_ROWS, flag};
   if (T == 0 || vc == 0) return hipSuccess;
   const int nblk = (vc + CE_PROB_ROWS - 1) / CE_PROB_ROWS;
-  if (T % 8 || h % 4 || nblk > nparts) return hipErrorInvalidValue;   // one partial row per CE_PROB_ROWS vocabulary rows
-  const int bx = (T / 4 + 255) / 256, nr = (T + 3) / 4 < 256 ? (T + 3) / 4 : 256, nq = p_all && rows > 0 ? 512 : 0;
+  if (T % 8 || (acc && h % 4) || nblk > nparts) return hipErrorInvalidValue;   // one partial row per CE_PROB_ROWS vocabulary rows
+  const int bx = (T / 4 + 255) / 256, nr = !acc ? 0 : (T + 3) / 4 < 256 ? (T + 3) / 4 : 256, nq = p_all && rows > 0 ? 512 : 0;
   RP_LAUNCH(ce_chunk_ref_kernel, dim3((T + 255) / 256), dim3(256), 0, st, (const float2*)pmax, nparts, T, m, l_in, l_out, alpha, flag);
   RP_LAUNCH(ce_chunk_apply_kernel, dim3(bx * nblk + nr + nq), dim3(256), 0, st, z, vc, T, (const float*)m, (bf16*)p, pmax, (const float*)alpha,
             acc, h, (bf16*)p_all, rows, bx, bx * nblk, nr, flag);

@@ -973,8 +973,8 @@ rp_status rp_lmhead_ce_fwd_bwd(rp_ctx* ctx, int slot_id, const void* x, const in
       X.mark("ce_slow_path", 0, 0);
       X.chk(gemm_launch(X.st, GEMM_NT, g), "lm head logits");
       RUN(X, "ce_slow_path", 0, 0,
-          k_ce_chunk_redo(X.st, zc, vc, T, part, nparts, X.at<float>(P.h_m), l_in, l_out, X.at<float>(P.h_alpha), pc, acc,
-                          D.h, keep_p ? pall : nullptr, v0, flag, &owed));
+          k_ce_chunk_redo(X.st, zc, vc, T, part, nparts, X.at<float>(P.h_m), l_in, l_out, X.at<float>(P.h_alpha), pc,
+                          keep_p || v0 == 0 ? nullptr : acc, D.h, keep_p ? pall : nullptr, v0, flag, &owed));
       if (!keep_p) add_dx(pc, Wc, vc, v0 == 0);
     }
     if (keep_p) for (int v0 = 0; v0 < D.V; v0 += piece) add_dx(pall + (size_t)v0 * T, Wv + (size_t)v0 * D.h, D.V - v0 < piece ? D.V - v0 : piece, v0 == 0);
