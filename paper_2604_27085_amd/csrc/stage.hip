@@ -1220,8 +1220,17 @@ rp_status rp_op_attn_bwd(void* stream, const void* q, const void* k, const void*
   if (a != kh && !scratch) return fail(nullptr, RP_EINVAL, "rp_op_attn_bwd: grouped queries need the scratch buffer");
   if (ldq % 8 || ldk % 8 || ldv % 8 || ldo % 8 || lddo % 8 || lddq % 8 || lddk % 8 || lddv % 8) return fail(nullptr, RP_EINVAL, "rp_op_attn_bwd: strides must be multiples of 8");
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  // dQ first, with delta in passing, unless dq takes the place of something that the dK/dV kernel still reads
-  const bool in_place = dq == q || dq == dout || dq == o;
+  // dQ first, with delta in passing, unless dq lies in memory that is still needed then: q and dout for dK/dV, o for the other rows'
+  // delta, scratch for the partials.  (Judged by the first and the last byte: columns of one array that lie beside each other count as
+  // overlapping, and take the order that is right for both.)
+  const long T = (long)batch * seq;
+  auto meets_dq = [&](const void* p, size_t bytes) {
+    const char *d0 = static_cast<const char*>(dq), *p0 = static_cast<const char*>(p);
+    return p0 && T > 0 && p0 < d0 + ((T - 1) * lddq + a * d) * 2 && d0 < p0 + bytes;
+  };
+  auto rows = [&](long ld) { return (size_t)(((T - 1) * ld + a * d) * 2); };
+  const bool in_place = meets_dq(q, rows(ldq)) || meets_dq(dout, rows(lddo)) || meets_dq(o, rows(ldo)) ||
+                        meets_dq(a != kh ? scratch : nullptr, (size_t)T * a * d * 8);
   hipError_t e = in_place ? k_attn_delta(st, o, dout, delta, ldo, lddo, batch, seq, a, d) : hipSuccess;
   static const int order[2][3] = {{1, 0, 2}, {0, 2, 1}};
   for (int i = 0; i < 3 && e == hipSuccess; ++i)

@@ -94,3 +94,36 @@ def test_backward_in_place(d):
         want = want or got
         for x, y in zip(got[:3], want):
             assert float((x - y).norm() / y.norm()) < 1e-3
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("place", ["o, from row 9 on", "scratch", "end of scratch", "beside q"])
+def test_backward_with_dq_in_memory_that_is_free_by_then(d, place):
+    """dq inside o at another offset, inside scratch (both free when delta and the partials have been used), and in columns beside q of
+    one array: the same results as in memory of its own but for delta's rounding, as above."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_27085_amd import binding as B
+    b, n, a, kh = 2, 264, 4, 2
+    T, w = b * n, a * d
+    g = torch.Generator(device="cuda:0").manual_seed(6)
+    mk = lambda k: torch.empty((T, k * d), dtype=torch.bfloat16, device="cuda:0").normal_(0.0, 1.0, generator=g)  # noqa: E731
+    q, k, v, do = mk(a), mk(kh), mk(kh), mk(a)
+    lse = torch.empty((b, a, n), dtype=torch.float32, device="cuda:0")
+    st = torch.cuda.current_stream().cuda_stream
+    got = []
+    for where in ("own", place):
+        scratch = torch.full((2 * T * w,), float("nan"), dtype=torch.float32, device="cuda:0")
+        room = torch.zeros((T + 9, w), dtype=torch.bfloat16, device="cuda:0")
+        both = torch.cat((q, torch.zeros_like(q)), 1)
+        o, dk, dv, delta = room[:T], torch.empty_like(k), torch.empty_like(v), torch.empty_like(lse)
+        half = scratch.view(torch.bfloat16).view(-1, w)
+        q1, ldq = (both, 2 * w) if where == "beside q" else (q, w)
+        dq, lddq = {"own": (torch.empty_like(q), w), "scratch": (half[:T], w), "end of scratch": (half[-T:], w),
+                    "o, from row 9 on": (room[9:], w), "beside q": (both[:, w:], 2 * w)}[where]
+        B.rp_op_attn_fwd(st, q1, k, v, o, lse, ldq, kh * d, kh * d, w, b, n, a, kh, d)
+        B.rp_op_attn_bwd(st, q1, k, v, o, do, lse, delta, dq, dk, dv, scratch, ldq, kh * d, kh * d, w, w, lddq, kh * d, kh * d, b, n, a, kh, d)
+        torch.cuda.synchronize()
+        got.append([t.double().clone() for t in (dq, dk, dv)])
+    for x, y in zip(got[1], got[0]):
+        assert float((x - y).norm() / y.norm()) < 1e-3
