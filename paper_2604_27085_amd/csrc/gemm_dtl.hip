@@ -577,8 +577,6 @@ RP_DEV void dtl_block(const GemmArgs& p, int blk, int gm = 0, int gn = 0) {
   epilogue<IS, true>(p, Mlim, half, smem, wave, lane, wrow, n0 + wn * 128 + 64, part_row);
 }
 
-// SWB: the instance for EPI_SWIGLU_BWD alone.  Its epilogue is the longest of all; compiled together with the others a third of its
-// scalars live in vector registers (8192 x 12288 x 4096 NN 830 -> 812 us with its loads a batch ahead).
 // The entry of the table and the tile column of a workgroup of a grouped product (the table's length is known on the device only:
 // surplus workgroups leave).
 RP_DEV bool grouped_tile(const GemmArgs& p, int& tile_m, int& tile_n) {
@@ -588,6 +586,8 @@ RP_DEV bool grouped_tile(const GemmArgs& p, int& tile_m, int& tile_n) {
   return true;
 }
 
+// SWB: the instance for EPI_SWIGLU_BWD alone.  Its epilogue is the longest of all; compiled together with the others a third of its
+// scalars live in vector registers (8192 x 12288 x 4096 NN 830 -> 812 us with its loads a batch ahead).
 template <bool TA, bool TB, bool GRP, bool SWB>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) gemm_dtl_kernel(const GemmArgs p) {
   GemmArgs q = p;
@@ -606,7 +606,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
 // 633, and 690 -> 675 for the gradient of the layer's input.  Stages, us (h = 4096, 128 experts | h = 2880, 32 experts of 2880):
 // forward of 512, 1024, 2048, 3072 | 512, 1000, 1504 tokens 1226 -> 1151, 1373 -> 1288, 1653 -> 1565, 1954 -> 1895 | 558 -> 515,
 // 614 -> 563, 700 -> 658.  With two tiles per group the second reading, which the Infinity Cache serves otherwise, comes from HBM:
-// 4096 | 2048 tokens (256 rows per group) 2585 -> 2620 | 908 -> 907, gemm_pair_kernel 620 -> 751.  grouped_once draws the line.
+// 4096 | 2048 tokens (256 rows per group) 2585 -> 2620 | 908 -> 907, gemm_pair_kernel 620 -> 751.  The caller draws the line (grp_once).
 template <bool TB>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) gemm_once_kernel(const GemmArgs p) {
   int tile_m = 0, tile_n = 0;
@@ -667,13 +667,9 @@ static hipError_t dtl_launch_one(hipStream_t st, const GemmArgs& a) {
   return hipGetLastError();
 }
 
-// Groups of one tile each, judged by what the host knows: with 256 rows or fewer in all groups the table has at most rows / 256 + groups
-// + 1 entries, and 112 rows per entry are 195 rows per group (of which 188 and 192 gain 3-6 %, 256 lose 1 %).
-static bool grouped_once(const GemmArgs& a) { return (long)a.M <= 112L * a.grp_max_tiles; }
-
 hipError_t gemm_dtl_launch(hipStream_t st, const GemmArgs& a, int layout) {
   if (a.grp_tab) {
-    const bool once = grouped_once(a);
+    const bool once = a.grp_once;
     if (layout == GEMM_NT) return once ? dtl_launch_one<false, false, true, false, true>(st, a) : dtl_launch_one<false, false, true>(st, a);
     if (layout == GEMM_NN) return once ? dtl_launch_one<false, true, true, false, true>(st, a) : dtl_launch_one<false, true, true>(st, a);
     return hipErrorInvalidValue;

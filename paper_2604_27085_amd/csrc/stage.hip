@@ -277,6 +277,16 @@ struct Exec {
     mark("gemm_256x256_TN", fl, by);
     chk(gemm_wgrad_launch(st, q.n, q.g), "weight gradients");
   }
+  // Whether the grouped products load the experts' weights non-temporally: where an expert has one tile of rows on average, and the
+  // stage's experts do not all fit into the 256 MB Infinity Cache, which then serves the next reading (the backward's, or the next call's).
+  // Forward stage, us, ordinary | non-temporal loads (E experts, h x m, rows per expert, bytes of the stage's expert weights):
+  //   128, 4096 x 1536, 4.8 GB: 176 rows 1469 | 1441, 208 1606 | 1483, 224 1747 | 1655, 240 1759 | 1706, 256 1992 | 2000
+  //   32, 2880 x 2880, 1.6 GB: 176 rows 597 | 557, 208 636 | 590, 240 699 | 679, 256 817 | 814;  8, 4096 x 14336, 2.8 GB: 240 955 | 894, 256 1025 | 1024
+  //   16, 2048 x 768, 100 rows: one layer (151 MB) 137 | 146, two (302 MB) 301 | 289;  32, 1024 x 512, 64 rows: two layers (201 MB) 224 | 241, four 487 | 469
+  //   4096 x 1536: 4 experts (151 MB) 194 | 207, 5 (189 MB) 209 | 207, 6 (226 MB) 225 | 217, 8 (302 MB) 232 | 222;  2880 x 2880: 4 (199 MB) 177 | 191
+  bool experts_once() const {
+    return T * D.topk <= 240L * D.E && 6.0 * D.L * D.E * D.h * (double)D.m > 200.0 * 1048576.0;
+  }
   // Grouped GEMM over expert-sorted slot rows: C[slot, N] = A[row_map ? row_map[slot] : slot, K] * op(B_e), B_e the
   // matrix of the expert that owns the slot.  set = the layer's saved internals (routing plan).
   GemmArgs grouped_args(const char* set, const void* A, long lda, int a_rows, bool gather, const void* B, long ldb, long strideB, void* C,
@@ -288,6 +298,7 @@ struct Exec {
     g.grp_ntiles = reinterpret_cast<const int*>(set + P.lb.m_ntiles);
     g.grp_max_tiles = P.moe_max_tiles;
     g.grp_strideB = strideB;
+    g.grp_once = experts_once();
     if (gather) { g.row_map = reinterpret_cast<const int*>(set + P.lb.m_tok); g.row_map_rows = a_rows; }
     return g;
   }
@@ -297,7 +308,8 @@ struct Exec {
     return 2.0 * ((double)g.M * g.K + (double)D.E * g.N * g.K) + (g.C2 ? 3.0 : 2.0) * g.M * (double)g.N;
   }
   void gemm_grouped(int layout, const GemmArgs& g) {
-    mark(layout == GEMM_NT ? "gemm_grouped_NT" : "gemm_grouped_NN", grouped_flops(g), grouped_bytes(g));
+    mark(g.grp_once ? (layout == GEMM_NT ? "gemm_grouped_once_NT" : "gemm_grouped_once_NN") : (layout == GEMM_NT ? "gemm_grouped_NT" : "gemm_grouped_NN"),
+         grouped_flops(g), grouped_bytes(g));
     chk(gemm_launch(st, layout, g), "gemm_grouped");
   }
   // C[M,N] (fp32) = A * B^T, overwritten; one pass, no reduction split, so the result does not depend on scheduling
