@@ -287,6 +287,14 @@ struct Exec {
   bool experts_once() const {
     return T * D.topk <= 240L * D.E && 6.0 * D.L * D.E * D.h * (double)D.m > 200.0 * 1048576.0;
   }
+  // Whether the down projection and the gradient of its input run in one launch (gemm_pair_kernel): its tiles follow each other expert by
+  // expert, 256 rows at a time, where each product alone takes four such rows of tiles at once.  With one tile per expert nothing is lost by
+  // that; with several the expert's matrix is read more often, which shows once it is larger than what the caches turn around.
+  // Backward stage, us, joined | apart (E experts, h x m, bytes of one matrix, rows per expert):
+  //   16, 4096 x 7168, 59 MB: 192 rows 1699 | 1730, 256 2461 | 2484, 384 3000 | 2983, 1024 7687 | 7540, 2048 16731 | 16371
+  //   8, 4096 x 14336, 117 MB: 192 rows 1724 | 1836, 256 2197 | 2151, 512 3845 | 3824, 1024 6716 | 6556, 2048 12905 | 12465
+  //   16, 4096 x 4096, 34 MB: 512 rows 2596 | 2631, 1024 5252 | 5233;  32, 2880 x 2880, 17 MB: 256 rows 1625 | 1720, 1024 5239 | 5293
+  bool pair_pays() const { return T * D.topk <= 240L * D.E || 2.0 * D.h * D.m <= 48.0e6; }
   // Grouped GEMM over expert-sorted slot rows: C[slot, N] = A[row_map ? row_map[slot] : slot, K] * op(B_e), B_e the
   // matrix of the expert that owns the slot.  set = the layer's saved internals (routing plan).
   GemmArgs grouped_args(const char* set, const void* A, long lda, int a_rows, bool gather, const void* B, long ldb, long strideB, void* C,
@@ -857,7 +865,7 @@ rp_status rp_stage_backward(rp_ctx* ctx, int slot_id, int phases, const void* x_
       // the stage output goes straight to x_out: the backward needs the layer outputs below the last one only
       void* z = (l == L - 1 && x_out) ? x_out : set_of(l) + P.lb.z;
       if (router_logits) X.router = router_logits + (size_t)l * X.T * X.D.E;
-      X.moe_dz = l == L - 1 && do_bwd ? dy : nullptr;
+      X.moe_dz = X.D.E > 0 && l == L - 1 && do_bwd && X.pair_pays() ? dy : nullptr;
       layer_forward(X, W, set_of(l), x, z, P.moe_f_bwd);
       x = z;
     }
