@@ -18,6 +18,9 @@ torch = pytest.importorskip("torch")
     (32, 300, 16, 4, 128),    # the whole group of four
     (16, 330, 32, 16, 128),   # the whole group of two
     (2, 129, 8, 8, 128),      # no groups
+    (1, 128, 4, 2, 64),       # both of two: one key tile
+    (4, 256, 16, 8, 128),     # both of two: two key tiles and 64 heads in all
+    (3, 256, 20, 10, 64),     # one of two: 60
 ])
 def test_heads_per_workgroup(batch, seq, a, kh, d):
     if not torch.cuda.is_available():

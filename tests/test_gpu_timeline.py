@@ -14,6 +14,10 @@ torch = pytest.importorskip("torch")
     (24, 300, 64, 8, 64, 16),     # four heads of eight
     (1, 264, 8, 2, 128, 8),       # one head
     (1, 264, 4, 4, 128, 0),       # no groups
+    (1, 128, 4, 2, 64, 0),        # groups of two in one key tile
+    (4, 256, 16, 8, 128, 0),      # in two, 64 heads in all
+    (3, 256, 20, 10, 64, 20),     # 60 heads
+    (1, 256, 4, 2, 128, 4),
 ])
 def test_reduction_of_dkv_partials_is_recorded_as_launched(batch, seq, a, kh, d, partials):
     if not torch.cuda.is_available():
