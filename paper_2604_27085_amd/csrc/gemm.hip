@@ -719,26 +719,29 @@ hipError_t gemm_group_launch(hipStream_t st, int n, const int* layouts, const Ge
   return hipGetLastError();
 }
 
-hipError_t gemm_wgrad_launch(hipStream_t st, int n, const GemmArgs* g) {
-  if (n < 0 || n > GEMM_WGRAD_MAX) return hipErrorInvalidValue;
-  GemmArgs q[GEMM_WGRAD_MAX];
+bool gemm_wgrad_joined(int n, const GemmArgs* g) {
+  if (n < 2 || n > GEMM_WGRAD_MAX) return false;
   double apart = 0.0;
   long tiles = 0;
+  for (int i = 0; i < n; ++i) {
+    GemmArgs q = g[i];
+    if (prepare(GEMM_TN, q) != hipSuccess) return false;
+    const Choice ch = choose(q, 0);
+    apart += tile_cost(ch.tile, ch.splits, q.M, q.N, (q.K + 63) / 64, q.epi);
+    tiles += (long)((q.M + 255) / 256) * ((q.N + 255) / 256);
+  }
+  return tile_cost(1, 1, (int)(256 * tiles), 256, (g[0].K + 63) / 64, EPI_F32) < apart;
+}
+
+hipError_t gemm_wgrad_launch(hipStream_t st, int n, const GemmArgs* g) {
+  if (n < 1 || n > GEMM_WGRAD_MAX) return hipErrorInvalidValue;
+  GemmArgs q[GEMM_WGRAD_MAX];
   for (int i = 0; i < n; ++i) {
     q[i] = g[i];
     const hipError_t e = prepare(GEMM_TN, q[i]);
     if (e != hipSuccess) return e;
-    const Choice ch = choose(q[i], 0);
-    const int k_tiles = (q[i].K + 63) / 64;
-    apart += tile_cost(ch.tile, ch.splits, q[i].M, q[i].N, k_tiles, q[i].epi);
-    tiles += (long)((q[i].M + 255) / 256) * ((q[i].N + 255) / 256);
   }
-  if (n > 1 && tile_cost(1, 1, (int)(256 * tiles), 256, (q[0].K + 63) / 64, EPI_F32) < apart) return gemm_wgrad_run(st, n, q);
-  for (int i = 0; i < n; ++i) {
-    const hipError_t e = gemm_launch(st, GEMM_TN, g[i]);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  return gemm_wgrad_run(st, n, q);
 }
 
 hipError_t gemm_pair_launch(hipStream_t st, const GemmArgs& nt, const GemmArgs& nn) {

@@ -103,7 +103,8 @@ hipError_t gemm_pair_run(hipStream_t st, const GemmArgs& nt, const GemmArgs& nn)
 // Weight gradients (layout TN, fp32, accumulating, the same reduction) that do not depend on each other: in one launch of 256x256 tiles
 // when the tile model finds that cheaper than one by one, which it is when their last rounds would stay partly empty.
 #define GEMM_WGRAD_MAX 4
-hipError_t gemm_wgrad_launch(hipStream_t st, int n, const GemmArgs* g);
+bool gemm_wgrad_joined(int n, const GemmArgs* g);                        // whether it does
+hipError_t gemm_wgrad_launch(hipStream_t st, int n, const GemmArgs* g);  // in one launch, for arguments of which that is true
 hipError_t gemm_wgrad_run(hipStream_t st, int n, const GemmArgs* g);     // the shared launch (gemm_dtl.hip): arguments prepared
 // dq [T, a * d] = scale * dS^T k per head, from the blocks of dS that the dK/dV kernel left (attention.hip; head_bytes each, d = 128).
 hipError_t gemm_attn_dq(hipStream_t st, const void* ds, size_t head_bytes, const void* k, long ldk, void* dq, long lddq, int batch, int seq,

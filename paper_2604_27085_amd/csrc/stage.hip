@@ -268,13 +268,17 @@ struct Exec {
   }
   void run_late(const Late& q) {
     if (q.n == 0) return;
+    if (!gemm_wgrad_joined(q.n, q.g)) {
+      for (int i = 0; i < q.n; ++i) { mark_gemm(GEMM_TN, q.g[i]); chk(gemm_launch(st, GEMM_TN, q.g[i]), "weight gradient"); }
+      return;
+    }
     double fl = 0.0, by = 0.0;
     for (int i = 0; i < q.n; ++i) {
       const GemmArgs& g = q.g[i];
       fl += 2.0 * g.M * (double)g.N * g.K;
       by += 2.0 * ((double)g.M + g.N) * g.K + 8.0 * g.M * (double)g.N;
     }
-    mark("gemm_256x256_TN", fl, by);
+    mark("gemm_wgrad_TN", fl, by);
     chk(gemm_wgrad_launch(st, q.n, q.g), "weight gradients");
   }
   // Whether the grouped products load the experts' weights non-temporally: where an expert has one tile of rows on average, and the

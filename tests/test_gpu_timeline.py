@@ -37,3 +37,28 @@ def test_reduction_of_dkv_partials_is_recorded_as_launched(batch, seq, a, kh, d,
     # fp32 partials of dk and dv read, bf16 sums written
     want = [batch * seq * (2 * 4.0 * partials * d + 2 * 2.0 * kh * d)] if partials else []
     assert [t[2] for t in rec] == want
+
+
+# A layer's large weight gradients share a launch where the tile model finds that cheaper; one that is alone never does.
+@pytest.mark.parametrize("h,m,T,joined", [(2048, 6144, 512, True), (256, 1536, 264, False)])
+def test_weight_gradients_are_recorded_as_launched(h, m, T, joined):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_27085_amd import binding as B, harness as H
+    c = synth.shrink(synth.CONFIGS["C1"], n_layers=1, hidden=h, ffn=m, n_q_heads=4, n_kv_heads=2, head_dim=64, vocab=0, seq=T, batch=1, lora_rank=0, lora=())
+    r = H.StageRunner(H.cfg_from_dict(c), 1, T)
+    r.slots[0].view(torch.bfloat16).normal_(0.0, 0.02)
+    x = torch.empty((T, h), dtype=torch.bfloat16, device="cuda:0").normal_()
+    dy, dx = torch.empty_like(x).normal_(), torch.empty_like(x)
+    torch.cuda.synchronize()
+    r.bind()
+    B.rp_trace_start(r.ctx, 256)
+    B.rp_stage_backward(r.ctx, 0, B.PHASE_BOTH, x, dy, dx, None, r.grads, None, None, 1, T, r.ws, r.wsbytes)
+    rec = [t for t in B.rp_trace_stop(r.ctx, 256) if t[0].endswith("_TN")]
+    r.close()
+    if joined:      # those of gate and up, down, and whatever else is large; the others share a launch with other small products
+        assert [t[0] for t in rec] == ["gemm_wgrad_TN"]
+        assert rec[0][1] >= 2.0 * T * 3 * h * m
+    else:           # gate and up alone, on the tile that the product picks by itself
+        assert len(rec) == 1 and rec[0][0] not in ("gemm_wgrad_TN", "gemm_256x256_TN")
+        assert rec[0][1] == 2.0 * T * 2 * h * m and rec[0][2] == 2.0 * T * (2 * m + h) + 8.0 * 2 * m * h
