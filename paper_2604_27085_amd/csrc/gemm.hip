@@ -458,9 +458,13 @@ __global__ void __launch_bounds__(256) gemm_arrange_kernel(const bf16* __restric
 //     of the chip is busy;
 //   - the small tiles are bound by what a CU can fetch -- 50 bytes/ns of data that comes from HBM, however many loads are
 //     in flight (80 from the Infinity Cache, 150 from L2) -- so their K tile costs its operand bytes.
-// A split into `splits` slices adds the merge kernel and its traffic, which for accumulating outputs is chip time as well from 64 MB
-// on, what the caches do not hold: 2040 x 5120 x 151936 TN in eight slices or three, frozen head on one stream 5175 | 5150 us, on three 5385 | 5310; the bf16
-// results of short batches are 2-3 % slower with fewer slices.  Added to the elapsed time is the chip time the
+// A split into `splits` slices adds the merge kernel and its traffic.  For accumulating outputs the part of it beyond 64 MB counts as chip
+// time as well; where that changes the choice it is fewer slices of a head's input gradient (K = 151936), which cost nothing on one
+// stream and leave more to the others.  Whole frozen head, us, one stream | three, without that term and with it: 3000 x 2048 in eight slices
+// or five 3302 | 3299 -> 3302 | 3290, 2040 x 2880 eight or five 3156 | 3066 -> 3155 | 3027, 1504 x 4096 eight or five 3122 | 3087 -> 3114 | 3050,
+// 2504 x 4096 eight or three 5170 | 5098 -> 5151 | 5058, 2040 x 5120 eight or three 5090 | 5077 -> 5080 | 4992.  The 64 MB are a bound drawn
+// between these (250 MB and more in eight slices) and the weight gradients and bf16 results of short batches, which are 2-3 % slower
+// with fewer slices; nothing was measured in between.  Added to the elapsed time is the chip time the
 // workgroups use up (their summed time over 256 CUs): what is left over belongs to other streams, so a small tile has to buy
 // enough latency for the extra operand traffic it causes.  The weight of that term, both ends measured on whole stage calls,
 // one stream | three streams at once, against choosing by elapsed time alone: a backward stage of 928 tokens at h = 2048
