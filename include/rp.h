@@ -133,10 +133,21 @@ RP_API const char* rp_last_error(const rp_ctx* ctx);
 /* ---- sizes and layouts (pure host functions, no HIP calls) ------------------------------------ */
 
 /* weight_blob_bytes: size of the packed stage weights (host blob == device slot, same layout);
- * grad_blob_bytes: size of the fp32 gradient blob; workspace_bytes: device scratch a stage call or a
- * head call needs for (batch, seq).  Any output pointer may be NULL. */
+ * grad_blob_bytes: size of the fp32 gradient blob; workspace_bytes: device scratch with which every stage call and
+ * head call for (batch, seq) runs on its fastest path (less is accepted, see rp_query_least_workspace).  Any output
+ * pointer may be NULL. */
 RP_API rp_status rp_query_sizes(const rp_stage_cfg* cfg, int batch, int seq, size_t* weight_blob_bytes,
                          size_t* grad_blob_bytes, size_t* workspace_bytes);
+
+/* The smallest workspace that rp_stage_forward, rp_stage_backward (every phase) and rp_lmhead_ce_fwd_bwd accept for
+ * (batch, seq); rp_round_* as the stage calls.  0 for calls the stage has not.  Between it and workspace_bytes of
+ * rp_query_sizes a call does without what the buffer does not hold -- the scratch of a forward stage's reduction
+ * splits; dS of the attention backward (taken in as many passes over heads as fit), a second dU buffer and the
+ * partials that let a layer's gain and weight gradients share launches; the probabilities of the whole vocabulary in
+ * a frozen head and its larger chunks -- with the same results up to the order of fp32 sums and bf16 rounding.  Any
+ * output pointer may be NULL. */
+RP_API rp_status rp_query_least_workspace(const rp_stage_cfg* cfg, int batch, int seq, size_t* forward_bytes,
+                         size_t* backward_bytes, size_t* head_bytes);
 
 /* Size of a device weight slot: the packed blob followed by the tensors the library derives from it when the weights
  * arrive (the block-diagonal LoRA B matrices of the fused q|k|v and gate|up projections).  Equal to weight_blob_bytes
@@ -173,7 +184,8 @@ RP_API rp_status rp_stage_bind_weights(rp_ctx* ctx, int slot_id, void* dev_slot,
  * input of layer l (the activation checkpoint kept under full recomputation, Sec. 2.1.1).
  * router_logits [dev] fp32 [n_layers, T, E] for MoE stages, else NULL: read when the caller supplies the logits,
  * overwritten with the logits the stage computed when cfg.moe_router is set (the library keeps no copy of its own).
- * Waits on the slot's per-layer upload events.  workspace [dev], at least workspace_bytes of rp_query_sizes.
+ * Waits on the slot's per-layer upload events.  workspace [dev], workspace_bytes of rp_query_sizes or
+ * less (see rp_query_least_workspace).
  * Errors: RP_EINVAL, RP_ENOMEM (workspace), RP_ESTATE (slot not uploaded), RP_EHIP. */
 RP_API rp_status rp_stage_forward(rp_ctx* ctx, int slot_id, const void* x_in, void* x_out, void* const* layer_inputs_out,
                            float* router_logits, int batch, int seq, void* workspace, size_t workspace_bytes);

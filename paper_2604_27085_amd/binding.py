@@ -81,6 +81,7 @@ _SIGS = {
     "rp_ctx_create": [C.POINTER(_vp), _i, _vp, _vp, _pcfg],
     "rp_ctx_destroy": [_vp],
     "rp_query_sizes": [_pcfg, _i, _i, _psz, _psz, _psz],
+    "rp_query_least_workspace": [_pcfg, _i, _i, _psz, _psz, _psz],
     "rp_slot_bytes": [_pcfg, _psz],
     "rp_weight_layout": [_pcfg, _i, _i, _psz, _psz],
     "rp_grad_layout": [_pcfg, _i, _i, _psz, _psz],
@@ -155,6 +156,12 @@ def rp_query_sizes(cfg, batch, seq):
     w, g, ws = C.c_size_t(), C.c_size_t(), C.c_size_t()
     _check(lib.rp_query_sizes(C.byref(cfg), batch, seq, C.byref(w), C.byref(g), C.byref(ws)))
     return w.value, g.value, ws.value
+
+
+def rp_query_least_workspace(cfg, batch, seq):
+    f, b, h = C.c_size_t(), C.c_size_t(), C.c_size_t()
+    _check(lib.rp_query_least_workspace(C.byref(cfg), batch, seq, C.byref(f), C.byref(b), C.byref(h)))
+    return f.value, b.value, h.value
 
 
 def rp_slot_bytes(cfg):

@@ -676,6 +676,17 @@ rp_status rp_query_sizes(const rp_stage_cfg* cfg, int batch, int seq, size_t* we
   return RP_OK;
 }
 
+rp_status rp_query_least_workspace(const rp_stage_cfg* cfg, int batch, int seq, size_t* forward_bytes, size_t* backward_bytes, size_t* head_bytes) {
+  rp_status s = validate_cfg(cfg, nullptr);
+  if (s == RP_OK) s = validate_shape(nullptr, batch, seq);
+  if (s != RP_OK) return s;
+  const Plan P = make_plan(*cfg, batch, seq, true);
+  if (forward_bytes) *forward_bytes = cfg->n_layers > 0 ? P.fwd_bytes : 0;
+  if (backward_bytes) *backward_bytes = cfg->n_layers > 0 ? P.bwd_min : 0;
+  if (head_bytes) *head_bytes = P.head_bytes;
+  return RP_OK;
+}
+
 rp_status rp_slot_bytes(const rp_stage_cfg* cfg, size_t* slot_bytes) {
   rp_status s = validate_cfg(cfg, nullptr);
   if (s != RP_OK) return s;

@@ -1,5 +1,6 @@
 """CPU-side checks of the C-ABI library: it loads, exports every symbol the headers declare, and its pure host
 functions (sizes, layouts, argument validation) behave.  No kernel is launched here."""
+import ctypes
 import ctypes as C
 import os
 import re
@@ -138,3 +139,21 @@ def test_workspace_covers_paper_activation_formula():
     per_layer = accounting.activation_bytes_per_layer(c["seq"], c["batch"], c["hidden"], c["ffn"], c["n_q_heads"], c["n_kv_heads"])
     assert ws >= c["n_layers"] * per_layer
     assert ws <= 3.0 * c["n_layers"] * per_layer + 2 ** 31
+
+
+def test_least_workspace():
+    """What a call accepts at least: the sizes that fit a worker whose memory was planned without the optional regions."""
+    pinned = {"C1": 71601920, "C2": 1963180288, "C3": 5660213248, "C4": 12240814080, "C5": 12032855296, "C6": 5157074944}
+    for name, c in synth.CONFIGS.items():
+        cfg = H.cfg_from_dict(c)
+        least = B.rp_query_least_workspace(cfg, c["batch"], c["seq"])
+        assert max(least) == pinned[name]
+        assert max(least) <= B.rp_query_sizes(cfg, c["batch"], c["seq"])[2]
+        assert 0 < least[0] <= least[1] and (least[2] > 0) == (cfg.vocab > 0)
+    head = B.make_cfg(0, 5120, 64, 8, 128, 25600, vocab=151936, train_base=0)
+    assert B.rp_query_least_workspace(head, 1, 2040) == (0, 0, 571275264)
+    assert B.lib.rp_query_least_workspace(ctypes.byref(head), 1, 2040, None, None, None) == B.RP_OK
+    assert B.lib.rp_query_least_workspace(None, 1, 8, None, None, None) == B.RP_EINVAL
+    with pytest.raises(B.RpError) as e:
+        B.rp_query_least_workspace(head, 1, 100)          # T not a multiple of 8
+    assert e.value.code == B.RP_EUNSUPPORTED
