@@ -124,6 +124,29 @@ def test_gemm_operands_loaded_straight_into_lds(rp, shape, layout):
         np.testing.assert_array_equal(got, want)
 
 
+@pytest.mark.parametrize("M,N,K", [(300, 520, 2624), (256, 264, 64), (1, 8, 2560)])
+def test_gemm_residual_with_rows_on_8_byte_boundaries(rp, M, N, K):
+    """The residual's row stride is a multiple of 4 only, and its rows start 8 bytes off a 16-byte boundary: the four-wave kernel, which
+    reads it ahead in rows of 64 columns, against the eight-wave kernel bit for bit and against the fp64 product."""
+    B, H = rp
+    rng = np.random.default_rng(800 + M)
+    a, b, res = rnd(rng, (M, K)), rnd(rng, (N, K), 0.05), rnd(rng, (M, N))
+    ldr = N + 4
+    R = torch.full((M * ldr + 4,), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    R[4:].view(M, ldr)[:, :N] = dev(H, res)
+    A, Bm = dev(H, a), dev(H, b)
+    outs = []
+    for tile in (1, 7):
+        Cm = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+        torch.cuda.synchronize()
+        B.rp_op_gemm(stream(), 0, 0, A, Bm, Cm, M, N, K, K, K, N, R=R[4:], ldr=ldr, tile=tile)
+        torch.cuda.synchronize()
+        outs.append(H.to_f32(Cm))
+    ref = a.astype(np.float64) @ b.T.astype(np.float64) + res
+    assert rel_l2(outs[1], ref) < 4e-3
+    np.testing.assert_array_equal(outs[0], outs[1])
+
+
 @pytest.mark.parametrize("layout", [0, 1])
 def test_gemm_b_operand_in_fragment_order(rp, layout):
     """Tile 6: B (and the second pair's B) pre-arranged in the fragment order of the matrix instruction and streamed
