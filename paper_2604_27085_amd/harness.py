@@ -156,7 +156,9 @@ class StageRunner:
         # the head gets a workspace of its own so that it can run between the two phases of a fused last stage
         self.ws_head = self.ws
         if cfg.vocab > 0 and cfg.n_layers > 0:
-            self.ws_head = torch.empty(self.wsbytes, dtype=torch.uint8, device=self.device)
+            alone = B.StageCfg.from_buffer_copy(cfg)      # the head as a stage of its own asks for what the head takes
+            alone.n_layers = 0
+            self.ws_head = torch.empty(B.rp_query_sizes(alone, batch, seq)[2], dtype=torch.uint8, device=self.device)
         self.grads = torch.zeros(max(self.gbytes, 4) // 4, dtype=torch.float32, device=self.device)
         self.T = batch * seq
 
@@ -220,7 +222,7 @@ class StageRunner:
         if dx is None:
             dx = torch.empty_like(x)
         B.rp_lmhead_ce_fwd_bwd(self.ctx, slot, x, labels, loss, dx, self.grads if (train and self.gbytes) else None,
-                               grad_scale, self.batch, self.seq, self.ws_head, self.wsbytes)
+                               grad_scale, self.batch, self.seq, self.ws_head, self.ws_head.numel())
         return loss, dx
 
     def enable_rounds(self, streams_per_direction=1):
