@@ -88,7 +88,7 @@ typedef struct {
                           it a trainable head runs as 1, a frozen one keeps one pass's; a frozen head also does so in a
                           workspace too small for all of them);  1: the
                           two-sweep schedule (softmax statistics, then the logits
-                          again for the gradients): no vocabulary-sized buffer, one more logit-sized product -- same
+                          again for the gradients): no buffer beyond one pass's, one more logit-sized product -- same
                           results within bf16 noise */
 } rp_stage_cfg;
 

@@ -103,8 +103,8 @@ RP_API rp_status rp_op_attn_fwd(void* stream, const void* q, const void* k, cons
                          long ldv, long ldo, int batch, int seq, int a, int kh, int d);
 /* delta fp32 [batch, a, seq] is scratch (rowsum(dO*O)); dq [T,a,d], dk, dv [T,kh,d] overwritten.  scratch: device
  * fp32 [2, T, a, d], needed when a > kh (partials of dk, dv, one per query head or per two or four heads of a group, summed in
- * head order); may be NULL when a == kh.  dq may take the place of q, dout or o (same strides), or lie in o or in scratch at any offset; nothing
- * else may overlap. */
+ * head order); may be NULL when a == kh.  dq may take the place of q, dout or o (same strides); dq, dk and dv
+ * may lie in o, and dq in scratch, at any offset. */
 RP_API rp_status rp_op_attn_bwd(void* stream, const void* q, const void* k, const void* v, const void* o, const void* dout,
                          const float* lse, float* delta, void* dq, void* dk, void* dv, float* scratch, long ldq, long ldk,
                          long ldv, long ldo, long lddo, long lddq, long lddk, long lddv, int batch, int seq, int a, int kh,
