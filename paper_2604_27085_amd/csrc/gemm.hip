@@ -51,7 +51,8 @@ struct TileLoader {
 
   // fold_half (only !TR): the tile's rows are the two halves of a folded index range -- rows [0, BX/2) are x0/2 + row,
   // rows [BX/2, BX) are fold_half + x0/2 + row - BX/2 (the gate and up rows of one SwiGLU column block).
-  RP_DEV void init(long ld, int x0, int Xdim, int tid, int fold_half = 0) {
+  // row_map (only !TR): row gx is read from row row_map[gx] of the buffer.
+  RP_DEV void init(long ld, int x0, int Xdim, int tid, int fold_half = 0, const int* row_map = nullptr) {
     row0 = tid / S::CH;
     ch = tid % S::CH;
     kstep = TR ? (uint32_t)ld * 2u : 2u;
@@ -62,7 +63,8 @@ struct TileLoader {
         const int gl = fold_half ? (x0 >> 1) + (row < BX / 2 ? row : row - BX / 2) : x0 + row;
         const int gx = fold_half && row >= BX / 2 ? fold_half + gl : gl;
         const bool in = gl < (fold_half ? fold_half : Xdim);
-        voff[it] = in ? (uint32_t)((long)gx * ld + ch * 8) * 2u : OOB;
+        const long src = (row_map && in) ? row_map[gx] : gx;
+        voff[it] = in ? (uint32_t)(src * ld + ch * 8) * 2u : OOB;
       } else {
         const int gx = x0 + ch * 8;
         voff[it] = gx < Xdim ? (uint32_t)((long)row * ld + gx) * 2u : OOB;
@@ -121,7 +123,9 @@ struct Cfg {
 // every wave streams the fragments of its 64 columns straight into registers, 1 KB per load instruction, through a ring
 // that holds one K tile and is refilled fragment by fragment right after a fragment's last MFMA -- a whole K tile of
 // latency per load.  Half of the LDS stores and a third of the LDS reads of the staged kernel go away.
-template <int WGM, int WGN, int BK, bool TA, bool TB, int KG, bool GATED, bool BD>
+//
+// GRP: grouped mode.  Tile rows are the entries of the table.
+template <int WGM, int WGN, int BK, bool TA, bool TB, int KG, bool GATED, bool BD, bool GRP>
 __global__ void __launch_bounds__(WGM* WGN* KG * 64)
     __attribute__((amdgpu_waves_per_eu(Cfg<WGM, WGN, BK, TA, TB, KG>::WPS, Cfg<WGM, WGN, BK, TA, TB, KG>::WPS)))
     gemm_kernel(const GemmArgs p) {
@@ -145,9 +149,24 @@ __global__ void __launch_bounds__(WGM* WGN* KG * 64)
   const int wm = wmn / WGN, wn = wmn % WGN;
   const int ks0 = kg * KSL;
 
-  int tile_m, tile_n;
-  tile_of_block(p.M, p.N, BM, BN, tile_m, tile_n);
-  const int m0 = tile_m * BM;
+  int tile_m, tile_n, m0, Mlim = p.M;
+  const bf16* Bbase = static_cast<const bf16*>(p.B);
+  const int* row_map = nullptr;
+  if constexpr (GRP) {
+    static_assert(!TA && KG == 1 && !GATED && !BD && BM == 256, "grouped mode");
+    const int tiles_n = (p.N + BN - 1) / BN;
+    tile_m = (int)blockIdx.x / tiles_n;
+    tile_n = (int)blockIdx.x % tiles_n;
+    if (tile_m >= *p.grp_ntiles) return;
+    const int4 g = p.grp_tab[tile_m];
+    m0 = g.y;
+    Mlim = g.y + g.z;
+    Bbase += (long)g.x * p.grp_strideB;
+    row_map = p.row_map;
+  } else {
+    tile_of_block(p.M, p.N, BM, BN, tile_m, tile_n);
+    m0 = tile_m * BM;
+  }
   const int n0 = tile_n * BN;
   const int nk1 = (p.K + BK - 1) / BK;
   const int nk_all = nk1 + (p.K2 + BK - 1) / BK;
@@ -158,10 +177,10 @@ __global__ void __launch_bounds__(WGM* WGN* KG * 64)
 
   LA la, la2;
   LB lb, lb2;
-  la.init(p.lda, m0, p.M, tid);
+  la.init(p.lda, m0, Mlim, tid, 0, row_map);
   const int fold = (!TB && p.epi == EPI_SWIGLU_FWD) ? p.N >> 1 : 0;   // uniform
   lb.init(p.ldb, n0, p.N, tid, fold);
-  const rsrc_t rsA = make_rsrc(p.A, p.bytesA), rsB = make_rsrc(p.B, p.bytesB);
+  const rsrc_t rsA = make_rsrc(p.A, p.bytesA), rsB = make_rsrc(Bbase, p.bytesB);
   rsrc_t rsA2 = rsA, rsB2 = rsB;
   la2 = la;
   lb2 = lb;
@@ -326,20 +345,20 @@ __global__ void __launch_bounds__(WGM* WGN* KG * 64)
   }
   // a folded tile's wave columns: waves 0, 1 of a row hold gate columns, waves 2, 3 the up columns that go with them
   const int wcol = fold ? (n0 >> 1) + (wn & 1) * WAVE_N + (wn >> 1) * fold : n0 + wn * WAVE_N;
-  epilogue(p, p.M, acc, smem, wmn, lane, m0 + wm * WAVE_M, wcol, p.part_row0 + tile_m * WGM + wm);
+  epilogue(p, Mlim, acc, smem, wmn, lane, m0 + wm * WAVE_M, wcol, p.part_row0 + tile_m * WGM + wm);
 }
 
-template <int WGM, int WGN, int BK, bool TA, bool TB, int KG = 1, bool GATED = false, bool BD = false>
+template <int WGM, int WGN, int BK, bool TA, bool TB, int KG = 1, bool GATED = false, bool BD = false, bool GRP = false>
 hipError_t launch_one(hipStream_t st, const GemmArgs& a) {
   using C = Cfg<WGM, WGN, BK, TA, TB, KG>;
   static bool attr_done = false;
-  auto kern = gemm_kernel<WGM, WGN, BK, TA, TB, KG, GATED, BD>;
+  auto kern = gemm_kernel<WGM, WGN, BK, TA, TB, KG, GATED, BD, GRP>;
   if (!attr_done) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, C::SMEM);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  const int tiles = ((a.M + C::BM - 1) / C::BM) * ((a.N + C::BN - 1) / C::BN);
+  const int tiles = (GRP ? a.grp_max_tiles : (a.M + C::BM - 1) / C::BM) * ((a.N + C::BN - 1) / C::BN);
   RP_LAUNCH(kern, dim3(tiles, a.splits > 0 ? a.splits : 1), dim3(C::NTHR), C::SMEM, st, a);
   return hipGetLastError();
 }
@@ -352,6 +371,10 @@ hipError_t launch_tile(hipStream_t st, const GemmArgs& a, int tile) {
   }
   if (a.b_direct) {   // B in fragment order: its memory layout no longer matters, one instance serves NT and NN
     if constexpr (!TA) return launch_one<2, 4, 64, false, false, 1, false, true>(st, a);
+    return hipErrorInvalidValue;
+  }
+  if (a.grp_tab) {
+    if constexpr (!TA) return launch_one<2, 4, 64, TA, TB, 1, false, false, true>(st, a);
     return hipErrorInvalidValue;
   }
   switch (tile) {
@@ -641,8 +664,13 @@ hipError_t gemm_launch(hipStream_t st, int layout, const GemmArgs& a_in, int til
   // faster -- unless a kernel is asked for by name (hint 1: eight waves, hint 7: four) or the variant has no
   // counterpart there.
   // Skinny outputs (the LoRA products, bound by reading the other operand once) stay on the eight-wave kernel too: +14 %.
-  // Grouped products always take it: it is the kernel that knows their tile table.
-  const bool dtl = a.grp_tab || (tile == 1 && tile_hint != 1 && !a.run_flag && !a.b_direct && (tile_hint == 7 || (a.K + a.K2 >= 2560 && a.M > 64 && a.N > 64)));
+  // Grouped products take it too (it spares a tile's empty rows their matrix instructions), but for reductions of up to 16 K tiles over
+  // weights that the caches hold (grp_cached): these are bound by that fixed cost, and by fetching the larger code.  Forward
+  // of a layer, us, eight waves | four: 8 experts of 256 x 96, 136 tokens 71 | 79 (a product 11 | 16), 1064 92 | 100; of 512 x 512, 136 | 4096 tokens
+  // 83 | 87, 151 | 161; of 768 x 3072, 16384 tokens 1004 | 1039; 32 of 512 x 1024, 4096 tokens 220 | 233.  With weights from
+  // memory the four waves are ahead: 64 of 1024 x 512 (201 MB), 4096 | 16384 tokens 276 | 268, 857 | 833; 128 of 2048 x 768, 16384 2521 | 2468.
+  const bool short_grp = a.grp_tab && a.grp_cached && !a.grp_once && a.K <= 1024;
+  const bool dtl = a.grp_tab ? !short_grp : (tile == 1 && tile_hint != 1 && !a.run_flag && !a.b_direct && (tile_hint == 7 || (a.K + a.K2 >= 2560 && a.M > 64 && a.N > 64)));
   if (dtl) {
     e = gemm_dtl_launch(st, a, layout);
   } else {

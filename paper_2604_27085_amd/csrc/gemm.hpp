@@ -57,8 +57,9 @@ struct GemmArgs {
   // the grid is sized for grp_max_tiles and surplus workgroups exit); B of group g starts grp_strideB elements after
   // B.  row_map (optional): row r of A is read from row row_map[r] of the A buffer (gather fused into the loads).
   // 256x256 tiles, NT or NN, no second operand pair.
-  // grp_once: no group's weights are wanted again soon, they are loaded non-temporally (gemm_once_kernel).
-  const int4* grp_tab; const int* grp_ntiles; int grp_max_tiles; long grp_strideB; const int* row_map; int grp_once;
+  // grp_once: no group's weights are wanted again soon, they are loaded non-temporally (gemm_once_kernel).  grp_cached: all
+  // groups' weights together stay in the caches from one product to the next.
+  const int4* grp_tab; const int* grp_ntiles; int grp_max_tiles; long grp_strideB; const int* row_map; int grp_once, grp_cached;
   int row_map_rows;            // rows of the A buffer that row_map indexes
   void* C2; long ldc2;         // EPI_SWIGLU_FWD: the activation output
   const int* run_flag;         // optional [dev]: the kernel returns at once when *run_flag == 0 (conditional slow paths)

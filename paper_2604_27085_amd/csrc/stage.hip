@@ -288,9 +288,8 @@ struct Exec {
   //   32, 2880 x 2880, 1.6 GB: 176 rows 597 | 557, 208 636 | 590, 240 699 | 679, 256 817 | 814;  8, 4096 x 14336, 2.8 GB: 240 955 | 894, 256 1025 | 1024
   //   16, 2048 x 768, 100 rows: one layer (151 MB) 137 | 146, two (302 MB) 301 | 289;  32, 1024 x 512, 64 rows: two layers (201 MB) 224 | 241, four 487 | 469
   //   4096 x 1536: 4 experts (151 MB) 194 | 207, 5 (189 MB) 209 | 207, 6 (226 MB) 225 | 217, 8 (302 MB) 232 | 222;  2880 x 2880: 4 (199 MB) 177 | 191
-  bool experts_once() const {
-    return T * D.topk <= 240L * D.E && 6.0 * D.L * D.E * D.h * (double)D.m > 200.0 * 1048576.0;
-  }
+  double expert_bytes() const { return 6.0 * D.L * D.E * D.h * (double)D.m; }    // of all layers
+  bool experts_once() const { return T * D.topk <= 240L * D.E && expert_bytes() > 200.0 * 1048576.0; }
   // Whether the down projection and the gradient of its input run in one launch (gemm_pair_kernel): its tiles follow each other expert by
   // expert, 256 rows at a time, where each product alone takes four such rows of tiles at once.  With one tile per expert nothing is lost by
   // that; with several the expert's matrix is read more often, which shows once it is larger than what the caches turn around.
@@ -311,6 +310,7 @@ struct Exec {
     g.grp_max_tiles = P.moe_max_tiles;
     g.grp_strideB = strideB;
     g.grp_once = experts_once();
+    g.grp_cached = expert_bytes() <= 128.0 * 1048576.0;
     if (gather) { g.row_map = reinterpret_cast<const int*>(set + P.lb.m_tok); g.row_map_rows = a_rows; }
     return g;
   }

@@ -1,5 +1,5 @@
 """Expert stages whose down projection and the gradient of its input share a launch, against the two phases run apart, where they cannot: the
-same bits.  And where they share it, read from the timeline: up to 240 rows per expert, or while one down matrix has at most 48 MB."""
+same bits (of the four-wave kernel and, up to a reduction of 1024, the eight-wave one).  And where they share it, read from the timeline: up to 240 rows per expert, or while one down matrix has at most 48 MB."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -23,7 +23,9 @@ def _runner(layers, E, K, h, m, batch, seq, r=0):
 @pytest.mark.parametrize("layers,E,K,h,m,batch,seq", [
     (1, 8, 2, 256, 96, 1, 8),          # experts without rows, a tile column that is not full
     (2, 8, 2, 360, 360, 1, 904),       # experts with one tile and with two; the pair is the last layer's only
-    (1, 6, 4, 1032, 520, 3, 232),      # several tile columns, ragged
+    (1, 6, 4, 1032, 520, 3, 232),      # several tile columns, ragged; a reduction beyond 1024 and one within
+    (1, 3, 1, 1024, 1032, 1, 40),      # 1024 and 1032
+    (1, 24, 2, 1032, 1024, 1, 48),     # the same above 128 MiB of weights: four waves everywhere
 ])
 def test_phases_together_and_apart(layers, E, K, h, m, batch, seq):
     if not torch.cuda.is_available():
