@@ -402,7 +402,12 @@ void linear_bwd(Exec& X, const LayerW& W, const LayerG& G, int w_id, const Fused
   const int nr = f.n * X.D.r, T = (int)X.T;
   void* ud = X.at<void>(X.ud_next());
   Exec::Group q;
-  if (X.pending_dA) X.add(q, GEMM_TN, X.dA);      // of the projection before
+  if (X.pending_dA) {      // of the projection before
+    // (without adapters here the first group is dX, which for few tokens would be drawn into the shared launch: 64 tokens, h = 5120, an
+    // adapter on down only, dX of gate and up by itself 627 us a stage, together with dA 692)
+    X.add(q, GEMM_TN, X.dA);
+    if (!f.n) X.run(q);
+  }
   X.pending_dA = false;
   // the weight gradient joins the first group when it is small enough to share a launch, else it waits for the layer's end, or runs
   // behind dX

@@ -62,3 +62,25 @@ def test_weight_gradients_are_recorded_as_launched(h, m, T, joined):
     else:           # gate and up alone, on the tile that the product picks by itself
         assert len(rec) == 1 and rec[0][0] not in ("gemm_wgrad_TN", "gemm_256x256_TN")
         assert rec[0][1] == 2.0 * T * 2 * h * m and rec[0][2] == 2.0 * T * (2 * m + h) + 8.0 * 2 * m * h
+
+
+def test_an_adapter_gradient_that_waited_leaves_the_next_projection_alone():
+    """An adapter on down only: its dA waits for the next projection, which has no small products of its own and whose dX, narrow at 64
+    tokens, must not be drawn into a launch with it."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_27085_amd import binding as B, harness as H
+    T, h, m = 64, 1024, 4096
+    r = H.StageRunner(B.make_cfg(1, h, 8, 2, 128, m, lora_rank=16, lora=("down",), train_base=0), 1, T)
+    r.slots[0].view(torch.bfloat16).normal_(0.0, 0.02)
+    x = torch.empty((T, h), dtype=torch.bfloat16, device="cuda:0").normal_()
+    dy, dx = torch.empty_like(x).normal_(), torch.empty_like(x)
+    torch.cuda.synchronize()
+    r.bind()
+    B.rp_trace_start(r.ctx, 256)
+    B.rp_stage_backward(r.ctx, 0, B.PHASE_BACKWARD | B.PHASE_RECOMPUTE, x, dy, dx, None, r.grads, None, None, 1, T, r.ws, r.wsbytes)
+    rec = B.rp_trace_stop(r.ctx, 256)
+    r.close()
+    wide = [t for t in rec if t[1] == 2.0 * T * 2 * m * h]      # gate and up: forward and dX
+    assert sorted(t[0][-3:] for t in wide) == ["_NN", "_NT"]
+    assert all(t[1] < 2.0 * T * 2 * m * h for t in rec if t[0] == "gemm_group")
