@@ -48,7 +48,18 @@ __global__ void __launch_bounds__(1024) ce_finalize_kernel(const float* __restri
   __shared__ int redi[16];
   __shared__ float bc;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  if (last.part && *last.flag) {      // uniform.  All threads on min(T, 1024) tokens at a time, the rows split over what is left of them
+  const int owed = last.part ? *last.flag : 0;      // uniform; waited for behind the loop, which is run again where it is set
+  int cnt = 0;
+  float sum = 0.f;
+  auto add_up = [&]() {
+    cnt = 0;
+    sum = 0.f;
+    for (int t = tid; t < T; t += 1024) {
+      if (labels[t] != -100) { ++cnt; sum += (l ? lse[t] + logf(l[t]) : lse[t]) - zlab[t]; }
+    }
+  };
+  add_up();
+  if (owed) {      // all threads on min(T, 1024) tokens at a time, the rows split over what is left of them
     __shared__ float part[1024];
     const int width = T < 1024 ? (T + 63) / 64 * 64 : 1024, ns = 1024 / width, sl = tid / width, tl = tid - sl * width;
     for (int t0 = 0; t0 < T; t0 += width) {
@@ -71,11 +82,7 @@ __global__ void __launch_bounds__(1024) ce_finalize_kernel(const float* __restri
       }
       __syncthreads();      // (also makes l visible to the threads that read it below)
     }
-  }
-  int cnt = 0;
-  float sum = 0.f;
-  for (int t = tid; t < T; t += 1024) {
-    if (labels[t] != -100) { ++cnt; sum += (l ? lse[t] + logf(l[t]) : lse[t]) - zlab[t]; }
+    add_up();
   }
   sum = wave_sum(sum);
   float fc = wave_sum((float)cnt);
@@ -137,8 +144,16 @@ __global__ void __launch_bounds__(1024) ce_chunk_stats_kernel(const float2* __re
                                                               float* __restrict__ l_in, float* __restrict__ l_out, int* __restrict__ flag, const CeSums prev) {
   __shared__ float2 red[CE_SLICES][64];
   const int lane = threadIdx.x & 63, sl = threadIdx.x >> 6, t = blockIdx.x * 64 + lane;
+  const int owed = prev.part ? *prev.flag : 0;      // uniform; waited for behind the loop
   float lin = sl == 0 && t < T ? l_in[t] : 0.f;
-  if (prev.part && *prev.flag) {      // uniform
+  float mx = -INFINITY, sum = 0.f;
+  if (t < T)
+    for (int i = sl; i < nslab; i += CE_SLICES) {
+      const float2 v = part[(long)i * T + t];
+      mx = fmaxf(mx, v.x);
+      sum += v.y;
+    }
+  if (owed) {
     float s = 0.f;
     if (t < T)
       for (int i = sl; i < prev.rows; i += CE_SLICES) s += prev.part[(long)i * T + t].y;
@@ -151,13 +166,6 @@ __global__ void __launch_bounds__(1024) ce_chunk_stats_kernel(const float2* __re
     }
     __syncthreads();
   }
-  float mx = -INFINITY, sum = 0.f;
-  if (t < T)
-    for (int i = sl; i < nslab; i += CE_SLICES) {
-      const float2 v = part[(long)i * T + t];
-      mx = fmaxf(mx, v.x);
-      sum += v.y;
-    }
   red[sl][lane] = make_float2(mx, sum);
   __syncthreads();
   if (sl == 0 && t < T) {
