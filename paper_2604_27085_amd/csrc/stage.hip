@@ -181,7 +181,7 @@ struct Exec {
   Late* late = nullptr;            // where set, large weight gradients are noted here and run together at the layer's end
   size_t dkvp = 0;                 // dK/dV partials
   // An adapter's dA has no other small product to share a launch with behind its projection's dX, and joins the first group of the
-  // next projection (its dU then has the other one of two buffers to go to).  Backward stage of 64 tokens at h = 4096
+  // next projection that has adapters (its dU then has the other one of two buffers to go to).  Backward stage of 64 tokens at h = 4096
   // with seven adapters 459 -> 429 us, 2 x 508 1172 -> 1153, 4096 3644 -> 3616; beyond that dA fills the chip by itself.
   GemmArgs dA;
   bool pending_dA = false, two_ud = false, second_ud = false;
