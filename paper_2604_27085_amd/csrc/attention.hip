@@ -1189,13 +1189,14 @@ hipError_t launch_dq(hipStream_t st, const AttnArgs& p) {
 // longer, 1 to 4 us, and the partials and the launch that adds them are 3 us and what their traffic takes.  Forward and backward of the
 // attention entry points, us, one head | two:  d = 64, 4 heads: 1 x 64 tokens 21.4 | 18.0, 1 x 128 23.0 | 22.8, 64 x 128 30.8 | 25.6;  d = 128,
 // 16 heads: 1 x 64 23.7 | 21.2, 1 x 128 31.8 | 30.9, 4 x 128 36.6 | 31.8.  Two key tiles, heads x sequences at d = 64 and d = 128: 4: 28.4 | 30.6 and
-// 39.0 | 42.4, 16: 29.4 | 31.0 and 41.1 | 42.6, 32: 30.3 | 31.6 and 43.6 | 43.2, 64: 33.2 | 32.0 and 46.3 | 45.0, 256: 46.6 | 39.8 and 85.7 | 62.9.
+// 39.0 | 42.4, 16: 29.4 | 31.0 and 41.1 | 42.6, 32: 30.3 | 31.6 and 43.6 | 43.2, 64: 33.2 | 32.0 and 46.3 | 45.0, 256: 46.6 | 39.8 and 85.7 | 62.9;
+// 48 heads x sequences, 160 and 256 tokens: 25.7 | 25.9 and 31.5 | 31.7, 36.9 | 35.1 and 46.2 | 43.8.
 // (One tile, 4 heads, d = 128, 1 x 128 tokens: 30.2 | 30.6.)
 // Orders by runs of key tiles (from 96 tiles on, see k_attn_bwd) keep one head: 16384 x 64 at four heads is 3 % slower.
 int heads_per_workgroup(int seq, int batch, int a, int kh, int d) {
   const long nkv = (seq + 127) / 128;
   const double per_cu = (double)a * batch * nkv * (nkv + 1) / 256.0, most = d == 128 ? 1.0 : 0.45;
-  if (a == 2 * kh && (nkv == 1 || (nkv == 2 && a * batch >= 64))) return 2;
+  if (a == 2 * kh && (nkv == 1 || (nkv == 2 && a * batch >= (d == 128 ? 48 : 64)))) return 2;
   int hpw = 1;
   while (nkv < 96 && hpw < 4 && (a / kh) % (2 * hpw) == 0 && 2.0 * hpw * 2.0 * nkv <= most * per_cu) hpw *= 2;
   return hpw;

@@ -17,6 +17,7 @@ torch = pytest.importorskip("torch")
     (1, 128, 4, 2, 64, 0),        # groups of two in one key tile
     (4, 256, 16, 8, 128, 0),      # in two, 64 heads in all
     (3, 256, 20, 10, 64, 20),     # 60 heads
+    (3, 160, 16, 8, 128, 0),      # 48 heads, enough at head dimension 128
     (1, 256, 4, 2, 128, 4),
 ])
 def test_reduction_of_dkv_partials_is_recorded_as_launched(batch, seq, a, kh, d, partials):
