@@ -181,7 +181,7 @@ struct Exec {
   Late* late = nullptr;            // where set, large weight gradients are noted here and run together at the layer's end
   size_t dkvp = 0;                 // dK/dV partials
   // An adapter's dA has no other small product to share a launch with behind its projection's dX, and joins the first group of the
-  // next projection that has adapters (its dU then has the other one of two buffers to go to).  Backward stage of 64 tokens at h = 4096
+  // next projection (its dU then has the other one of two buffers to go to).  Backward stage of 64 tokens at h = 4096
   // with seven adapters 459 -> 429 us, 2 x 508 1172 -> 1153, 4096 3644 -> 3616; beyond that dA fills the chip by itself.
   GemmArgs dA;
   bool pending_dA = false, two_ud = false, second_ud = false;
@@ -402,12 +402,7 @@ void linear_bwd(Exec& X, const LayerW& W, const LayerG& G, int w_id, const Fused
   const int nr = f.n * X.D.r, T = (int)X.T;
   void* ud = X.at<void>(X.ud_next());
   Exec::Group q;
-  if (X.pending_dA) {      // of the projection before
-    // (without adapters here the first group is dX, which for few tokens would be drawn into the shared launch: 64 tokens, h = 5120, an
-    // adapter on down only, dX of gate and up by itself 627 us a stage, together with dA 692)
-    X.add(q, GEMM_TN, X.dA);
-    if (!f.n) X.run(q);
-  }
+  if (X.pending_dA) X.add(q, GEMM_TN, X.dA);      // of the projection before
   X.pending_dA = false;
   // the weight gradient joins the first group when it is small enough to share a launch, else it waits for the layer's end, or runs
   // behind dX
@@ -427,7 +422,13 @@ void linear_bwd(Exec& X, const LayerW& W, const LayerG& G, int w_id, const Fused
     wgrad(true);
     X.run(q);
   } else {
+    // A dA that waited shares a launch with a small weight gradient (h = 256, two layers with a head, adapters on q and v, 1504 tokens: 588
+    // us, in a launch of its own 600), but with dX alone, which for few tokens it draws in, only while that reads little.  dA by itself |
+    // together with dX, us a stage, by the bytes of the weight that dX reads, at 8 and 64 tokens: 8 MiB 231 | 225 and 237 | 234, 16 MiB 202 | 199
+    // and 207 | 207, 32 MiB 337 | 338 and 372 | 371, 48 MiB 200 | 204 and 205 | 207, 192 MiB 301 | 331 and 335 | 359, 500 MiB 517 | 613 and 592 | 681.
+    const int waited = q.n;
     wgrad(true);
+    if (waited && q.n == waited && (long)N * K > 8 << 20) X.run(q);
   }
   const void* lora_a = f.n ? W.t(f.a_id[0]) : nullptr;
   if (sw_gu) X.add(q, GEMM_NN, X.bf16_args(dy, N, W.t(w_id), K, sw_dgu, 2 * K, T, K, N, 1.f, f.n ? ud : nullptr, nr, lora_a, K, f.n ? nr : 0, sw_gu, 2 * K, EPI_SWIGLU_BWD));

@@ -65,13 +65,14 @@ def test_weight_gradients_are_recorded_as_launched(h, m, T, joined):
         assert rec[0][1] == 2.0 * T * 2 * h * m and rec[0][2] == 2.0 * T * (2 * m + h) + 8.0 * 2 * m * h
 
 
-def test_an_adapter_gradient_that_waited_leaves_the_next_projection_alone():
+@pytest.mark.parametrize("m,joined", [(4096, True), (4104, False)])
+def test_an_adapter_gradient_that_waited_and_the_next_projection(m, joined):
     """An adapter on down only: its dA waits for the next projection, which has no small products of its own and whose dX, narrow at 64
-    tokens, must not be drawn into a launch with it."""
+    tokens, is drawn into a launch with it up to a weight of 16 MiB, and is left alone above."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2604_27085_amd import binding as B, harness as H
-    T, h, m = 64, 1024, 4096
+    T, h = 64, 1024
     r = H.StageRunner(B.make_cfg(1, h, 8, 2, 128, m, lora_rank=16, lora=("down",), train_base=0), 1, T)
     r.slots[0].view(torch.bfloat16).normal_(0.0, 0.02)
     x = torch.empty((T, h), dtype=torch.bfloat16, device="cuda:0").normal_()
@@ -83,5 +84,27 @@ def test_an_adapter_gradient_that_waited_leaves_the_next_projection_alone():
     rec = B.rp_trace_stop(r.ctx, 256)
     r.close()
     wide = [t for t in rec if t[1] == 2.0 * T * 2 * m * h]      # gate and up: forward and dX
-    assert sorted(t[0][-3:] for t in wide) == ["_NN", "_NT"]
-    assert all(t[1] < 2.0 * T * 2 * m * h for t in rec if t[0] == "gemm_group")
+    assert sorted(t[0][-3:] for t in wide) == (["_NT"] if joined else ["_NN", "_NT"])
+    assert any(t[1] > 2.0 * T * 2 * m * h for t in rec if t[0] == "gemm_group") == joined
+
+
+def test_an_adapter_gradient_that_waited_joins_a_small_weight_gradient():
+    """Adapters on q and v, trained weights: the second layer's dA waits for the first layer's down, whose weight gradient is small enough
+    for a shared launch; the first layer's own has no projection behind it."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_27085_amd import binding as B, harness as H
+    T, h, m, rank = 512, 256, 688, 8
+    r = H.StageRunner(B.make_cfg(2, h, 4, 2, 64, m, lora_rank=rank, lora=("q", "v"), train_base=1), 1, T)
+    r.slots[0].view(torch.bfloat16).normal_(0.0, 0.02)
+    x = torch.empty((T, h), dtype=torch.bfloat16, device="cuda:0").normal_()
+    dy, dx = torch.empty_like(x).normal_(), torch.empty_like(x)
+    torch.cuda.synchronize()
+    r.bind()
+    B.rp_trace_start(r.ctx, 256)
+    B.rp_stage_backward(r.ctx, 0, B.PHASE_BOTH, x, dy, dx, None, r.grads, None, None, 1, T, r.ws, r.wsbytes)
+    rec = B.rp_trace_stop(r.ctx, 256)
+    r.close()
+    dA = 2.0 * T * 2 * rank * h
+    assert sum(t[0].endswith("_TN") and t[1] == dA for t in rec) == 1
+    assert any(t[0] == "gemm_group" and t[1] >= dA + 2.0 * T * h * m for t in rec)
