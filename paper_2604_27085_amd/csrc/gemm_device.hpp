@@ -84,8 +84,29 @@ RP_DEV void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Local row (relative to the wave's block, minus the lane's 4*lk) of accumulator register v of MFMA tile row i.
-RP_DEV constexpr int acc_row(int i, int v) { return i * 32 + 8 * (v >> 2) + (v & 3); }
+// Which element of a wave's 128x64 block the register acc[i][j][v] of a lane is, for the two matrix instructions the kernels use.
+// A lane owns one column of each of NJ groups of CW columns (column lc of a group) and, of every 32 rows, NV rows in quads: row
+// acc_row(i, w) + 4 * lg.  The elements of column group g are held by acc[i][reg_j(g)][reg_v(g, w)].
+//   L16 = false: v_mfma_f32_32x32x16_bf16, acc[i][j] is one 32x32 tile
+//   L16 = true : v_mfma_f32_16x16x32_bf16, acc[i][j] holds the 16x16 tiles (0,0), (0,1), (1,0), (1,1) of 32x32 elements, four registers each
+template <bool L16>
+struct AccMap {
+  static constexpr int NJ = L16 ? 4 : 2, CW = 64 / NJ, NV = L16 ? 8 : 16;
+  static constexpr RP_DEV int acc_row(int i, int w) { return i * 32 + (L16 ? 16 : 8) * (w >> 2) + (w & 3); }
+  static constexpr RP_DEV int reg_j(int g) { return L16 ? g >> 1 : g; }
+  static constexpr RP_DEV int reg_v(int g, int w) { return L16 ? (w >> 2) * 8 + (g & 1) * 4 + (w & 3) : w; }
+};
+// Sum / maximum over the lanes that share a column.
+template <bool L16>
+RP_DEV float column_lanes_max(float x) {
+  if constexpr (L16) x = fmaxf(x, __shfl_xor(x, 16, 64));
+  return fmaxf(x, __shfl_xor(x, 32, 64));
+}
+template <bool L16>
+RP_DEV float column_lanes_sum(float x) {
+  if constexpr (L16) x += __shfl_xor(x, 16, 64);
+  return x + __shfl_xor(x, 32, 64);
+}
 
 // max(a, b, c) as one instruction (the accumulators need no NaN canonicalisation)
 RP_DEV float max3(float a, float b, float c) {
@@ -94,28 +115,32 @@ RP_DEV float max3(float a, float b, float c) {
   return r;
 }
 
-// Maximum of a lane's 64 accumulators of tile column j (all of the wave's 128 rows after the exchange between the
-// half-waves).
-RP_DEV float column_max(const f32x16 (&acc)[TM][TN], int j) {
-  float mx = acc[0][j][0];
+// Maximum of the block's 128 rows of the lane's column in column group g.
+template <bool L16>
+RP_DEV float column_max(const f32x16 (&acc)[TM][TN], int g) {
+  using L = AccMap<L16>;
+  const int j = L::reg_j(g);
+  float mx = acc[0][j][L::reg_v(g, 0)];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int v = (i == 0 ? 1 : 0); v + 1 < 16; v += 2) mx = max3(mx, acc[i][j][v], acc[i][j][v + 1]);
-  mx = fmaxf(mx, acc[0][j][15]);
-  return fmaxf(mx, __shfl_xor(mx, 32, 64));
+    for (int w = (i == 0 ? 1 : 0); w + 1 < L::NV; w += 2) mx = max3(mx, acc[i][j][L::reg_v(g, w)], acc[i][j][L::reg_v(g, w + 1)]);
+  mx = fmaxf(mx, acc[0][j][L::reg_v(g, L::NV - 1)]);
+  return column_lanes_max<L16>(mx);
 }
 
-// The accumulator of tile column j whose local row is lab_local (= label row - first row of the wave's block - 4*lk),
+// The accumulator of column group g whose local row is lab_local (= label row - first row of the wave's block - 4*lg),
 // if this lane holds it.  Called only when some lane of the wave has its label inside the block.
-RP_DEV bool label_logit(const f32x16 (&acc)[TM][TN], int j, int lab_local, float& z) {
+template <bool L16>
+RP_DEV bool label_logit(const f32x16 (&acc)[TM][TN], int g, int lab_local, float& z) {
+  using L = AccMap<L16>;
   bool found = false;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const bool hit = lab_local == acc_row(i, v);
-      z = hit ? acc[i][j][v] : z;
+    for (int w = 0; w < L::NV; ++w) {
+      const bool hit = lab_local == L::acc_row(i, w);
+      z = hit ? acc[i][L::reg_j(g)][L::reg_v(g, w)] : z;
       found |= hit;
     }
   return found;
@@ -148,8 +173,7 @@ RP_DEV void swiglu_bwd_store(const GemmArgs& p, const bf16* staged, const uint4&
   }
 }
 
-// Epilogue.  acc[i][j][v] is element (i*32 + 8*(v/4) + 4*lk + v%4, j*32 + lr) of the wave's 128x64 block whose top
-// left corner is (wrow0, wcol0).  Every wave stages its block through its own 18 KB of LDS (all waves must have
+// Epilogue.  acc (elements as AccMap<L16> says) is the wave's 128x64 block whose top left corner is (wrow0, wcol0).  Every wave stages its block through its own 18 KB of LDS (all waves must have
 // finished the K loop) so that global accesses are 16 bytes per lane and cover whole 128-byte lines; no workgroup
 // barrier inside.
 // part_row: row of the cross-entropy partial array this wave writes (EPI_CE_STATS).
@@ -159,10 +183,12 @@ RP_DEV void swiglu_bwd_store(const GemmArgs& p, const bf16* staged, const uint4&
 // IS: rows of C between the 32-row MFMA tiles of the wave's block (32: the block is 128 consecutive rows).
 // j0, j1 (wave-uniform): the 32-column halves [j0, j1) of the block this wave writes -- both, except in the plain
 // epilogues of the two-group tile, where the groups take one half each.
-template <int IS = 32, bool PIPE = false>
+template <int IS = 32, bool PIPE = false, bool L16 = false>
 RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsigned char* smem, int wave, int lane,
                      int wrow0, int wcol0, int part_row, int j0 = 0, int j1 = TN) {
-  const int lr = lane & 31, lk = lane >> 5;
+  using L = AccMap<L16>;
+  const int lr = lane & (L::CW - 1), lk = lane / L::CW;   // the lane's column of a column group; its quad of rows
+  auto el = [&](int i, int g, int w) __attribute__((always_inline)) { return acc[i][L::reg_j(g)][L::reg_v(g, w)]; };
   unsigned char* const stg = smem + wave * STG_BYTES;
   const int rr = lane >> 3, cc = lane & 7;   // read-back: 8 rows per pass, 8 chunks of 16 bytes per row
   auto out_row = [&](int t) __attribute__((always_inline)) { return wrow0 + (t >> 2) * IS + (t & 3) * 8 + rr; };   // row of C of local row 8 t + rr
@@ -171,9 +197,9 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
     bf16* s16 = reinterpret_cast<bf16*>(stg);
     unsigned short* const h16 = reinterpret_cast<unsigned short*>(stg);
     // two rows of a column are converted by one instruction and go out as the halves of its result
-    auto stage2 = [&](int i, int j, int v, float x0, float x1) {
+    auto stage2 = [&](int i, int g, int w, float x0, float x1) {
       const uint32_t pk = pack_bf16x2(x0, x1);
-      unsigned short* const d = h16 + (acc_row(i, v) + 4 * lk) * STG_LD + j * 32 + lr;
+      unsigned short* const d = h16 + (L::acc_row(i, w) + 4 * lk) * STG_LD + g * L::CW + lr;
       d[0] = (unsigned short)pk;
       d[STG_LD] = (unsigned short)(pk >> 16);
     };
@@ -183,73 +209,75 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
       // the vocabulary are excluded from both (their staged values are never stored)
       constexpr float LOG2E = 1.4426950408889634f;
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int col = wcol0 + j * 32 + lr;
+      for (int g = 0; g < L::NJ; ++g) {
+        const int col = wcol0 + g * L::CW + lr;
         const bool colok = col < p.N;
         const int lab = colok ? p.labels[col] - p.row_offset : -1;
         const float nr = colok ? -LOG2E * p.lse[col] : 0.f;
         const float cap = RP_CE_P_CLAMP * LOG2E;
         float mx, sum = 0.f, sum2 = 0.f;
         if (wrow0 + WAVE_M <= M) {   // wave-uniform: no row of the block is past the end
-          mx = column_max(acc, j);
+          mx = column_max<L16>(acc, g);
           if (__ballot(lab >= wrow0 && lab < wrow0 + WAVE_M)) {
             float z = 0.f;
-            if (label_logit(acc, j, lab - wrow0 - 4 * lk, z)) p.zlab[col] = z;
+            if (label_logit<L16>(acc, g, lab - wrow0 - 4 * lk, z)) p.zlab[col] = z;
           }
 #pragma unroll
           for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int v = 0; v < 16; v += 2) {
-              const float e0 = __builtin_amdgcn_exp2f(fminf(fmaf(acc[i][j][v], LOG2E, nr), cap));
-              const float e1 = __builtin_amdgcn_exp2f(fminf(fmaf(acc[i][j][v + 1], LOG2E, nr), cap));
+            for (int v = 0; v < L::NV; v += 2) {
+              const float e0 = __builtin_amdgcn_exp2f(fminf(fmaf(el(i, g, v), LOG2E, nr), cap));
+              const float e1 = __builtin_amdgcn_exp2f(fminf(fmaf(el(i, g, v + 1), LOG2E, nr), cap));
               sum += e0; sum2 += e1;
-              stage2(i, j, v, e0, e1);
+              stage2(i, g, v, e0, e1);
             }
         } else {
           mx = -INFINITY;
 #pragma unroll
           for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int v = 0; v < 16; v += 2) {
-              const int row = wrow0 + i * 32 + 8 * (v >> 2) + 4 * lk + (v & 3);
+            for (int v = 0; v < L::NV; v += 2) {
+              const int row = wrow0 + L::acc_row(i, v) + 4 * lk;
               float e0 = 0.f, e1 = 0.f;
               if (row < M) {
-                mx = fmaxf(mx, acc[i][j][v]);
-                if (row == lab) p.zlab[col] = acc[i][j][v];
-                e0 = __builtin_amdgcn_exp2f(fminf(fmaf(acc[i][j][v], LOG2E, nr), cap));
+                mx = fmaxf(mx, el(i, g, v));
+                if (row == lab) p.zlab[col] = el(i, g, v);
+                e0 = __builtin_amdgcn_exp2f(fminf(fmaf(el(i, g, v), LOG2E, nr), cap));
               }
               if (row + 1 < M) {
-                mx = fmaxf(mx, acc[i][j][v + 1]);
-                if (row + 1 == lab) p.zlab[col] = acc[i][j][v + 1];
-                e1 = __builtin_amdgcn_exp2f(fminf(fmaf(acc[i][j][v + 1], LOG2E, nr), cap));
+                mx = fmaxf(mx, el(i, g, v + 1));
+                if (row + 1 == lab) p.zlab[col] = el(i, g, v + 1);
+                e1 = __builtin_amdgcn_exp2f(fminf(fmaf(el(i, g, v + 1), LOG2E, nr), cap));
               }
               sum += e0; sum2 += e1;
-              stage2(i, j, v, e0, e1);
+              stage2(i, g, v, e0, e1);
             }
-          mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+          mx = column_lanes_max<L16>(mx);
         }
         sum += sum2;
-        sum += __shfl_xor(sum, 32, 64);
+        sum = column_lanes_sum<L16>(sum);
         if (lk == 0 && colok) p.part[(long)part_row * p.part_ld + col] = make_float2(mx, sum);
       }
     } else if (p.epi != EPI_CE_DZ) {
       if (p.alpha == 1.f) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
+        for (int g = 0; g < L::NJ; ++g) {
+          const int j = L::reg_j(g);
           if (j < j0 || j >= j1) continue;
 #pragma unroll
           for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int v = 0; v < 16; v += 2) stage2(i, j, v, acc[i][j][v], acc[i][j][v + 1]);
+            for (int v = 0; v < L::NV; v += 2) stage2(i, g, v, el(i, g, v), el(i, g, v + 1));
         }
       } else {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
+        for (int g = 0; g < L::NJ; ++g) {
+          const int j = L::reg_j(g);
           if (j < j0 || j >= j1) continue;
 #pragma unroll
           for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int v = 0; v < 16; v += 2) stage2(i, j, v, p.alpha * acc[i][j][v], p.alpha * acc[i][j][v + 1]);
+            for (int v = 0; v < L::NV; v += 2) stage2(i, g, v, p.alpha * el(i, g, v), p.alpha * el(i, g, v + 1));
         }
       }
     } else {
@@ -258,21 +286,21 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
       // is the label is fixed up in the staging buffer afterwards.
       constexpr float LOG2E = 1.4426950408889634f;
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int col = wcol0 + j * 32 + lr;
+      for (int g = 0; g < L::NJ; ++g) {
+        const int col = wcol0 + g * L::CW + lr;
         const bool colok = col < p.N;
         const int lab = colok ? p.labels[col] - p.row_offset - wrow0 : -1;
         const float nl = colok ? -LOG2E * p.lse[col] : 0.f, cf = colok ? p.coef[col] : 0.f;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int v = 0; v < 16; v += 2)
-            stage2(i, j, v, __builtin_amdgcn_exp2f(fmaf(acc[i][j][v], LOG2E, nl)) * cf,
-                   __builtin_amdgcn_exp2f(fmaf(acc[i][j][v + 1], LOG2E, nl)) * cf);
+          for (int v = 0; v < L::NV; v += 2)
+            stage2(i, g, v, __builtin_amdgcn_exp2f(fmaf(el(i, g, v), LOG2E, nl)) * cf,
+                   __builtin_amdgcn_exp2f(fmaf(el(i, g, v + 1), LOG2E, nl)) * cf);
         if (__ballot(lab >= 0 && lab < WAVE_M)) {   // wave-uniform, rare
           float z = 0.f;
-          if (label_logit(acc, j, lab - 4 * lk, z))
-            s16[lab * STG_LD + j * 32 + lr] = (bf16)((__builtin_amdgcn_exp2f(fmaf(z, LOG2E, nl)) - 1.f) * cf);
+          if (label_logit<L16>(acc, g, lab - 4 * lk, z))
+            s16[lab * STG_LD + g * L::CW + lr] = (bf16)((__builtin_amdgcn_exp2f(fmaf(z, LOG2E, nl)) - 1.f) * cf);
         }
       }
     }
@@ -406,30 +434,30 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
       // rows are vocabulary entries, columns tokens: the maximum of every column over the wave's 128 rows, from the
       // registers, before the tile goes out
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int col = wcol0 + j * 32 + lr;
+      for (int g = 0; g < L::NJ; ++g) {
+        const int col = wcol0 + g * L::CW + lr;
         const bool colok = col < p.N;
         const int lab = colok ? p.labels[col] - p.row_offset : -1;
         float mx;
         if (wrow0 + WAVE_M <= M) {   // wave-uniform: no row of the block is past the end
-          mx = column_max(acc, j);
+          mx = column_max<L16>(acc, g);
           if (__ballot(lab >= wrow0 && lab < wrow0 + WAVE_M)) {
             float z = 0.f;
-            if (label_logit(acc, j, lab - wrow0 - 4 * lk, z)) p.zlab[col] = z;
+            if (label_logit<L16>(acc, g, lab - wrow0 - 4 * lk, z)) p.zlab[col] = z;
           }
         } else {
           mx = -INFINITY;
 #pragma unroll
           for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              const int row = wrow0 + i * 32 + 8 * (v >> 2) + 4 * lk + (v & 3);
+            for (int v = 0; v < L::NV; ++v) {
+              const int row = wrow0 + L::acc_row(i, v) + 4 * lk;
               if (row < M) {
-                mx = fmaxf(mx, acc[i][j][v]);
-                if (row == lab) p.zlab[col] = acc[i][j][v];
+                mx = fmaxf(mx, el(i, g, v));
+                if (row == lab) p.zlab[col] = el(i, g, v);
               }
             }
-          mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+          mx = column_lanes_max<L16>(mx);
         }
         if (lk == 0 && colok) p.part[(long)part_row * p.part_ld + col] = make_float2(mx, 0.f);
       }
@@ -464,9 +492,9 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
 #pragma unroll
           for (int i = 2 * h; i < 2 * h + 2; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
+            for (int g = 0; g < L::NJ; ++g)
 #pragma unroll
-              for (int v = 0; v < 16; ++v) f[(acc_row(i & 1, v) + 4 * lk) * LDF + j * 32 + lr] = p.alpha * acc[i][j][v];
+              for (int w = 0; w < L::NV; ++w) f[(L::acc_row(i & 1, w) + 4 * lk) * LDF + g * L::CW + lr] = p.alpha * acc[i][L::reg_j(g)][L::reg_v(g, w)];
           wave_lds_fence();
           if (h == 0) load_r(1);
 #pragma unroll
@@ -506,7 +534,9 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
       for (int i = 0; i < TM; ++i) {
         float* const d = s32 + (i * 32 + 4 * lk) * (STG_LD / 2) + lr;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) d[acc_row(0, v) * (STG_LD / 2)] = p.alpha * acc[i][j][v];
+        for (int g = 0; g < L::NJ / 2; ++g)
+#pragma unroll
+          for (int w = 0; w < L::NV; ++w) d[L::acc_row(0, w) * (STG_LD / 2) + g * L::CW] = p.alpha * acc[i][j][L::reg_v(g, w)];
       }
       wave_lds_fence();
       const int gcol = wcol0 + j * 32 + cc * 4;
@@ -536,12 +566,15 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
         float* const d = s32 + (i * 32 + 4 * lk) * (STG_LD / 2) + lr;
-        if (unit) {
 #pragma unroll
-          for (int v = 0; v < 16; ++v) d[acc_row(0, v) * (STG_LD / 2)] = acc[i][j][v];
-        } else {
+        for (int g = 0; g < L::NJ / 2; ++g) {
+          if (unit) {
 #pragma unroll
-          for (int v = 0; v < 16; ++v) d[acc_row(0, v) * (STG_LD / 2)] = p.alpha * acc[i][j][v];
+            for (int w = 0; w < L::NV; ++w) d[L::acc_row(0, w) * (STG_LD / 2) + g * L::CW] = acc[i][j][L::reg_v(g, w)];
+          } else {
+#pragma unroll
+            for (int w = 0; w < L::NV; ++w) d[L::acc_row(0, w) * (STG_LD / 2) + g * L::CW] = p.alpha * acc[i][j][L::reg_v(g, w)];
+          }
         }
       }
       wave_lds_fence();
@@ -596,40 +629,40 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
   } else if (p.epi == EPI_F32_ATOMIC) {
     float* Cp = reinterpret_cast<float*>(p.C);
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int col = wcol0 + j * 32 + lr;
+    for (int g = 0; g < L::NJ; ++g) {
+      const int col = wcol0 + g * L::CW + lr, j = L::reg_j(g);
       if (col >= p.N || j < j0 || j >= j1) continue;
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int row = wrow0 + i * 32 + 8 * (v >> 2) + 4 * lk + (v & 3);
-          if (row < M) atomicAdd(Cp + (long)row * p.ldc + col, p.alpha * acc[i][j][v]);
+        for (int v = 0; v < L::NV; ++v) {
+          const int row = wrow0 + L::acc_row(i, v) + 4 * lk;
+          if (row < M) atomicAdd(Cp + (long)row * p.ldc + col, p.alpha * el(i, g, v));
         }
     }
   } else if (p.epi == EPI_CE_STATS) {
     // rows are vocabulary entries, columns are tokens: every lane reduces its own column over the wave's 128 rows
     constexpr float LOG2E = 1.4426950408889634f;
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int col = wcol0 + j * 32 + lr;
+    for (int g = 0; g < L::NJ; ++g) {
+      const int col = wcol0 + g * L::CW + lr;
       const bool colok = col < p.N;
       const int lab = colok ? p.labels[col] - p.row_offset : -1;
       float mx, s = 0.f;
       if (wrow0 + WAVE_M <= M) {   // wave-uniform: no row of the block is past the end
-        mx = column_max(acc, j);
+        mx = column_max<L16>(acc, g);
         if (__ballot(lab >= wrow0 && lab < wrow0 + WAVE_M)) {
           float z = 0.f;
-          if (label_logit(acc, j, lab - wrow0 - 4 * lk, z)) p.zlab[col] = z;
+          if (label_logit<L16>(acc, g, lab - wrow0 - 4 * lk, z)) p.zlab[col] = z;
         }
         const float nm = -LOG2E * mx;
         float s2 = 0.f;   // two chains
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int v = 0; v < 16; v += 2) {
-            s += __builtin_amdgcn_exp2f(fmaf(acc[i][j][v], LOG2E, nm));
-            s2 += __builtin_amdgcn_exp2f(fmaf(acc[i][j][v + 1], LOG2E, nm));
+          for (int v = 0; v < L::NV; v += 2) {
+            s += __builtin_amdgcn_exp2f(fmaf(el(i, g, v), LOG2E, nm));
+            s2 += __builtin_amdgcn_exp2f(fmaf(el(i, g, v + 1), LOG2E, nm));
           }
         s += s2;
       } else {
@@ -637,25 +670,25 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int row = wrow0 + i * 32 + 8 * (v >> 2) + 4 * lk + (v & 3);
+          for (int v = 0; v < L::NV; ++v) {
+            const int row = wrow0 + L::acc_row(i, v) + 4 * lk;
             if (row < M) {
-              mx = fmaxf(mx, acc[i][j][v]);
-              if (row == lab) p.zlab[col] = acc[i][j][v];
+              mx = fmaxf(mx, el(i, g, v));
+              if (row == lab) p.zlab[col] = el(i, g, v);
             }
           }
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        mx = column_lanes_max<L16>(mx);
         if (mx > -INFINITY) {
 #pragma unroll
           for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              const int row = wrow0 + i * 32 + 8 * (v >> 2) + 4 * lk + (v & 3);
-              if (row < M) s += __expf(acc[i][j][v] - mx);
+            for (int v = 0; v < L::NV; ++v) {
+              const int row = wrow0 + L::acc_row(i, v) + 4 * lk;
+              if (row < M) s += __expf(el(i, g, v) - mx);
             }
         }
       }
-      s += __shfl_xor(s, 32, 64);
+      s = column_lanes_sum<L16>(s);
       if (lk == 0 && colok) p.part[(long)part_row * p.part_ld + col] = make_float2(mx, s);
     }
   }

@@ -3,12 +3,13 @@
 // each -- one wave per SIMD, 256 accumulator registers per lane (the AGPR half of the register file).
 //
 // Against the eight-wave kernel of gemm.hip a K tile of the same output tile costs a third fewer fragment reads (every
-// fragment feeds four MFMAs), no LDS stores and hardly any vector or scalar arithmetic: the loop is 64 MFMAs, 32
-// fragment reads, 16 loads and a barrier.  What pays for it is that nothing covers a stall -- there is no second wave on
-// the SIMD -- so the loop is laid out slot by slot (one MFMA plus at most one memory instruction, which has to issue
-// within the 32 cycles the MFMA runs), every fragment is read a 16-deep step ahead and every load one to two K tiles
-// ahead.  Measured on MI355X (8192^3, same box): 1.38-1.42 PFLOP/s against 1.29-1.31 for the eight-wave kernel as NT,
-// 1.43 against 1.31 as NN, 1.30 against 1.20 as TN; matrix pipe busy 85 % of the kernel's cycles against 77-78 %.
+// fragment feeds eight MFMAs), no LDS stores and hardly any vector or scalar arithmetic: the loop is 128 MFMAs, 32
+// fragment reads (TN: 64 half ones), 16 loads and a barrier.  What bounds it is the power that the matrix pipe draws: the chip clocks
+// down until it fits, so what an instruction costs in energy counts before what it costs in slots.  v_mfma_f32_16x16x32_bf16 moves half
+// the accumulators of the 32x32x16 instruction per FLOP and gives the same bits (mfma16 in common.hpp).  Measured on MI355X (8192 x 8192 x
+// 2048 | 4096 | 8192 | 16384, same box, 32x32x16 -> 16x16x32, us): NT 223 | 405 | 781 | 1562 -> 194 | 361 | 709 | 1436 (1.38 -> 1.55
+// PFLOP/s at 8192), NN 222 | 404 | 779 | 1559 -> 197 | 367 | 714 | 1445, TN 222 | 404 | 783 | 1569 -> 200 | 370 | 721 | 1453.
+// Where the reads, the loads and the barrier stand among the MFMAs no longer matters (four plans within 0.5 %).
 //
 //   LDS       a ring of five 32 KB units; a unit is one operand of one K tile of 64: 256 rows of 128 bytes -- a load
 //             fetches whole 128-byte lines (rows of 64 bytes, as a K tile of 32 would have, double the requests to L2:
@@ -16,10 +17,9 @@
 //             c ^ ((r >> 1) & 7): fragment reads meet no bank conflict, and since a load instruction fills 1 KB of LDS
 //             with consecutive lanes while the 16 bytes a lane fetches are free to choose, the swizzle costs nothing.
 //             Units are used in the order B(0), A(0), B(1), A(1), ...: unit u lives in ring slot u mod 5.
-//   loads     eight per wave and unit, one every other slot where no fragment is read.  B(t+2) is issued in the
-//             first half of tile t (into the slot of A(t-1), free since the barrier of tile t-1), A(t+2) behind the
-//             barrier of tile t (into the slot of B(t)).
-//   barrier   one per K tile, at slot 44 of 64: by then the wave has all its fragments of tile t.  Before it the wave
+//   loads     eight per wave and unit, in slots of their own.  B(t+2) is issued in the first half of tile t (into the slot of A(t-1),
+//             free since the barrier of tile t-1), A(t+2) behind the barrier of tile t (into the slot of B(t)).
+//   barrier   one per K tile, at slot 74 of 128: by then the wave has all its fragments of tile t.  Before it the wave
 //             waits for its own loads of tile t+1 (s_waitcnt vmcnt(8): B(t+2) may be in flight); after it tile t+1 is
 //             complete in LDS and its first fragments are read under the last step of tile t.
 //   tail      tiles past the end are "loaded" with an offset outside the descriptor (no memory traffic), which keeps
@@ -28,14 +28,13 @@
 // The loads are inline assembly: the compiler orders a buffer-load-to-LDS builtin against every later LDS read with
 // s_waitcnt vmcnt(0), which would serialise the pipeline; here the counts are kept by hand, and no compiler-visible
 // memory instruction may be pending when the loop is entered (see the rare paths of the load state).
-//   NN        B's units keep the operand's [K, N] layout (64 rows of 512 bytes; the 64-byte segment of MFMA tile column
-//             s of row k at segment s ^ (k & 3)), its fragments are two transposing reads (ds_read_b64_tr_b16) each:
-//             twelve read instructions and four loads per 16-slot step, a slot plan of its own.
-//   TN        the same for A: sixteen reads per step, one per slot, the loads on top of them.
+//   NN        B's units keep the operand's [K, N] layout (64 rows of 512 bytes; the 32-byte segment of MFMA tile column s of row k at
+//             segment s ^ seg_swizzle(k)), its fragments are two transposing reads (ds_read_b64_tr_b16) each.
+//   TN        the same for A.
 // Second operand pair, row map, reduction slices and every epilogue of gemm_device.hpp (applied to the two 128x64 halves
-// of a wave's block in turn) as in gemm.hip; results are bit-identical to its 256x256 tile (same MFMA, same order of the
-// reduction).  Most grouped products (GRP below) run here.  gemm_launch picks this kernel for reductions of 40 K tiles or more and outputs
-// that are not skinny: its fixed cost per output tile is higher than the eight-wave kernel's.
+// of a wave's block in turn) as in gemm.hip; results are bit-identical to its 256x256 tile (the same order of the
+// reduction).  Most grouped products (GRP below) run here.  gemm_launch picks this kernel for reductions of 40 K tiles or more and
+// outputs that are not skinny: its fixed cost per output tile is higher than the eight-wave kernel's.
 #include "gemm_device.hpp"
 #include <type_traits>
 #include <utility>
@@ -58,6 +57,62 @@ constexpr int UNIT_BYTES = 256 * BK * 2;          // one operand of one K tile: 
 constexpr int NUNIT = 5;
 constexpr int DTL_SMEM = NUNIT * UNIT_BYTES;      // 160 KB: the whole LDS of a CU; the epilogue's four staging areas (72 KB) reuse it
 static_assert(DTL_SMEM >= 4 * STG_BYTES, "epilogue staging does not fit");
+
+// [K, X] units: 64 rows of 512 bytes, sixteen 32-byte segments = the columns of one 16x16 tile each; segment s of row k lies at
+// s ^ seg_swizzle(k).  A transposing read touches the rows 8 g + c (c < 4) of the tile's segment for four lane groups g: eight rows at a
+// time (two groups), which then lie in eight different places of the banks.
+RP_DEV int seg_swizzle(int k) { return ((k & 3) << 1) | ((k >> 3) & 1); }
+
+// acc += a b in the accumulator's own registers of the AGPR half.  (Written with the builtin the compiler moves the 64 accumulators of the
+// loop around: 100 to 400 copies per K tile.)  The hazards are the loop's to keep: fragments come from LDS reads, for which the compiler
+// waits, an accumulator is next used 64 instructions later, and nothing reads one before the wait behind the loop.
+RP_DEV void mfma16_in_place(f32x4& acc, const uint4& a, const uint4& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(__builtin_bit_cast(bf16x8, a)), "v"(__builtin_bit_cast(bf16x8, b)));
+}
+
+// Where the reads and loads of a K tile go (see the slot plan in dtl_block): RB reads of B's and RA of A's fragments per step.
+template <int RB, int RA>
+struct SlotPlan {
+  static constexpr int BAR = 74, N = RB + RA;
+  static constexpr int first(int s) { return s == 0 ? 2 : 76; }
+  static constexpr int span(int s) { return s == 0 ? 56 : 52; }
+  static constexpr int at(int s, int n) { return first(s) + n * span(s) / N; }      // slot of read n of the coming step
+  // number of the read in slot sl, B's first; -1: none
+  static constexpr int read(int sl) {
+    const int s = sl >= 76 ? 1 : 0;
+    for (int n = 0; n < N; ++n)
+      if (at(s, n) == sl) return n;
+    return -1;
+  }
+  // A's tiles in the order 6, 7, 0, 1, .. 5
+  static constexpr int a_read(int n) { return (n + RA / 8 * 6) % RA; }
+  // number of the load in slot sl: 0..7 B's, 8..15 A's; each in the first slot without a read from its place on
+  static constexpr int load_slot(int n) {
+    int sl = 0;
+    for (int q = 0; q <= n; ++q) {
+      const int want = q < 8 ? 4 + 7 * q : 77 + 4 * (q - 8);
+      sl = want > sl + 1 ? want : sl + 1;
+      while (read(sl) >= 0) ++sl;
+    }
+    return sl;
+  }
+  static constexpr int load(int sl) {
+    for (int n = 0; n < 16; ++n)
+      if (load_slot(n) == sl) return n;
+    return -1;
+  }
+  static constexpr bool sound() {
+    for (int n = 0; n < N; ++n)
+      if (n > 0 && (at(0, n) == at(0, n - 1) || at(1, n) == at(1, n - 1))) return false;
+    // A's tiles 0 .. 5 are read again behind their last MFMA; B's loads are out before the barrier, A's before the state moves on
+    for (int n = 2 * (RA / 8); n < RA; ++n) {
+      const int tile = a_read(n) / (RA / 8);
+      if (at(0, RB + n) < 8 * tile + 8 || at(1, RB + n) - 64 < 8 * tile + 8) return false;
+    }
+    return load_slot(7) < BAR && load_slot(8) > BAR && load_slot(15) < 120 && at(0, N - 1) < 60 && at(1, N - 1) < 128;
+  }
+};
+static_assert(SlotPlan<8, 8>::sound() && SlotPlan<16, 8>::sound() && SlotPlan<16, 16>::sound(), "slot plan");
 
 // 64 lanes x 16 bytes from the buffer (per-lane byte offset voff, wave-uniform soff) to LDS bytes [lds + IMM,
 // lds + IMM + 1024) of the workgroup, lane l at + 16 l.  Lanes whose offset lies outside the descriptor deliver zeros.
@@ -153,7 +208,7 @@ RP_DEV void dtl_block(const GemmArgs& p, int blk, int gm = 0, int gn = 0) {
     } else {
       const int kr = 2 * (8 * wave + i) + (lane >> 5);
       const int pos = lane & 31;
-      const int gn = n0 + (((pos >> 2) ^ (kr & 3)) * 32) + (pos & 3) * 8;
+      const int gn = n0 + ((pos >> 1) ^ seg_swizzle(kr)) * 16 + (pos & 1) * 8;
       return gn < p.N ? (uint32_t)((long)kr * ldb + gn) * 2u : OOB;
     }
   };
@@ -168,7 +223,7 @@ RP_DEV void dtl_block(const GemmArgs& p, int blk, int gm = 0, int gn = 0) {
     } else {
       const int kr = 2 * (8 * wave + i) + (lane >> 5);
       const int pos = lane & 31;
-      const int gm = m0 + (((pos >> 2) ^ (kr & 3)) * 32) + (pos & 3) * 8;
+      const int gm = m0 + ((pos >> 1) ^ seg_swizzle(kr)) * 16 + (pos & 1) * 8;
       return gm < (first ? Mlim : p.M) ? (uint32_t)((long)kr * lda + gm) * 2u : OOB;
     }
   };
@@ -226,7 +281,7 @@ RP_DEV void dtl_block(const GemmArgs& p, int blk, int gm = 0, int gn = 0) {
       // Whatever the compiler reloads from scratch memory on this path counts in vmcnt like the loads above; left
       // pending, its own s_waitcnt before the first use of such a register would sit in the K loop and drain the
       // pipeline every tile.
-      __builtin_amdgcn_s_waitcnt(0x0f70);
+      __builtin_amdgcn_s_waitcnt(0x0070);
     }
     ld_soff = s < nk ? (uint32_t)ld_k0 * ld_kstepA : OOB;   // (from s, not from the flag: the scalar offset has to stay provably wave-uniform)
     ld_soffB = s < nk ? (uint32_t)ld_k0 * ld_kstepB : OOB;
@@ -244,7 +299,7 @@ RP_DEV void dtl_block(const GemmArgs& p, int blk, int gm = 0, int gn = 0) {
         vcA[i] |= TA ? mkr : ((i & 1) ? mk1 : mk0);
         vcB[i] |= TB ? mkr : ((i & 1) ? mk1 : mk0);
       }
-      __builtin_amdgcn_s_waitcnt(0x0f70);   // as at the end of the pair switch
+      __builtin_amdgcn_s_waitcnt(0x0070);   // as at the end of the pair switch
     }
     ld_k0 += BK;
   };
@@ -264,61 +319,60 @@ RP_DEV void dtl_block(const GemmArgs& p, int blk, int gm = 0, int gn = 0) {
     load_to_lds<i * 1024>(ld_ldsA, vcA[i], rcA, ld_soff);
   };
 
-  f32x16 acc[2][TM][TN];
+  // acc[i][j]: 16x16 tile (i, j) of the wave's 8 x 8
+  f32x4 acc[8][8];
 #pragma unroll
-  for (int h = 0; h < 2; ++h)
+  for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[h][i][j][v] = 0.f;
+    for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // fragment reads: lane -> row lr of a 32-row MFMA tile, data chunk 2*ks + lk, at chunk position chunk ^ ((lr >> 1) & 7).
-  // fkA[ks] / fkB[ks]: byte offset of the lane's chunk of step ks in the wave's first MFMA tile of a unit; MFMA tile i
-  // (j) lies another 4 KB further each.
-  const int s7 = (lr >> 1) & 7;
-  uint32_t fkA[4], fkB[4];
+  // Fragments: lane -> row lane % 16 of a tile, eight reduction indices from 8 (lane / 16) on of a 32-deep step, i.e. the 16-byte chunk
+  // 4 ks + lane / 16 at chunk position chunk ^ ((row >> 1) & 7).  fkA[ks] / fkB[ks]: byte offset of the lane's chunk of step ks in the
+  // wave's first tile of a unit; tile i (j) lies another 2 KB further each.  Grouped: blocks of 32 rows alternate between the wave rows.
+  // B's fragments have a set of registers per step; those of A are read again as soon as their eight MFMAs are through, but for the last
+  // two, which alternate.
+  const int r16 = lane & 15, g16 = lane >> 4;
+  uint32_t fkA[2], fkB[2];
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    fkA[ks] = (uint32_t)((wm * (GRP ? 32 : 128) + lr) * 128 + ((2 * ks + lk) ^ s7) * 16);
-    fkB[ks] = (uint32_t)((wn * 128 + lr) * 128 + ((2 * ks + lk) ^ s7) * 16);
+  for (int ks = 0; ks < 2; ++ks) {
+    const uint32_t ch = (uint32_t)((4 * ks + g16) ^ ((r16 >> 1) & 7)) * 16u;
+    fkA[ks] = (uint32_t)((wm * (GRP ? 32 : 128) + r16) * 128) + ch;
+    fkB[ks] = (uint32_t)((wn * 128 + r16) * 128) + ch;
   }
-  uint4 af[2][4], bfr[2][4];
-  auto read_a = [&](int set, uint32_t off, int i) { af[set][i] = *reinterpret_cast<const uint4*>(smem + off + i * (GRP ? 8192 : 4096)); };
-  auto read_b = [&](int set, uint32_t off, int j) { bfr[set][j] = *reinterpret_cast<const uint4*>(smem + off + j * 4096); };
-  // TB: a fragment of B is two transposing reads (reduction rows +0..3 and +4..7 of the lane's half of the 16-deep step).
-  // fkBt[j]: byte offset of the lane's first read of step 0 for MFMA tile column j of the wave: reduction row
-  // 8*lk + (l%16)/4, the tile column's segment moved by the row's swizzle, columns 16*((l/16)%2) + 4*(l%4) of the tile.
-  [[maybe_unused]] uint32_t fkBt[4];
-  if constexpr (TB) {
-    const int l16 = lane & 15, g16 = lane >> 4, c2 = l16 >> 2;
+  uint4 af[10], bfr[2][8];
+  // register of A's tile i in the steps of parity s
+  auto areg = [](int s, int i) constexpr { return i < 6 ? i : i + 2 * s; };
+  // A transposed operand's fragment is two transposing reads (reduction rows +0..3 and +4..7 of the lane's eight): byte offset of the
+  // lane's first read of step 0 for tile x of the operand -- reduction row 8 g16 + r16 / 4, the tile's segment moved by the row's
+  // swizzle (the same for both reads and both steps), columns 4 (r16 % 4) of the segment.
+  [[maybe_unused]] uint32_t fkBt[8], fkAt[8];
+  {
+    const int kr = 8 * g16 + (r16 >> 2);
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      fkBt[j] = (uint32_t)((8 * lk + c2) * 512 + (((wn * 4 + j) ^ c2) * 64) + 32 * (g16 & 1) + 8 * (l16 & 3));
+    for (int x = 0; x < 8; ++x) {
+      fkBt[x] = (uint32_t)(kr * 512 + ((wn * 8 + x) ^ seg_swizzle(kr)) * 32 + (r16 & 3) * 8);
+      fkAt[x] = (uint32_t)(kr * 512 + ((wm * 8 + x) ^ seg_swizzle(kr)) * 32 + (r16 & 3) * 8);
+    }
   }
-  [[maybe_unused]] uint32_t fkAt[4];
-  if constexpr (TA) {
-    const int l16 = lane & 15, g16 = lane >> 4, c2 = l16 >> 2;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      fkAt[i] = (uint32_t)((8 * lk + c2) * 512 + (((wm * 4 + i) ^ c2) * 64) + 32 * (g16 & 1) + 8 * (l16 & 3));
-  }
-  [[maybe_unused]] auto read_at = [&](int set, uint32_t off, int i, int half) {
+  auto read_tr = [&](uint4& f, uint32_t off, int half) __attribute__((always_inline)) {
     typedef short s16x4 __attribute__((ext_vector_type(4)));
     typedef __attribute__((address_space(3))) s16x4* lds_ptr;
     const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(smem + off + half * 2048));
     const uint2 u = __builtin_bit_cast(uint2, v);
-    if (half == 0) { af[set][i].x = u.x; af[set][i].y = u.y; }
-    else { af[set][i].z = u.x; af[set][i].w = u.y; }
+    if (half == 0) { f.x = u.x; f.y = u.y; }
+    else { f.z = u.x; f.w = u.y; }
   };
-  [[maybe_unused]] auto read_bt = [&](int set, uint32_t off, int j, int half) {   // off includes the step: + ks * 8192
-    typedef short s16x4 __attribute__((ext_vector_type(4)));
-    typedef __attribute__((address_space(3))) s16x4* lds_ptr;
-    const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(smem + off + half * 2048));
-    const uint2 u = __builtin_bit_cast(uint2, v);
-    if (half == 0) { bfr[set][j].x = u.x; bfr[set][j].y = u.y; }
-    else { bfr[set][j].z = u.x; bfr[set][j].w = u.y; }
+  // read number n (0 .. RB - 1) of B's fragments of a step into register set s, read number n of A's; ringA, ringB: the units' offsets
+  constexpr int RB = TB ? 16 : 8, RA = TA ? 16 : 8;
+  auto read_b = [&](auto stag, auto ntag, uint32_t ringB) __attribute__((always_inline)) {
+    constexpr int st = decltype(stag)::value, n = decltype(ntag)::value;
+    if constexpr (TB) read_tr(bfr[st][n >> 1], ringB + fkBt[n >> 1] + st * 16384, n & 1);
+    else bfr[st][n] = *reinterpret_cast<const uint4*>(smem + (ringB + fkB[st]) + n * 2048);
+  };
+  auto read_a = [&](auto stag, auto ntag, uint32_t ringA) __attribute__((always_inline)) {
+    constexpr int st = decltype(stag)::value, n = decltype(ntag)::value;
+    if constexpr (TA) read_tr(af[areg(st, n >> 1)], ringA + fkAt[n >> 1] + st * 16384, n & 1);
+    else af[areg(st, n)] = *reinterpret_cast<const uint4*>(smem + (ringA + fkA[st]) + (GRP ? (n >> 1) * 8192 + (n & 1) * 2048 : n * 2048));
   };
 
   // prologue: tiles 0 and 1 set out (in the order of the K loop: B, then A); tile 0 has landed everywhere after the barrier
@@ -328,203 +382,68 @@ RP_DEV void dtl_block(const GemmArgs& p, int blk, int gm = 0, int gn = 0) {
     issue_b(IC<0>{}); issue_b(IC<1>{}); issue_b(IC<2>{}); issue_b(IC<3>{}); issue_b(IC<4>{}); issue_b(IC<5>{}); issue_b(IC<6>{}); issue_b(IC<7>{});
     issue_a(IC<0>{}); issue_a(IC<1>{}); issue_a(IC<2>{}); issue_a(IC<3>{}); issue_a(IC<4>{}); issue_a(IC<5>{}); issue_a(IC<6>{}); issue_a(IC<7>{});
   }
-  if constexpr (!TB) tile_setup(2);   // (the loops for transposed operands set the state of tile t+2 up in their first slots)
+  tile_setup(2);
   __builtin_amdgcn_s_waitcnt(0x0f70 | (16 & 15) | ((16 >> 4) << 14));   // vmcnt(16)
   __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if constexpr (!TA) read_a(0, UNIT_BYTES + fkA[0], i);
-    else { read_at(0, UNIT_BYTES + fkAt[i], i, 0); read_at(0, UNIT_BYTES + fkAt[i], i, 1); }
-  }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    if constexpr (!TB) read_b(0, fkB[0], j);
-    else { read_bt(0, fkBt[j], j, 0); read_bt(0, fkBt[j], j, 1); }
-  }
+  for_seq([&](auto n) __attribute__((always_inline)) { read_b(IC<0>{}, n, 0u); }, std::make_integer_sequence<int, RB>{});
+  for_seq([&](auto n) __attribute__((always_inline)) { read_a(IC<0>{}, n, (uint32_t)UNIT_BYTES); }, std::make_integer_sequence<int, RA>{});
 
-  // Slot plan of tile t (64 slots of one MFMA; 16-deep step ks = slots 16 ks .. 16 ks + 15, fragment set ks & 1).  A slot
-  // holds at most one memory instruction: with one wave per SIMD whatever a slot issues beside its MFMA has to fit into
-  // the 32 cycles the MFMA runs, and a load or a fragment read that meets a busy texture unit or LDS queue already
-  // takes most of them.
-  //   slots 16 ks + 0..7   the fragment reads of step ks + 1 (of step 0 of tile t+1 for ks = 3), one per slot
-  //   slots 8..15, 24..31  every other one: the loads of B of tile t+2; its ring slot (A of tile t-1) is free since
-  //                        the barrier of tile t-1
-  //   slot  BAR = 44       every read of this tile has returned.  vmcnt(8): the wave's loads of tile t+1 have landed
-  //                        (those of B of tile t+2 may be in flight); barrier: tile t+1 is complete in LDS, this
-  //                        tile's two ring slots are free
-  //   slots 45..47, 56..60 the loads of A of tile t+2, into the slot of B of this tile
-  //   slots 61, 62         the state of the loads of tile t+3
-  constexpr int BAR = 44;
-  auto main_loop = [&](auto wtag, auto nitag) __attribute__((always_inline)) {
-    constexpr int W = decltype(wtag)::value, NB = decltype(nitag)::value;   // NB: blocks of 32 rows
-    uint32_t ring = 0;                 // ring slot of B of the current tile; A follows
-    uint32_t curA = UNIT_BYTES, curB = 0, nA = 0;
-    uint32_t fa = curA + fkA[1], fb = curB + fkB[1];   // offsets of the reads of the coming step
+  // Slot plan of tile t: 128 slots of one MFMA, step s = slots 64 s .. 64 s + 63, the eight MFMAs of A's tile i in slots 8 i .. 8 i + 7 of a
+  // step.  With one wave per SIMD whatever a slot issues beside its MFMA has to fit into the 16 cycles that runs; a slot holds at most
+  // one memory instruction, and the reads and loads are spread evenly.
+  //   step 0, slots 2 .. 57      the fragment reads of step 1: B's, then A's tiles 6, 7 (which alternate their registers), 0, 1, .. 5
+  //   slots 4 .. 60              the loads of B of tile t+2; its ring slot (A of tile t-1) is free since the barrier of tile t-1
+  //   slot  BAR = 74             every read of this tile has returned.  vmcnt(8): the wave's loads of tile t+1 have landed (those of B of tile
+  //                              t+2 may be in flight); barrier: tile t+1 is complete in LDS, this tile's two ring slots are free
+  //   slots 76 .. 127            the reads of step 0 of tile t+1
+  //   slots 77 .. 112            the loads of A of tile t+2, into the slot of B of this tile
+  //   slots 120, 123             the state of the loads of tile t+3
+  auto main_loop = [&](auto nitag) __attribute__((always_inline)) {
+    constexpr int NB = decltype(nitag)::value;   // blocks of 32 rows
+    using P = SlotPlan<RB, RA>;
+    uint32_t ringB = 0, ringA = UNIT_BYTES;      // units of the tile whose fragments are read
     for (int t = 0; t < nk; ++t) {
       auto slot = [&](auto sltag) __attribute__((always_inline)) {
-        constexpr int sl = decltype(sltag)::value;
-        constexpr int ks = sl >> 4, I = sl & 15, i = I >> 2, jj = I & 3, set = ks & 1;
-        if constexpr (sl == BAR) {
+        constexpr int sl = decltype(sltag)::value, st = sl >> 6, i = (sl & 63) >> 3, j = sl & 7;
+        if constexpr (sl == P::BAR) {
           __builtin_amdgcn_s_waitcnt(0x0f70 | 8);
           __syncthreads();
         }
-        // one wait per step for all of its fragments (read eight slots or more ago) instead of one per fragment
-        if constexpr (I == 0 && ks < 3) __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-        if constexpr (i < NB) acc[jj >> 1][i][jj & 1] = mfma32(af[set][i], bfr[set][jj], acc[jj >> 1][i][jj & 1]);
-        if constexpr (I < NB) read_a(set ^ 1, fa, I);
-        if constexpr (I >= 4 && I < 8) read_b(set ^ 1, fb, I - 4);
-        // address arithmetic for the reads of the coming step, in slots without a memory instruction
-        if constexpr (sl == 8 + (W & 1)) fa = curA + fkA[2];
-        if constexpr (sl == 10 + (W & 1)) fb = curB + fkB[2];
-        if constexpr (sl == 24 + (W & 1)) fa = curA + fkA[3];
-        if constexpr (sl == 26 + (W & 1)) fb = curB + fkB[3];
-        if constexpr (sl == 28 + (W & 1)) ring = ring + 2 * UNIT_BYTES >= (uint32_t)DTL_SMEM ? ring + 2 * UNIT_BYTES - DTL_SMEM : ring + 2 * UNIT_BYTES;
-        if constexpr (sl == 30 + (W & 1)) nA = ring + UNIT_BYTES == (uint32_t)DTL_SMEM ? 0u : ring + UNIT_BYTES;
-        if constexpr (sl == 40) fa = nA + fkA[0];
-        if constexpr (sl == 41) fb = ring + fkB[0];
-        if constexpr (sl == 63) { fa = nA + fkA[1]; fb = ring + fkB[1]; }
-        if constexpr ((sl < 32) && (I >= 8) && ((I & 1) != (W & 1))) issue_b(IC<((ks * 8 + I - 8) >> 1)>{});
-        if constexpr (sl >= 45 && sl < 48) issue_a(IC<(sl - 45)>{});
-        if constexpr (sl >= 56 && sl < 61) issue_a(IC<(sl - 56 + 3)>{});
-        if constexpr (sl == 61) setup_pair(t + 3);
-        if constexpr (sl == 62) { setup_mask(); setup_lds(); }
-        __builtin_amdgcn_sched_barrier(0);
-      };
-      for_seq(slot, std::make_integer_sequence<int, 64>{});
-      curB = ring;
-      curA = nA;
-    }
-  };
-  // The same for TB.  A step reads twelve fragments' worth of instructions (four for A, two each for the four of B), so
-  // only four slots of a step are left for loads and none are empty:
-  //   slots 16 ks + 0..3, 4..11  the fragment reads of A and B of step ks + 1 (of step 0 of tile t+1 for ks = 3)
-  //   slots 1, 2                 the state of the loads of tile t+2
-  //   slots 12..15, 28..31       the loads of B of tile t+2
-  //   slot  46                   vmcnt(8); barrier
-  //   slots 47, 53, 55, 57, 60..63  the loads of A of tile t+2
-  [[maybe_unused]] auto main_loop_tb = [&](auto nitag) __attribute__((always_inline)) {
-    constexpr int BARB = 46, NB = decltype(nitag)::value;
-    uint32_t ring = 0;
-    uint32_t curA = UNIT_BYTES, nA = 0;
-    uint32_t fa = curA + fkA[1];
-    uint32_t fbj[4], nfbj[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) { fbj[j] = fkBt[j]; nfbj[j] = 0; }
-    for (int t = 0; t < nk; ++t) {
-      auto slot = [&](auto sltag) __attribute__((always_inline)) {
-        constexpr int sl = decltype(sltag)::value;
-        constexpr int ks = sl >> 4, I = sl & 15, i = I >> 2, jj = I & 3, set = ks & 1;
-        if constexpr (sl == BARB) {
-          __builtin_amdgcn_s_waitcnt(0x0f70 | 8);
-          __syncthreads();
-        }
-        if constexpr (I == 0 && ks < 3) __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-        if constexpr (i < NB) acc[jj >> 1][i][jj & 1] = mfma32(af[set][i], bfr[set][jj], acc[jj >> 1][i][jj & 1]);
-        if constexpr (I < NB) read_a(set ^ 1, fa, I);
-        if constexpr (I >= 4 && I < 12) {
-          constexpr int j = (I - 4) >> 1, half = (I - 4) & 1;
-          if constexpr (ks < 3) read_bt(set ^ 1, fbj[j] + (ks + 1) * 8192, j, half);
-          else read_bt(0, nfbj[j], j, half);
-        }
-        if constexpr (sl == 1) setup_pair(t + 2);
-        if constexpr (sl == 2) { setup_mask(); setup_lds(); }
-        if constexpr (sl == 13) fa = curA + fkA[2];
-        if constexpr (sl == 14) ring = ring + 2 * UNIT_BYTES >= (uint32_t)DTL_SMEM ? ring + 2 * UNIT_BYTES - DTL_SMEM : ring + 2 * UNIT_BYTES;
-        if constexpr (sl == 15) nA = ring + UNIT_BYTES == (uint32_t)DTL_SMEM ? 0u : ring + UNIT_BYTES;
-        if constexpr (sl == 29) fa = curA + fkA[3];
-        if constexpr (sl == 44) { nfbj[0] = ring + fkBt[0]; nfbj[1] = ring + fkBt[1]; }
-        if constexpr (sl == 45) { nfbj[2] = ring + fkBt[2]; nfbj[3] = ring + fkBt[3]; fa = nA + fkA[0]; }
-        if constexpr (sl == 59) fa = nA + fkA[1];
-        if constexpr (sl >= 12 && sl < 16) issue_b(IC<(sl - 12)>{});
-        if constexpr (sl >= 28 && sl < 32) issue_b(IC<(sl - 28 + 4)>{});
-        if constexpr (sl == 47) issue_a(IC<0>{});
-        if constexpr (sl == 53) issue_a(IC<1>{});
-        if constexpr (sl == 55) issue_a(IC<2>{});
-        if constexpr (sl == 57) issue_a(IC<3>{});
-        if constexpr (sl >= 60) issue_a(IC<(sl >= 60 ? sl - 60 + 4 : 0)>{});
-        __builtin_amdgcn_sched_barrier(0);
-      };
-      for_seq(slot, std::make_integer_sequence<int, 64>{});
-      curA = nA;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) fbj[j] = nfbj[j];
-    }
-  };
-  // TN: sixteen transposing reads per step, one per slot (two per slot in step 2, so that the tile's last read is
-  // five slots old at the barrier), the loads on top of them:
-  //   slots 1, 2                    the state of the loads of tile t+2
-  //   slots 3, 7, .., 31            the loads of B of tile t+2
-  //   slots 32..39                  the reads of step 3, two per slot;  40..43 the read offsets of tile t+1
-  //   slot  44                      vmcnt(8); barrier
-  //   slots 45, 46, 47, 51, 55, 59, 62, 63   the loads of A of tile t+2
-  //   slots 48..63                  the reads of step 0 of tile t+1
-  [[maybe_unused]] auto main_loop_tn = [&]() __attribute__((always_inline)) {
-    constexpr int BARB = 44;
-    uint32_t ring = 0, nA = 0;
-    uint32_t faj[4], fbj[4], nfaj[4], nfbj[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) { faj[j] = UNIT_BYTES + fkAt[j]; fbj[j] = fkBt[j]; nfaj[j] = 0; nfbj[j] = 0; }
-    for (int t = 0; t < nk; ++t) {
-      auto slot = [&](auto sltag) __attribute__((always_inline)) {
-        constexpr int sl = decltype(sltag)::value;
-        constexpr int ks = sl >> 4, I = sl & 15, i = I >> 2, jj = I & 3, set = ks & 1;
-        if constexpr (sl == BARB) {
-          __builtin_amdgcn_s_waitcnt(0x0f70 | 8);
-          __syncthreads();
-        }
-        if constexpr (I == 0 && ks < 3) __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-        acc[jj >> 1][i][jj & 1] = mfma32(af[set][i], bfr[set][jj], acc[jj >> 1][i][jj & 1]);
-        if constexpr (ks < 2 || ks == 3) {   // one read per slot: A fragments in slots 0..7, B in 8..15
-          constexpr int f = (I & 7) >> 1, half = I & 1;
-          if constexpr (ks < 2) {
-            if constexpr (I < 8) read_at(set ^ 1, faj[f] + (ks + 1) * 8192, f, half);
-            else read_bt(set ^ 1, fbj[f] + (ks + 1) * 8192, f, half);
-          } else {
-            if constexpr (I < 8) read_at(0, nfaj[f], f, half);
-            else read_bt(0, nfbj[f], f, half);
+        if constexpr (i < 2 * NB) mfma16_in_place(acc[i][j], af[areg(st, i)], bfr[st][j]);
+        constexpr int rd = P::read(sl);
+        if constexpr (rd >= 0) {
+          constexpr int rs = sl < 64 ? 1 : 0;    // the step whose fragments these are
+          if constexpr (rd < RB) read_b(IC<rs>{}, IC<rd>{}, ringB);
+          else {
+            constexpr int n = P::a_read(rd - RB), tile = TA ? n >> 1 : n;
+            if constexpr (tile < 2 * NB) read_a(IC<rs>{}, IC<n>{}, ringA);
           }
-        } else if constexpr (I < 8) {        // step 2: the reads of step 3, two per slot
-          constexpr int f = I >> 1, half = I & 1;
-          read_at(set ^ 1, faj[f] + 3 * 8192, f, half);
-          read_bt(set ^ 1, fbj[f] + 3 * 8192, f, half);
         }
-        if constexpr (sl == 1) setup_pair(t + 2);
-        if constexpr (sl == 2) { setup_mask(); setup_lds(); }
-        if constexpr (sl == 13) ring = ring + 2 * UNIT_BYTES >= (uint32_t)DTL_SMEM ? ring + 2 * UNIT_BYTES - DTL_SMEM : ring + 2 * UNIT_BYTES;
-        if constexpr (sl == 14) nA = ring + UNIT_BYTES == (uint32_t)DTL_SMEM ? 0u : ring + UNIT_BYTES;
-        if constexpr (sl >= 40 && sl < 44) { nfaj[sl - 40] = nA + fkAt[sl - 40]; nfbj[sl - 40] = ring + fkBt[sl - 40]; }
-        if constexpr (sl < 32 && (sl & 3) == 3) issue_b(IC<(sl >> 2)>{});
-        if constexpr (sl >= 45 && sl < 48) issue_a(IC<(sl - 45)>{});
-        if constexpr (sl == 51) issue_a(IC<3>{});
-        if constexpr (sl == 55) issue_a(IC<4>{});
-        if constexpr (sl == 59) issue_a(IC<5>{});
-        if constexpr (sl == 62) issue_a(IC<6>{});
-        if constexpr (sl == 63) issue_a(IC<7>{});
+        if constexpr (sl == 66) {
+          ringB = ringB + 2 * UNIT_BYTES >= (uint32_t)DTL_SMEM ? ringB + 2 * UNIT_BYTES - DTL_SMEM : ringB + 2 * UNIT_BYTES;
+        }
+        if constexpr (sl == 68) {
+          ringA = ringA + 2 * UNIT_BYTES >= (uint32_t)DTL_SMEM ? ringA + 2 * UNIT_BYTES - DTL_SMEM : ringA + 2 * UNIT_BYTES;
+        }
+        constexpr int ld = P::load(sl);
+        if constexpr (ld >= 0 && ld < 8) issue_b(IC<ld>{});
+        if constexpr (ld >= 8) issue_a(IC<ld - 8>{});
+        if constexpr (sl == 120) setup_pair(t + 3);
+        if constexpr (sl == 123) { setup_mask(); setup_lds(); }
         __builtin_amdgcn_sched_barrier(0);
       };
-      for_seq(slot, std::make_integer_sequence<int, 64>{});
-#pragma unroll
-      for (int j = 0; j < 4; ++j) { faj[j] = nfaj[j]; fbj[j] = nfbj[j]; }
+      for_seq(slot, std::make_integer_sequence<int, 128>{});
     }
   };
-  if constexpr (TA) {
-    main_loop_tn();
-  } else {
-    // (one plan for all four waves: staggering the waves' load slots against each other measured 0.5-1.5 % slower)
-    auto run = [&](auto nitag) __attribute__((always_inline)) {
-      if constexpr (TB) main_loop_tb(nitag);
-      else main_loop(IC<1>{}, nitag);
-    };
-    if constexpr (GRP) {
-      switch (NI) {
-        case 1: run(IC<1>{}); break;
-        case 2: run(IC<2>{}); break;
-        case 3: run(IC<3>{}); break;
-        default: run(IC<4>{});
-      }
-    } else {
-      run(IC<4>{});
+  if constexpr (GRP) {
+    switch (NI) {
+      case 1: main_loop(IC<1>{}); break;
+      case 2: main_loop(IC<2>{}); break;
+      case 3: main_loop(IC<3>{}); break;
+      default: main_loop(IC<4>{});
     }
+  } else {
+    main_loop(IC<4>{});
   }
   __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): the empty loads past the end write LDS too
   __syncthreads();                      // every wave is done with the operand stages: the epilogue reuses the LDS
@@ -539,7 +458,7 @@ RP_DEV void dtl_block(const GemmArgs& p, int blk, int gm = 0, int gn = 0) {
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(half[i][j][v]) : "a"(acc[h][i][j][v]));
+        for (int v = 0; v < 16; ++v) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(half[i][j][v]) : "a"(acc[2 * i + (v >> 3)][4 * h + 2 * j + ((v >> 2) & 1)][v & 3]));
   };
   asm volatile("s_nop 7\n\ts_nop 7");   // the last MFMA has long retired (a barrier ago); the copies are invisible to the hazard checks
   constexpr int IS = GRP ? 64 : 32;      // a wave's blocks of 32 rows: every other one, or consecutive
@@ -551,10 +470,10 @@ RP_DEV void dtl_block(const GemmArgs& p, int blk, int gm = 0, int gn = 0) {
     q.epi = EPI_BF16;
     const int gcol = (n0 >> 1) + wn * 64;
     fetch(1);
-    epilogue<IS, true>(q, Mlim, half, smem, wave, lane, wrow, gcol + fold, part_row);
+    epilogue<IS, true, true>(q, Mlim, half, smem, wave, lane, wrow, gcol + fold, part_row);
     q.N = fold;     // the last tile's gate columns end where the up columns begin
     fetch(0);
-    epilogue<IS, true>(q, Mlim, half, smem, wave, lane, wrow, gcol, part_row);
+    epilogue<IS, true, true>(q, Mlim, half, smem, wave, lane, wrow, gcol, part_row);
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -562,19 +481,19 @@ RP_DEV void dtl_block(const GemmArgs& p, int blk, int gm = 0, int gn = 0) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           float up;
-          asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(up) : "a"(acc[1][i][j][v]));
+          asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(up) : "a"(acc[2 * i + (v >> 3)][4 + 2 * j + ((v >> 2) & 1)][v & 3]));
           const float g = bf16_bits_to_f32(f32_to_bf16_bits(half[i][j][v])), u = bf16_bits_to_f32(f32_to_bf16_bits(up));
           half[i][j][v] = silu_f32(g) * u;
         }
     q.C = p.C2;
     q.ldc = p.ldc2;
-    epilogue<IS, true>(q, Mlim, half, smem, wave, lane, wrow, gcol, part_row);
+    epilogue<IS, true, true>(q, Mlim, half, smem, wave, lane, wrow, gcol, part_row);
     return;
   }
   fetch(0);
-  epilogue<IS, true>(p, Mlim, half, smem, wave, lane, wrow, n0 + wn * 128, part_row);
+  epilogue<IS, true, true>(p, Mlim, half, smem, wave, lane, wrow, n0 + wn * 128, part_row);
   fetch(1);
-  epilogue<IS, true>(p, Mlim, half, smem, wave, lane, wrow, n0 + wn * 128 + 64, part_row);
+  epilogue<IS, true, true>(p, Mlim, half, smem, wave, lane, wrow, n0 + wn * 128 + 64, part_row);
 }
 
 // The entry of the table and the tile column of a workgroup of a grouped product (the table's length is known on the device only:

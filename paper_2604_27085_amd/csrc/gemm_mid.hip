@@ -303,7 +303,7 @@ RP_DEV void mid_block(const GemmArgs& p, int blk, int slice, int nslices) {
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) d[acc_row(i, v) * ST_LD + j * 32] = acc[i][j][v];
+        for (int v = 0; v < 16; ++v) d[AccMap<false>::acc_row(i, v) * ST_LD + j * 32] = acc[i][j][v];
   }
   __syncthreads();
 
