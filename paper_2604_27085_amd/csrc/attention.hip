@@ -1,20 +1,25 @@
 // Causal grouped-query attention on the gfx950 matrix cores, flash style: no s x s matrix leaves the CU, except
 // that a backward with room for it keeps dS in bf16 (see attn_ds_block).
 //
-// All three kernels use v_mfma_f32_32x32x16_bf16 with the score tile computed TRANSPOSED relative to the row that is
-// being normalised: the 32x32 accumulator layout gives every lane one column and 16 rows, so with queries (forward,
-// dQ) as columns the softmax reductions are in-lane plus one exchange with lane^32, and the probabilities already sit
-// in the register layout the next MFMA wants as its B operand.  Within a 16-deep step that layout holds, for lane
-// half h, the reduction indices {4h..4h+3, 8+4h..8+4h+3}; the A operand of the same MFMA is read from LDS in exactly
-// that order.  An operand whose reduction index is contiguous in memory (K for Q.K^T, V for dO.V^T, Q and dO in the
-// score products of the dK/dV kernel) is read with plain 16-byte LDS loads from a [rows][D + 8] tile; an operand
-// whose reduction index is the row index of the tile (V for P.V, K for dS.K, Q and dO for dK/dV) is read with the
-// transposing LDS load from a [rows][D + 32] tile.  A tile needed both ways (K in the dQ kernel, Q and dO in the dK/dV
-// kernels) has the row stride D + 24, which serves both kinds of reads (the transposing ones with some bank conflicts), and is
-// stored once; nothing is transposed in registers.  Global loads are 16-byte buffer loads whose descriptor ends with the
+// All kernels use v_mfma_f32_16x16x32_bf16 with the score tile computed TRANSPOSED relative to the row that is
+// being normalised: the accumulator layout gives every lane one column and four rows of a 16x16 tile, so with queries (forward,
+// dQ) as columns the softmax reductions are in-lane plus an exchange between the four lane groups (lane / 16), and the probabilities
+// already sit in the register layout the next MFMA wants as its B operand.  Two 16-row tiles make one 32-deep step; within it that
+// layout holds, for lane group g, the reduction indices {4g..4g+3, 16+4g..16+4g+3}; the A operand of the same MFMA is read from LDS in
+// exactly that order.  A wave owns 32 columns (two column tiles), so every fragment feeds two MFMAs.  An operand whose reduction index
+// is contiguous in memory (K for Q.K^T, V for dO.V^T, Q and dO in the score products of the dK/dV kernel) is read with plain 16-byte
+// LDS loads; an operand whose reduction index is the row index of the tile (V for P.V, K for dS.K, Q and dO for dK/dV) is read with
+// the transposing LDS load; nothing is transposed in registers.  All tiles have the row stride D + 16, which serves both kinds of reads
+// without bank conflicts.  Global loads are 16-byte buffer loads whose descriptor ends with the
 // sequence, so rows past the end read as zero without a branch.
+// Against v_mfma_f32_32x32x16_bf16 with strides of D + 8, D + 24 and D + 32, same box, us: backward (dQ by recomputation) 8192 x 32 heads
+// of 128 1802 -> 1666, 4096 x 16 282 -> 263, 2 x 508 x 32 53.5 -> 52.0, 3 x 1500 x 64 heads of 64 260 -> 235; forward 8192 x 32 509 -> 494,
+// 4096 x 16 91.2 -> 90.3, 3 x 1500 x 64 of 64 78.3 -> 76.3, but 1000 x 16 24.0 -> 25.2 and 512 x 32 of 64 9.9 -> 10.9.  The strides are most of
+// it (backward with D + 24 1802 -> 1735); what starts the dK/dV products (stat_start) saves an MFMA in nine of their score phase.  The
+// score products of the next key tile between the exponentials of this one (in slots that the compiler keeps, no spills) are 3 % slower in
+// the forward kernel of eight waves: what bounds it is the issue of the vector instructions, not a wave's serial chain.
 //
-//   forward : workgroup = NW waves x 32*QT queries of one head, loop over 64-key tiles up to the diagonal; NW = 8 (one
+//   forward : workgroup = NW waves x 32 queries of one head, loop over 64-key tiles up to the diagonal; NW = 8 (one
 //             workgroup per CU, two sets of K/V tiles, one barrier per tile) when the grid is large enough, else 4
 //   dQ      : same decomposition; recomputes S^T and dP^T, accumulates dQ^T, and works out delta = rowsum(dO * O) for itself and
 //             for dK/dV, which runs behind it; with kept dS it is a product of gemm_mid.hip behind dK/dV instead
@@ -84,13 +89,17 @@ RP_DEV uint4 buf_load16(rsrc_t r, uint32_t voff) {
 }
 
 // Softmax statistics of a 64-query tile for the dK/dV kernels, one per lane: wave 0 fetches lse, wave 1 delta.  The load is only
-// issued here; what the score products take is worked out when the tile is stored to LDS (stat_chunk), a tile later.  (Worked out
+// issued here; what the score products take is worked out when the tile is stored to LDS (stat_start), a tile later.  (Worked out
 // where it is loaded, it makes the two waves wait for memory in every tile and the others for them: dK/dV of 8192 tokens, 32 heads
 // of 128: 1252 -> 1109 us; 4096 x 16 heads 172 -> 162; 2048 x 64 188 -> 169.)
 RP_DEV rsrc_t stat_rsrc(const float* lse, const float* delta, int wave, long head, int seq) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(wave == 0 ? lse : delta) + head * seq, 0, seq * 4, 0x00020000);
 }
 RP_DEV float stat_load(rsrc_t r, int q) { return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, q * 4, 0, 0)); }
+
+// Row stride of a tile in LDS (elements): 8 banks past a multiple of 64, so that neither the 16-byte reads of 16 rows by four lane groups nor
+// the transposing ones (32 lanes a phase: eight rows of 32 bytes) meet on a bank.
+constexpr int tile_ld(int d) { return d + 16; }
 
 // ---- 64 x D tile: global -> registers -> LDS -----------------------------------------------------------------
 template <int D, int NT>
@@ -116,36 +125,42 @@ struct Tile64 {
 };
 
 // A-operand fragment from a [64][LD] tile whose rows are the reduction index (keys or queries) and whose columns are
-// the MFMA rows: the 8 values are tile rows {16g + 4h + e, 16g + 8 + 4h + e}, e = 0..3, at column x -- the order in
-// which the 32x32 accumulator of the score tile holds them.  base = S + (4h + (l%16)/4)*LD + 16*((l/16)&1) + 4*(l%4).
+// the MFMA rows: the 8 values of lane group g = lane / 16 are tile rows {4g + e, 16 + 4g + e}, e = 0..3, at column lane % 16 -- the
+// order in which two 16-row tiles of scores hold them.  base = S + tr_base(lane) + first row * LD + first column.
 template <int LD>
-RP_DEV uint4 read_frag_tr(const bf16* base, int g, int x_off) {
+RP_DEV uint4 read_frag_tr(const bf16* base) {
   typedef short s16x4 __attribute__((ext_vector_type(4)));
   typedef __attribute__((address_space(3))) s16x4* lds_ptr;
-  const bf16* q = base + 16 * g * LD + x_off;
-  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(q));
-  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(q + 8 * LD));
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(base));
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(base + 16 * LD));
   const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
   return make_uint4(l2.x, l2.y, h2.x, h2.y);
 }
 template <int LD>
 RP_DEV int tr_base(int lane) {
-  const int lk = lane >> 5, l16 = lane & 15, g16 = lane >> 4;
-  return (4 * lk + (l16 >> 2)) * LD + 16 * (g16 & 1) + 4 * (l16 & 3);
+  return (4 * (lane >> 4) + ((lane & 15) >> 2)) * LD + 4 * (lane & 3);
 }
 
-RP_DEV uint4 pack_frag(const f32x16& s, int off) {
-  return make_uint4(pack_bf16x2(s[off + 0], s[off + 1]), pack_bf16x2(s[off + 2], s[off + 3]),
-                    pack_bf16x2(s[off + 4], s[off + 5]), pack_bf16x2(s[off + 6], s[off + 7]));
+// Two 16-row score tiles, one above the other, as the B operand of the next product: 32 reduction indices in the order of read_frag_tr.
+RP_DEV uint4 pack_frag(const f32x4& a, const f32x4& b) {
+  return make_uint4(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(b[0], b[1]), pack_bf16x2(b[2], b[3]));
 }
 
-// max over lanes l and l ^ 32, in the vector unit: the exchange through LDS is a round trip of the wave in every key tile.  Forward of
-// 8192 tokens, 64 heads of 64: 702 -> 673 us (with the mask test on one limit per lane); the eight-wave kernel, whose waves pair up
-// around that wait, is 4 % slower with it (521 -> 542) and keeps the exchange
-RP_DEV float half_max(float x) {
-  const uint32_t u = __float_as_uint(x);
-  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+// Maxima of two columns over the four lanes l % 16 that hold each, in every lane, with vector instructions only: the exchange through
+// LDS is a round trip of the wave in every key tile.
+RP_DEV void column_max2(float& x, float& y) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  const uint32_t m = __float_as_uint(fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1])));     // x in the lower half of the wave, y in the upper
+  const auto c = __builtin_amdgcn_permlane16_swap(m, m, false, false);
+  const uint32_t n = __float_as_uint(fmaxf(__uint_as_float(c[0]), __uint_as_float(c[1])));
+  const auto d = __builtin_amdgcn_permlane32_swap(n, n, false, false);
+  x = __uint_as_float(d[0]);
+  y = __uint_as_float(d[1]);
+}
+// Sum over the four lanes that hold a column.
+RP_DEV float column_sum(float x) {
+  x += __shfl_xor(x, 16, 64);
+  return x + __shfl_xor(x, 32, 64);
 }
 RP_DEV float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -158,37 +173,25 @@ RP_DEV float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 #define MFMA_PHASE_BEGIN() __builtin_amdgcn_s_setprio(1)
 #define MFMA_PHASE_END() __builtin_amdgcn_s_setprio(0)
 
-// x as the sum of three bf16 numbers (most significant first) in the first three slots of an MFMA operand chunk, zeros
-// in the other five: 24 mantissa bits survive, so an MFMA step against ones adds x to an fp32 accumulator exactly
-// enough for a softmax exponent.
-RP_DEV uint4 split3(float x) {
-  const uint32_t h = f32_to_bf16_bits(x);
-  const float r1 = x - bf16_bits_to_f32(h);
-  const uint32_t m = f32_to_bf16_bits(r1);
-  const uint32_t l = f32_to_bf16_bits(r1 - bf16_bits_to_f32(m));
-  return make_uint4(h | (m << 16), l, 0u, 0u);
+// What the products of the dK/dV kernels start from for a query (wave 0: -lse / scale, wave 1: -delta; rows of the score tiles are
+// queries, so a lane's four rows of a tile are four consecutive numbers: one 16-byte LDS read is the accumulators' first value, and the
+// tiles come out as q.k - lse/scale and dO.v - delta); padded query rows get P = exp(-3e4 scale) = 0.
+RP_DEV float stat_start(float raw, int wave, bool in, float scale) {
+  return wave == 0 ? (in ? -raw / scale : -3.0e4f) : (in ? -raw : 0.f);
 }
-// The pad chunk of a Q row (wave 0: -lse / scale) or dO row (wave 1: -delta); padded query rows get P = exp(-3e4 scale) = 0.
-RP_DEV uint4 stat_chunk(float raw, int wave, bool in, float scale) {
-  return split3(wave == 0 ? (in ? -raw / scale : -3.0e4f) : (in ? -raw : 0.f));
-}
-// The other operand of that step: ones in the same three slots for the lanes that hold reduction indices 0..7.
-RP_DEV uint4 ones3(int lk) { return lk == 0 ? make_uint4(0x3F803F80u, 0x00003F80u, 0u, 0u) : make_uint4(0u, 0u, 0u, 0u); }
 
-// Writes a wave's 32 x D transposed accumulator (columns = the wave's 32 rows of the output) through LDS to global.
+// Writes a wave's 32 x D transposed accumulator (16x16 tiles; columns = the wave's 32 rows of the output) through LDS to global.
 template <int D>
-RP_DEV void store_acc_T(const f32x16 (&acc)[D / 32], float mul, bf16* stage /* [32][D+8] */, bf16* __restrict__ out,
+RP_DEV void store_acc_T(const f32x4 (&acc)[D / 16][2], const float (&mul)[2], bf16* stage /* [32][D+8] */, bf16* __restrict__ out,
                         long ld, int row0, int nrows, int lane) {
-  const int lr = lane & 31, lk = lane >> 5;
+  const int lr = lane & 15, lg = lane >> 4;
 #pragma unroll
-  for (int dt = 0; dt < D / 32; ++dt)
+  for (int dt = 0; dt < D / 16; ++dt)
 #pragma unroll
-    for (int vg = 0; vg < 4; ++vg) {
-      const int dd = 32 * dt + 8 * vg + 4 * lk;
-      *reinterpret_cast<uint2*>(stage + lr * (D + 8) + dd) =
-          make_uint2(pack_bf16x2(acc[dt][4 * vg] * mul, acc[dt][4 * vg + 1] * mul),
-                     pack_bf16x2(acc[dt][4 * vg + 2] * mul, acc[dt][4 * vg + 3] * mul));
-    }
+    for (int c = 0; c < 2; ++c)
+      *reinterpret_cast<uint2*>(stage + (16 * c + lr) * (D + 8) + 16 * dt + 4 * lg) =
+          make_uint2(pack_bf16x2(acc[dt][c][0] * mul[c], acc[dt][c][1] * mul[c]),
+                     pack_bf16x2(acc[dt][c][2] * mul[c], acc[dt][c][3] * mul[c]));
   __syncthreads();
 #pragma unroll
   for (int it = 0; it < (32 * (D / 8)) / 64; ++it) {
@@ -203,15 +206,15 @@ RP_DEV void store_acc_T(const f32x16 (&acc)[D / 32], float mul, bf16* stage /* [
 
 // Same for an fp32 destination; stage is [32][D + 4] floats per wave.
 template <int D>
-RP_DEV void store_acc_T_f32(const f32x16 (&acc)[D / 32], float mul, float* stage, float* __restrict__ out, long ld,
+RP_DEV void store_acc_T_f32(const f32x4 (&acc)[D / 16][2], float mul, float* stage, float* __restrict__ out, long ld,
                             int row0, int nrows, int lane) {
-  const int lr = lane & 31, lk = lane >> 5;
+  const int lr = lane & 15, lg = lane >> 4;
 #pragma unroll
-  for (int dt = 0; dt < D / 32; ++dt)
+  for (int dt = 0; dt < D / 16; ++dt)
 #pragma unroll
-    for (int vg = 0; vg < 4; ++vg)
-      *reinterpret_cast<float4*>(stage + lr * (D + 4) + 32 * dt + 8 * vg + 4 * lk) =
-          make_float4(acc[dt][4 * vg] * mul, acc[dt][4 * vg + 1] * mul, acc[dt][4 * vg + 2] * mul, acc[dt][4 * vg + 3] * mul);
+    for (int c = 0; c < 2; ++c)
+      *reinterpret_cast<float4*>(stage + (16 * c + lr) * (D + 4) + 16 * dt + 4 * lg) =
+          make_float4(acc[dt][c][0] * mul, acc[dt][c][1] * mul, acc[dt][c][2] * mul, acc[dt][c][3] * mul);
   __syncthreads();
 #pragma unroll
   for (int it = 0; it < (32 * (D / 4)) / 64; ++it) {
@@ -225,9 +228,9 @@ RP_DEV void store_acc_T_f32(const f32x16 (&acc)[D / 32], float mul, float* stage
 }
 
 // ================================================================================================ forward
-template <int D, int QT, int NW>
-__global__ void __launch_bounds__(NW * 64, (QT == 1 && NW <= 4) ? 2 : 1) attn_fwd_kernel(const AttnArgs p) {
-  constexpr int LDK = D + 8, LDV = D + 32, KS = D / 16, DT = D / 32, NT = NW * 64, BQ = NW * 32 * QT;
+template <int D, int NW>
+__global__ void __launch_bounds__(NW * 64, NW <= 4 ? 2 : 1) attn_fwd_kernel(const AttnArgs p) {
+  constexpr int LDK = tile_ld(D), LDV = LDK, KS = D / 32, DT = D / 16, NT = NW * 64, BQ = NW * 32;
   using T64 = Tile64<D, NT>;
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn_smem[];   // fwd_smem_bytes(D, NW)
   bf16* const smem = reinterpret_cast<bf16*>(dyn_smem);
@@ -237,7 +240,7 @@ __global__ void __launch_bounds__(NW * 64, (QT == 1 && NW <= 4) ? 2 : 1) attn_fw
   bf16* const Ks = smem;
   bf16* const Vs = smem + 64 * LDK;
 
-  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lk = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nQ = (p.seq + BQ - 1) / BQ;
   const int nhb = p.a * p.batch;
@@ -246,38 +249,32 @@ __global__ void __launch_bounds__(NW * 64, (QT == 1 && NW <= 4) ? 2 : 1) attn_fw
   const int hb = xcd_head(rank % nhb, nhb);
   const int hq = hb % p.a, b = hb / p.a;
   const int g = hq / (p.a / p.kh);
-  const int q0 = qtile * BQ, qw0 = q0 + w * 32 * QT;
+  const int q0 = qtile * BQ, qw0 = q0 + w * 32;
   const long tok0 = (long)b * p.seq;
   const bf16* qb = p.q + tok0 * p.ldq + hq * D;
   const rsrc_t rk = seq_rsrc(p.k + tok0 * p.ldk + g * D, p.ldk, p.seq, D);
   const rsrc_t rv = seq_rsrc(p.v + tok0 * p.ldv + g * D, p.ldv, p.seq, D);
 
-  uint4 qf[QT][KS];
+  // a lane's queries are qw0 + lr and qw0 + 16 + lr (column tiles c = 0, 1)
+  uint4 qf[2][KS];
 #pragma unroll
-  for (int t = 0; t < QT; ++t) {
-    const int qpos = qw0 + 32 * t + lr;
+  for (int c = 0; c < 2; ++c) {
+    const int qpos = qw0 + 16 * c + lr;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      qf[t][ks] = make_uint4(0u, 0u, 0u, 0u);
-      if (qpos < p.seq) qf[t][ks] = *reinterpret_cast<const uint4*>(qb + (long)qpos * p.ldq + 16 * ks + 8 * lk);
+      qf[c][ks] = make_uint4(0u, 0u, 0u, 0u);
+      if (qpos < p.seq) qf[c][ks] = *reinterpret_cast<const uint4*>(qb + (long)qpos * p.ldq + 32 * ks + 8 * lg);
     }
   }
   const int kv_end = (q0 + BQ < p.seq) ? (q0 + BQ) : p.seq;
   const int nkv = (kv_end + 63) / 64;
 
-  float m_run[QT], l_run[QT];
-  f32x16 oacc[QT][DT];
+  float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
+  f32x4 oacc[DT][2];
 #pragma unroll
-  for (int t = 0; t < QT; ++t) {
-    m_run[t] = -INFINITY;
-    l_run[t] = 0.f;
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) oacc[t][dt][v] = 0.f;
-  }
+  for (int dt = 0; dt < DT; ++dt) oacc[dt][0] = oacc[dt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const bf16* const kfrag0 = Ks + lr * LDK + 8 * lk;
+  const bf16* const kfrag0 = Ks + lr * LDK + 8 * lg;
   const bf16* const vfrag0 = Vs + tr_base<LDV>(lane);
   uint4 kreg[T64::NREG], vreg[T64::NREG];
   T64::load(kreg, rk, p.ldk, 0, tid);
@@ -319,14 +316,14 @@ __global__ void __launch_bounds__(NW * 64, (QT == 1 && NW <= 4) ? 2 : 1) attn_fw
     // rather than skip it: they would wait at the next barrier anyway, and a skipped update would make the compiler
     // keep a second copy of the accumulator.
     {
-      f32x16 sT[QT][2];
-      const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      // every LDS fragment is requested AHEAD products before the one that consumes it, so that the MFMAs do not each
+      f32x4 sT[4][2];       // 16 keys x 16 queries each
+      const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+      // every LDS fragment is requested AHEAD pairs of products before the pair that consumes it, so that the MFMAs do not each
       // wait out an LDS round trip
       constexpr int AHEAD = 3;
       {
-        constexpr int NS = 2 * KS;
-        auto sfrag_at = [&](int n) { return *reinterpret_cast<const uint4*>(kfrag + 32 * (n & 1) * LDK + 16 * (n >> 1)); };
+        constexpr int NS = 4 * KS;
+        auto sfrag_at = [&](int n) { return *reinterpret_cast<const uint4*>(kfrag + 16 * (n & 3) * LDK + 32 * (n >> 2)); };
         uint4 ring[AHEAD];
 #pragma unroll
         for (int n = 0; n < AHEAD; ++n) ring[n] = sfrag_at(n);
@@ -335,82 +332,88 @@ __global__ void __launch_bounds__(NW * 64, (QT == 1 && NW <= 4) ? 2 : 1) attn_fw
         for (int n = 0; n < NS; ++n) {
           const uint4 a = ring[n % AHEAD];
           if (n + AHEAD < NS) ring[n % AHEAD] = sfrag_at(n + AHEAD);
-          const int ks = n >> 1, kt = n & 1;
+          const int ks = n >> 2, kt = n & 3;
 #pragma unroll
-          for (int t = 0; t < QT; ++t) sT[t][kt] = mfma32(a, qf[t][ks], ks == 0 ? zero16 : sT[t][kt]);
+          for (int c = 0; c < 2; ++c) sT[kt][c] = mfma16(a, qf[c][ks], ks == 0 ? zero4 : sT[kt][c]);
           __builtin_amdgcn_sched_barrier(0);
         }
         MFMA_PHASE_END();
       }
       // the first V fragments are requested now, under the softmax arithmetic
-      constexpr int NU = 4 * DT;
-      auto ufrag_at = [&](int n) { return read_frag_tr<LDV>(vfrag, n / DT, 32 * (n % DT)); };
+      constexpr int NU = 2 * DT;
+      auto ufrag_at = [&](int n) { return read_frag_tr<LDV>(vfrag + 32 * (n / DT) * LDV + 16 * (n % DT)); };
       uint4 uring[AHEAD];
 #pragma unroll
       for (int n = 0; n < AHEAD; ++n) uring[n] = ufrag_at(n);
       __builtin_amdgcn_sched_barrier(0);
       const bool need_mask = (kv0 + 63 > qw0) || (kv0 + 64 > p.seq);   // wave-uniform
+      if (need_mask) {
 #pragma unroll
-      for (int t = 0; t < QT; ++t) {
-        if (need_mask) {
-          const int qpos = qw0 + 32 * t + lr;
-          const int klim = (qpos < p.seq - 1 ? qpos : p.seq - 1) - (kv0 + 4 * lk);   // keys up to klim past the lane's first
+        for (int c = 0; c < 2; ++c) {
+          const int qpos = qw0 + 16 * c + lr;
+          const int klim = (qpos < p.seq - 1 ? qpos : p.seq - 1) - (kv0 + 4 * lg);   // keys up to klim past the lane's first
 #pragma unroll
-          for (int kt = 0; kt < 2; ++kt)
+          for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) sT[t][kt][v] = (32 * kt + 8 * (v >> 2) + (v & 3) > klim) ? -INFINITY : sT[t][kt][v];
+            for (int e = 0; e < 4; ++e) sT[kt][c][e] = (16 * kt + e > klim) ? -INFINITY : sT[kt][c][e];
         }
-        float mx = -INFINITY;
+      }
+      float mx[2];
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
+      for (int c = 0; c < 2; ++c) {
+        mx[c] = -INFINITY;
 #pragma unroll
-          for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sT[t][kt][v]);
-        mx = (NW < 8 ? half_max(mx) : fmaxf(mx, __shfl_xor(mx, 32, 64))) * p.scale_log2e;
-        // The accumulator is rescaled on every key tile, without a branch: a conditional rescale (only when the
-        // maximum grows) makes the compiler carry a second copy of the accumulator through the loop, which costs more
-        // than the multiplies.  The first key tile contains key 0 <= qpos, so m_run is finite from then on.
-        {
-          // m_run is a reference exponent, not the exact running maximum: it moves only when a row's maximum outgrows
-          // it by 2^8 (the probabilities stay below 256, harmless in fp32 sums and bf16 operands), so after the first
-          // few key tiles almost every tile skips the rescale of the accumulator.  The skip is a wave-uniform branch,
-          // and alpha passes through an empty asm statement so that the multiplies cannot be hoisted out of it.
-          const bool grow = mx > m_run[t] + 8.f;
-          if (__builtin_amdgcn_ballot_w64(grow) != 0ull) {
-            const float m_new = grow ? mx : m_run[t];
-            float alpha = fast_exp2(m_run[t] - m_new);
-            asm volatile("" : "+v"(alpha));
-            l_run[t] *= alpha;
-            m_run[t] = m_new;
+        for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
+          for (int e = 0; e < 4; ++e) mx[c] = fmaxf(mx[c], sT[kt][c][e]);
+      }
+      column_max2(mx[0], mx[1]);
+      // m_run is a reference exponent, not the exact running maximum: it moves only when a row's maximum outgrows
+      // it by 2^8 (the probabilities stay below 256, harmless in fp32 sums and bf16 operands), so after the first
+      // few key tiles almost every tile skips the rescale of the accumulator.  The skip is a wave-uniform branch,
+      // and alpha passes through an empty asm statement so that the multiplies cannot be hoisted out of it.  The first key tile
+      // contains key 0 <= qpos, so m_run is finite from then on.
+      const bool grow0 = mx[0] * p.scale_log2e > m_run[0] + 8.f, grow1 = mx[1] * p.scale_log2e > m_run[1] + 8.f;
+      if (__builtin_amdgcn_ballot_w64(grow0 || grow1) != 0ull) {
 #pragma unroll
-              for (int v = 0; v < 16; ++v) oacc[t][dt][v] *= alpha;
-          }
+        for (int c = 0; c < 2; ++c) {
+          const float m_new = (c ? grow1 : grow0) ? mx[c] * p.scale_log2e : m_run[c];
+          float alpha = fast_exp2(m_run[c] - m_new);
+          asm volatile("" : "+v"(alpha));
+          l_run[c] *= alpha;
+          m_run[c] = m_new;
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) oacc[dt][c][e] *= alpha;
         }
+      }
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
         float psum = 0.f;
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
+        for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const float e = fast_exp2(__builtin_fmaf(sT[t][kt][v], p.scale_log2e, -m_run[t]));
-            sT[t][kt][v] = e;
-            psum += e;
+          for (int e = 0; e < 4; ++e) {
+            const float x = fast_exp2(__builtin_fmaf(sT[kt][c][e], p.scale_log2e, -m_run[c]));
+            sT[kt][c][e] = x;
+            psum += x;
           }
-        l_run[t] += psum;
+        l_run[c] += psum;
       }
       {
-        uint4 pf[4][QT];
+        uint4 pf[2][2];
 #pragma unroll
-        for (int gk = 0; gk < 4; ++gk)
+        for (int k2 = 0; k2 < 2; ++k2)
 #pragma unroll
-          for (int t = 0; t < QT; ++t) pf[gk][t] = pack_frag(sT[t][gk >> 1], 8 * (gk & 1));
+          for (int c = 0; c < 2; ++c) pf[k2][c] = pack_frag(sT[2 * k2][c], sT[2 * k2 + 1][c]);
         MFMA_PHASE_BEGIN();
 #pragma unroll
         for (int n = 0; n < NU; ++n) {
           const uint4 a = uring[n % AHEAD];
           if (n + AHEAD < NU) uring[n % AHEAD] = ufrag_at(n + AHEAD);
 #pragma unroll
-          for (int t = 0; t < QT; ++t) oacc[t][n % DT] = mfma32(a, pf[n / DT][t], oacc[t][n % DT]);
+          for (int c = 0; c < 2; ++c) oacc[n % DT][c] = mfma16(a, pf[n / DT][c], oacc[n % DT][c]);
           __builtin_amdgcn_sched_barrier(0);
         }
         MFMA_PHASE_END();
@@ -419,13 +422,15 @@ __global__ void __launch_bounds__(NW * 64, (QT == 1 && NW <= 4) ? 2 : 1) attn_fw
   }
 
   __syncthreads();
+  float inv[2];
 #pragma unroll
-  for (int t = 0; t < QT; ++t) {
-    const int qpos = qw0 + 32 * t + lr;
-    const float l_tot = l_run[t] + __shfl_xor(l_run[t], 32, 64);
-    if (lk == 0 && qpos < p.seq) p.lse[((long)b * p.a + hq) * p.seq + qpos] = m_run[t] * 0.6931471805599453f + logf(l_tot);
-    store_acc_T<D>(oacc[t], 1.f / l_tot, smem + w * 32 * LDK, p.o + tok0 * p.ldo + hq * D, p.ldo, qw0 + 32 * t, p.seq, lane);
+  for (int c = 0; c < 2; ++c) {
+    const int qpos = qw0 + 16 * c + lr;
+    const float l_tot = column_sum(l_run[c]);
+    if (lg == 0 && qpos < p.seq) p.lse[((long)b * p.a + hq) * p.seq + qpos] = m_run[c] * 0.6931471805599453f + logf(l_tot);
+    inv[c] = 1.f / l_tot;
   }
+  store_acc_T<D>(oacc, inv, smem + w * 32 * LDK, p.o + tok0 * p.ldo + hq * D, p.ldo, qw0, p.seq, lane);
 }
 
 // ================================================================================================ delta = rowsum(dO * O)
@@ -459,18 +464,17 @@ __global__ void __launch_bounds__(256) attn_delta_kernel(const bf16* __restrict_
 }
 
 // ================================================================================================ dQ
-template <int D, int QT, int NW>
-__global__ void __launch_bounds__(NW * 64, (QT == 1 && NW <= 4) ? 2 : 1) attn_bwd_dq_kernel(const AttnArgs p) {
-  // K is read both ways (plain for S, transposing for dQ += dS K): its tile has the row stride d + 24 that serves both
-  // (see attn_bwd_dkv_pair_kernel) and is stored once
-  constexpr int LDK = D + 8, LDU = D + 24, KS = D / 16, DT = D / 32, NT = NW * 64, BQ = NW * 32 * QT;
+template <int D, int NW>
+__global__ void __launch_bounds__(NW * 64, NW <= 4 ? 2 : 1) attn_bwd_dq_kernel(const AttnArgs p) {
+  // K is read both ways (plain for S, transposing for dQ += dS K) and stored once
+  constexpr int LDK = tile_ld(D), LDU = LDK, KS = D / 32, DT = D / 16, NT = NW * 64, BQ = NW * 32;
   using T64 = Tile64<D, NT>;
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn_smem[];   // dq_smem_bytes(D, NW)
   bf16* const smem = reinterpret_cast<bf16*>(dyn_smem);
   bf16* const Ks = smem;
   bf16* const Vs = smem + 64 * LDU;
 
-  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lk = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nQ = (p.seq + BQ - 1) / BQ;
   const int nhb = p.a * p.batch;
@@ -479,60 +483,56 @@ __global__ void __launch_bounds__(NW * 64, (QT == 1 && NW <= 4) ? 2 : 1) attn_bw
   const int hb = xcd_head(rank % nhb, nhb);
   const int hq = hb % p.a, b = hb / p.a;
   const int g = hq / (p.a / p.kh);
-  const int q0 = qtile * BQ, qw0 = q0 + w * 32 * QT;
+  const int q0 = qtile * BQ, qw0 = q0 + w * 32;
   const long tok0 = (long)b * p.seq;
   const bf16* qb = p.q + tok0 * p.ldq + hq * D;
   const bf16* dob = p.dout + tok0 * p.lddo + hq * D;
   const rsrc_t rk = seq_rsrc(p.k + tok0 * p.ldk + g * D, p.ldk, p.seq, D);
   const rsrc_t rv = seq_rsrc(p.v + tok0 * p.ldv + g * D, p.ldv, p.seq, D);
 
-  uint4 qf[QT][KS], dof[QT][KS];
-  float lse2[QT], dl[QT];
+  uint4 qf[2][KS], dof[2][KS];     // a lane's queries: column tiles c = 0, 1 (see the forward kernel)
+  float lse2[2], dl[2];
 #pragma unroll
-  for (int t = 0; t < QT; ++t) {
-    const int qpos = qw0 + 32 * t + lr;
+  for (int c = 0; c < 2; ++c) {
+    const int qpos = qw0 + 16 * c + lr;
     const bool qok = qpos < p.seq;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      qf[t][ks] = make_uint4(0u, 0u, 0u, 0u);
-      dof[t][ks] = make_uint4(0u, 0u, 0u, 0u);
+      qf[c][ks] = make_uint4(0u, 0u, 0u, 0u);
+      dof[c][ks] = make_uint4(0u, 0u, 0u, 0u);
       if (qok) {
-        qf[t][ks] = *reinterpret_cast<const uint4*>(qb + (long)qpos * p.ldq + 16 * ks + 8 * lk);
-        dof[t][ks] = *reinterpret_cast<const uint4*>(dob + (long)qpos * p.lddo + 16 * ks + 8 * lk);
+        qf[c][ks] = *reinterpret_cast<const uint4*>(qb + (long)qpos * p.ldq + 32 * ks + 8 * lg);
+        dof[c][ks] = *reinterpret_cast<const uint4*>(dob + (long)qpos * p.lddo + 32 * ks + 8 * lg);
       }
     }
     const long stat = ((long)b * p.a + hq) * p.seq + qpos;
-    lse2[t] = qok ? p.lse_in[stat] * 1.4426950408889634f : INFINITY;   // padded rows get P = 0
+    lse2[c] = qok ? p.lse_in[stat] * 1.4426950408889634f : INFINITY;   // padded rows get P = 0
     if (p.o_in) {   // uniform: this wave is the only one that holds the row's dO, so delta costs one read of O and no kernel
       float s = 0.f;
       if (qok) {
-        const bf16* orow = p.o_in + (tok0 + qpos) * p.ldo + hq * D + 8 * lk;
+        const bf16* orow = p.o_in + (tok0 + qpos) * p.ldo + hq * D + 8 * lg;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-          const uint4 u = *reinterpret_cast<const uint4*>(orow + 16 * ks), d = dof[t][ks];
+          const uint4 u = *reinterpret_cast<const uint4*>(orow + 32 * ks), d = dof[c][ks];
           s += bf16_lo(u.x) * bf16_lo(d.x) + bf16_hi(u.x) * bf16_hi(d.x) + bf16_lo(u.y) * bf16_lo(d.y) + bf16_hi(u.y) * bf16_hi(d.y) +
                bf16_lo(u.z) * bf16_lo(d.z) + bf16_hi(u.z) * bf16_hi(d.z) + bf16_lo(u.w) * bf16_lo(d.w) + bf16_hi(u.w) * bf16_hi(d.w);
         }
       }
-      dl[t] = s + __shfl_xor(s, 32, 64);
-      if (qok && lk == 0) p.delta[stat] = dl[t];
+      dl[c] = column_sum(s);
+      if (qok && lg == 0) p.delta[stat] = dl[c];
     } else {
-      dl[t] = qok ? p.delta[stat] : 0.f;
+      dl[c] = qok ? p.delta[stat] : 0.f;
     }
   }
 
   const int kv_end = (q0 + BQ < p.seq) ? (q0 + BQ) : p.seq;
   const int nkv = (kv_end + 63) / 64;
-  f32x16 dqacc[QT][DT];
+  f32x4 dqacc[DT][2];
 #pragma unroll
-  for (int t = 0; t < QT; ++t)
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) dqacc[t][dt][v] = 0.f;
+  for (int dt = 0; dt < DT; ++dt) dqacc[dt][0] = dqacc[dt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const bf16* const kfrag0 = Ks + lr * LDU + 8 * lk;
-  const bf16* const vfrag0 = Vs + lr * LDK + 8 * lk;
+  const bf16* const kfrag0 = Ks + lr * LDU + 8 * lg;
+  const bf16* const vfrag0 = Vs + lr * LDK + 8 * lg;
   const bf16* const ktfrag0 = Ks + tr_base<LDU>(lane);
   uint4 kreg[T64::NREG], vreg[T64::NREG];
   T64::load(kreg, rk, p.ldk, 0, tid);
@@ -569,59 +569,71 @@ __global__ void __launch_bounds__(NW * 64, (QT == 1 && NW <= 4) ? 2 : 1) attn_bw
     const int kv0 = j * 64;
     {   // a wave whose queries all precede this tile's keys runs it fully masked (see the forward kernel)
       const bool need_mask = (kv0 + 63 > qw0) || (kv0 + 64 > p.seq);
-      const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
       // the two 32-key halves of the tile one after the other: half as many score registers live at a time
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt) {
-        f32x16 sT[QT], dpT[QT];
+      for (int k2 = 0; k2 < 2; ++k2) {
+        f32x4 sT[2][2], dpT[2][2];     // [16 keys][16 queries]
+        {
+          constexpr int NS = 4 * KS, AHEAD = 4;     // n = (ks * 2 + kt) * 2 + which
+          auto sfrag_at = [&](int n) {
+            const int row = 32 * k2 + 16 * ((n >> 1) & 1), at = 32 * (n >> 2);
+            return *reinterpret_cast<const uint4*>((n & 1) ? vfrag + row * LDK + at : kfrag + row * LDU + at);
+          };
+          uint4 ring[AHEAD];
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          const uint4 ak = *reinterpret_cast<const uint4*>(kfrag + 32 * kt * LDU + 16 * ks);
-          const uint4 av = *reinterpret_cast<const uint4*>(vfrag + 32 * kt * LDK + 16 * ks);
+          for (int n = 0; n < AHEAD; ++n) ring[n] = sfrag_at(n);
 #pragma unroll
-          for (int t = 0; t < QT; ++t) {
-            sT[t] = mfma32(ak, qf[t][ks], ks == 0 ? zero16 : sT[t]);
-            dpT[t] = mfma32(av, dof[t][ks], ks == 0 ? zero16 : dpT[t]);
+          for (int n = 0; n < NS; ++n) {
+            const uint4 a = ring[n % AHEAD];
+            if (n + AHEAD < NS) ring[n % AHEAD] = sfrag_at(n + AHEAD);
+            const int ks = n >> 2, kt = (n >> 1) & 1;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+              if (n & 1) dpT[kt][c] = mfma16(a, dof[c][ks], ks == 0 ? zero4 : dpT[kt][c]);
+              else sT[kt][c] = mfma16(a, qf[c][ks], ks == 0 ? zero4 : sT[kt][c]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
           }
         }
         // one wave-uniform branch per half tile around two whole element loops (a test per element would be
         // compiled into a branch per element)
         if (need_mask) {
 #pragma unroll
-          for (int t = 0; t < QT; ++t) {
-            const int qpos = qw0 + 32 * t + lr;
-            const int klim = (qpos < p.seq - 1 ? qpos : p.seq - 1) - (kv0 + 32 * kt + 4 * lk);   // local key index <= klim
+          for (int c = 0; c < 2; ++c) {
+            const int qpos = qw0 + 16 * c + lr;
+            const int klim = (qpos < p.seq - 1 ? qpos : p.seq - 1) - (kv0 + 32 * k2 + 4 * lg);   // local key index <= klim
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              float pr = fast_exp2(__builtin_fmaf(sT[t][v], p.scale_log2e, -lse2[t]));
-              pr = (8 * (v >> 2) + (v & 3) > klim) ? 0.f : pr;
-              sT[t][v] = pr * (dpT[t][v] - dl[t]);   // dS^T
-            }
+            for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                float pr = fast_exp2(__builtin_fmaf(sT[kt][c][e], p.scale_log2e, -lse2[c]));
+                pr = (16 * kt + e > klim) ? 0.f : pr;
+                sT[kt][c][e] = pr * (dpT[kt][c][e] - dl[c]);   // dS^T
+              }
           }
         } else {
 #pragma unroll
-          for (int t = 0; t < QT; ++t)
+          for (int c = 0; c < 2; ++c)
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-              sT[t][v] = fast_exp2(__builtin_fmaf(sT[t][v], p.scale_log2e, -lse2[t])) * (dpT[t][v] - dl[t]);   // dS^T
+            for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                sT[kt][c][e] = fast_exp2(__builtin_fmaf(sT[kt][c][e], p.scale_log2e, -lse2[c])) * (dpT[kt][c][e] - dl[c]);   // dS^T
         }
-        {   // the 2*DT accumulator updates as one sequence, K^T fragments requested AHEAD updates early
-          constexpr int NU = 2 * DT, AHEAD = 2;
-          uint4 df[2][QT];
-#pragma unroll
-          for (int g2 = 0; g2 < 2; ++g2)
-#pragma unroll
-            for (int t = 0; t < QT; ++t) df[g2][t] = pack_frag(sT[t], 8 * g2);
-          auto ufrag_at = [&](int n) { return read_frag_tr<LDU>(ktfrag, 2 * kt + n / DT, 32 * (n % DT)); };
+        {   // the DT pairs of accumulator updates as one sequence, K^T fragments requested AHEAD pairs early
+          constexpr int AHEAD = 2;
+          const uint4 df[2] = {pack_frag(sT[0][0], sT[1][0]), pack_frag(sT[0][1], sT[1][1])};
+          auto ufrag_at = [&](int n) { return read_frag_tr<LDU>(ktfrag + 32 * k2 * LDU + 16 * n); };
           uint4 uring[AHEAD];
 #pragma unroll
           for (int n = 0; n < AHEAD; ++n) uring[n] = ufrag_at(n);
 #pragma unroll
-          for (int n = 0; n < NU; ++n) {
+          for (int n = 0; n < DT; ++n) {
             const uint4 a = uring[n % AHEAD];
-            if (n + AHEAD < NU) uring[n % AHEAD] = ufrag_at(n + AHEAD);
+            if (n + AHEAD < DT) uring[n % AHEAD] = ufrag_at(n + AHEAD);
 #pragma unroll
-            for (int t = 0; t < QT; ++t) dqacc[t][n % DT] = mfma32(a, df[n / DT][t], dqacc[t][n % DT]);
+            for (int c = 0; c < 2; ++c) dqacc[n][c] = mfma16(a, df[c], dqacc[n][c]);
             __builtin_amdgcn_sched_barrier(0);
           }
         }
@@ -629,9 +641,38 @@ __global__ void __launch_bounds__(NW * 64, (QT == 1 && NW <= 4) ? 2 : 1) attn_bw
     }
   }
   __syncthreads();
+  const float mul[2] = {p.scale, p.scale};
+  store_acc_T<D>(dqacc, mul, smem + w * 32 * LDK, p.dq + tok0 * p.lddq + hq * D, p.lddq, qw0, p.seq, lane);
+}
+
+// P = exp(s) and dS = P dP in place, for 32 queries (rows) x 32 keys of the dK/dV kernels; q0: the query of row 0 of this lane.
+RP_DEV void softmax_grad(f32x4 (&s)[2][2], f32x4 (&dp)[2][2], bool need_mask, int q0, const int (&kpos)[2], int seq, float scale_log2e) {
+  if (need_mask) {
 #pragma unroll
-  for (int t = 0; t < QT; ++t)
-    store_acc_T<D>(dqacc[t], p.scale, smem + w * 32 * LDK, p.dq + tok0 * p.lddq + hq * D, p.lddq, qw0 + 32 * t, p.seq, lane);
+    for (int c = 0; c < 2; ++c) {
+      const bool kok = kpos[c] < seq;
+#pragma unroll
+      for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float pr = fast_exp2(s[qt][c][e] * scale_log2e);
+          pr = (kpos[c] > q0 + 16 * qt + e || !kok) ? 0.f : pr;
+          s[qt][c][e] = pr;
+          dp[qt][c][e] = pr * dp[qt][c][e];
+        }
+    }
+  } else {
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float pr = fast_exp2(s[qt][c][e] * scale_log2e);
+          s[qt][c][e] = pr;
+          dp[qt][c][e] = pr * dp[qt][c][e];
+        }
+  }
 }
 
 // ================================================================================================ dK, dV in one kernel
@@ -645,14 +686,15 @@ __global__ void __launch_bounds__(NW * 64, (QT == 1 && NW <= 4) ? 2 : 1) attn_bw
 template <int D, bool MULTI>
 __global__ void __launch_bounds__(256) attn_bwd_dkv_fused_kernel(const AttnArgs p) {
   const int hpw = MULTI ? p.hpw : 1;
-  constexpr int LDK = D + 24, KS = D / 16, DT = D / 32;
+  constexpr int LDK = tile_ld(D), KS = D / 32, DT = D / 16;
   using T64 = Tile64<D, 256>;
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn_smem[];
   bf16* const smem = reinterpret_cast<bf16*>(dyn_smem);             // 2*64*LDK elements; one layout for both kinds of reads, see the pair kernel
   bf16* const Qs = smem;
   bf16* const dOs = smem + 64 * LDK;
+  float* const stat = reinterpret_cast<float*>(smem + 2 * 64 * LDK);     // [2][64], see stat_start
 
-  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lk = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ah = p.a / hpw, nhb = ah * p.batch;     // workgroups per key tile
   // Workgroups of one query head stream the same Q and dO tiles, a few tiles apart (key tile j starts at query tile 2j
@@ -678,40 +720,33 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_fused_kernel(const AttnArgs 
   const long tok0 = (long)b * p.seq;
   const bf16* kb = p.k + tok0 * p.ldk + g * D;
   const bf16* vb = p.v + tok0 * p.ldv + g * D;
-  const int kpos = kw0 + lr;
-  const bool kok = kpos < p.seq;
+  // a lane's keys are kw0 + lr and kw0 + 16 + lr (column tiles c = 0, 1)
+  const int kpos[2] = {kw0 + lr, kw0 + 16 + lr};
 
-  uint4 kf[KS], vf[KS];
+  uint4 kf[2][KS], vf[2][KS];
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    kf[ks] = make_uint4(0u, 0u, 0u, 0u);
-    vf[ks] = make_uint4(0u, 0u, 0u, 0u);
-    if (kok) {
-      kf[ks] = *reinterpret_cast<const uint4*>(kb + (long)kpos * p.ldk + 16 * ks + 8 * lk);
-      vf[ks] = *reinterpret_cast<const uint4*>(vb + (long)kpos * p.ldv + 16 * ks + 8 * lk);
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      kf[c][ks] = make_uint4(0u, 0u, 0u, 0u);
+      vf[c][ks] = make_uint4(0u, 0u, 0u, 0u);
+      if (kpos[c] < p.seq) {
+        kf[c][ks] = *reinterpret_cast<const uint4*>(kb + (long)kpos[c] * p.ldk + 32 * ks + 8 * lg);
+        vf[c][ks] = *reinterpret_cast<const uint4*>(vb + (long)kpos[c] * p.ldv + 32 * ks + 8 * lg);
+      }
     }
-  }
-  f32x16 dkacc[DT], dvacc[DT];
+  f32x4 dkacc[DT][2], dvacc[DT][2];
 #pragma unroll
-  for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) { dkacc[dt][v] = 0.f; dvacc[dt][v] = 0.f; }
+  for (int dt = 0; dt < DT; ++dt) dkacc[dt][0] = dkacc[dt][1] = dvacc[dt][0] = dvacc[dt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   const int nQ = (p.seq + 63) / 64;
   const int qt0 = kv0 / 64;
   const int niter = nQ - qt0;
 
-  const bf16* qfrag = Qs + lr * LDK + 8 * lk;
-  const bf16* dofrag = dOs + lr * LDK + 8 * lk;
+  const bf16* qfrag = Qs + lr * LDK + 8 * lg;
+  const bf16* dofrag = dOs + lr * LDK + 8 * lg;
   const bf16* qtfrag = Qs + tr_base<LDK>(lane);
   const bf16* dotfrag = dOs + tr_base<LDK>(lane);
-  // The per-query terms of the softmax recomputation ride along in the products: the pad chunk of a Q row holds
-  // -lse/scale split into three bf16 numbers, that of a dO row -delta, and one extra MFMA step against ones3() adds
-  // them, so the score tile comes out as q.k - lse/scale and the dP tile as dO.v - delta.  (Rows of the score tile are
-  // queries here: without this every lane would need sixteen different lse and delta values per tile.)
-  const bf16* qx = Qs + lr * LDK + D;
-  const bf16* dox = dOs + lr * LDK + D;
-  const uint4 one_f = ones3(lk);
 
   uint4 qreg[T64::NREG], doreg[T64::NREG];
   float st_reg = 0.f;
@@ -745,28 +780,27 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_fused_kernel(const AttnArgs 
     __syncthreads();
     T64::template store<LDK>(qreg, Qs, tid);
     T64::template store<LDK>(doreg, dOs, tid);
-    if (w < 2) *reinterpret_cast<uint4*>((w == 0 ? Qs : dOs) + lane * LDK + D) = stat_chunk(st_reg, w, (qt0 + it) * 64 + lane < p.seq, p.scale);
+    if (w < 2) stat[64 * w + lane] = stat_start(st_reg, w, (qt0 + it) * 64 + lane < p.seq, p.scale);
     __syncthreads();
     if (ia + 1 < total) prefetch(ia + 1);
     const int q0 = (qt0 + it) * 64;
     {   // a wave whose keys all follow this tile's queries runs it fully masked (see the forward kernel)
       const bool need_mask = (q0 < kw0 + 31) || (kw0 + 32 > p.seq);   // wave-uniform
-      const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
       // the two 32-query halves of the tile one after the other: half as many score registers live at a time
 #pragma unroll
       for (int t2 = 0; t2 < 2; ++t2) {
-        f32x16 s = zero16, dp = zero16;
-        // One wave per SIMD: nothing else covers the LDS latency, so every fragment is requested AHEAD MFMAs before
-        // the one that consumes it.  Score phase: 2*(KS+1) products, alternately S and dP; the last pair are the
-        // extra steps that bring in -lse/scale and -delta.
+        f32x4 s[2][2], dp[2][2], s0[2], dp0[2];     // [16 queries][16 keys]; what they start from
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt) {
+          s0[qt] = *reinterpret_cast<const f32x4*>(stat + 32 * t2 + 16 * qt + 4 * lg);
+          dp0[qt] = *reinterpret_cast<const f32x4*>(stat + 64 + 32 * t2 + 16 * qt + 4 * lg);
+        }
+        // Little else covers the LDS latency, so every fragment is requested AHEAD pairs of MFMAs before the pair that consumes it.
+        // Score phase: alternately S and dP.
         constexpr int AHEAD = 4;
         {
-          constexpr int NS = 2 * (KS + 1);
-          auto sfrag_at = [&](int n) {
-            const int ks = n >> 1;
-            const bf16* src = ks < KS ? ((n & 1) ? dofrag : qfrag) + 16 * ks : ((n & 1) ? dox : qx);
-            return *reinterpret_cast<const uint4*>(src + 32 * t2 * LDK);
-          };
+          constexpr int NS = 4 * KS;     // n = (ks * 2 + qt) * 2 + which
+          auto sfrag_at = [&](int n) { return *reinterpret_cast<const uint4*>(((n & 1) ? dofrag : qfrag) + (32 * t2 + 16 * ((n >> 1) & 1)) * LDK + 32 * (n >> 2)); };
           uint4 ring[AHEAD];
 #pragma unroll
           for (int n = 0; n < AHEAD; ++n) ring[n] = sfrag_at(n);
@@ -774,51 +808,39 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_fused_kernel(const AttnArgs 
           for (int n = 0; n < NS; ++n) {
             const uint4 a = ring[n % AHEAD];
             if (n + AHEAD < NS) ring[n % AHEAD] = sfrag_at(n + AHEAD);
-            const int ks = n >> 1;
-            if (n & 1) dp = mfma32(a, ks < KS ? vf[ks] : one_f, dp);
-            else s = mfma32(a, ks < KS ? kf[ks] : one_f, s);
+            const int ks = n >> 2, qt = (n >> 1) & 1;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+              if (n & 1) dp[qt][c] = mfma16(a, vf[c][ks], ks == 0 ? dp0[qt] : dp[qt][c]);
+              else s[qt][c] = mfma16(a, kf[c][ks], ks == 0 ? s0[qt] : s[qt][c]);
+            }
             __builtin_amdgcn_sched_barrier(0);
           }
         }
         // the first fragments of the update phase are requested now, under the exponentials
-        constexpr int NU = 4 * DT;
-        auto ufrag_at = [&](int n) {   // n = (g2 * DT + dt) * 2 + which
-          return read_frag_tr<LDK>((n & 1) ? qtfrag : dotfrag, 2 * t2 + n / (2 * DT), 32 * ((n >> 1) % DT));
-        };
+        constexpr int NU = 2 * DT;
+        auto ufrag_at = [&](int n) { return read_frag_tr<LDK>(((n & 1) ? qtfrag : dotfrag) + 32 * t2 * LDK + 16 * (n >> 1)); };
         uint4 uring[AHEAD];
 #pragma unroll
         for (int n = 0; n < AHEAD; ++n) uring[n] = ufrag_at(n);
         __builtin_amdgcn_sched_barrier(0);
-        // rows of the score tile are queries: q = q0 + 32*t2 + 8*(v/4) + 4*lk + v%4
+        // rows of the score tiles are queries: q = q0 + 32*t2 + 16*qt + 4*lg + e
         // the branch is taken per tile, not per element: away from the diagonal nothing below compares positions
-        if (need_mask) {
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int qpos = q0 + 32 * t2 + 8 * (v >> 2) + 4 * lk + (v & 3);
-            float pr = fast_exp2(s[v] * p.scale_log2e);
-            pr = (kpos > qpos || !kok) ? 0.f : pr;
-            s[v] = pr;                         // P
-            dp[v] = pr * dp[v];                // dS
-          }
-        } else {
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const float pr = fast_exp2(s[v] * p.scale_log2e);
-            s[v] = pr;
-            dp[v] = pr * dp[v];
-          }
-        }
-        // the 4*DT accumulator updates as one sequence, fragments AHEAD updates early
+        softmax_grad(s, dp, need_mask, q0 + 32 * t2 + 4 * lg, kpos, p.seq, p.scale_log2e);
+        // the 2*DT pairs of accumulator updates as one sequence, fragments AHEAD pairs early
         {
-          const uint4 pfg[2] = {pack_frag(s, 0), pack_frag(s, 8)};
-          const uint4 dfg[2] = {pack_frag(dp, 0), pack_frag(dp, 8)};
+          const uint4 pfg[2] = {pack_frag(s[0][0], s[1][0]), pack_frag(s[0][1], s[1][1])};
+          const uint4 dfg[2] = {pack_frag(dp[0][0], dp[1][0]), pack_frag(dp[0][1], dp[1][1])};
 #pragma unroll
           for (int n = 0; n < NU; ++n) {
             const uint4 a = uring[n % AHEAD];
             if (n + AHEAD < NU) uring[n % AHEAD] = ufrag_at(n + AHEAD);
-            const int g2 = n / (2 * DT), dt = (n >> 1) % DT;
-            if (n & 1) dkacc[dt] = mfma32(a, dfg[g2], dkacc[dt]);
-            else dvacc[dt] = mfma32(a, pfg[g2], dvacc[dt]);
+            const int dt = n >> 1;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+              if (n & 1) dkacc[dt][c] = mfma16(a, dfg[c], dkacc[dt][c]);
+              else dvacc[dt][c] = mfma16(a, pfg[c], dvacc[dt][c]);
+            }
             __builtin_amdgcn_sched_barrier(0);
           }
         }
@@ -827,8 +849,9 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_fused_kernel(const AttnArgs 
   }
   __syncthreads();
   if (grp == hpw) {
-    store_acc_T<D>(dkacc, p.scale, smem + w * 32 * (D + 8), p.dk + tok0 * p.lddk + g * D, p.lddk, kw0, p.seq, lane);
-    store_acc_T<D>(dvacc, 1.f, smem + w * 32 * (D + 8), p.dv + tok0 * p.lddv + g * D, p.lddv, kw0, p.seq, lane);
+    const float one[2] = {1.f, 1.f}, sc[2] = {p.scale, p.scale};
+    store_acc_T<D>(dkacc, sc, smem + w * 32 * (D + 8), p.dk + tok0 * p.lddk + g * D, p.lddk, kw0, p.seq, lane);
+    store_acc_T<D>(dvacc, one, smem + w * 32 * (D + 8), p.dv + tok0 * p.lddv + g * D, p.lddv, kw0, p.seq, lane);
   } else {
     float* const stage = reinterpret_cast<float*>(smem) + w * 32 * (D + 4);
     const long ldp = (long)ah * D;
@@ -852,22 +875,18 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_fused_kernel(const AttnArgs 
 template <int D, bool MULTI, bool DS>
 __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p) {
   const int hpw = MULTI ? p.hpw : 1;
-  // One LDS layout serves both kinds of fragment reads, so that every Q and dO tile is stored once: a row stride of
-  // D + 24 elements is 12 banks past a multiple of 64, which keeps the 16 rows of a plain 16-byte read phase on distinct
-  // banks; the transposing 8-byte reads (32 lanes a phase: 4 rows x 64 bytes) overlap on a quarter of their banks
-  // (SQ_LDS_BANK_CONFLICT: 22 % of the LDS-active cycles).  Measured cheaper than storing the tiles twice (-3 %); a
-  // layout with the transposing stride D + 32 and the 16-byte chunks of a row permuted (c ^ (row / 4 & 3)) removes the
-  // conflicts altogether (LDS-active cycles -20 %) and is not faster; neither is a variant with one workgroup barrier
-  // per tile and a flag handshake inside the pair.  No unit is more than half busy: the waves wait on their own chain.
-  constexpr int LDU = D + 24, KS = D / 16, DT = D / 32, DH = DT / 2;
-  static_assert(DT % 2 == 0, "the head dimension is split over two waves");
+  // One LDS layout serves both kinds of fragment reads (tile_ld), so that every Q and dO tile is stored once.  No unit is more than half
+  // busy: the waves wait on their own chain.
+  constexpr int LDU = tile_ld(D), KS = D / 32, DH = D / 32;     // DH: 16-row tiles of half the head dimension
+  static_assert(D % 32 == 0, "the head dimension is split over two waves");
   using T64 = Tile64<D, 512>;
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn_smem[];
   bf16* const smem = reinterpret_cast<bf16*>(dyn_smem);             // two sets (tile parity) of Q | dO, then the exchange
   constexpr int TSET = 2 * 64 * LDU;
   uint4* const exch = reinterpret_cast<uint4*>(smem + 2 * TSET);    // [8 waves][4 fragments][64 lanes]
+  float* const stat = reinterpret_cast<float*>(exch + 8 * 4 * 64);  // [2 sets][2][64], see stat_start
 
-  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lk = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
   const int w8 = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int w = w8 >> 1, h = w8 & 1;
   const int ah = p.a / hpw, nhb = ah * p.batch;
@@ -889,38 +908,35 @@ __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p
   const long tok0 = (long)b * p.seq;
   const bf16* kb = p.k + tok0 * p.ldk + g * D;
   const bf16* vb = p.v + tok0 * p.ldv + g * D;
-  const int kpos = kw0 + lr;
-  const bool kok = kpos < p.seq;
+  // a lane's keys are kw0 + lr and kw0 + 16 + lr (column tiles c = 0, 1)
+  const int kpos[2] = {kw0 + lr, kw0 + 16 + lr};
 
-  uint4 kf[KS], vf[KS];
+  uint4 kf[2][KS], vf[2][KS];
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    kf[ks] = make_uint4(0u, 0u, 0u, 0u);
-    vf[ks] = make_uint4(0u, 0u, 0u, 0u);
-    if (kok) {
-      kf[ks] = *reinterpret_cast<const uint4*>(kb + (long)kpos * p.ldk + 16 * ks + 8 * lk);
-      vf[ks] = *reinterpret_cast<const uint4*>(vb + (long)kpos * p.ldv + 16 * ks + 8 * lk);
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      kf[c][ks] = make_uint4(0u, 0u, 0u, 0u);
+      vf[c][ks] = make_uint4(0u, 0u, 0u, 0u);
+      if (kpos[c] < p.seq) {
+        kf[c][ks] = *reinterpret_cast<const uint4*>(kb + (long)kpos[c] * p.ldk + 32 * ks + 8 * lg);
+        vf[c][ks] = *reinterpret_cast<const uint4*>(vb + (long)kpos[c] * p.ldv + 32 * ks + 8 * lg);
+      }
     }
-  }
-  f32x16 dkacc[DH], dvacc[DH];
+  f32x4 dkacc[DH][2], dvacc[DH][2];
 #pragma unroll
-  for (int dt = 0; dt < DH; ++dt)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) { dkacc[dt][v] = 0.f; dvacc[dt][v] = 0.f; }
+  for (int dt = 0; dt < DH; ++dt) dkacc[dt][0] = dkacc[dt][1] = dvacc[dt][0] = dvacc[dt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   const int nQ = (p.seq + 63) / 64;
   const int qt0 = kv0 / 64;
   const int niter = nQ - qt0;
 
   // this wave's 32 queries of a tile: rows 32*h .. 32*h + 31
-  const bf16* qfrag = smem + (32 * h + lr) * LDU + 8 * lk;
+  const bf16* qfrag = smem + (32 * h + lr) * LDU + 8 * lg;
   const bf16* dofrag = qfrag + 64 * LDU;
-  const bf16* qx = smem + (32 * h + lr) * LDU + D;
-  const bf16* dox = qx + 64 * LDU;
-  // this wave's half of the head dimension: columns 32*DH*h .. of the transposed tiles
-  const bf16* qtfrag = smem + tr_base<LDU>(lane) + 32 * DH * h;
+  // this wave's half of the head dimension: columns 16*DH*h .. of the transposed tiles
+  const bf16* qtfrag = smem + tr_base<LDU>(lane) + 16 * DH * h;
   const bf16* dotfrag = qtfrag + 64 * LDU;
-  const uint4 one_f = ones3(lk);
   uint4* const ex_mine = exch + (w8 * 4) * 64 + lane;
   const uint4* const ex_theirs = exch + ((w8 ^ 1) * 4) * 64 + lane;
 
@@ -950,12 +966,10 @@ __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p
   if (total > 0) prefetch(0);
 
   constexpr int AHEAD = 2;     // two waves per SIMD cover each other's LDS latency: a short ring is enough
-  // the update products of one 32-query half t2 with the fragments pf (P) and df (dS): 4 * DH MFMAs
+  // the update products of one 32-query half t2 with the fragments pf (P) and df (dS): 2 * DH pairs of MFMAs
   auto update_half = [&](int set, int t2, const uint4 (&pf)[2], const uint4 (&df)[2]) {
-    constexpr int NU = 4 * DH;
-    auto ufrag_at = [&](int n) {   // n = (g2 * DH + dt) * 2 + which
-      return read_frag_tr<LDU>(((n & 1) ? qtfrag : dotfrag) + set * TSET, 2 * t2 + n / (2 * DH), 32 * ((n >> 1) % DH));
-    };
+    constexpr int NU = 2 * DH;     // n = dt * 2 + which
+    auto ufrag_at = [&](int n) { return read_frag_tr<LDU>(((n & 1) ? qtfrag : dotfrag) + set * TSET + 32 * t2 * LDU + 16 * (n >> 1)); };
     uint4 uring[AHEAD];
 #pragma unroll
     for (int n = 0; n < AHEAD; ++n) uring[n] = ufrag_at(n);
@@ -964,9 +978,12 @@ __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p
     for (int n = 0; n < NU; ++n) {
       const uint4 a = uring[n % AHEAD];
       if (n + AHEAD < NU) uring[n % AHEAD] = ufrag_at(n + AHEAD);
-      const int g2 = n / (2 * DH), dt = (n >> 1) % DH;
-      if (n & 1) dkacc[dt] = mfma32(a, df[g2], dkacc[dt]);
-      else dvacc[dt] = mfma32(a, pf[g2], dvacc[dt]);
+      const int dt = n >> 1;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        if (n & 1) dkacc[dt][c] = mfma16(a, df[c], dkacc[dt][c]);
+        else dvacc[dt][c] = mfma16(a, pf[c], dvacc[dt][c]);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
     MFMA_PHASE_END();
@@ -981,7 +998,7 @@ __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p
     update_half(it_prev & 1, h ^ 1, ppf, pdf);
   };
   int it_cur = 0;                        // query tile of the current head
-  [[maybe_unused]] const uint32_t ds_lane = (uint32_t)((w & 1) * 8192 + h * 2048 + lane * 16);    // where the lane stores in a block
+  [[maybe_unused]] const uint32_t ds_lane = (uint32_t)((w & 1) * 8192 + h * 2048 + (lg & 1) * 1024 + (lg >> 1) * 512 + lr * 16);    // where the lane stores in a block
   [[maybe_unused]] const uint32_t ds_bytes = (uint32_t)attn_ds_block((nQ + 1) / 2, 0) * 16384u;
   [[maybe_unused]] int ds_h = b * p.a + hg * hpw;
   for (int ia = 0; ia < total; ++ia) {
@@ -991,22 +1008,22 @@ __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p
     bf16* const q_set = smem + (ia & 1) * TSET;
     T64::template store<LDU>(qreg, q_set, tid);
     T64::template store<LDU>(doreg, q_set + 64 * LDU, tid);
-    if (w8 < 2) *reinterpret_cast<uint4*>(q_set + (64 * w8 + lane) * LDU + D) = stat_chunk(st_reg, w8, (qt0 + it) * 64 + lane < p.seq, p.scale);
+    if (w8 < 2) stat[128 * (ia & 1) + 64 * w8 + lane] = stat_start(st_reg, w8, (qt0 + it) * 64 + lane < p.seq, p.scale);
     if (ia > 0) partner_update(ia - 1);
     __syncthreads();
     if (ia + 1 < total) prefetch(ia + 1);
     const int q0 = (qt0 + it) * 64;
     const int qh0 = q0 + 32 * h;                                            // first query of this wave's half
     const bool need_mask = (qh0 < kw0 + 31) || (kw0 + 32 > p.seq);          // wave-uniform
-    const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    f32x16 s = zero16, dp = zero16;
+    f32x4 s[2][2], dp[2][2], s0[2], dp0[2];      // [16 queries][16 keys]; what they start from
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt) {
+      s0[qt] = *reinterpret_cast<const f32x4*>(stat + 128 * (ia & 1) + 32 * h + 16 * qt + 4 * lg);
+      dp0[qt] = *reinterpret_cast<const f32x4*>(stat + 128 * (ia & 1) + 64 + 32 * h + 16 * qt + 4 * lg);
+    }
     {
-      constexpr int NS = 2 * (KS + 1);
-      auto sfrag_at = [&](int n) {
-        const int ks = n >> 1;
-        const bf16* src = ks < KS ? ((n & 1) ? dofrag : qfrag) + 16 * ks : ((n & 1) ? dox : qx);
-        return *reinterpret_cast<const uint4*>(src + (ia & 1) * TSET);
-      };
+      constexpr int NS = 4 * KS;     // n = (ks * 2 + qt) * 2 + which
+      auto sfrag_at = [&](int n) { return *reinterpret_cast<const uint4*>(((n & 1) ? dofrag : qfrag) + (ia & 1) * TSET + 16 * ((n >> 1) & 1) * LDU + 32 * (n >> 2)); };
       uint4 ring[AHEAD];
 #pragma unroll
       for (int n = 0; n < AHEAD; ++n) ring[n] = sfrag_at(n);
@@ -1015,47 +1032,35 @@ __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p
       for (int n = 0; n < NS; ++n) {
         const uint4 a = ring[n % AHEAD];
         if (n + AHEAD < NS) ring[n % AHEAD] = sfrag_at(n + AHEAD);
-        const int ks = n >> 1;
-        if (n & 1) dp = mfma32(a, ks < KS ? vf[ks] : one_f, dp);
-        else s = mfma32(a, ks < KS ? kf[ks] : one_f, s);
+        const int ks = n >> 2, qt = (n >> 1) & 1;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          if (n & 1) dp[qt][c] = mfma16(a, vf[c][ks], ks == 0 ? dp0[qt] : dp[qt][c]);
+          else s[qt][c] = mfma16(a, kf[c][ks], ks == 0 ? s0[qt] : s[qt][c]);
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
       MFMA_PHASE_END();
     }
-    // rows of the score tile are queries: q = qh0 + 8*(v/4) + 4*lk + v%4
-    if (need_mask) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int qpos = qh0 + 8 * (v >> 2) + 4 * lk + (v & 3);
-        float pr = fast_exp2(s[v] * p.scale_log2e);
-        pr = (kpos > qpos || !kok) ? 0.f : pr;
-        s[v] = pr;                         // P
-        dp[v] = pr * dp[v];                // dS
-      }
-    } else {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const float pr = fast_exp2(s[v] * p.scale_log2e);
-        s[v] = pr;
-        dp[v] = pr * dp[v];
-      }
-    }
-    const uint4 pfg[2] = {pack_frag(s, 0), pack_frag(s, 8)};
-    const uint4 dfg[2] = {pack_frag(dp, 0), pack_frag(dp, 8)};
+    // rows of the score tiles are queries: q = qh0 + 16*qt + 4*lg + e
+    softmax_grad(s, dp, need_mask, qh0 + 4 * lg, kpos, p.seq, p.scale_log2e);
+    const uint4 pfg[2] = {pack_frag(s[0][0], s[1][0]), pack_frag(s[0][1], s[1][1])};
+    const uint4 dfg[2] = {pack_frag(dp[0][0], dp[1][0]), pack_frag(dp[0][1], dp[1][1])};
     // the partner read last tile's fragments before the barrier above: the slots are free
     ex_mine[0] = pfg[0]; ex_mine[64] = pfg[1]; ex_mine[128] = dfg[0]; ex_mine[192] = dfg[1];
     if constexpr (DS) {
-      // a fragment holds, for lane half lk, queries {4lk..4lk+3, 8+4lk..8+4lk+3} of 16: after the exchange 8lk..8lk+7
+      // fragment c holds, for key 16c + lr and lane group lg, queries {4lg..4lg+3, 16+4lg..16+4lg+3} of 32: after the exchange between
+      // neighbouring groups eight queries from 16 (lg & 1) + 8 (lg >> 1) on
       const rsrc_t rds = __builtin_amdgcn_make_buffer_rsrc(p.ds + (size_t)ds_h * (ds_bytes / 2), 0, (int)ds_bytes, 0x00020000);
       const int j = qt0 + it;
       const uint32_t at = (uint32_t)attn_ds_block(j >> 1, 2 * kvt + (w >> 1)) * 16384u + (uint32_t)((j & 1) * 4096);
 #pragma unroll
-      for (int f = 0; f < 2; ++f) {
+      for (int c = 0; c < 2; ++c) {
         typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-        const auto p0 = __builtin_amdgcn_permlane32_swap(dfg[f].x, dfg[f].z, false, false);
-        const auto p1 = __builtin_amdgcn_permlane32_swap(dfg[f].y, dfg[f].w, false, false);
+        const auto p0 = __builtin_amdgcn_permlane16_swap(dfg[c].x, dfg[c].z, false, false);
+        const auto p1 = __builtin_amdgcn_permlane16_swap(dfg[c].y, dfg[c].w, false, false);
         const u32x4 o = {p0[0], p1[0], p0[1], p1[1]};
-        __builtin_amdgcn_raw_buffer_store_b128(o, rds, (int)(ds_lane + 1024 * f), (int)at, 2);
+        __builtin_amdgcn_raw_buffer_store_b128(o, rds, (int)(ds_lane + 256 * c), (int)at, 2);
       }
       if (MULTI && it + 1 == niter) ++ds_h;
     }
@@ -1066,8 +1071,9 @@ __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p
   __syncthreads();
   if (grp == hpw) {
     bf16* const stage = smem + w8 * 32 * (D / 2 + 8);
-    store_acc_T<D / 2>(dkacc, p.scale, stage, p.dk + tok0 * p.lddk + g * D + h * (D / 2), p.lddk, kw0, p.seq, lane);
-    store_acc_T<D / 2>(dvacc, 1.f, stage, p.dv + tok0 * p.lddv + g * D + h * (D / 2), p.lddv, kw0, p.seq, lane);
+    const float one[2] = {1.f, 1.f}, sc[2] = {p.scale, p.scale};
+    store_acc_T<D / 2>(dkacc, sc, stage, p.dk + tok0 * p.lddk + g * D + h * (D / 2), p.lddk, kw0, p.seq, lane);
+    store_acc_T<D / 2>(dvacc, one, stage, p.dv + tok0 * p.lddv + g * D + h * (D / 2), p.lddv, kw0, p.seq, lane);
   } else {
     float* const stage = reinterpret_cast<float*>(smem) + w8 * 32 * (D / 2 + 4);
     const long ldp = (long)ah * D;
@@ -1106,10 +1112,10 @@ __global__ void __launch_bounds__(256) attn_dkv_reduce_kernel(const float* __res
 
 // operand tiles, or the epilogue's staging of every wave's 32 x d block, whichever is larger
 constexpr int max_i(int a, int b) { return a > b ? a : b; }
-constexpr int fwd_smem_bytes(int d, int nw) { return max_i((nw >= 8 ? 2 : 1) * (64 * (d + 8) + 64 * (d + 32)), nw * 32 * (d + 8)) * 2; }
-constexpr int dq_smem_bytes(int d, int nw) { return max_i((nw >= 8 ? 2 : 1) * (64 * (d + 24) + 64 * (d + 8)), nw * 32 * (d + 8)) * 2; }
-constexpr int dkv_fused_smem_bytes(int d) { return max_i(2 * 64 * (d + 24) * 2, 4 * 32 * (d + 4) * 4); }
-constexpr int dkv_pair_smem_bytes(int d) { return 2 * (2 * 64 * (d + 24)) * 2 + 8 * 4 * 64 * 16; }
+constexpr int fwd_smem_bytes(int d, int nw) { return max_i((nw >= 8 ? 2 : 1) * (2 * 64 * tile_ld(d)), nw * 32 * (d + 8)) * 2; }
+constexpr int dq_smem_bytes(int d, int nw) { return max_i((nw >= 8 ? 2 : 1) * (2 * 64 * tile_ld(d)), nw * 32 * (d + 8)) * 2; }
+constexpr int dkv_fused_smem_bytes(int d) { return max_i(2 * 64 * tile_ld(d) * 2 + 512, 4 * 32 * (d + 4) * 4); }
+constexpr int dkv_pair_smem_bytes(int d) { return 2 * (2 * 64 * tile_ld(d)) * 2 + 8 * 4 * 64 * 16 + 1024; }
 void fill_common(AttnArgs& p, int batch, int seq, int a, int kh, int d) {
   p.batch = batch; p.seq = seq; p.a = a; p.kh = kh;
   p.scale = 1.0f / sqrtf((float)d);
@@ -1124,16 +1130,16 @@ hipError_t set_smem(K kern, int bytes, bool& done) {
   return e;
 }
 
-template <int D, int QT, int NW>
+template <int D, int NW>
 hipError_t launch_fwd(hipStream_t st, const AttnArgs& p) {
-  constexpr int BQ = NW * 32 * QT;
+  constexpr int BQ = NW * 32;
   static bool done = false;
-  hipError_t e = set_smem(attn_fwd_kernel<D, QT, NW>, fwd_smem_bytes(D, NW), done);
+  hipError_t e = set_smem(attn_fwd_kernel<D, NW>, fwd_smem_bytes(D, NW), done);
   if (e != hipSuccess) return e;
   const int grid = ((p.seq + BQ - 1) / BQ) * p.a * p.batch;
   AttnArgs pf = p;
   pf.fold = NW <= 4 && grid > 256 && grid <= 512;
-  RP_LAUNCH((attn_fwd_kernel<D, QT, NW>), dim3(grid), dim3(NW * 64), fwd_smem_bytes(D, NW), st, pf);
+  RP_LAUNCH((attn_fwd_kernel<D, NW>), dim3(grid), dim3(NW * 64), fwd_smem_bytes(D, NW), st, pf);
   return hipGetLastError();
 }
 
@@ -1164,16 +1170,16 @@ hipError_t launch_dkv_pair(hipStream_t st, const AttnArgs& p, int grid) {
   return p.hpw > 1 ? launch_dkv_pair_one<D, true, false>(st, p, grid) : launch_dkv_pair_one<D, false, false>(st, p, grid);
 }
 
-template <int D, int QT, int NW>
+template <int D, int NW>
 hipError_t launch_dq(hipStream_t st, const AttnArgs& p) {
-  constexpr int BQ = NW * 32 * QT;
+  constexpr int BQ = NW * 32;
   static bool done = false;
-  hipError_t e = set_smem(attn_bwd_dq_kernel<D, QT, NW>, dq_smem_bytes(D, NW), done);
+  hipError_t e = set_smem(attn_bwd_dq_kernel<D, NW>, dq_smem_bytes(D, NW), done);
   if (e != hipSuccess) return e;
   const int grid = ((p.seq + BQ - 1) / BQ) * p.a * p.batch;
   AttnArgs pf = p;
   pf.fold = NW <= 4 && grid > 256 && grid <= 512;
-  RP_LAUNCH((attn_bwd_dq_kernel<D, QT, NW>), dim3(grid), dim3(NW * 64), dq_smem_bytes(D, NW), st, pf);
+  RP_LAUNCH((attn_bwd_dq_kernel<D, NW>), dim3(grid), dim3(NW * 64), dq_smem_bytes(D, NW), st, pf);
   return hipGetLastError();
 }
 
@@ -1216,9 +1222,9 @@ hipError_t k_attn_fwd(hipStream_t st, const void* q, const void* k, const void* 
   // eight waves per workgroup (256 queries) store every K/V tile once for twice the products; enough workgroups needed
   // (d = 128 only: at d = 64 the four-wave kernel fits three waves per SIMD and is 20 % faster than the eight-wave one)
   const bool big = (long)((seq + 255) / 256) * a * batch >= 1024;
-  if (d == 128 && big) return launch_fwd<128, 1, 8>(st, p);
-  if (d == 128) return launch_fwd<128, 1, 4>(st, p);
-  if (d == 64) return launch_fwd<64, 1, 4>(st, p);
+  if (d == 128 && big) return launch_fwd<128, 8>(st, p);
+  if (d == 128) return launch_fwd<128, 4>(st, p);
+  if (d == 64) return launch_fwd<64, 4>(st, p);
   return hipErrorInvalidValue;
 }
 
@@ -1286,8 +1292,8 @@ hipError_t k_attn_bwd(hipStream_t st, int part, const void* q, const void* k, co
     return gemm_attn_dq(st, ds, k_attn_ds_bytes(seq, d), k, ldk, dq, lddq, batch, seq, a, kh, d, p.scale);
   } else {
     const bool big = (long)((seq + 255) / 256) * a * batch >= 1024;
-    if (d == 128 && big) return launch_dq<128, 1, 8>(st, p);
-    return d == 128 ? launch_dq<128, 1, 4>(st, p) : launch_dq<64, 1, 4>(st, p);
+    if (d == 128 && big) return launch_dq<128, 8>(st, p);
+    return d == 128 ? launch_dq<128, 4>(st, p) : launch_dq<64, 4>(st, p);
   }
   return hipGetLastError();
 }
