@@ -670,7 +670,9 @@ hipError_t gemm_launch(hipStream_t st, int layout, const GemmArgs& a_in, int til
   // 83 | 87, 151 | 161; of 768 x 3072, 16384 tokens 1004 | 1039; 32 of 512 x 1024, 4096 tokens 220 | 233.  With weights from
   // memory the four waves are ahead: 64 of 1024 x 512 (201 MB), 4096 | 16384 tokens 276 | 268, 857 | 833; 128 of 2048 x 768, 16384 2521 | 2468.
   const bool short_grp = a.grp_tab && a.grp_cached && !a.grp_once && a.K <= 1024;
-  const bool dtl = a.grp_tab ? !short_grp : (tile == 1 && tile_hint != 1 && !a.run_flag && !a.b_direct && (tile_hint == 7 || (a.K + a.K2 >= 2560 && a.M > 64 && a.N > 64)));
+  // (the four-wave kernel addresses the 256 rows of an output tile with 31-bit byte offsets)
+  const bool near_rows = a.ldc < 1L << 21 && a.ldr < 1L << 21 && a.ldc2 < 1L << 21;
+  const bool dtl = !near_rows ? false : a.grp_tab ? !short_grp : (tile == 1 && tile_hint != 1 && !a.run_flag && !a.b_direct && (tile_hint == 7 || (a.K + a.K2 >= 2560 && a.M > 64 && a.N > 64)));
   if (dtl) {
     e = gemm_dtl_launch(st, a, layout);
   } else {

@@ -148,29 +148,25 @@ RP_DEV bool label_logit(const f32x16 (&acc)[TM][TN], int g, int lab_local, float
 
 // SwiGLU backward of 8 columns of a row: d = the staged product (the gradient of silu(gate) * up), g and u = gate and up;
 // d_gate = d * up * s * (1 + gate * (1 - s)),  d_up = d * gate * s,  s = sigmoid(gate).
-RP_DEV void swiglu_bwd_store(const GemmArgs& p, const bf16* staged, const uint4& gv, const uint4& uv, bf16* out, bool in) {
-  const uint4 dv = *reinterpret_cast<const uint4*>(staged);
-  const uint32_t dw[4] = {dv.x, dv.y, dv.z, dv.w}, gw[4] = {gv.x, gv.y, gv.z, gv.w},
-                 uw[4] = {uv.x, uv.y, uv.z, uv.w};
-  uint32_t og[4], ou[4];
+RP_DEV void swiglu_bwd8(const uint4& d, const uint4& g, const uint4& u, uint4& og, uint4& ou) {
+  const uint32_t dw[4] = {d.x, d.y, d.z, d.w}, gw[4] = {g.x, g.y, g.z, g.w}, uw[4] = {u.x, u.y, u.z, u.w};
+  uint32_t o1[4], o2[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     float dg2[2], du2[2];
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
-      const float d = hh ? bf16_hi(dw[e]) : bf16_lo(dw[e]), g = hh ? bf16_hi(gw[e]) : bf16_lo(gw[e]),
+      const float dd = hh ? bf16_hi(dw[e]) : bf16_lo(dw[e]), gg = hh ? bf16_hi(gw[e]) : bf16_lo(gw[e]),
                   up = hh ? bf16_hi(uw[e]) : bf16_lo(uw[e]);
-      const float sg = sigmoid_f32(g);
-      dg2[hh] = d * up * sg * (1.f + g * (1.f - sg));
-      du2[hh] = d * g * sg;
+      const float sg = sigmoid_f32(gg);
+      dg2[hh] = dd * up * sg * (1.f + gg * (1.f - sg));
+      du2[hh] = dd * gg * sg;
     }
-    og[e] = pack_bf16x2(dg2[0], dg2[1]);
-    ou[e] = pack_bf16x2(du2[0], du2[1]);
+    o1[e] = pack_bf16x2(dg2[0], dg2[1]);
+    o2[e] = pack_bf16x2(du2[0], du2[1]);
   }
-  if (in) {
-    *reinterpret_cast<uint4*>(out) = make_uint4(og[0], og[1], og[2], og[3]);
-    *reinterpret_cast<uint4*>(out + p.N) = make_uint4(ou[0], ou[1], ou[2], ou[3]);
-  }
+  og = make_uint4(o1[0], o1[1], o1[2], o1[3]);
+  ou = make_uint4(o2[0], o2[1], o2[2], o2[3]);
 }
 
 // Epilogue.  acc (elements as AccMap<L16> says) is the wave's 128x64 block whose top left corner is (wrow0, wcol0).  Every wave stages its block through its own 18 KB of LDS (all waves must have
@@ -178,12 +174,9 @@ RP_DEV void swiglu_bwd_store(const GemmArgs& p, const bf16* staged, const uint4&
 // barrier inside.
 // part_row: row of the cross-entropy partial array this wave writes (EPI_CE_STATS).
 // M: rows of C that exist (the end of the group's rows in grouped mode).
-// PIPE: what a tile adds or reads from memory is requested a batch ahead (up to 64 registers more: for the kernel of one wave per SIMD,
-// where nothing else covers the latency; the eight-wave kernels spill with it, 4096 x 2048 x 2048 75 -> 82 us).
-// IS: rows of C between the 32-row MFMA tiles of the wave's block (32: the block is 128 consecutive rows).
 // j0, j1 (wave-uniform): the 32-column halves [j0, j1) of the block this wave writes -- both, except in the plain
 // epilogues of the two-group tile, where the groups take one half each.
-template <int IS = 32, bool PIPE = false, bool L16 = false>
+template <bool L16 = false>
 RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsigned char* smem, int wave, int lane,
                      int wrow0, int wcol0, int part_row, int j0 = 0, int j1 = TN) {
   using L = AccMap<L16>;
@@ -191,7 +184,7 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
   auto el = [&](int i, int g, int w) __attribute__((always_inline)) { return acc[i][L::reg_j(g)][L::reg_v(g, w)]; };
   unsigned char* const stg = smem + wave * STG_BYTES;
   const int rr = lane >> 3, cc = lane & 7;   // read-back: 8 rows per pass, 8 chunks of 16 bytes per row
-  auto out_row = [&](int t) __attribute__((always_inline)) { return wrow0 + (t >> 2) * IS + (t & 3) * 8 + rr; };   // row of C of local row 8 t + rr
+  auto out_row = [&](int t) __attribute__((always_inline)) { return wrow0 + t * 8 + rr; };   // row of C of local row 8 t + rr
 
   if ((p.epi == EPI_BF16 && !p.R) || p.epi == EPI_CE_DZ || p.epi == EPI_SWIGLU_BWD || p.epi == EPI_CE_P || p.epi == EPI_SWIGLU_FWD) {
     bf16* s16 = reinterpret_cast<bf16*>(stg);
@@ -307,39 +300,6 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
     wave_lds_fence();
     bf16* Cp = reinterpret_cast<bf16*>(p.C);
     if (p.epi == EPI_SWIGLU_BWD) {
-      if constexpr (PIPE) {
-        // as below, with the loads of four row groups in flight while the four before are worked on: older than those groups' stores,
-        // they do not wait for them
-        const bf16* Rp = reinterpret_cast<const bf16*>(p.R);
-        const int gcol = wcol0 + cc * 8;
-        constexpr int NB = 4;
-        uint4 gv[2][NB], uv[2][NB];
-        auto load_gu = [&](int t0, int set) __attribute__((always_inline)) {
-#pragma unroll
-          for (int u = 0; u < NB; ++u) {
-            const int grow = out_row(t0 + u);
-            gv[set][u] = make_uint4(0u, 0u, 0u, 0u);
-            uv[set][u] = gv[set][u];
-            if (grow < M && gcol < p.N) {
-              gv[set][u] = *reinterpret_cast<const uint4*>(Rp + (long)grow * p.ldr + gcol);
-              uv[set][u] = *reinterpret_cast<const uint4*>(Rp + (long)grow * p.ldr + p.N + gcol);
-            }
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        };
-        load_gu(0, 0);
-#pragma unroll
-        for (int t0 = 0; t0 < WAVE_M / 8; t0 += NB) {
-          const int set = (t0 / NB) & 1;
-          if (t0 + NB < WAVE_M / 8) load_gu(t0 + NB, set ^ 1);
-#pragma unroll
-          for (int u = 0; u < NB; ++u) {
-            const int row = (t0 + u) * 8 + rr, grow = out_row(t0 + u);
-            swiglu_bwd_store(p, s16 + row * STG_LD + cc * 8, gv[set][u], uv[set][u], Cp + (long)grow * p.ldc + gcol, grow < M && gcol < p.N);
-          }
-        }
-        return;
-      }
       // a lane takes 8 columns of a row of the staged product d (the gradient of silu(gate) * up), reads gate and up
       // there and writes  d_gate = d * up * s * (1 + gate * (1 - s)),  d_up = d * gate * s,  s = sigmoid(gate);
       // the loads of four row groups are in flight before anything is stored
@@ -362,27 +322,11 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
           const int row = (t0 + u) * 8 + rr, grow = out_row(t0 + u);
-          const uint4 dv = *reinterpret_cast<const uint4*>(s16 + row * STG_LD + cc * 8);
-          const uint32_t dw[4] = {dv.x, dv.y, dv.z, dv.w}, gw[4] = {gv[u].x, gv[u].y, gv[u].z, gv[u].w},
-                         uw[4] = {uv[u].x, uv[u].y, uv[u].z, uv[u].w};
-          uint32_t og[4], ou[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            float dg2[2], du2[2];
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-              const float d = hh ? bf16_hi(dw[e]) : bf16_lo(dw[e]), g = hh ? bf16_hi(gw[e]) : bf16_lo(gw[e]),
-                          up = hh ? bf16_hi(uw[e]) : bf16_lo(uw[e]);
-              const float sg = sigmoid_f32(g);
-              dg2[hh] = d * up * sg * (1.f + g * (1.f - sg));
-              du2[hh] = d * g * sg;
-            }
-            og[e] = pack_bf16x2(dg2[0], dg2[1]);
-            ou[e] = pack_bf16x2(du2[0], du2[1]);
-          }
+          uint4 dg, du;
+          swiglu_bwd8(*reinterpret_cast<const uint4*>(s16 + row * STG_LD + cc * 8), gv[u], uv[u], dg, du);
           if (grow < M && gcol < p.N) {
-            *reinterpret_cast<uint4*>(Cp + (long)grow * p.ldc + gcol) = make_uint4(og[0], og[1], og[2], og[3]);
-            *reinterpret_cast<uint4*>(Cp + (long)grow * p.ldc + p.N + gcol) = make_uint4(ou[0], ou[1], ou[2], ou[3]);
+            *reinterpret_cast<uint4*>(Cp + (long)grow * p.ldc + gcol) = dg;
+            *reinterpret_cast<uint4*>(Cp + (long)grow * p.ldc + p.N + gcol) = du;
           }
         }
       }
@@ -400,7 +344,7 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
       const int lcol = j0 * 32 + (lane & 3) * 8, gcol = wcol0 + lcol;
 #pragma unroll
       for (int t = 0; t < WAVE_M / 16; ++t) {
-        const int row = t * 16 + (lane >> 2), grow = wrow0 + (t >> 1) * IS + (t & 1) * 16 + (lane >> 2);
+        const int row = t * 16 + (lane >> 2), grow = wrow0 + row;
         if (grow < M && gcol < p.N)
           *reinterpret_cast<uint4*>(Cp + (long)grow * p.ldc + gcol) = *reinterpret_cast<const uint4*>(s16 + row * STG_LD + lcol);
       }
@@ -461,100 +405,6 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
         }
         if (lk == 0 && colok) p.part[(long)part_row * p.part_ld + col] = make_float2(mx, 0.f);
       }
-    }
-    if constexpr (PIPE) {
-      if (p.epi == EPI_BF16) {
-        // The residual is added in fp32: 64 rows x 64 columns at a time through [64][68] floats, 8 columns of a row per lane, the residual
-        // of the next 64 rows (of the first, while they are staged) in flight meanwhile.  8192 x 8192 x 4096 NT with a residual 492 ->
-        // 445 us, without one 430.
-        constexpr int LDF = 68, NR8 = 8;
-        static_assert(64 * LDF * 4 <= STG_BYTES, "staging");
-        float* const f = reinterpret_cast<float*>(stg);
-        const int gcol = wcol0 + cc * 8;
-        uint4 rv[2][NR8];
-        auto load_r = [&](int h) __attribute__((always_inline)) {
-#pragma unroll
-          for (int u = 0; u < NR8; ++u) {
-            const int grow = out_row(8 * h + u);
-            rv[h][u] = make_uint4(0u, 0u, 0u, 0u);
-            if (grow < M && gcol < p.N) {      // ldr is a multiple of 4 only
-              const uint2* const src = reinterpret_cast<const uint2*>(reinterpret_cast<const bf16*>(p.R) + (long)grow * p.ldr + gcol);
-              const uint2 lo = src[0], hi = src[1];
-              rv[h][u] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-            }
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        };
-        load_r(0);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          if (h) wave_lds_fence();
-#pragma unroll
-          for (int i = 2 * h; i < 2 * h + 2; ++i)
-#pragma unroll
-            for (int g = 0; g < L::NJ; ++g)
-#pragma unroll
-              for (int w = 0; w < L::NV; ++w) f[(L::acc_row(i & 1, w) + 4 * lk) * LDF + g * L::CW + lr] = p.alpha * acc[i][L::reg_j(g)][L::reg_v(g, w)];
-          wave_lds_fence();
-          if (h == 0) load_r(1);
-#pragma unroll
-          for (int u = 0; u < NR8; ++u) {
-            const int grow = out_row(8 * h + u);
-            const float* const src = f + (u * 8 + rr) * LDF + cc * 8;
-            const float4 x = *reinterpret_cast<const float4*>(src), y = *reinterpret_cast<const float4*>(src + 4);
-            const uint4 r = rv[h][u];
-            if (grow < M && gcol < p.N)
-              *reinterpret_cast<uint4*>(reinterpret_cast<bf16*>(p.C) + (long)grow * p.ldc + gcol) =
-                  make_uint4(pack_bf16x2(x.x + bf16_lo(r.x), x.y + bf16_hi(r.x)), pack_bf16x2(x.z + bf16_lo(r.y), x.w + bf16_hi(r.y)),
-                             pack_bf16x2(y.x + bf16_lo(r.z), y.y + bf16_hi(r.z)), pack_bf16x2(y.z + bf16_lo(r.w), y.w + bf16_hi(r.w)));
-          }
-        }
-        return;
-    }
-    // fp32 staging, one 32-column half at a time: [128][36] floats (144-byte rows); an output that accumulates is read eight row groups
-    // ahead of those that are worked on (8192 x 8192 x 4096 NT 500 -> 489 us)
-    float* const s32 = reinterpret_cast<float*>(stg);
-    constexpr int NB = 8;
-    float* const Cf = reinterpret_cast<float*>(p.C) + (long)blockIdx.y * p.c_slice_stride;   // slice of a reduction split
-    float4 o[2][NB];
-    auto load_o = [&](int j, int t0, int set) __attribute__((always_inline)) {
-      const int gcol = wcol0 + j * 32 + cc * 4;
-#pragma unroll
-      for (int u = 0; u < NB; ++u) {
-        const int grow = out_row(t0 + u);
-        o[set][u] = (p.beta && grow < M && gcol < p.N) ? *reinterpret_cast<const float4*>(Cf + (long)grow * p.ldc + gcol) : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    load_o(0, 0, 0);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      if (j > 0) wave_lds_fence();
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        float* const d = s32 + (i * 32 + 4 * lk) * (STG_LD / 2) + lr;
-#pragma unroll
-        for (int g = 0; g < L::NJ / 2; ++g)
-#pragma unroll
-          for (int w = 0; w < L::NV; ++w) d[L::acc_row(0, w) * (STG_LD / 2) + g * L::CW] = p.alpha * acc[i][j][L::reg_v(g, w)];
-      }
-      wave_lds_fence();
-      const int gcol = wcol0 + j * 32 + cc * 4;
-#pragma unroll
-      for (int t0 = 0; t0 < WAVE_M / 8; t0 += NB) {
-        const int set = (t0 / NB) & 1;
-        if (t0 + NB < WAVE_M / 8) load_o(j, t0 + NB, set ^ 1);
-        else if (j + 1 < TN) load_o(j + 1, 0, set ^ 1);
-#pragma unroll
-        for (int u = 0; u < NB; ++u) {
-          const int row = (t0 + u) * 8 + rr, grow = out_row(t0 + u);
-          float4 x = *reinterpret_cast<const float4*>(s32 + row * (STG_LD / 2) + cc * 4);
-          x.x += o[set][u].x; x.y += o[set][u].y; x.z += o[set][u].z; x.w += o[set][u].w;
-          if (grow < M && gcol < p.N) *reinterpret_cast<float4*>(Cf + (long)grow * p.ldc + gcol) = x;
-        }
-      }
-    }
-    return;
     }
     // fp32 staging, one 32-column half at a time: [128][36] floats (144-byte rows)
     float* s32 = reinterpret_cast<float*>(stg);

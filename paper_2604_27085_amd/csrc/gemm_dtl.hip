@@ -143,6 +143,258 @@ RP_DEV i32x4 raw_rsrc(const void* base, uint32_t bytes) {
   return r;
 }
 
+// What a kernel makes of its tile.  OUT_ROWS: bf16 (plus residual), fp32 (accumulating), SwiGLU forward; OUT_SWIGLU_BWD: that epilogue;
+// both on transposed accumulators, straight from the registers.  OUT_COLS: the epilogues in which a lane owns columns (cross-entropy), and
+// the rare ones, through LDS (gemm_device.hpp).
+enum { OUT_ROWS = 0, OUT_SWIGLU_BWD = 1, OUT_COLS = 2 };
+
+RP_DEV float acc_read(const f32x4& a, int e) {
+  float x;
+  asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(a[e]));
+  return x;
+}
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+RP_DEV void buf_store16(rsrc_t r, uint32_t off, const uint4& v) {
+  __builtin_amdgcn_raw_buffer_store_b128(u32x4{v.x, v.y, v.z, v.w}, r, (int)off, 0, 0);
+}
+
+// A transposed accumulator gives lane group g (lane / 16) columns 4 g .. 4 g + 3 of the row lane % 16 of a 16x16 tile.  Of two tiles side by
+// side, after an exchange between neighbouring groups, it holds eight consecutive columns from pair_column(g) of the 32 on.
+RP_DEV int pair_column(int g) { return ((g & 1) << 4) | ((g >> 1) << 3); }
+RP_DEV uint4 join_pair(const uint2& l, const uint2& r) {
+  const auto x = __builtin_amdgcn_permlane16_swap(l.x, r.x, false, false), y = __builtin_amdgcn_permlane16_swap(l.y, r.y, false, false);
+  return make_uint4(x[0], y[0], x[1], y[1]);
+}
+// Two 16-byte chunks of every row of a row tile, l on the left of r (four lanes hold 64 bytes of a row each) -> 128 bytes of rows 0 .. 7 (a) and of
+// rows 8 .. 15 (b), in order, after an exchange between the lanes of rows eight apart; hi: the lane's row is one of the latter.
+RP_DEV uint32_t from_row8(uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xf, 0xf, false); }    // row_ror:8
+RP_DEV void word_to_lines(bool hi, uint32_t l, uint32_t r, uint32_t& a, uint32_t& b) {
+  const uint32_t t = from_row8(hi ? l : r);
+  a = hi ? t : l;
+  b = hi ? r : t;
+}
+RP_DEV void to_lines(bool hi, const uint4& l, const uint4& r, uint4& a, uint4& b) {
+  word_to_lines(hi, l.x, r.x, a.x, b.x);
+  word_to_lines(hi, l.y, r.y, a.y, b.y);
+  word_to_lines(hi, l.z, r.z, a.z, b.z);
+  word_to_lines(hi, l.w, r.w, a.w, b.w);
+}
+RP_DEV void unpack8(const uint4& u, float (&f)[8]) {
+  f[0] = bf16_lo(u.x); f[1] = bf16_hi(u.x); f[2] = bf16_lo(u.y); f[3] = bf16_hi(u.y);
+  f[4] = bf16_lo(u.z); f[5] = bf16_hi(u.z); f[6] = bf16_lo(u.w); f[7] = bf16_hi(u.w);
+}
+RP_DEV uint4 pack8(const float (&f)[8]) {
+  return make_uint4(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7]));
+}
+
+// The wave's 128x128 block of transposed tiles to memory, from the registers: no LDS, no barrier.  Whatever goes in or out does so as whole
+// 128-byte lines, eight rows an instruction (64 bytes of sixteen rows are as good for stores alone, but loads of half lines cost more).
+// Rows and columns past the end fall outside the descriptors.  A tile is bound by what it moves while the CU's matrix pipe stands still, and
+// more of it in flight is not better: columns outermost, a step's loads ahead, of as few rows as cover the latency.  Against staging each
+// half of the block through LDS, same box, us: 8192 x 8192 x 2048 NT 205 -> 191, with a residual 234 -> 221 (4 | 8 row tiles a step 226 | 230, all
+// at once 224), fp32 accumulating TN 285 -> 278 (rows outermost, two | four row tiles ahead 296 | 308); 8192 x 24576 x 4096 with SwiGLU forward
+// 1220 -> 1173; 8192 x 12288 x 4096 with SwiGLU backward 737 -> 697 (2 | 4 row tiles a step 701 | 714).
+template <bool GRP, bool SWB>
+RP_DEV void store_rows(const GemmArgs& p, f32x4 (&acc)[8][8], int m0, int Mlim, int n0, int wm, int wn, int lane, int fold) {
+  const int r16 = lane & 15, g = lane >> 4;
+  const bool hi = r16 & 8;
+  const int rows = Mlim - m0 < 256 ? Mlim - m0 : 256;                 // of the tile, from m0 on
+  // descriptor of the tile's rows of a matrix with `cols` columns of es bytes and row stride ld
+  auto tile_rsrc = [&](const void* base, long ld, int es, int cols) {
+    return make_rsrc(static_cast<const char*>(base) + (long)m0 * ld * es, (uint32_t)(((long)(rows - 1) * ld + cols) * es));
+  };
+  // byte offset of the lane's 16 bytes in row tile i, 128 bytes of a row from column c on; d = 0, 8: its upper, lower rows
+  auto at = [&](int i, int d, int c, int lim, long ld, int es) __attribute__((always_inline)) {
+    const int col = c + (hi ? 64 / es : 0) + (es == 2 ? pair_column(g) : 4 * g);
+    const int row = (GRP ? (i >> 1) * 64 + wm * 32 + (i & 1) * 16 : wm * 128 + i * 16) + (r16 & 7) + d;
+    return col < lim ? ((uint32_t)row * (uint32_t)ld + (uint32_t)col) * (uint32_t)es : OOB;
+  };
+  if (p.alpha != 1.f) {       // uniform, rare
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float x = p.alpha * acc_read(acc[i][j], e);
+          float y;
+          asm volatile("v_accvgpr_write_b32 %0, %1" : "=a"(y) : "v"(x));
+          acc[i][j][e] = y;
+        }
+    asm volatile("s_nop 7");
+  }
+  // tiles j, j + 1 as bf16, eight columns a lane
+  auto pair = [&](int i, int j) __attribute__((always_inline)) {
+    uint2 t[2];
+#pragma unroll
+    for (int w = 0; w < 2; ++w)
+      t[w] = make_uint2(pack_bf16x2(acc_read(acc[i][j + w], 0), acc_read(acc[i][j + w], 1)), pack_bf16x2(acc_read(acc[i][j + w], 2), acc_read(acc[i][j + w], 3)));
+    return join_pair(t[0], t[1]);
+  };
+  if constexpr (!SWB) {
+    if (fold) {
+      // gate | up, and silu(gate) * up from the rounded values (what a SwiGLU kernel would read back); tiles j and j + 4 go together
+      const int c0 = (n0 >> 1) + wn * 64;                             // gate column of the wave
+      const rsrc_t rg = tile_rsrc(p.C, p.ldc, 2, fold), ru = tile_rsrc(static_cast<const bf16*>(p.C) + fold, p.ldc, 2, fold), ra = tile_rsrc(p.C2, p.ldc2, 2, fold);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        uint4 gv[2], uv[2];
+        to_lines(hi, pair(i, 0), pair(i, 2), gv[0], gv[1]);
+        to_lines(hi, pair(i, 4), pair(i, 6), uv[0], uv[1]);
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+          const uint32_t o = at(i, 8 * w, c0, fold, p.ldc, 2);
+          buf_store16(rg, o, gv[w]);
+          buf_store16(ru, o, uv[w]);
+          float gf[8], uf[8];
+          unpack8(gv[w], gf);
+          unpack8(uv[w], uf);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) gf[e] = silu_f32(gf[e]) * uf[e];
+          buf_store16(ra, at(i, 8 * w, c0, fold, p.ldc2, 2), pack8(gf));
+        }
+      }
+      return;
+    }
+  }
+  const int c0 = n0 + wn * 128;
+  if constexpr (SWB) {
+    const rsrc_t rg = tile_rsrc(p.R, p.ldr, 2, p.N), ru = tile_rsrc(static_cast<const bf16*>(p.R) + p.N, p.ldr, 2, p.N),
+                 sg = tile_rsrc(p.C, p.ldc, 2, p.N), su = tile_rsrc(static_cast<const bf16*>(p.C) + p.N, p.ldc, 2, p.N);
+    constexpr int RT = 1, NS = 16 / RT;      // step n: 64 columns (n / (NS / 2)), RT row tiles
+    uint4 gv[2][2 * RT], uv[2][2 * RT];
+    auto load_gu = [&](int n) __attribute__((always_inline)) {
+#pragma unroll
+      for (int u = 0; u < 2 * RT; ++u) {
+        const uint32_t o = at(RT * (n % (NS / 2)) + (u >> 1), 8 * (u & 1), c0 + 64 * (n / (NS / 2)), p.N, p.ldr, 2);
+        gv[n & 1][u] = buf_load16(rg, o, 0);
+        uv[n & 1][u] = buf_load16(ru, o, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    load_gu(0);
+#pragma unroll
+    for (int n = 0; n < NS; ++n) {
+      if (n + 1 < NS) load_gu(n + 1);
+#pragma unroll
+      for (int t = 0; t < RT; ++t) {
+        const int i = RT * (n % (NS / 2)) + t, q = n / (NS / 2);
+        uint4 d[2];
+        to_lines(hi, pair(i, 4 * q), pair(i, 4 * q + 2), d[0], d[1]);
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+          uint4 dg, du;
+          swiglu_bwd8(d[w], gv[n & 1][2 * t + w], uv[n & 1][2 * t + w], dg, du);
+          const uint32_t o = at(i, 8 * w, c0 + 64 * q, p.N, p.ldc, 2);
+          buf_store16(sg, o, dg);
+          buf_store16(su, o, du);
+        }
+      }
+    }
+    return;
+  }
+  if (p.epi == EPI_BF16) {
+    const rsrc_t rc = tile_rsrc(p.C, p.ldc, 2, p.N);
+    if (!p.R) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          uint4 v[2];
+          to_lines(hi, pair(i, 4 * q), pair(i, 4 * q + 2), v[0], v[1]);
+#pragma unroll
+          for (int w = 0; w < 2; ++w) buf_store16(rc, at(i, 8 * w, c0 + 64 * q, p.N, p.ldc, 2), v[w]);
+        }
+      return;
+    }
+    const rsrc_t rr = tile_rsrc(p.R, p.ldr, 2, p.N);
+    constexpr int RT = 2, NS = 16 / RT;      // step n: 64 columns (n / (NS / 2)), RT row tiles
+    uint4 rv[2][2 * RT];
+    auto load_r = [&](int n) __attribute__((always_inline)) {
+#pragma unroll
+      for (int u = 0; u < 2 * RT; ++u) rv[n & 1][u] = buf_load16(rr, at(RT * (n % (NS / 2)) + (u >> 1), 8 * (u & 1), c0 + 64 * (n / (NS / 2)), p.N, p.ldr, 2), 0);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    load_r(0);
+#pragma unroll
+    for (int n = 0; n < NS; ++n) {
+      if (n + 1 < NS) load_r(n + 1);
+#pragma unroll
+      for (int t = 0; t < RT; ++t) {
+        const int i = RT * (n % (NS / 2)) + t, q = n / (NS / 2);
+        uint4 x[2][2];      // [left, right chunk][columns 0 .. 3, 4 .. 7] in fp32
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          uint32_t f[8];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const auto y = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc_read(acc[i][4 * q + 2 * c], e)), __float_as_uint(acc_read(acc[i][4 * q + 2 * c + 1], e)), false, false);
+            f[e] = y[0];
+            f[4 + e] = y[1];
+          }
+          x[c][0] = make_uint4(f[0], f[1], f[2], f[3]);
+          x[c][1] = make_uint4(f[4], f[5], f[6], f[7]);
+        }
+        uint4 v[2][2];      // [upper, lower rows][columns]
+#pragma unroll
+        for (int e = 0; e < 2; ++e) to_lines(hi, x[0][e], x[1][e], v[0][e], v[1][e]);
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+          float r[8];
+          unpack8(rv[n & 1][2 * t + w], r);
+          const uint32_t f[8] = {v[w][0].x, v[w][0].y, v[w][0].z, v[w][0].w, v[w][1].x, v[w][1].y, v[w][1].z, v[w][1].w};
+#pragma unroll
+          for (int e = 0; e < 8; ++e) r[e] += __uint_as_float(f[e]);
+          buf_store16(rc, at(i, 8 * w, c0 + 64 * q, p.N, p.ldc, 2), pack8(r));
+        }
+      }
+    }
+    return;
+  }
+  // fp32, plus the old output where it accumulates; blockIdx.y: slice of a reduction split
+  const rsrc_t rc = tile_rsrc(reinterpret_cast<float*>(p.C) + (long)blockIdx.y * p.c_slice_stride, p.ldc, 4, p.N);
+  auto raw = [&](int i, int j) __attribute__((always_inline)) {
+    return make_uint4(__float_as_uint(acc_read(acc[i][j], 0)), __float_as_uint(acc_read(acc[i][j], 1)), __float_as_uint(acc_read(acc[i][j], 2)), __float_as_uint(acc_read(acc[i][j], 3)));
+  };
+  if (!p.beta) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        uint4 v[2];
+        to_lines(hi, raw(i, 2 * q), raw(i, 2 * q + 1), v[0], v[1]);
+#pragma unroll
+        for (int w = 0; w < 2; ++w) buf_store16(rc, at(i, 8 * w, c0 + 32 * q, p.N, p.ldc, 4), v[w]);
+      }
+    return;
+  }
+  constexpr int RT = 4, NS = 32 / RT;      // step n: 32 columns (n / (NS / 4)), RT row tiles
+  uint4 ov[2][2 * RT];
+  auto load_o = [&](int n) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < 2 * RT; ++u) ov[n & 1][u] = buf_load16(rc, at(RT * (n % (NS / 4)) + (u >> 1), 8 * (u & 1), c0 + 32 * (n / (NS / 4)), p.N, p.ldc, 4), 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  load_o(0);
+#pragma unroll
+  for (int n = 0; n < NS; ++n) {
+    if (n + 1 < NS) load_o(n + 1);
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      const int i = RT * (n % (NS / 4)) + t, q = n / (NS / 4);
+      uint4 v[2];
+      to_lines(hi, raw(i, 2 * q), raw(i, 2 * q + 1), v[0], v[1]);
+#pragma unroll
+      for (int w = 0; w < 2; ++w) {
+        const uint4 o = ov[n & 1][2 * t + w];
+        buf_store16(rc, at(i, 8 * w, c0 + 32 * q, p.N, p.ldc, 4),
+                    make_uint4(__float_as_uint(__uint_as_float(v[w].x) + __uint_as_float(o.x)), __float_as_uint(__uint_as_float(v[w].y) + __uint_as_float(o.y)),
+                               __float_as_uint(__uint_as_float(v[w].z) + __uint_as_float(o.z)), __float_as_uint(__uint_as_float(v[w].w) + __uint_as_float(o.w))));
+      }
+    }
+  }
+}
+
 // TB: the B operand is [K, N] (reduction index strided, the NN product); its units keep that layout and its fragments
 // are read with the transposing LDS load.  TA (with TB: the TN product): the same for A, which is [K, M].
 // GRP: grouped mode.  A group's last tile of 256 rows is rarely full (2048 tokens on 8 of 128 experts: 128 rows per expert on
@@ -153,7 +405,7 @@ RP_DEV i32x4 raw_rsrc(const void* base, uint32_t bytes) {
 // 2995 -> 2876.  What bounds the 128-row tiles then is the experts' weights (gate/up 3.5 GB in 706 us, matrix pipe 31 % busy).
 // blk: the output tile of the product (-1: the workgroup's number); grouped: the entry gm of the table and the tile column gn.
 // ONCE: B is loaded non-temporally (see gemm_once_kernel).
-template <bool TA, bool TB, bool GRP, bool ONCE = false>
+template <bool TA, bool TB, bool GRP, bool ONCE = false, int OUT = OUT_ROWS>
 RP_DEV void dtl_block(const GemmArgs& p, int blk, int gm = 0, int gn = 0) {
   static_assert((!TA || TB) && !(GRP && TA), "not a layout of this library");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -409,7 +661,10 @@ RP_DEV void dtl_block(const GemmArgs& p, int blk, int gm = 0, int gn = 0) {
           __builtin_amdgcn_s_waitcnt(0x0f70 | 8);
           __syncthreads();
         }
-        if constexpr (i < 2 * NB) mfma16_in_place(acc[i][j], af[areg(st, i)], bfr[st][j]);
+        if constexpr (i < 2 * NB) {
+          if constexpr (OUT == OUT_COLS) mfma16_in_place(acc[i][j], af[areg(st, i)], bfr[st][j]);
+          else mfma16_in_place(acc[i][j], bfr[st][j], af[areg(st, i)]);      // the transposed tile
+        }
         constexpr int rd = P::read(sl);
         if constexpr (rd >= 0) {
           constexpr int rs = sl < 64 ? 1 : 0;    // the step whose fragments these are
@@ -445,55 +700,30 @@ RP_DEV void dtl_block(const GemmArgs& p, int blk, int gm = 0, int gn = 0) {
   } else {
     main_loop(IC<4>{});
   }
-  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): the empty loads past the end write LDS too
-  __syncthreads();                      // every wave is done with the operand stages: the epilogue reuses the LDS
-
-  // The accumulators live in the AGPR half of the register file, which only MFMAs and copies can address.  Left to the
-  // compiler all 256 are copied out at once behind the loop and half of them spilled; here each 128x64 half is copied
-  // out right before its epilogue.
-  f32x16 half[TM][TN];
-  auto fetch = [&](int h) __attribute__((always_inline)) {
+  asm volatile("s_nop 7\n\ts_nop 7");   // the last MFMA has retired; the copies out of the accumulators are invisible to the hazard checks
+  if constexpr (OUT != OUT_COLS) {
+    // (nothing here reads LDS; the empty loads past the end still write it, but it is the workgroup's to its end)
+    store_rows<GRP, OUT == OUT_SWIGLU_BWD>(p, acc, m0, Mlim, n0, wm, wn, lane, fold);
+  } else {
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): the empty loads past the end write LDS too
+    __syncthreads();                      // every wave is done with the operand stages: the epilogue reuses the LDS
+    // The accumulators live in the AGPR half of the register file, which only MFMAs and copies can address.  Left to the
+    // compiler all 256 are copied out at once behind the loop and half of them spilled; here each 128x64 half is copied
+    // out right before its epilogue.
+    f32x16 half[TM][TN];
+    auto write_half = [&](auto htag) __attribute__((always_inline)) {
+      constexpr int h = decltype(htag)::value;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(half[i][j][v]) : "a"(acc[2 * i + (v >> 3)][4 * h + 2 * j + ((v >> 2) & 1)][v & 3]));
-  };
-  asm volatile("s_nop 7\n\ts_nop 7");   // the last MFMA has long retired (a barrier ago); the copies are invisible to the hazard checks
-  constexpr int IS = GRP ? 64 : 32;      // a wave's blocks of 32 rows: every other one, or consecutive
-  const int wrow = m0 + wm * (GRP ? 32 : 128);
-  const int part_row = p.part_row0 + tile_m * 2 + wm;
-  if (fold) {
-    // gate | up as by EPI_BF16, then silu(gate) * up from the rounded values (what the SwiGLU kernel would read back)
-    GemmArgs q = p;
-    q.epi = EPI_BF16;
-    const int gcol = (n0 >> 1) + wn * 64;
-    fetch(1);
-    epilogue<IS, true, true>(q, Mlim, half, smem, wave, lane, wrow, gcol + fold, part_row);
-    q.N = fold;     // the last tile's gate columns end where the up columns begin
-    fetch(0);
-    epilogue<IS, true, true>(q, Mlim, half, smem, wave, lane, wrow, gcol, part_row);
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          float up;
-          asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(up) : "a"(acc[2 * i + (v >> 3)][4 + 2 * j + ((v >> 2) & 1)][v & 3]));
-          const float g = bf16_bits_to_f32(f32_to_bf16_bits(half[i][j][v])), u = bf16_bits_to_f32(f32_to_bf16_bits(up));
-          half[i][j][v] = silu_f32(g) * u;
-        }
-    q.C = p.C2;
-    q.ldc = p.ldc2;
-    epilogue<IS, true, true>(q, Mlim, half, smem, wave, lane, wrow, gcol, part_row);
-    return;
+          for (int v = 0; v < 16; ++v) half[i][j][v] = acc_read(acc[2 * i + (v >> 3)][4 * h + 2 * j + ((v >> 2) & 1)], v & 3);
+      epilogue<true>(p, Mlim, half, smem, wave, lane, m0 + wm * 128, n0 + wn * 128 + 64 * h, p.part_row0 + tile_m * 2 + wm);
+    };
+    write_half(IC<0>{});
+    write_half(IC<1>{});
   }
-  fetch(0);
-  epilogue<IS, true, true>(p, Mlim, half, smem, wave, lane, wrow, n0 + wn * 128, part_row);
-  fetch(1);
-  epilogue<IS, true, true>(p, Mlim, half, smem, wave, lane, wrow, n0 + wn * 128 + 64, part_row);
 }
 
 // The entry of the table and the tile column of a workgroup of a grouped product (the table's length is known on the device only:
@@ -505,17 +735,19 @@ RP_DEV bool grouped_tile(const GemmArgs& p, int& tile_m, int& tile_n) {
   return true;
 }
 
-// SWB: the instance for EPI_SWIGLU_BWD alone.  Its epilogue is the longest of all; compiled together with the others a third of its
-// scalars live in vector registers (8192 x 12288 x 4096 NN 830 -> 812 us with its loads a batch ahead).
-template <bool TA, bool TB, bool GRP, bool SWB>
+template <bool TA, bool TB, bool GRP, int OUT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) gemm_dtl_kernel(const GemmArgs p) {
-  GemmArgs q = p;
-  if constexpr (SWB) q.epi = EPI_SWIGLU_BWD;
   int tile_m = 0, tile_n = 0;
   if constexpr (GRP) {
     if (!grouped_tile(p, tile_m, tile_n)) return;
   }
-  dtl_block<TA, TB, GRP>(q, -1, tile_m, tile_n);
+  if constexpr (OUT == OUT_COLS && TB) {      // only the atomic output comes here with these layouts
+    GemmArgs q = p;
+    q.epi = EPI_F32_ATOMIC;
+    dtl_block<TA, TB, GRP, false, OUT>(q, -1);
+  } else {
+    dtl_block<TA, TB, GRP, false, OUT>(p, -1, tile_m, tile_n);
+  }
 }
 
 // Grouped products whose groups have one tile each: a group's weights are then read once in the launch (every 256 columns by one
@@ -570,10 +802,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
 
 }  // namespace
 
-template <bool TA, bool TB, bool GRP = false, bool SWB = false, bool ONCE = false>
+template <bool TA, bool TB, bool GRP = false, int OUT = OUT_ROWS, bool ONCE = false>
 static hipError_t dtl_launch_one(hipStream_t st, const GemmArgs& a) {
   static bool attr_done = false;
-  auto kern = gemm_dtl_kernel<TA, TB, GRP, SWB>;
+  auto kern = gemm_dtl_kernel<TA, TB, GRP, OUT>;
   if constexpr (ONCE) kern = gemm_once_kernel<TB>;
   if (!attr_done) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, DTL_SMEM);
@@ -589,14 +821,20 @@ static hipError_t dtl_launch_one(hipStream_t st, const GemmArgs& a) {
 hipError_t gemm_dtl_launch(hipStream_t st, const GemmArgs& a, int layout) {
   if (a.grp_tab) {
     const bool once = a.grp_once;
-    if (layout == GEMM_NT) return once ? dtl_launch_one<false, false, true, false, true>(st, a) : dtl_launch_one<false, false, true>(st, a);
-    if (layout == GEMM_NN) return once ? dtl_launch_one<false, true, true, false, true>(st, a) : dtl_launch_one<false, true, true>(st, a);
+    if (layout == GEMM_NT) return once ? dtl_launch_one<false, false, true, OUT_ROWS, true>(st, a) : dtl_launch_one<false, false, true>(st, a);
+    if (layout == GEMM_NN) return once ? dtl_launch_one<false, true, true, OUT_ROWS, true>(st, a) : dtl_launch_one<false, true, true>(st, a);
     return hipErrorInvalidValue;
   }
+  const bool rows = a.epi == EPI_BF16 || a.epi == EPI_F32 || a.epi == EPI_SWIGLU_FWD;
   switch (layout) {
-    case GEMM_NT: return dtl_launch_one<false, false>(st, a);
-    case GEMM_NN: return a.epi == EPI_SWIGLU_BWD ? dtl_launch_one<false, true, false, true>(st, a) : dtl_launch_one<false, true>(st, a);
-    default: return dtl_launch_one<true, true>(st, a);
+    case GEMM_NT: return rows ? dtl_launch_one<false, false>(st, a) : dtl_launch_one<false, false, false, OUT_COLS>(st, a);
+    case GEMM_NN:
+      if (a.epi == EPI_SWIGLU_BWD) return dtl_launch_one<false, true, false, OUT_SWIGLU_BWD>(st, a);
+      if (!rows && a.epi != EPI_F32_ATOMIC) return hipErrorInvalidValue;
+      return rows ? dtl_launch_one<false, true>(st, a) : dtl_launch_one<false, true, false, OUT_COLS>(st, a);
+    default:
+      if (!rows && a.epi != EPI_F32_ATOMIC) return hipErrorInvalidValue;
+      return rows ? dtl_launch_one<true, true>(st, a) : dtl_launch_one<true, true, false, OUT_COLS>(st, a);
   }
 }
 
