@@ -18,10 +18,9 @@
 // Measured on MI355X the 256x256 tile asks L2 for one byte per 128 FLOP; the matrix pipe is busy 75-79 % of the kernel's
 // cycles and the chip runs power-limited near 1.65 GHz under it.  Tried and dropped here: touching lines two tiles
 // ahead to pull them into L2, touching the first lines of the workgroup's successor tile before the epilogue,
-// staggered K-loop starts, a reduction split merged by the last workgroup to arrive.  The NT product on 256x256 tiles
-// has a faster kernel of its own (gemm_dtl.hip: four waves of 128x128, one per SIMD, operands loaded straight into
-// LDS); this file keeps every other tile and layout, and the eight-wave 256x256 NT instance as the reference it is
-// tested against bit for bit.
+// staggered K-loop starts, a reduction split merged by the last workgroup to arrive.  Most products on 256x256 tiles run
+// on a kernel of their own (gemm_dtl.hip: four waves of 128x128, one per SIMD, operands loaded straight into LDS); the eight-wave 256x256
+// kernel here is for short reductions and skinny outputs, and the reference that one is tested against bit for bit.
 // Outputs too small to fill the chip with 256x256 tiles use a 256x128 tile worked
 // on by two wave groups that split every K tile (merged through LDS) or the small tiles; products that would still leave
 // CUs idle are split along the reduction: the slices write partial products to scratch memory and a
@@ -489,16 +488,16 @@ __global__ void __launch_bounds__(256) gemm_arrange_kernel(const bf16* __restric
 // between these (250 MB and more in eight slices) and the weight gradients and bf16 results of short batches, which are 2-3 % slower
 // with fewer slices; nothing was measured in between.  Added to the elapsed time is the chip time the
 // workgroups use up (their summed time over 256 CUs): what is left over belongs to other streams, so a small tile has to buy
-// enough latency for the extra operand traffic it causes.  The weight of that term, both ends measured on whole stage calls,
-// one stream | three streams at once, against choosing by elapsed time alone: a backward stage of 928 tokens at h = 2048
-// takes 730 | 507 us at weight 1, 786 | 478 at 2; one of 4096 tokens 1959 | 1764 and 2083 | 1632 (the larger tile on half of
-// the chip); one of 2 x 508 tokens at h = 4096 1288 | 968 and 1307 | 962.  1.3 is the last value at which no call on one
-// stream loses.  What it costs: a forward stage of 1000 tokens at h = 2048 is 229 -> 180 us on one stream against the 256x128
-// tiles alone, but 127 -> 143 when three such calls really run at once.
-constexpr double CHIP_WEIGHT = 1.3;
+// enough latency for the extra operand traffic it causes.  The weight of that term, measured on whole stage calls, three streams at once | one
+// stream, us, with weight 0.7 | 1.0 | 1.3 and, in front, with the 256x256 tile as expensive as its eight-wave kernel was (0.95 + 0.6 a K tile, 6 for
+// the epilogue) at 1.3: backward of a full fine-tune of 4096 tokens at h = 2048 1585 | 1440 | 1441 | 1441 and 1669 | 1730 | 1733 | 1740 (its products
+// of 128 tiles leave half of the chip to others); forward of 1000 tokens there 137 | 137 | 132 | 132 and 205 | 210 | 215 | 215; LoRA backward of
+// 2 x 508 at h = 4096 960 | 960 | 967 | 966 and 1115 | 1122 | 1145 | 1150; mixture-of-experts backward of 2048 3068 | 3053 | 3054 | 3050 and 3179 | 3250 |
+// 3243 | 3235.
+constexpr double CHIP_WEIGHT = 0.7;
 struct TileModel { int bm, bn; double tau, tau_fill, epi; };
 constexpr TileModel TILE_MODEL[9] = {{},                          // by tile number
-                                     {256, 256, 0.95, 0.60, 6.0}, {256, 128, 0.60, 0.35, 4.0}, {128, 128, 0.55, 0.0, 3.5},
+                                     {256, 256, 0.78, 0.58, 4.5}, {256, 128, 0.60, 0.35, 4.0}, {128, 128, 0.55, 0.0, 3.5},
                                      {128, 64, 0.36, 0.0, 3.5},   {256, 128, 0.53, 0.40, 5.0}, {}, {}, {64, 64, 0.31, 0.0, 3.5}};
 
 double tile_cost(int tile, int splits, int M, int N, int k_tiles, int epi) {
@@ -658,21 +657,26 @@ hipError_t gemm_launch(hipStream_t st, int layout, const GemmArgs& a_in, int til
     a.C = a.split_ws; a.ldc = a.N; a.beta = 0; a.c_slice_stride = (long)a.M * a.N;
     a.epi = EPI_F32; a.R = nullptr;
   }
-  // Products on 256x256 tiles run the four-wave kernel that loads its operands straight into LDS (gemm_dtl.hip) when
-  // the reduction is at least 40 K tiles long -- its per-tile fixed cost (four waves doing the epilogue in two halves, a
-  // deeper prologue) is higher, and at K = 2048 with a cross-entropy or SwiGLU epilogue the eight-wave kernel is 9 %
-  // faster -- unless a kernel is asked for by name (hint 1: eight waves, hint 7: four) or the variant has no
-  // counterpart there.
-  // Skinny outputs (the LoRA products, bound by reading the other operand once) stay on the eight-wave kernel too: +14 %.
+  // Products on 256x256 tiles run the four-wave kernel that loads its operands straight into LDS (gemm_dtl.hip) unless a kernel is asked for by
+  // name (hint 1: eight waves, hint 7: four), the variant has no counterpart there, or the reduction is short: its 16x16x32 instructions are
+  // ahead per K tile, its start and its one wave per SIMD cost more.  Eight waves | four, us, K = 256, 512, 1024, 2048: 8192 x 8192 NT 48.4 | 49.5,
+  // 71.1 | 68.7, 119 | 109, 217 | 191, with a residual 109 | 88, 131 | 104, 176 | 145, 281 | 228, fp32 accumulating TN 121 | 127, 142 | 144, 192 | 187,
+  // 293 | 278; 4096 x 4096 NT 15.2 | 15.4, 20.3 | 19.7, 32.1 | 29.5, 57.5 | 50.1; on half of the chip (128 tiles), where the power does
+  // not bind, 2048 x 4096 NT 12.8 | 14.6, 17.4 | 18.9, 25.8 | 26.7, 42.3 | 42.4.  Cross-entropy epilogues, which stage their tile, are
+  // longer in four waves: with them from 40 K tiles on.
+  // Skinny outputs (the LoRA products, bound by reading the other operand once) stay on the eight-wave kernel: +14 %.
   // Grouped products take it too (it spares a tile's empty rows their matrix instructions), but for reductions of up to 16 K tiles over
   // weights that the caches hold (grp_cached): these are bound by that fixed cost, and by fetching the larger code.  Forward
   // of a layer, us, eight waves | four: 8 experts of 256 x 96, 136 tokens 71 | 79 (a product 11 | 16), 1064 92 | 100; of 512 x 512, 136 | 4096 tokens
   // 83 | 87, 151 | 161; of 768 x 3072, 16384 tokens 1004 | 1039; 32 of 512 x 1024, 4096 tokens 220 | 233.  With weights from
   // memory the four waves are ahead: 64 of 1024 x 512 (201 MB), 4096 | 16384 tokens 276 | 268, 857 | 833; 128 of 2048 x 768, 16384 2521 | 2468.
   const bool short_grp = a.grp_tab && a.grp_cached && !a.grp_once && a.K <= 1024;
+  const bool ce = a.epi == EPI_CE_P || a.epi == EPI_CE_STATS || a.epi == EPI_CE_DZ || a.epi == EPI_F32_COLMAX;
+  const long big_tiles = (long)((a.M + 255) / 256) * ((a.N + 255) / 256) * ch.splits;
+  const int dtl_min_k = ce ? 2560 : big_tiles <= 128 ? 2048 : 512;
   // (the four-wave kernel addresses the 256 rows of an output tile with 31-bit byte offsets)
   const bool near_rows = a.ldc < 1L << 21 && a.ldr < 1L << 21 && a.ldc2 < 1L << 21;
-  const bool dtl = !near_rows ? false : a.grp_tab ? !short_grp : (tile == 1 && tile_hint != 1 && !a.run_flag && !a.b_direct && (tile_hint == 7 || (a.K + a.K2 >= 2560 && a.M > 64 && a.N > 64)));
+  const bool dtl = !near_rows ? false : a.grp_tab ? !short_grp : (tile == 1 && tile_hint != 1 && !a.run_flag && !a.b_direct && (tile_hint == 7 || (a.K + a.K2 >= dtl_min_k && a.M > 64 && a.N > 64)));
   if (dtl) {
     e = gemm_dtl_launch(st, a, layout);
   } else {

@@ -31,10 +31,9 @@
 //   NN        B's units keep the operand's [K, N] layout (64 rows of 512 bytes; the 32-byte segment of MFMA tile column s of row k at
 //             segment s ^ seg_swizzle(k)), its fragments are two transposing reads (ds_read_b64_tr_b16) each.
 //   TN        the same for A.
-// Second operand pair, row map, reduction slices and every epilogue of gemm_device.hpp (applied to the two 128x64 halves
-// of a wave's block in turn) as in gemm.hip; results are bit-identical to its 256x256 tile (the same order of the
-// reduction).  Most grouped products (GRP below) run here.  gemm_launch picks this kernel for reductions of 40 K tiles or more and
-// outputs that are not skinny: its fixed cost per output tile is higher than the eight-wave kernel's.
+// Second operand pair, row map, reduction slices and every epilogue as in gemm.hip; results are bit-identical to its 256x256 tile (the same
+// order of the reduction).  Most grouped products (GRP below) run here, and of the others those that gemm_launch sends (all but short
+// reductions and skinny outputs).
 #include "gemm_device.hpp"
 #include <type_traits>
 #include <utility>
