@@ -662,8 +662,9 @@ hipError_t gemm_launch(hipStream_t st, int layout, const GemmArgs& a_in, int til
   // ahead per K tile, its start and its one wave per SIMD cost more.  Eight waves | four, us, K = 256, 512, 1024, 2048: 8192 x 8192 NT 48.4 | 49.5,
   // 71.1 | 68.7, 119 | 109, 217 | 191, with a residual 109 | 88, 131 | 104, 176 | 145, 281 | 228, fp32 accumulating TN 121 | 127, 142 | 144, 192 | 187,
   // 293 | 278; 4096 x 4096 NT 15.2 | 15.4, 20.3 | 19.7, 32.1 | 29.5, 57.5 | 50.1; on half of the chip (128 tiles), where the power does
-  // not bind, 2048 x 4096 NT 12.8 | 14.6, 17.4 | 18.9, 25.8 | 26.7, 42.3 | 42.4.  Cross-entropy epilogues, which stage their tile, are
-  // longer in four waves: with them from 40 K tiles on.
+  // not bind, 2048 x 4096 NT 12.8 | 14.6, 17.4 | 18.9, 25.8 | 26.7, 42.3 | 42.4.  Cross-entropy epilogues that stage their tile are
+  // longer in four waves: with them from 40 K tiles on.  The probabilities (EPI_CE_P) go out from the registers there: trainable head of
+  // 151936 x 2048, 4096 tokens, 6437 us with eight waves, 6246 with four.
   // Skinny outputs (the LoRA products, bound by reading the other operand once) stay on the eight-wave kernel: +14 %.
   // Grouped products take it too (it spares a tile's empty rows their matrix instructions), but for reductions of up to 16 K tiles over
   // weights that the caches hold (grp_cached): these are bound by that fixed cost, and by fetching the larger code.  Forward
@@ -671,7 +672,7 @@ hipError_t gemm_launch(hipStream_t st, int layout, const GemmArgs& a_in, int til
   // 83 | 87, 151 | 161; of 768 x 3072, 16384 tokens 1004 | 1039; 32 of 512 x 1024, 4096 tokens 220 | 233.  With weights from
   // memory the four waves are ahead: 64 of 1024 x 512 (201 MB), 4096 | 16384 tokens 276 | 268, 857 | 833; 128 of 2048 x 768, 16384 2521 | 2468.
   const bool short_grp = a.grp_tab && a.grp_cached && !a.grp_once && a.K <= 1024;
-  const bool ce = a.epi == EPI_CE_P || a.epi == EPI_CE_STATS || a.epi == EPI_CE_DZ || a.epi == EPI_F32_COLMAX;
+  const bool ce = a.epi == EPI_CE_STATS || a.epi == EPI_CE_DZ || a.epi == EPI_F32_COLMAX;
   const long big_tiles = (long)((a.M + 255) / 256) * ((a.N + 255) / 256) * ch.splits;
   const int dtl_min_k = ce ? 2560 : big_tiles <= 128 ? 2048 : 512;
   // (the four-wave kernel addresses the 256 rows of an output tile with 31-bit byte offsets)

@@ -196,7 +196,7 @@ RP_DEV void epilogue(const GemmArgs& p, int M, const f32x16 (&acc)[TM][TN], unsi
       d[0] = (unsigned short)pk;
       d[STG_LD] = (unsigned short)(pk >> 16);
     };
-    if (p.epi == EPI_CE_P) {
+    if (!L16 && p.epi == EPI_CE_P) {      // (the four-wave kernel has its own)
       // p = exp(z - ref) for a frozen head's later vocabulary chunks: every lane owns token columns, so the chunk's
       // per-token maximum and sum of exponentials over the wave's 128 rows come from the registers; rows past the end of
       // the vocabulary are excluded from both (their staged values are never stored)

@@ -142,10 +142,10 @@ RP_DEV i32x4 raw_rsrc(const void* base, uint32_t bytes) {
   return r;
 }
 
-// What a kernel makes of its tile.  OUT_ROWS: bf16 (plus residual), fp32 (accumulating), SwiGLU forward; OUT_SWIGLU_BWD: that epilogue;
-// both on transposed accumulators, straight from the registers.  OUT_COLS: the epilogues in which a lane owns columns (cross-entropy), and
-// the rare ones, through LDS (gemm_device.hpp).
-enum { OUT_ROWS = 0, OUT_SWIGLU_BWD = 1, OUT_COLS = 2 };
+// What a kernel makes of its tile.  OUT_ROWS: bf16 (plus residual), fp32 (accumulating), SwiGLU forward; OUT_SWIGLU_BWD, OUT_CE_P: those
+// epilogues; all on transposed accumulators, straight from the registers.  OUT_COLS: the other cross-entropy epilogues, in which a lane owns
+// columns, and the rare ones, through LDS (gemm_device.hpp).
+enum { OUT_ROWS = 0, OUT_SWIGLU_BWD = 1, OUT_COLS = 2, OUT_CE_P = 3 };
 
 RP_DEV float acc_read(const f32x4& a, int e) {
   float x;
@@ -391,6 +391,118 @@ RP_DEV void store_rows(const GemmArgs& p, f32x4 (&acc)[8][8], int m0, int Mlim, 
                                __float_as_uint(__uint_as_float(v[w].z) + __uint_as_float(o.z)), __float_as_uint(__uint_as_float(v[w].w) + __uint_as_float(o.w))));
       }
     }
+  }
+}
+
+// 16 numbers a lane, one per column, reduced over the sixteen lanes r of its row: the lane ends with the result of column r.  Each step halves the
+// columns a lane keeps (by bits 3, 2, 1, 0 of r) in an exchange with the lane that differs in that bit (and, in the second step, the lower ones).
+template <class Op>
+RP_DEV float reduce_columns(float (&v)[16], int r, Op op) {
+  auto step = [&](auto ntag, auto dtag, bool up) __attribute__((always_inline)) {
+    constexpr int n = decltype(ntag)::value, dpp = decltype(dtag)::value;
+#pragma unroll
+    for (int k = 0; k < n; ++k) {
+      const float give = up ? v[k] : v[k + n];
+      v[k] = op(up ? v[k + n] : v[k], __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(give), dpp, 0xf, 0xf, false)));
+    }
+  };
+  step(IC<8>{}, IC<0x128>{}, r & 8);      // row_ror:8
+  step(IC<4>{}, IC<0x141>{}, r & 4);      // row_half_mirror
+  step(IC<2>{}, IC<0x4e>{}, r & 2);       // quad_perm [2, 3, 0, 1]
+  step(IC<1>{}, IC<0xb1>{}, r & 1);       // quad_perm [1, 0, 3, 2]
+  return v[0];
+}
+
+// EPI_CE_P of the wave's 128x128 block (rows are vocabulary entries, columns tokens) from transposed accumulators: a lane holds four consecutive
+// tokens of a row per tile.  The probabilities go out as in store_rows; the columns' maxima and sums are formed over the lane's eight rows
+// and then over the sixteen lanes that share its columns, 64 columns at a time, one per lane.  Bound by issue (two conversions, a
+// maximum, a sum and an exponential per number); frozen head of 151936 x 5120, 2040 tokens, staged through LDS 4964 us, from the registers
+// 4867; the trainable one of 2048, 4096 tokens 6434 and 6200.
+RP_DEV void store_ce_p(const GemmArgs& p, f32x4 (&acc)[8][8], int m0, int n0, int wm, int wn, int lane, int part_row) {
+  constexpr float LOG2E = 1.4426950408889634f, CAP = RP_CE_P_CLAMP * LOG2E;
+  const int r16 = lane & 15, g = lane >> 4;
+  const bool hi = r16 & 8;
+  const int rows = p.M - m0 < 256 ? p.M - m0 : 256, w0 = wm * 128;
+  const uint32_t ldc2 = (uint32_t)p.ldc * 2u;
+  const rsrc_t rc = make_rsrc(static_cast<const char*>(p.C) + (long)m0 * p.ldc * 2, (uint32_t)(((long)(rows - 1) * p.ldc + p.N) * 2));
+  const rsrc_t rl = make_rsrc(p.lse, (uint32_t)p.N * 4u), rt = make_rsrc(p.labels, (uint32_t)p.N * 4u);
+  auto columns = [&](auto qtag, auto fulltag) __attribute__((always_inline)) {
+    constexpr int q = decltype(qtag)::value;
+    constexpr bool FULL = decltype(fulltag)::value;
+    const int c0 = n0 + wn * 128 + 64 * q;
+    const int line = c0 + (hi ? 32 : 0) + pair_column(g);
+    const uint32_t at = (line < p.N ? (uint32_t)line * 2u : OOB) + (uint32_t)(r16 & 7) * ldc2;      // (past the end stays past the end)
+    float nr[16], mx[16], sum[16];
+    bool any = false;       // one of the lane's tokens has its label in the block
+    auto label_row = [&](uint32_t t) { return (int)t - p.row_offset - m0 - w0; };
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int c = c0 + 16 * j + 4 * g;
+      const uint4 l = buf_load16(rl, (uint32_t)c * 4u, 0), t = buf_load16(rt, (uint32_t)c * 4u, 0);      // past the end: zeros
+      const uint32_t lw[4] = {l.x, l.y, l.z, l.w}, tw[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        nr[4 * j + e] = -LOG2E * __uint_as_float(lw[e]);
+        any |= c < p.N && (uint32_t)label_row(tw[e]) < 128u;
+        mx[4 * j + e] = -INFINITY;
+        sum[4 * j + e] = 0.f;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const bool in = FULL || w0 + 16 * i + r16 < rows;
+      uint2 pk[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        float x[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float z = acc_read(acc[i][4 * q + j], e);
+          if constexpr (!FULL) z = in ? z : -INFINITY;       // (no probability, no maximum)
+          mx[4 * j + e] = fmaxf(mx[4 * j + e], z);
+          x[e] = __builtin_amdgcn_exp2f(fminf(fmaf(z, LOG2E, nr[4 * j + e]), CAP));
+          sum[4 * j + e] += x[e];
+        }
+        pk[j] = make_uint2(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]));
+      }
+      uint4 v[2];
+      to_lines(hi, join_pair(pk[0], pk[1]), join_pair(pk[2], pk[3]), v[0], v[1]);
+#pragma unroll
+      for (int w = 0; w < 2; ++w) {
+        buf_store16(rc, at + (uint32_t)(w0 + i * 16 + 8 * w) * ldc2, v[w]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (__builtin_amdgcn_ballot_w64(any)) {      // rare
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int c = c0 + 16 * j + 4 * g;
+        const uint4 t = buf_load16(rt, (uint32_t)c * 4u, 0);
+        const uint32_t tw[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int lab = label_row(tw[e]);
+          float z = 0.f;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const float x = acc_read(acc[i][4 * q + j], e);
+            z = lab >> 4 == i ? x : z;
+          }
+          if (c < p.N && (uint32_t)lab < 128u && (lab & 15) == r16) p.zlab[c + e] = z;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    const float m = reduce_columns(mx, r16, [](float a, float b) { return fmaxf(a, b); }), s = reduce_columns(sum, r16, [](float a, float b) { return a + b; });
+    const int col = c0 + 16 * (r16 >> 2) + 4 * g + (r16 & 3);
+    if (col < p.N) p.part[(long)part_row * p.part_ld + col] = make_float2(m, s);
+  };
+  if (rows == 256) {
+    columns(IC<0>{}, std::true_type{});
+    columns(IC<1>{}, std::true_type{});
+  } else {
+    columns(IC<0>{}, std::false_type{});
+    columns(IC<1>{}, std::false_type{});
   }
 }
 
@@ -702,7 +814,8 @@ RP_DEV void dtl_block(const GemmArgs& p, int blk, int gm = 0, int gn = 0) {
   asm volatile("s_nop 7\n\ts_nop 7");   // the last MFMA has retired; the copies out of the accumulators are invisible to the hazard checks
   if constexpr (OUT != OUT_COLS) {
     // (nothing here reads LDS; the empty loads past the end still write it, but it is the workgroup's to its end)
-    store_rows<GRP, OUT == OUT_SWIGLU_BWD>(p, acc, m0, Mlim, n0, wm, wn, lane, fold);
+    if constexpr (OUT == OUT_CE_P) store_ce_p(p, acc, m0, n0, wm, wn, lane, p.part_row0 + tile_m * 2 + wm);
+    else store_rows<GRP, OUT == OUT_SWIGLU_BWD>(p, acc, m0, Mlim, n0, wm, wn, lane, fold);
   } else {
     __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): the empty loads past the end write LDS too
     __syncthreads();                      // every wave is done with the operand stages: the epilogue reuses the LDS
@@ -826,7 +939,9 @@ hipError_t gemm_dtl_launch(hipStream_t st, const GemmArgs& a, int layout) {
   }
   const bool rows = a.epi == EPI_BF16 || a.epi == EPI_F32 || a.epi == EPI_SWIGLU_FWD;
   switch (layout) {
-    case GEMM_NT: return rows ? dtl_launch_one<false, false>(st, a) : dtl_launch_one<false, false, false, OUT_COLS>(st, a);
+    case GEMM_NT:
+      if (a.epi == EPI_CE_P) return dtl_launch_one<false, false, false, OUT_CE_P>(st, a);
+      return rows ? dtl_launch_one<false, false>(st, a) : dtl_launch_one<false, false, false, OUT_COLS>(st, a);
     case GEMM_NN:
       if (a.epi == EPI_SWIGLU_BWD) return dtl_launch_one<false, true, false, OUT_SWIGLU_BWD>(st, a);
       if (!rows && a.epi != EPI_F32_ATOMIC) return hipErrorInvalidValue;
