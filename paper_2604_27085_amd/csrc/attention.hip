@@ -1,23 +1,26 @@
 // Causal grouped-query attention on the gfx950 matrix cores, flash style: no s x s matrix leaves the CU, except
 // that a backward with room for it keeps dS in bf16 (see attn_ds_block).
 //
-// All kernels use v_mfma_f32_16x16x32_bf16 with the score tile computed TRANSPOSED relative to the row that is
-// being normalised: the accumulator layout gives every lane one column and four rows of a 16x16 tile, so with queries (forward,
-// dQ) as columns the softmax reductions are in-lane plus an exchange between the four lane groups (lane / 16), and the probabilities
-// already sit in the register layout the next MFMA wants as its B operand.  Two 16-row tiles make one 32-deep step; within it that
-// layout holds, for lane group g, the reduction indices {4g..4g+3, 16+4g..16+4g+3}; the A operand of the same MFMA is read from LDS in
-// exactly that order.  A wave owns 32 columns (two column tiles), so every fragment feeds two MFMAs.  An operand whose reduction index
-// is contiguous in memory (K for Q.K^T, V for dO.V^T, Q and dO in the score products of the dK/dV kernel) is read with plain 16-byte
-// LDS loads; an operand whose reduction index is the row index of the tile (V for P.V, K for dS.K, Q and dO for dK/dV) is read with
-// the transposing LDS load; nothing is transposed in registers.  All tiles have the row stride D + 16, which serves both kinds of reads
-// without bank conflicts.  Global loads are 16-byte buffer loads whose descriptor ends with the
-// sequence, so rows past the end read as zero without a branch.
-// Against v_mfma_f32_32x32x16_bf16 with strides of D + 8, D + 24 and D + 32, same box, us: backward (dQ by recomputation) 8192 x 32 heads
-// of 128 1802 -> 1666, 4096 x 16 282 -> 263, 2 x 508 x 32 53.5 -> 52.0, 3 x 1500 x 64 heads of 64 260 -> 235; forward 8192 x 32 509 -> 494,
-// 4096 x 16 91.2 -> 90.3, 3 x 1500 x 64 of 64 78.3 -> 76.3, but 1000 x 16 24.0 -> 25.2 and 512 x 32 of 64 9.9 -> 10.9.  The strides are most of
-// it (backward with D + 24 1802 -> 1735); what starts the dK/dV products (stat_start) saves an MFMA in nine of their score phase.  The
-// score products of the next key tile between the exponentials of this one (in slots that the compiler keeps, no spills) are 3 % slower in
-// the forward kernel of eight waves: what bounds it is the issue of the vector instructions, not a wave's serial chain.
+// All kernels compute the score tile TRANSPOSED relative to the row that is being normalised: an accumulator gives every lane one column, so
+// with queries (forward, dQ) as columns the softmax reductions are in-lane plus an exchange between the lanes that share a column, and the
+// probabilities already sit in the register layout the next MFMA wants as its B operand; the A operand of that MFMA is read from LDS in exactly
+// that order of the reduction.  An operand whose reduction index is contiguous in memory (K for Q.K^T, V for dO.V^T, Q and dO in the score
+// products of the dK/dV kernel) is read with plain 16-byte LDS loads; an operand whose reduction index is the row index of the tile (V for
+// P.V, K for dS.K, Q and dO for dK/dV) is read with the transposing LDS load; nothing is transposed in registers.  Global loads are 16-byte
+// buffer loads whose descriptor ends with the sequence, so rows past the end read as zero without a branch.
+//
+// The backward kernels use v_mfma_f32_16x16x32_bf16: a lane has four rows of a 16x16 tile, four lane groups (lane / 16) share a column, and two
+// 16-row tiles make one 32-deep step, which for lane group g holds the reduction indices {4g..4g+3, 16+4g..16+4g+3}.  A wave owns 32 columns
+// (two column tiles), so every fragment feeds two MFMAs.  All their tiles have the row stride D + 16, which serves both kinds of reads
+// without bank conflicts.  The forward kernel uses v_mfma_f32_32x32x16_bf16 (16 rows a lane, two half-waves share a column) on a K tile of row
+// stride D + 8 and a V tile of D + 32.
+// What was measured, 32x32x16 | 16x16x32 everywhere, two runs each on one box, us.  Backward (strides D + 8 and D + 24 | D + 16), 4096 x 16 heads of
+// 128 280 | 261, 8192 x 32 1811 | 1671, 16384 x 64 14760 | 13865, 1000 x 16 72.2 | 72.0, 2 x 508 x 32 53.5 | 51.9, 3 x 1500 x 64 heads of 64 261 | 234,
+// 512 x 32 of 64 34.4 | 34.2; the strides are most of it (backward 8192 x 32 with D + 24 1802 -> 1735), and what starts the dK/dV products
+// (stat_start) saves an MFMA in nine of their score phase.  Forward (D + 8 and D + 32 | D + 16), where the softmax takes as many issue slots as the
+// products and the narrower tile doubles their number: 128 x 16 heads of 128 7.2 | 7.6, 1000 x 16 23.9 | 25.2, 2 x 508 x 32 15.3 | 16.0, 4096 x 32
+// 141 | 146, 8192 x 16 267 | 277, 16384 x 64 3890 | 3930, 31744 x 64 14430 | 14770, 512 x 32 of 64 10.2 | 11.0, 1000 x 64 of 64 17.9 | 19.1; the
+// narrower one is ahead by 1 to 3 % at 4096 x 16 and 8192 x 32 of 128 and from 3 x 1500 x 64 of 64 on (77 | 75).
 //
 //   forward : workgroup = NW waves x 32 queries of one head, loop over 64-key tiles up to the diagonal; NW = 8 (one
 //             workgroup per CU, two sets of K/V tiles, one barrier per tile) when the grid is large enough, else 4
@@ -146,17 +149,6 @@ RP_DEV uint4 pack_frag(const f32x4& a, const f32x4& b) {
   return make_uint4(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(b[0], b[1]), pack_bf16x2(b[2], b[3]));
 }
 
-// Maxima of two columns over the four lanes l % 16 that hold each, in every lane, with vector instructions only: the exchange through
-// LDS is a round trip of the wave in every key tile.
-RP_DEV void column_max2(float& x, float& y) {
-  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-  const uint32_t m = __float_as_uint(fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1])));     // x in the lower half of the wave, y in the upper
-  const auto c = __builtin_amdgcn_permlane16_swap(m, m, false, false);
-  const uint32_t n = __float_as_uint(fmaxf(__uint_as_float(c[0]), __uint_as_float(c[1])));
-  const auto d = __builtin_amdgcn_permlane32_swap(n, n, false, false);
-  x = __uint_as_float(d[0]);
-  y = __uint_as_float(d[1]);
-}
 // Sum over the four lanes that hold a column.
 RP_DEV float column_sum(float x) {
   x += __shfl_xor(x, 16, 64);
@@ -180,18 +172,9 @@ RP_DEV float stat_start(float raw, int wave, bool in, float scale) {
   return wave == 0 ? (in ? -raw / scale : -3.0e4f) : (in ? -raw : 0.f);
 }
 
-// Writes a wave's 32 x D transposed accumulator (16x16 tiles; columns = the wave's 32 rows of the output) through LDS to global.
+// A wave's staged 32 x D block to global.
 template <int D>
-RP_DEV void store_acc_T(const f32x4 (&acc)[D / 16][2], const float (&mul)[2], bf16* stage /* [32][D+8] */, bf16* __restrict__ out,
-                        long ld, int row0, int nrows, int lane) {
-  const int lr = lane & 15, lg = lane >> 4;
-#pragma unroll
-  for (int dt = 0; dt < D / 16; ++dt)
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-      *reinterpret_cast<uint2*>(stage + (16 * c + lr) * (D + 8) + 16 * dt + 4 * lg) =
-          make_uint2(pack_bf16x2(acc[dt][c][0] * mul[c], acc[dt][c][1] * mul[c]),
-                     pack_bf16x2(acc[dt][c][2] * mul[c], acc[dt][c][3] * mul[c]));
+RP_DEV void store_staged(const bf16* stage, bf16* __restrict__ out, long ld, int row0, int nrows, int lane) {
   __syncthreads();
 #pragma unroll
   for (int it = 0; it < (32 * (D / 8)) / 64; ++it) {
@@ -202,6 +185,21 @@ RP_DEV void store_acc_T(const f32x4 (&acc)[D / 16][2], const float (&mul)[2], bf
           *reinterpret_cast<const uint4*>(stage + row * (D + 8) + ch * 8);
   }
   __syncthreads();
+}
+
+// Writes a wave's 32 x D transposed accumulator (16x16 tiles; columns = the wave's 32 rows of the output) through LDS to global.
+template <int D>
+RP_DEV void store_acc_T(const f32x4 (&acc)[D / 16][2], float mul, bf16* stage /* [32][D+8] */, bf16* __restrict__ out,
+                        long ld, int row0, int nrows, int lane) {
+  const int lr = lane & 15, lg = lane >> 4;
+#pragma unroll
+  for (int dt = 0; dt < D / 16; ++dt)
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+      *reinterpret_cast<uint2*>(stage + (16 * c + lr) * (D + 8) + 16 * dt + 4 * lg) =
+          make_uint2(pack_bf16x2(acc[dt][c][0] * mul, acc[dt][c][1] * mul),
+                     pack_bf16x2(acc[dt][c][2] * mul, acc[dt][c][3] * mul));
+  store_staged<D>(stage, out, ld, row0, nrows, lane);
 }
 
 // Same for an fp32 destination; stage is [32][D + 4] floats per wave.
@@ -228,9 +226,54 @@ RP_DEV void store_acc_T_f32(const f32x4 (&acc)[D / 16][2], float mul, float* sta
 }
 
 // ================================================================================================ forward
+// The fragments of the forward kernel's 32x32 tiles.  The lane half h = lane / 32 holds, of 16 rows, {4h..4h+3, 8+4h..8+4h+3}: what read_frag_tr is
+// to the 16x16 tiles; the 8 values of the A operand are tile rows 16 g + those, at column lane % 32 from x_off on.
+template <int LD>
+RP_DEV uint4 read_frag_tr32(const bf16* base, int g, int x_off) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s16x4* lds_ptr;
+  const bf16* q = base + 16 * g * LD + x_off;
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(q));
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(q + 8 * LD));
+  const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+  return make_uint4(l2.x, l2.y, h2.x, h2.y);
+}
+template <int LD>
+RP_DEV int tr_base32(int lane) {
+  const int lk = lane >> 5, l16 = lane & 15, g16 = lane >> 4;
+  return (4 * lk + (l16 >> 2)) * LD + 16 * (g16 & 1) + 4 * (l16 & 3);
+}
+RP_DEV uint4 pack_frag32(const f32x16& s, int off) {
+  return make_uint4(pack_bf16x2(s[off + 0], s[off + 1]), pack_bf16x2(s[off + 2], s[off + 3]),
+                    pack_bf16x2(s[off + 4], s[off + 5]), pack_bf16x2(s[off + 6], s[off + 7]));
+}
+// max over lanes l and l ^ 32, in the vector unit: the exchange through LDS is a round trip of the wave in every key tile.  Forward of
+// 8192 tokens, 64 heads of 64: 702 -> 673 us (with the mask test on one limit per lane); the eight-wave kernel, whose waves pair up
+// around that wait, is 4 % slower with it (521 -> 542) and keeps the exchange
+RP_DEV float half_max(float x) {
+  const uint32_t u = __float_as_uint(x);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+// store_acc_T for 32x32 tiles.
+template <int D>
+RP_DEV void store_acc_T32(const f32x16 (&acc)[D / 32], float mul, bf16* stage /* [32][D+8] */, bf16* __restrict__ out, long ld, int row0, int nrows, int lane) {
+  const int lr = lane & 31, lk = lane >> 5;
+#pragma unroll
+  for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+    for (int vg = 0; vg < 4; ++vg) {
+      const int dd = 32 * dt + 8 * vg + 4 * lk;
+      *reinterpret_cast<uint2*>(stage + lr * (D + 8) + dd) =
+          make_uint2(pack_bf16x2(acc[dt][4 * vg] * mul, acc[dt][4 * vg + 1] * mul),
+                     pack_bf16x2(acc[dt][4 * vg + 2] * mul, acc[dt][4 * vg + 3] * mul));
+    }
+  store_staged<D>(stage, out, ld, row0, nrows, lane);
+}
+
 template <int D, int NW>
 __global__ void __launch_bounds__(NW * 64, NW <= 4 ? 2 : 1) attn_fwd_kernel(const AttnArgs p) {
-  constexpr int LDK = tile_ld(D), LDV = LDK, KS = D / 32, DT = D / 16, NT = NW * 64, BQ = NW * 32;
+  constexpr int LDK = D + 8, LDV = D + 32, KS = D / 16, DT = D / 32, NT = NW * 64, BQ = NW * 32;
   using T64 = Tile64<D, NT>;
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn_smem[];   // fwd_smem_bytes(D, NW)
   bf16* const smem = reinterpret_cast<bf16*>(dyn_smem);
@@ -240,7 +283,7 @@ __global__ void __launch_bounds__(NW * 64, NW <= 4 ? 2 : 1) attn_fwd_kernel(cons
   bf16* const Ks = smem;
   bf16* const Vs = smem + 64 * LDK;
 
-  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lk = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nQ = (p.seq + BQ - 1) / BQ;
   const int nhb = p.a * p.batch;
@@ -255,27 +298,25 @@ __global__ void __launch_bounds__(NW * 64, NW <= 4 ? 2 : 1) attn_fwd_kernel(cons
   const rsrc_t rk = seq_rsrc(p.k + tok0 * p.ldk + g * D, p.ldk, p.seq, D);
   const rsrc_t rv = seq_rsrc(p.v + tok0 * p.ldv + g * D, p.ldv, p.seq, D);
 
-  // a lane's queries are qw0 + lr and qw0 + 16 + lr (column tiles c = 0, 1)
-  uint4 qf[2][KS];
+  const int qpos = qw0 + lr;     // the lane's query
+  uint4 qf[KS];
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int qpos = qw0 + 16 * c + lr;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      qf[c][ks] = make_uint4(0u, 0u, 0u, 0u);
-      if (qpos < p.seq) qf[c][ks] = *reinterpret_cast<const uint4*>(qb + (long)qpos * p.ldq + 32 * ks + 8 * lg);
-    }
+  for (int ks = 0; ks < KS; ++ks) {
+    qf[ks] = make_uint4(0u, 0u, 0u, 0u);
+    if (qpos < p.seq) qf[ks] = *reinterpret_cast<const uint4*>(qb + (long)qpos * p.ldq + 16 * ks + 8 * lk);
   }
   const int kv_end = (q0 + BQ < p.seq) ? (q0 + BQ) : p.seq;
   const int nkv = (kv_end + 63) / 64;
 
-  float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
-  f32x4 oacc[DT][2];
+  float m_run = -INFINITY, l_run = 0.f;
+  f32x16 oacc[DT];
 #pragma unroll
-  for (int dt = 0; dt < DT; ++dt) oacc[dt][0] = oacc[dt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) oacc[dt][v] = 0.f;
 
-  const bf16* const kfrag0 = Ks + lr * LDK + 8 * lg;
-  const bf16* const vfrag0 = Vs + tr_base<LDV>(lane);
+  const bf16* const kfrag0 = Ks + lr * LDK + 8 * lk;
+  const bf16* const vfrag0 = Vs + tr_base32<LDV>(lane);
   uint4 kreg[T64::NREG], vreg[T64::NREG];
   T64::load(kreg, rk, p.ldk, 0, tid);
   T64::load(vreg, rv, p.ldv, 0, tid);
@@ -316,14 +357,14 @@ __global__ void __launch_bounds__(NW * 64, NW <= 4 ? 2 : 1) attn_fwd_kernel(cons
     // rather than skip it: they would wait at the next barrier anyway, and a skipped update would make the compiler
     // keep a second copy of the accumulator.
     {
-      f32x4 sT[4][2];       // 16 keys x 16 queries each
-      const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
-      // every LDS fragment is requested AHEAD pairs of products before the pair that consumes it, so that the MFMAs do not each
+      f32x16 sT[2];
+      const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      // every LDS fragment is requested AHEAD products before the one that consumes it, so that the MFMAs do not each
       // wait out an LDS round trip
       constexpr int AHEAD = 3;
       {
-        constexpr int NS = 4 * KS;
-        auto sfrag_at = [&](int n) { return *reinterpret_cast<const uint4*>(kfrag + 16 * (n & 3) * LDK + 32 * (n >> 2)); };
+        constexpr int NS = 2 * KS;
+        auto sfrag_at = [&](int n) { return *reinterpret_cast<const uint4*>(kfrag + 32 * (n & 1) * LDK + 16 * (n >> 1)); };
         uint4 ring[AHEAD];
 #pragma unroll
         for (int n = 0; n < AHEAD; ++n) ring[n] = sfrag_at(n);
@@ -332,88 +373,71 @@ __global__ void __launch_bounds__(NW * 64, NW <= 4 ? 2 : 1) attn_fwd_kernel(cons
         for (int n = 0; n < NS; ++n) {
           const uint4 a = ring[n % AHEAD];
           if (n + AHEAD < NS) ring[n % AHEAD] = sfrag_at(n + AHEAD);
-          const int ks = n >> 2, kt = n & 3;
-#pragma unroll
-          for (int c = 0; c < 2; ++c) sT[kt][c] = mfma16(a, qf[c][ks], ks == 0 ? zero4 : sT[kt][c]);
+          const int ks = n >> 1, kt = n & 1;
+          sT[kt] = mfma32(a, qf[ks], ks == 0 ? zero16 : sT[kt]);
           __builtin_amdgcn_sched_barrier(0);
         }
         MFMA_PHASE_END();
       }
       // the first V fragments are requested now, under the softmax arithmetic
-      constexpr int NU = 2 * DT;
-      auto ufrag_at = [&](int n) { return read_frag_tr<LDV>(vfrag + 32 * (n / DT) * LDV + 16 * (n % DT)); };
+      constexpr int NU = 4 * DT;
+      auto ufrag_at = [&](int n) { return read_frag_tr32<LDV>(vfrag, n / DT, 32 * (n % DT)); };
       uint4 uring[AHEAD];
 #pragma unroll
       for (int n = 0; n < AHEAD; ++n) uring[n] = ufrag_at(n);
       __builtin_amdgcn_sched_barrier(0);
       const bool need_mask = (kv0 + 63 > qw0) || (kv0 + 64 > p.seq);   // wave-uniform
       if (need_mask) {
+        const int klim = (qpos < p.seq - 1 ? qpos : p.seq - 1) - (kv0 + 4 * lk);   // keys up to klim past the lane's first
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const int qpos = qw0 + 16 * c + lr;
-          const int klim = (qpos < p.seq - 1 ? qpos : p.seq - 1) - (kv0 + 4 * lg);   // keys up to klim past the lane's first
+        for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-          for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) sT[kt][c][e] = (16 * kt + e > klim) ? -INFINITY : sT[kt][c][e];
-        }
+          for (int v = 0; v < 16; ++v) sT[kt][v] = (32 * kt + 8 * (v >> 2) + (v & 3) > klim) ? -INFINITY : sT[kt][v];
       }
-      float mx[2];
+      float mx = -INFINITY;
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        mx[c] = -INFINITY;
+      for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-        for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) mx[c] = fmaxf(mx[c], sT[kt][c][e]);
-      }
-      column_max2(mx[0], mx[1]);
+        for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sT[kt][v]);
+      mx = (NW < 8 ? half_max(mx) : fmaxf(mx, __shfl_xor(mx, 32, 64))) * p.scale_log2e;
       // m_run is a reference exponent, not the exact running maximum: it moves only when a row's maximum outgrows
       // it by 2^8 (the probabilities stay below 256, harmless in fp32 sums and bf16 operands), so after the first
       // few key tiles almost every tile skips the rescale of the accumulator.  The skip is a wave-uniform branch,
       // and alpha passes through an empty asm statement so that the multiplies cannot be hoisted out of it.  The first key tile
       // contains key 0 <= qpos, so m_run is finite from then on.
-      const bool grow0 = mx[0] * p.scale_log2e > m_run[0] + 8.f, grow1 = mx[1] * p.scale_log2e > m_run[1] + 8.f;
-      if (__builtin_amdgcn_ballot_w64(grow0 || grow1) != 0ull) {
+      const bool grow = mx > m_run + 8.f;
+      if (__builtin_amdgcn_ballot_w64(grow) != 0ull) {
+        const float m_new = grow ? mx : m_run;
+        float alpha = fast_exp2(m_run - m_new);
+        asm volatile("" : "+v"(alpha));
+        l_run *= alpha;
+        m_run = m_new;
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const float m_new = (c ? grow1 : grow0) ? mx[c] * p.scale_log2e : m_run[c];
-          float alpha = fast_exp2(m_run[c] - m_new);
-          asm volatile("" : "+v"(alpha));
-          l_run[c] *= alpha;
-          m_run[c] = m_new;
+        for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-          for (int dt = 0; dt < DT; ++dt)
+          for (int v = 0; v < 16; ++v) oacc[dt][v] *= alpha;
+      }
+      float psum = 0.f;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) oacc[dt][c][e] *= alpha;
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const float e = fast_exp2(__builtin_fmaf(sT[kt][v], p.scale_log2e, -m_run));
+          sT[kt][v] = e;
+          psum += e;
         }
-      }
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        float psum = 0.f;
-#pragma unroll
-        for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float x = fast_exp2(__builtin_fmaf(sT[kt][c][e], p.scale_log2e, -m_run[c]));
-            sT[kt][c][e] = x;
-            psum += x;
-          }
-        l_run[c] += psum;
-      }
+      l_run += psum;
       {
-        uint4 pf[2][2];
+        uint4 pf[4];
 #pragma unroll
-        for (int k2 = 0; k2 < 2; ++k2)
-#pragma unroll
-          for (int c = 0; c < 2; ++c) pf[k2][c] = pack_frag(sT[2 * k2][c], sT[2 * k2 + 1][c]);
+        for (int gk = 0; gk < 4; ++gk)
+          pf[gk] = pack_frag32(sT[gk >> 1], 8 * (gk & 1));
         MFMA_PHASE_BEGIN();
 #pragma unroll
         for (int n = 0; n < NU; ++n) {
           const uint4 a = uring[n % AHEAD];
           if (n + AHEAD < NU) uring[n % AHEAD] = ufrag_at(n + AHEAD);
-#pragma unroll
-          for (int c = 0; c < 2; ++c) oacc[n % DT][c] = mfma16(a, pf[n / DT][c], oacc[n % DT][c]);
+          oacc[n % DT] = mfma32(a, pf[n / DT], oacc[n % DT]);
           __builtin_amdgcn_sched_barrier(0);
         }
         MFMA_PHASE_END();
@@ -422,15 +446,9 @@ __global__ void __launch_bounds__(NW * 64, NW <= 4 ? 2 : 1) attn_fwd_kernel(cons
   }
 
   __syncthreads();
-  float inv[2];
-#pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int qpos = qw0 + 16 * c + lr;
-    const float l_tot = column_sum(l_run[c]);
-    if (lg == 0 && qpos < p.seq) p.lse[((long)b * p.a + hq) * p.seq + qpos] = m_run[c] * 0.6931471805599453f + logf(l_tot);
-    inv[c] = 1.f / l_tot;
-  }
-  store_acc_T<D>(oacc, inv, smem + w * 32 * LDK, p.o + tok0 * p.ldo + hq * D, p.ldo, qw0, p.seq, lane);
+  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+  if (lk == 0 && qpos < p.seq) p.lse[((long)b * p.a + hq) * p.seq + qpos] = m_run * 0.6931471805599453f + logf(l_tot);
+  store_acc_T32<D>(oacc, 1.f / l_tot, smem + w * 32 * LDK, p.o + tok0 * p.ldo + hq * D, p.ldo, qw0, p.seq, lane);
 }
 
 // ================================================================================================ delta = rowsum(dO * O)
@@ -641,8 +659,7 @@ __global__ void __launch_bounds__(NW * 64, NW <= 4 ? 2 : 1) attn_bwd_dq_kernel(c
     }
   }
   __syncthreads();
-  const float mul[2] = {p.scale, p.scale};
-  store_acc_T<D>(dqacc, mul, smem + w * 32 * LDK, p.dq + tok0 * p.lddq + hq * D, p.lddq, qw0, p.seq, lane);
+  store_acc_T<D>(dqacc, p.scale, smem + w * 32 * LDK, p.dq + tok0 * p.lddq + hq * D, p.lddq, qw0, p.seq, lane);
 }
 
 // P = exp(s) and dS = P dP in place, for 32 queries (rows) x 32 keys of the dK/dV kernels; q0: the query of row 0 of this lane.
@@ -849,9 +866,8 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_fused_kernel(const AttnArgs 
   }
   __syncthreads();
   if (grp == hpw) {
-    const float one[2] = {1.f, 1.f}, sc[2] = {p.scale, p.scale};
-    store_acc_T<D>(dkacc, sc, smem + w * 32 * (D + 8), p.dk + tok0 * p.lddk + g * D, p.lddk, kw0, p.seq, lane);
-    store_acc_T<D>(dvacc, one, smem + w * 32 * (D + 8), p.dv + tok0 * p.lddv + g * D, p.lddv, kw0, p.seq, lane);
+    store_acc_T<D>(dkacc, p.scale, smem + w * 32 * (D + 8), p.dk + tok0 * p.lddk + g * D, p.lddk, kw0, p.seq, lane);
+    store_acc_T<D>(dvacc, 1.f, smem + w * 32 * (D + 8), p.dv + tok0 * p.lddv + g * D, p.lddv, kw0, p.seq, lane);
   } else {
     float* const stage = reinterpret_cast<float*>(smem) + w * 32 * (D + 4);
     const long ldp = (long)ah * D;
@@ -1071,9 +1087,8 @@ __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p
   __syncthreads();
   if (grp == hpw) {
     bf16* const stage = smem + w8 * 32 * (D / 2 + 8);
-    const float one[2] = {1.f, 1.f}, sc[2] = {p.scale, p.scale};
-    store_acc_T<D / 2>(dkacc, sc, stage, p.dk + tok0 * p.lddk + g * D + h * (D / 2), p.lddk, kw0, p.seq, lane);
-    store_acc_T<D / 2>(dvacc, one, stage, p.dv + tok0 * p.lddv + g * D + h * (D / 2), p.lddv, kw0, p.seq, lane);
+    store_acc_T<D / 2>(dkacc, p.scale, stage, p.dk + tok0 * p.lddk + g * D + h * (D / 2), p.lddk, kw0, p.seq, lane);
+    store_acc_T<D / 2>(dvacc, 1.f, stage, p.dv + tok0 * p.lddv + g * D + h * (D / 2), p.lddv, kw0, p.seq, lane);
   } else {
     float* const stage = reinterpret_cast<float*>(smem) + w8 * 32 * (D / 2 + 4);
     const long ldp = (long)ah * D;
@@ -1112,7 +1127,7 @@ __global__ void __launch_bounds__(256) attn_dkv_reduce_kernel(const float* __res
 
 // operand tiles, or the epilogue's staging of every wave's 32 x d block, whichever is larger
 constexpr int max_i(int a, int b) { return a > b ? a : b; }
-constexpr int fwd_smem_bytes(int d, int nw) { return max_i((nw >= 8 ? 2 : 1) * (2 * 64 * tile_ld(d)), nw * 32 * (d + 8)) * 2; }
+constexpr int fwd_smem_bytes(int d, int nw) { return max_i((nw >= 8 ? 2 : 1) * (64 * (d + 8) + 64 * (d + 32)), nw * 32 * (d + 8)) * 2; }
 constexpr int dq_smem_bytes(int d, int nw) { return max_i((nw >= 8 ? 2 : 1) * (2 * 64 * tile_ld(d)), nw * 32 * (d + 8)) * 2; }
 constexpr int dkv_fused_smem_bytes(int d) { return max_i(2 * 64 * tile_ld(d) * 2 + 512, 4 * 32 * (d + 4) * 4); }
 constexpr int dkv_pair_smem_bytes(int d) { return 2 * (2 * 64 * tile_ld(d)) * 2 + 8 * 4 * 64 * 16 + 1024; }
