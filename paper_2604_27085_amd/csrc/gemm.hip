@@ -488,17 +488,17 @@ __global__ void __launch_bounds__(256) gemm_arrange_kernel(const bf16* __restric
 // between these (250 MB and more in eight slices) and the weight gradients and bf16 results of short batches, which are 2-3 % slower
 // with fewer slices; nothing was measured in between.  Added to the elapsed time is the chip time the
 // workgroups use up (their summed time over 256 CUs): what is left over belongs to other streams, so a small tile has to buy
-// enough latency for the extra operand traffic it causes.  The weight of that term, measured on whole stage calls, three streams at once | one
-// stream, us, with weight 0.7 | 1.0 | 1.3 and, in front, with the 256x256 tile as expensive as its eight-wave kernel was (0.95 + 0.6 a K tile, 6 for
-// the epilogue) at 1.3: backward of a full fine-tune of 4096 tokens at h = 2048 1585 | 1440 | 1441 | 1441 and 1669 | 1730 | 1733 | 1740 (its products
-// of 128 tiles leave half of the chip to others); forward of 1000 tokens there 137 | 137 | 132 | 132 and 205 | 210 | 215 | 215; LoRA backward of
-// 2 x 508 at h = 4096 960 | 960 | 967 | 966 and 1115 | 1122 | 1145 | 1150; mixture-of-experts backward of 2048 3068 | 3053 | 3054 | 3050 and 3179 | 3250 |
-// 3243 | 3235.
+// enough latency for the extra operand traffic it causes.  A worker runs its calls on one stream, so the weight is one at which none of them is
+// slower there.  Whole stage calls, us, weight 1.3 | 0.7 | 0.35 | 0, on one stream and with three calls at once: forward of 1000 tokens at
+// h = 2048 178 | 173 | 165 | 165 and 161 | 158 | 159 | 163; LoRA backward of 392 at h = 4096 710 | 688 | 689 | 688 and 580 | 569 | 578 | 577, of
+// 2 x 508 1069 | 1067 | 1070 | 1082 and 957 | 961 | 961 | 978; backward of a full fine-tune of 4096 at h = 2048 1593 | 1595 | 1600 | 1622 and
+// 1584 | 1582 | 1584 | 1617.
 constexpr double CHIP_WEIGHT = 0.7;
 struct TileModel { int bm, bn; double tau, tau_fill, epi; };
-constexpr TileModel TILE_MODEL[9] = {{},                          // by tile number
-                                     {256, 256, 0.78, 0.58, 4.5}, {256, 128, 0.60, 0.35, 4.0}, {128, 128, 0.55, 0.0, 3.5},
-                                     {128, 64, 0.36, 0.0, 3.5},   {256, 128, 0.53, 0.40, 5.0}, {}, {}, {64, 64, 0.31, 0.0, 3.5}};
+// by tile number; 256x256 tiles are 1 on the eight-wave kernel, 7 on the four-wave one
+constexpr TileModel TILE_MODEL[9] = {{},
+                                     {256, 256, 0.95, 0.60, 6.0}, {256, 128, 0.60, 0.35, 4.0}, {128, 128, 0.55, 0.0, 3.5},
+                                     {128, 64, 0.36, 0.0, 3.5},   {256, 128, 0.53, 0.40, 5.0}, {}, {256, 256, 0.78, 0.58, 4.5}, {64, 64, 0.31, 0.0, 3.5}};
 
 double tile_cost(int tile, int splits, int M, int N, int k_tiles, int epi) {
   TileModel t = TILE_MODEL[tile];
@@ -521,6 +521,45 @@ double tile_cost(int tile, int splits, int M, int N, int k_tiles, int epi) {
 }
 
 struct Choice { int tile, splits; };
+
+long big_tiles(const GemmArgs& a, int splits) { return (long)((a.M + 255) / 256) * ((a.N + 255) / 256) * splits; }
+
+// Which kernel a product on 256x256 tiles runs: the four-wave one that loads its operands straight into LDS (gemm_dtl.hip), unless a kernel
+// is asked for by name (hint 1: eight waves, hint 7: four), the variant has no counterpart there, or the reduction of a slice is short.  Its
+// 16x16x32 instructions are ahead per K tile where the power binds, that is with most of the chip busy; its start and its one wave per SIMD cost
+// more.  So the line lies by the share of the CUs that have a tile, over all rounds.  Eight waves | four, us, bf16 NT, K = 512, 1024, 1536, 2048:
+//   144 tiles (0.56) 17.1 | 19.3, 25.9 | 26.9, 35.0 | 36.3, 44.5 | 44.3     288 (0.56) 33.4 | 34.8, 52.3 | 53.1, 73.7 | 75.5, 95.3 | 92.1
+//   160 (0.63) 18.1 | 19.2, 26.7 | 27.9, 39.4 | 36.7, 47.2 | 45.6           192 (0.75) 19.0 | 19.5, 29.5 | 28.7, 39.4 | 39.2, 49.6 | 47.0
+//   224 (0.88) 20.7 | 20.7, 32.8 | 31.2, 45.0 | 40.5, 56.6 | 52.6           256 22.3 | 21.6, 34.0 | 31.1, 47.2 | 42.1, 60.7 | 53.2
+//   1024 84.7 | 81.7, 132 | 120 at 1024;  384 (0.75) 34.4 | 36.0, 58.2 | 57.6;  fp32 176 (0.69) 21.7 | 23.6, 31.0 | 32.2, -, 50.5 | 49.0
+// A residual and the SwiGLU epilogues are shorter from its registers: with a residual, 144 tiles 25.4 | 21.5, 33.3 | 29.0, 41.8 | 38.3, 50.6 | 46.7,
+// 288 53 | 41 and 113 | 98 at both ends; SwiGLU forward, 144 tiles 28.4 | 27.8, 38.3 | 36.4, 45.8 | 44.0, 55.6 | 54.4; backward, 192 tiles 43.7 |
+// 38.9, 58.4 | 62.1 (K = 1024, the one that loses), -, 83.0 | 79.0.  Outputs that accumulate, TN, K = 512, 768, 1024: 512 tiles 70.8 | 65.8, 83.5 | 77.3,
+// 95.8 | 86.6; 640 85.8 | 87.4, 101.8 | 101.2, 118 | 115; 1024 144 | 147, 169 | 166, 191 | 186 (but 2048 tiles with rows of 64 KB 415 | 425 at 1024, 500 |
+// 504 at 1536, 595 | 585 at 2048).
+// Cross-entropy epilogues that stage their tile are longer in four waves: with them from 40 K tiles on.  The probabilities (EPI_CE_P) go out
+// from the registers: trainable head of 151936 x 2048, 4096 tokens, 6437 us with eight waves, 6246 with four.  Skinny outputs (the LoRA
+// products, bound by reading the other operand once) stay on the eight-wave kernel: +14 %.
+bool four_waves(const GemmArgs& a, int splits, int tile_hint) {
+  if (tile_hint == 1 || a.run_flag || a.b_direct) return false;
+  if (tile_hint == 7) return true;
+  if (a.M <= 64 || a.N <= 64) return false;
+  const bool ce = a.epi == EPI_CE_STATS || a.epi == EPI_CE_DZ || a.epi == EPI_F32_COLMAX;
+  const long n = big_tiles(a, splits);
+  const double busy = n / (256.0 * ((n + 255) / 256));
+  int min_k = busy > 0.8 ? 512 : busy > 0.7 ? 1024 : busy > 0.6 ? 1536 : 2048;
+  if (splits == 1) {      // (slices write plain fp32)
+    if (n > 128 && (a.R || a.epi == EPI_CE_P)) min_k = 512;     // R: the residual, or gate and up of a SwiGLU backward
+    if (n > 128 && a.epi == EPI_SWIGLU_FWD) min_k = 512;
+    if (a.epi == EPI_F32 && a.beta && min_k < 768) min_k = 768;
+  }
+  return a.K + a.K2 >= (ce ? 2560 : splits * min_k);
+}
+
+// tile_cost of the kernel that would be launched
+double product_cost(const GemmArgs& a, int tile, int splits, int tile_hint) {
+  return tile_cost(tile == 1 && four_waves(a, splits, tile_hint) ? 7 : tile, splits, a.M, a.N, (a.K + 63) / 64 + (a.K2 + 63) / 64, a.epi);
+}
 
 // Bytes spanned by a [rows, cols] bf16 view with row stride ld; 0 for an empty view, ~0 when it does not fit 31 bits.
 unsigned extent_bytes(long rows, long cols, long ld) {
@@ -557,6 +596,12 @@ hipError_t gemm_arrange(hipStream_t st, const void* B, long ldb, int N, int K, i
 // split gains nothing (4096 x 2048 x 12288 NN in two slices 187 -> 180 us with its merge, but the product behind it 217 -> 224
 // and the backward stage of 4096 tokens 1864 -> 1873).  A slice keeps at least four K tiles of a small tile, sixteen of a large
 // one (four for a skinny output, which is bound by reading the other operand).
+// Up to 128 tiles of 256x256 leave half of the chip idle: the 256x128 tiles are ahead there at any reduction.  256x256 (the faster of its two kernels) |
+// 256x128 by two groups | by eight waves (gemm_mid.hip), us, K = 512, 1024, 2048, 4096, 6144: 4096 x 2048 NT 17.4 | 14.7 | 15.9, 25.6 | 22.1 | 22.7,
+// 42.4 | 37.3 | 35.7, 76.4 | 65.4 | 63.9, 110 | 94 | 91; NN 110 | 99 | 92 and fp32 accumulating TN 118 | 104 | 98 at 6144; 2048 x 3072 NT (96 tiles) 16.2 |
+// 12.9 | 14.0, 24.9 | 18.8 | 19.8, 42.3 | 31.2 | 32.1, 76.4 | 55.6 | 57.8, 110 | 85 | 85.  From 144 tiles on it is the other way round: 3072 x 3072 NT
+// 17.1 | 23.9 | 24.9 at 512, 77.9 | 104 | 101 at 4096.  (Three such calls at once fill the chip with 256x256 tiles and are faster with them: backward of
+// a full fine-tune of 4096 tokens at h = 2048 1519 us against 1582; but on one stream it takes 1663 against 1595.)
 static Choice choose(const GemmArgs& a, int tile_hint) {
   if (a.grp_tab) return {1, 1};      // the table's entries are rows of 256-row tiles
   if (a.b_direct || a.epi == EPI_CE_STATS || a.epi == EPI_CE_DZ || a.epi == EPI_F32_COLMAX || a.epi == EPI_CE_P) return {1, 1};
@@ -575,7 +620,8 @@ static Choice choose(const GemmArgs& a, int tile_hint) {
     const int min_per = (t == 1 || t == 5) && !skinny ? 16 : 4;
     for (int sp = 1; sp <= (may_split ? 16 : 1); ++sp) {
       if (sp > 1 && (k_tiles / sp < min_per || (size_t)sp * a.M * a.N * 4 > a.split_ws_bytes)) break;
-      const double c = tile_cost(t, sp, a.M, a.N, k_tiles, a.epi);
+      if (t == 1 && !tile_hint && !skinny && big_tiles(a, sp) <= 128) continue;
+      const double c = product_cost(a, t, sp, tile_hint);
       if (c < best_cost) { best_cost = c; best = {t, sp}; }
     }
     if (tile_hint) break;
@@ -640,6 +686,7 @@ hipError_t gemm_launch(hipStream_t st, int layout, const GemmArgs& a_in, int til
   if (e != hipSuccess) return e;
   const Choice ch = choose(a, tile_hint);
   const int tile = ch.tile;
+  const bool four = four_waves(a, ch.splits, tile_hint);
   if (a.grp_tab) {
     e = prepare_grouped(layout, a);
     if (e != hipSuccess) return e;
@@ -657,27 +704,15 @@ hipError_t gemm_launch(hipStream_t st, int layout, const GemmArgs& a_in, int til
     a.C = a.split_ws; a.ldc = a.N; a.beta = 0; a.c_slice_stride = (long)a.M * a.N;
     a.epi = EPI_F32; a.R = nullptr;
   }
-  // Products on 256x256 tiles run the four-wave kernel that loads its operands straight into LDS (gemm_dtl.hip) unless a kernel is asked for by
-  // name (hint 1: eight waves, hint 7: four), the variant has no counterpart there, or the reduction is short: its 16x16x32 instructions are
-  // ahead per K tile, its start and its one wave per SIMD cost more.  Eight waves | four, us, K = 256, 512, 1024, 2048: 8192 x 8192 NT 48.4 | 49.5,
-  // 71.1 | 68.7, 119 | 109, 217 | 191, with a residual 109 | 88, 131 | 104, 176 | 145, 281 | 228, fp32 accumulating TN 121 | 127, 142 | 144, 192 | 187,
-  // 293 | 278; 4096 x 4096 NT 15.2 | 15.4, 20.3 | 19.7, 32.1 | 29.5, 57.5 | 50.1; on half of the chip (128 tiles), where the power does
-  // not bind, 2048 x 4096 NT 12.8 | 14.6, 17.4 | 18.9, 25.8 | 26.7, 42.3 | 42.4.  Cross-entropy epilogues that stage their tile are
-  // longer in four waves: with them from 40 K tiles on.  The probabilities (EPI_CE_P) go out from the registers there: trainable head of
-  // 151936 x 2048, 4096 tokens, 6437 us with eight waves, 6246 with four.
-  // Skinny outputs (the LoRA products, bound by reading the other operand once) stay on the eight-wave kernel: +14 %.
-  // Grouped products take it too (it spares a tile's empty rows their matrix instructions), but for reductions of up to 16 K tiles over
+  // Grouped products run the four-wave kernel (it spares a tile's empty rows their matrix instructions), but for reductions of up to 16 K tiles over
   // weights that the caches hold (grp_cached): these are bound by that fixed cost, and by fetching the larger code.  Forward
   // of a layer, us, eight waves | four: 8 experts of 256 x 96, 136 tokens 71 | 79 (a product 11 | 16), 1064 92 | 100; of 512 x 512, 136 | 4096 tokens
   // 83 | 87, 151 | 161; of 768 x 3072, 16384 tokens 1004 | 1039; 32 of 512 x 1024, 4096 tokens 220 | 233.  With weights from
   // memory the four waves are ahead: 64 of 1024 x 512 (201 MB), 4096 | 16384 tokens 276 | 268, 857 | 833; 128 of 2048 x 768, 16384 2521 | 2468.
   const bool short_grp = a.grp_tab && a.grp_cached && !a.grp_once && a.K <= 1024;
-  const bool ce = a.epi == EPI_CE_STATS || a.epi == EPI_CE_DZ || a.epi == EPI_F32_COLMAX;
-  const long big_tiles = (long)((a.M + 255) / 256) * ((a.N + 255) / 256) * ch.splits;
-  const int dtl_min_k = ce ? 2560 : big_tiles <= 128 ? 2048 : 512;
   // (the four-wave kernel addresses the 256 rows of an output tile with 31-bit byte offsets)
   const bool near_rows = a.ldc < 1L << 21 && a.ldr < 1L << 21 && a.ldc2 < 1L << 21;
-  const bool dtl = !near_rows ? false : a.grp_tab ? !short_grp : (tile == 1 && tile_hint != 1 && !a.run_flag && !a.b_direct && (tile_hint == 7 || (a.K + a.K2 >= dtl_min_k && a.M > 64 && a.N > 64)));
+  const bool dtl = near_rows && (a.grp_tab ? !short_grp : tile == 1 && four);
   if (dtl) {
     e = gemm_dtl_launch(st, a, layout);
   } else {
@@ -766,10 +801,10 @@ bool gemm_wgrad_joined(int n, const GemmArgs* g) {
     GemmArgs q = g[i];
     if (prepare(GEMM_TN, q) != hipSuccess) return false;
     const Choice ch = choose(q, 0);
-    apart += tile_cost(ch.tile, ch.splits, q.M, q.N, (q.K + 63) / 64, q.epi);
+    apart += product_cost(q, ch.tile, ch.splits, 0);
     tiles += (long)((q.M + 255) / 256) * ((q.N + 255) / 256);
   }
-  return tile_cost(1, 1, (int)(256 * tiles), 256, (g[0].K + 63) / 64, EPI_F32) < apart;
+  return tile_cost(7, 1, (int)(256 * tiles), 256, (g[0].K + 63) / 64, EPI_F32) < apart;
 }
 
 hipError_t gemm_wgrad_launch(hipStream_t st, int n, const GemmArgs* g) {
