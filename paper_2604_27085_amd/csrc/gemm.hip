@@ -556,6 +556,9 @@ bool four_waves(const GemmArgs& a, int splits, int tile_hint) {
   return a.K + a.K2 >= (ce ? 2560 : splits * min_k);
 }
 
+// The four-wave kernel addresses the 256 rows of an output tile with 31-bit byte offsets: others run elsewhere, whoever launches.
+bool near_rows(const GemmArgs& a) { return a.ldc < 1L << 21 && a.ldr < 1L << 21 && a.ldc2 < 1L << 21; }
+
 // tile_cost of the kernel that would be launched
 double product_cost(const GemmArgs& a, int tile, int splits, int tile_hint) {
   return tile_cost(tile == 1 && four_waves(a, splits, tile_hint) ? 7 : tile, splits, a.M, a.N, (a.K + 63) / 64 + (a.K2 + 63) / 64, a.epi);
@@ -710,9 +713,7 @@ hipError_t gemm_launch(hipStream_t st, int layout, const GemmArgs& a_in, int til
   // 83 | 87, 151 | 161; of 768 x 3072, 16384 tokens 1004 | 1039; 32 of 512 x 1024, 4096 tokens 220 | 233.  With weights from
   // memory the four waves are ahead: 64 of 1024 x 512 (201 MB), 4096 | 16384 tokens 276 | 268, 857 | 833; 128 of 2048 x 768, 16384 2521 | 2468.
   const bool short_grp = a.grp_tab && a.grp_cached && !a.grp_once && a.K <= 1024;
-  // (the four-wave kernel addresses the 256 rows of an output tile with 31-bit byte offsets)
-  const bool near_rows = a.ldc < 1L << 21 && a.ldr < 1L << 21 && a.ldc2 < 1L << 21;
-  const bool dtl = near_rows && (a.grp_tab ? !short_grp : tile == 1 && four);
+  const bool dtl = near_rows(a) && (a.grp_tab ? !short_grp : tile == 1 && four);
   if (dtl) {
     e = gemm_dtl_launch(st, a, layout);
   } else {
@@ -799,7 +800,7 @@ bool gemm_wgrad_joined(int n, const GemmArgs* g) {
   long tiles = 0;
   for (int i = 0; i < n; ++i) {
     GemmArgs q = g[i];
-    if (prepare(GEMM_TN, q) != hipSuccess) return false;
+    if (prepare(GEMM_TN, q) != hipSuccess || !near_rows(q)) return false;
     const Choice ch = choose(q, 0);
     apart += product_cost(q, ch.tile, ch.splits, 0);
     tiles += (long)((q.M + 255) / 256) * ((q.N + 255) / 256);
@@ -814,6 +815,7 @@ hipError_t gemm_wgrad_launch(hipStream_t st, int n, const GemmArgs* g) {
     q[i] = g[i];
     const hipError_t e = prepare(GEMM_TN, q[i]);
     if (e != hipSuccess) return e;
+    if (!near_rows(q[i])) return hipErrorInvalidValue;
   }
   return gemm_wgrad_run(st, n, q);
 }
@@ -822,7 +824,7 @@ hipError_t gemm_pair_launch(hipStream_t st, const GemmArgs& nt, const GemmArgs& 
   GemmArgs a = nt, b = nn;
   if (a.M <= 0 || a.N <= 0 || b.N <= 0) return hipErrorInvalidValue;
   if (!a.grp_tab || a.grp_tab != b.grp_tab || a.grp_ntiles != b.grp_ntiles || a.grp_max_tiles != b.grp_max_tiles || a.epi != EPI_BF16 || b.epi != EPI_BF16 ||
-      a.R || b.R || a.alpha != 1.f || b.alpha != 1.f)
+      a.R || b.R || a.alpha != 1.f || b.alpha != 1.f || !near_rows(a) || !near_rows(b))
     return hipErrorInvalidValue;
   hipError_t e = prepare(GEMM_NT, a);
   if (e == hipSuccess) e = prepare_grouped(GEMM_NT, a);

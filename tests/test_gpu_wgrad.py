@@ -92,3 +92,36 @@ def test_adapter_gradients_that_wait_for_the_next_projection(names, batch, seq, 
                 off, cnt = B.rp_grad_layout(cfg, layer, B.T[t + n.upper()])
                 a0, a1 = out[0][1][off // 4:off // 4 + cnt], out[1][1][off // 4:off // 4 + cnt]
                 assert float((a1 - a0).norm() / a0.norm()) < 8e-3, (layer, t + n)
+
+
+def test_rows_too_far_apart_for_the_shared_launch():
+    """The shared launch addresses the 256 rows of an output tile with 31-bit offsets.  Rows of 2097280 fp32 numbers (the output projection of 16385
+    heads, whose last tile is ragged) are further apart than that: such a gradient is computed by itself, with the sums of the least workspace."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_27085_amd import binding as B, harness as H
+    T, h = 8, 256
+    cfg = B.make_cfg(1, h, 16385, 5, 128, 512, lora_rank=0, lora=())
+    s = H.StageRunner(cfg, 1, T)
+    g = torch.Generator(device="cuda:0").manual_seed(1)
+    s.slots[0].view(torch.bfloat16).normal_(0.0, 0.04, generator=g)
+    x = torch.empty((T, h), dtype=torch.bfloat16, device="cuda:0").normal_(0.0, 1.0, generator=g)
+    dy = torch.empty_like(x).normal_(0.0, 1.0, generator=g)
+    torch.cuda.synchronize()
+    s.bind()
+    off, n = B.rp_grad_layout(cfg, 0, B.T["WO"])
+    out = []
+    for nbytes in (B.rp_query_least_workspace(cfg, 1, T)[1], s.wsbytes):
+        s.grads.fill_(0.5)
+        torch.cuda.synchronize()
+        B.rp_trace_start(s.ctx, 512)
+        B.rp_stage_backward(s.ctx, 0, B.PHASE_BOTH, x, dy, torch.empty_like(x), None, s.grads, None, None, 1, T, s.ws, nbytes)
+        assert not any(t[0] == "gemm_wgrad_TN" for t in B.rp_trace_stop(s.ctx, 512))
+        out.append(s.grads[off // 4:off // 4 + n].view(h, n // h) - 0.5)
+    s.close()
+    # the last heads' columns by themselves: the whole gradient would hide one wrong tile
+    for part in (slice(0, None), slice(n // h - 128, None), slice(2064384, 2064640)):
+        a, b = out[0][:, part], out[1][:, part]
+        assert float(a.norm()) > 0 and float((b - a).norm() / a.norm()) < 1e-5
+    rows = out[1][-1], out[0][-1]
+    assert float((rows[0] - rows[1]).norm() / rows[1].norm()) < 1e-5
