@@ -52,16 +52,17 @@ def algorithmic_flops(c):
     return layers, head
 
 
-def measured_traffic(workload, kernel):
+def measured_traffic(workload, kernel, launches_per_step):
     """HBM bytes per launch of `kernel` from the rocprofv3 --pmc summary kept under profiles/ (FETCH_SIZE and WRITE_SIZE
-    scaled by a copy kernel of known size), or None when that summary has no line for this workload and kernel.  A
-    stored figure: counters cannot be read from inside this process."""
+    scaled by a copy kernel of known size), or None when that summary has no line for this workload and kernel, or one
+    of another number of launches a step: a name stands for several products, and its average for the ones it was
+    recorded with.  A stored figure: counters cannot be read from inside this process."""
     path = os.path.join(ROOT, "profiles", "bench_%s_hbm_traffic.md" % workload)
     try:
         with open(path) as f:
             for ln in f:
                 w = ln.split()
-                if len(w) >= 3 and w[0] == "traffic_bytes_per_launch" and w[1] == kernel:
+                if len(w) >= 4 and w[0] == "traffic_bytes_per_launch" and w[1] == kernel and float(w[3]) == launches_per_step:
                     return float(w[2])
     except OSError:
         pass
@@ -224,7 +225,7 @@ def measure(name, args, steps, warmup, full):
         ach = dby / (dms * 1e-3) / 1e9
         roofline = {"kernel": dname, "bound": "hbm", "achieved": round(ach, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                     "frac": round(ach / PEAK_HBM_GBS, 4)}
-    roofline.update({"traffic": measured_traffic(name, dname),
+    roofline.update({"traffic": measured_traffic(name, dname, dn / tsteps),
                      "traffic_source": "stored figure: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of this command, profiles/bench_%s_hbm_traffic.md" % name,
                      "launches_per_step": dn / tsteps, "avg_launch_us": round(dms / dn * 1e3, 2)})
     # class roll-ups against the targets: GEMMs and attention as fractions of the bf16 MFMA peak

@@ -38,3 +38,23 @@ def test_moe_flops_count_the_active_experts_only():
     dense_like = dict(c, n_experts=0, top_k=0)
     extra = bench.fl_gemm_fwd(c) - bench.fl_gemm_fwd(dense_like)
     assert extra == pytest.approx(2.0 * T * (c["top_k"] - 1) * 3 * c["hidden"] * c["ffn"], rel=1e-12)
+
+
+def test_stored_traffic_is_for_the_launches_it_was_recorded_with(tmp_path, monkeypatch):
+    """roofline.traffic is an average over the launches of a name: with others among them the stored figure says nothing."""
+    (tmp_path / "profiles").mkdir()
+    (tmp_path / "profiles" / "bench_C2_hbm_traffic.md").write_text(
+        "traffic_bytes_per_launch gemm_256x256_NN 1.7761e+09 5\ntraffic_bytes_per_launch gemm_256x256_NT 5e+08\n")
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    assert bench.measured_traffic("C2", "gemm_256x256_NN", 5.0) == 1.7761e9
+    assert bench.measured_traffic("C2", "gemm_256x256_NN", 17.0) is None
+    assert bench.measured_traffic("C2", "gemm_256x256_NT", 13.0) is None       # recorded without
+    assert bench.measured_traffic("C2", "gemm_256x256_TN", 1.0) is None
+    assert bench.measured_traffic("C9", "gemm_256x256_NN", 5.0) is None
+
+
+@pytest.mark.parametrize("name", ["C2", "C3", "C4", "C5"])
+def test_every_stored_figure_names_its_launches(name):
+    with open(os.path.join(ROOT, "profiles", "bench_%s_hbm_traffic.md" % name)) as f:
+        lines = [ln.split() for ln in f if ln.startswith("traffic_bytes_per_launch")]
+    assert lines and all(len(w) == 4 and float(w[2]) > 0 and float(w[3]) >= 1 for w in lines)
