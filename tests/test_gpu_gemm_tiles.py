@@ -65,13 +65,40 @@ def test_small_tiles_at_their_edges(rp, layout, tile):
 @pytest.mark.parametrize("seq,batch,ffn,hidden", [(8, 1, 384, 256), (36, 2, 64, 256), (136, 1, 328, 256), (264, 1, 72, 256),
                                                   (1040, 1, 4680, 512), (520, 1, 8264, 2560)])
 def test_short_stage_with_swiglu_epilogues(rp, seq, batch, ffn, hidden):
-    """The SwiGLU forward and backward ride in the epilogues of the small tiles, and of the two 256x256 kernels in the last
-    two (reductions of 512 and 2560); gate and up columns that end inside a tile; adapters on all projections."""
+    """The SwiGLU forward and backward ride in the epilogues of the small tiles, the forward of the last two (reductions of 512 and 2560) in that
+    of the four-wave 256x256 kernel; gate and up columns that end inside a tile; adapters on all projections."""
     c = synth.shrink(synth.CONFIGS["C1"], n_layers=1, hidden=hidden, ffn=ffn, vocab=0, seq=seq, batch=batch, lora=synth.LORA_ORDER,
                      x_from="normal")
     wl = synth.make_workload(c, 4242 + seq, gains_random=True)
     errs = pu.compare_chain(pu.oracle_chain(c, wl, dtype=np.float32), pu.gpu_chain(c, wl, rp[1]), c)
     assert max(errs.values()) <= 2e-2
+
+
+@pytest.mark.parametrize("hidden", [256, 512])
+def test_swiglu_epilogues_of_the_256x256_tiles(rp, hidden):
+    """Forward (408 tiles) and backward (208) on 256x256 tiles that end inside a tile in both directions: reductions of 256 run the eight-wave
+    kernel, whose tiles go out through LDS, those of 512 the four-wave one, straight from the registers."""
+    B, H = rp
+    T, m = 2040, 6408
+    c = synth.shrink(synth.CONFIGS["C1"], n_layers=1, hidden=hidden, ffn=m, vocab=0, seq=T, batch=1, lora_rank=0, lora=(), x_from="normal")
+    wl = synth.make_workload(c, 4300 + hidden, gains_random=True)
+    errs = pu.compare_chain(pu.oracle_chain(c, wl, dtype=np.float32), pu.gpu_chain(c, wl, H), c)
+    assert max(errs.values()) <= 2e-2
+    r = H.StageRunner(H.cfg_from_dict(c), 1, T)      # and those tiles they were
+    try:
+        r.slots[0].view(torch.bfloat16).normal_(0.0, 0.02)
+        x = torch.empty((T, hidden), dtype=torch.bfloat16, device="cuda:0").normal_()
+        dy, dx = torch.empty_like(x).normal_(), torch.empty_like(x)
+        torch.cuda.synchronize()
+        r.bind()
+        B.rp_trace_start(r.ctx, 256)
+        B.rp_stage_backward(r.ctx, 0, B.PHASE_BOTH, x, dy, dx, None, r.grads, None, None, 1, T, r.ws, r.wsbytes)
+        rec = B.rp_trace_stop(r.ctx, 256)
+    finally:
+        r.close()
+    product = 2.0 * T * hidden * m
+    assert [t[0] for t in rec if t[1] == 2 * product and t[0].endswith("NT")] == ["gemm_256x256_NT"]
+    assert [t[0] for t in rec if t[1] == product and t[0].endswith("NN")] == ["gemm_256x256_NN"]
 
 
 def operand(rng, rows, cols, std=1.0):
