@@ -885,7 +885,7 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_fused_kernel(const AttnArgs 
 // before the workgroup barrier that publishes the exchange -- and with the partner's 32 queries after it.  Same number of
 // MFMAs per workgroup as the one-wave-per-SIMD kernel, same LDS fragment traffic per CU, 8 KB of exchange per pair and tile.
 // DS: dS is kept as well (see attn_ds_block): a wave stores its 32 keys x 32 queries of every tile, 16 bytes of a key's row per lane
-// after one exchange between the half-waves.  The stores are older than the next tile's loads and overlap the updates: 
+// after one exchange between neighbouring lane groups.  The stores are older than the next tile's loads and overlap the updates:
 // 8192 tokens, 32 heads 1109 -> 1201 us, 4096 x 16 heads 162 -> 171 (stored past the L2: with ordinary stores, which push the Q and dO
 // tiles out of it, 1215), and dQ 726 -> 506 and 137 -> 80.
 template <int D, bool MULTI, bool DS>

@@ -415,9 +415,10 @@ RP_DEV float reduce_columns(float (&v)[16], int r, Op op) {
 
 // EPI_CE_P of the wave's 128x128 block (rows are vocabulary entries, columns tokens) from transposed accumulators: a lane holds four consecutive
 // tokens of a row per tile.  The probabilities go out as in store_rows; the columns' maxima and sums are formed over the lane's eight rows
-// and then over the sixteen lanes that share its columns, 64 columns at a time, one per lane.  Bound by issue (two conversions, a
-// maximum, a sum and an exponential per number); frozen head of 151936 x 5120, 2040 tokens, staged through LDS 4964 us, from the registers
-// 4867; the trainable one of 2048, 4096 tokens 6434 and 6200.
+// and then over the sixteen lanes that share its columns, 64 columns at a time, one per lane.  Frozen head of 151936 x 5120, 2040 tokens,
+// staged through LDS 4964 us, from the registers 4867; the trainable one of 2048, 4096 tokens 6434 and 6200.  A number takes two conversions, a
+// maximum, a sum and an exponential; besides, the four copies of `columns` with 48 numbers a lane each need more than the 512 registers:
+// 99 are spilled (184 bytes a lane; 203 instructions, all behind the K loop), and a chunk of 32768 x 4096 writes 310 MB for 256 MB of probabilities.
 RP_DEV void store_ce_p(const GemmArgs& p, f32x4 (&acc)[8][8], int m0, int n0, int wm, int wn, int lane, int part_row) {
   constexpr float LOG2E = 1.4426950408889634f, CAP = RP_CE_P_CLAMP * LOG2E;
   const int r16 = lane & 15, g = lane >> 4;
@@ -523,7 +524,6 @@ RP_DEV void dtl_block(const GemmArgs& p, int blk, int gm = 0, int gn = 0) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int lr = lane & 31, lk = lane >> 5;
 
   int tile_m, tile_n, m0, Mlim = p.M;
   const bf16* Bbase = static_cast<const bf16*>(p.B);
@@ -555,10 +555,9 @@ RP_DEV void dtl_block(const GemmArgs& p, int blk, int gm = 0, int gn = 0) {
   // Load instruction i (0..7 per operand) of this wave fills the 1 KB block 8*wave + i of a unit.
   //   reduction-contiguous operand: operand rows 8*(8*wave + i) .. + 7, lane l -> row + (l >> 3), chunk position l & 7,
   //     i.e. data chunk (l & 7) ^ ((row >> 1) & 7);
-  //   TB: the unit is [64 reduction rows][256 columns] (512-byte rows, eight 64-byte segments = MFMA tile columns each);
-  //     reduction rows 2*(8*wave + i), + 1, lane l -> row + (l >> 5), chunk position l & 31, whose segment (l & 31) >> 2
-  //     holds data segment ((l & 31) >> 2) ^ (row & 3): the four reduction rows a transposing read touches at once
-  //     lie in four different quarters of the banks.
+  //   TB: the unit is [64 reduction rows][256 columns] (512-byte rows of sixteen 32-byte segments, the columns of one 16x16 tile each);
+  //     reduction rows 2*(8*wave + i), + 1, lane l -> row + (l >> 5), chunk position l & 31, whose segment (l & 31) >> 1
+  //     holds data segment ((l & 31) >> 1) ^ seg_swizzle(row).
   uint32_t voA[8], voB[8];
   int lch[2];     // the lane's data chunk in even / odd instructions (rows 8 apart flip bit 2 of the swizzle)
   auto b_offset = [&](int i, long ldb) -> uint32_t {   // byte offset of the lane's chunk of load i of a B unit at reduction offset 0
