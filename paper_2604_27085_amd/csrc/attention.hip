@@ -885,9 +885,10 @@ __global__ void __launch_bounds__(256) attn_bwd_dkv_fused_kernel(const AttnArgs 
 // before the workgroup barrier that publishes the exchange -- and with the partner's 32 queries after it.  Same number of
 // MFMAs per workgroup as the one-wave-per-SIMD kernel, same LDS fragment traffic per CU, 8 KB of exchange per pair and tile.
 // DS: dS is kept as well (see attn_ds_block): a wave stores its 32 keys x 32 queries of every tile, 16 bytes of a key's row per lane
-// after one exchange between neighbouring lane groups.  The stores are older than the next tile's loads and overlap the updates:
-// 8192 tokens, 32 heads 1109 -> 1201 us, 4096 x 16 heads 162 -> 171 (stored past the L2: with ordinary stores, which push the Q and dO
-// tiles out of it, 1215), and dQ 726 -> 506 and 137 -> 80.
+// after one exchange between neighbouring lane groups.  The stores are older than the next tile's loads and overlap the updates, and go past
+// the L2 (ordinary stores push the Q and dO tiles out of it, +1 %).  In a stage, us, dQ by recomputation -> from kept dS (with the delta
+// kernel): 8192 tokens, 32 heads dK/dV 1121 -> 1209 and dQ 717 -> 553, 4096 x 16 heads 140 -> 157 and 120 -> 92; the stage 7664 -> 7600 and
+// 1602 -> 1585, 2048 x 64 heads 3178 -> 3145, 2 x 508 x 32 1067 -> 1064.
 template <int D, bool MULTI, bool DS>
 __global__ void __launch_bounds__(512) attn_bwd_dkv_pair_kernel(const AttnArgs p) {
   const int hpw = MULTI ? p.hpw : 1;
@@ -1202,18 +1203,18 @@ hipError_t launch_dq(hipStream_t st, const AttnArgs& p) {
 // the fp32 partials that are written and read back (147 MB each way at 3 x 1500 tokens, 64 heads of 64) and the workgroups'
 // start and end, and doubles the longest chain (key tile 0 sees every query tile).  It pays while that chain is short against
 // the work per CU.  Measured, backward in us, one head | two | four, with chain / work per CU of the last two in brackets:
-//   d = 128: 8192 x 32 heads 1837 | 1808 (.49) | 1802 (.98);  4096 x 64: 1016 | 970 (.48) | 970 (.97);  2 x 2048 x 64:
-//            621 | 562 (.47) | 537 (.94);  4096 x 32: 529 | 516 (.97)
-//   d = 64 (two workgroups share a CU, a chain runs at half the pace): 3 x 1500 x 64: 306 | 285 (.41) | 297 (.82);
-//            8192 x 64: 1996 | 1937 (.25) | 2014 (.49);  2048 x 64: 170 | 180 (.94)
+//   d = 128: 8192 x 32 heads 1669 | 1624 (.49) | 1620 (.98);  4096 x 64: 950 | 885 (.48) | 886 (.97);  2 x 2048 x 64:
+//            580 | 513 (.47) | 489 (.94);  4096 x 32: 478 | 457 (.97) | 610
+//   d = 64 (two workgroups share a CU, a chain runs at half the pace): 3 x 1500 x 64: 252 | 232 (.41) | 242 (.82);
+//            8192 x 64: 1780 | 1733 (.25) | 1786 (.49);  2048 x 64: 151 | 162 (.94) | 226
 // Groups of two heads in one key tile, or two, take both heads as well, beside that rule: the chain is then two to eight query tiles
 // longer, 1 to 4 us, and the partials and the launch that adds them are 3 us and what their traffic takes.  Forward and backward of the
-// attention entry points, us, one head | two:  d = 64, 4 heads: 1 x 64 tokens 21.4 | 18.0, 1 x 128 23.0 | 22.8, 64 x 128 30.8 | 25.6;  d = 128,
-// 16 heads: 1 x 64 23.7 | 21.2, 1 x 128 31.8 | 30.9, 4 x 128 36.6 | 31.8.  Two key tiles, heads x sequences at d = 64 and d = 128: 4: 28.4 | 30.6 and
-// 39.0 | 42.4, 16: 29.4 | 31.0 and 41.1 | 42.6, 32: 30.3 | 31.6 and 43.6 | 43.2, 64: 33.2 | 32.0 and 46.3 | 45.0, 256: 46.6 | 39.8 and 85.7 | 62.9;
-// 48 heads x sequences, 160 and 256 tokens: 25.7 | 25.9 and 31.5 | 31.7, 36.9 | 35.1 and 46.2 | 43.8.
-// (One tile, 4 heads, d = 128, 1 x 128 tokens: 30.2 | 30.6.)
-// Orders by runs of key tiles (from 96 tiles on, see k_attn_bwd) keep one head: 16384 x 64 at four heads is 3 % slower.
+// attention entry points, us, one head | two:  d = 64, 4 heads: 1 x 64 tokens 19.2 | 17.0, 1 x 128 24.3 | 22.2, 64 x 128 25.5 | 23.2;  d = 128,
+// 16 heads: 1 x 64 24.0 | 21.6, 1 x 128 31.4 | 30.8, 4 x 128 36.5 | 31.5.  Two key tiles, heads x sequences at d = 64 and d = 128: 4: 28.6 | 30.4 and
+// 39.1 | 42.0, 16: 29.4 | 30.8 and 40.8 | 42.6, 32: 30.3 | 31.6 and 43.2 | 43.0, 64: 32.4 | 31.6 and 45.7 | 44.0, 256: 44.0 | 37.1 and 82.6 | 58.8;
+// 48 heads x sequences, 160 and 256 tokens: 26.6 | 26.0 and 31.4 | 31.4, 36.8 | 35.2 and 46.2 | 43.3.
+// (One tile, 4 heads, d = 128, 1 x 128 tokens: 30.5 | 30.5.)
+// Orders by runs of key tiles (from 96 tiles on, see k_attn_bwd) keep one head: 16384 x 64 13100 | 13040 | 13270.
 int heads_per_workgroup(int seq, int batch, int a, int kh, int d) {
   const long nkv = (seq + 127) / 128;
   const double per_cu = (double)a * batch * nkv * (nkv + 1) / 256.0, most = d == 128 ? 1.0 : 0.45;
@@ -1234,7 +1235,9 @@ hipError_t k_attn_fwd(hipStream_t st, const void* q, const void* k, const void* 
   p.ldq = ldq; p.ldk = ldk; p.ldv = ldv; p.ldo = ldo;
   fill_common(p, batch, seq, a, kh, d);
   // workgroup = 4 waves x 32 queries; 64 queries per wave halve the LDS reads per MFMA but spill at d = 128
-  // eight waves per workgroup (256 queries) store every K/V tile once for twice the products; enough workgroups needed
+  // eight waves per workgroup (256 queries) store every K/V tile once for twice the products; enough workgroups needed.  Four | eight, us: 8192 x 32
+  // heads 510 | 487, 4096 x 64 269 | 263, 8192 x 24 (768 workgroups) 402 | 387, 4096 x 32 (512) 137 | 132, 2048 x 64 (512) 77.3 | 76.1, but with short
+  // chains 4 x 1024 x 64 (1024) 93.7 | 100.8; dQ with the rest of the backward 1658 | 1625, 878 | 877, 1303 | 1295, 461 | 444, 256 | 253, 291 | 302
   // (d = 128 only: at d = 64 the four-wave kernel fits three waves per SIMD and is 20 % faster than the eight-wave one)
   const bool big = (long)((seq + 255) / 256) * a * batch >= 1024;
   if (d == 128 && big) return launch_fwd<128, 8>(st, p);
