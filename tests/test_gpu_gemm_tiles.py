@@ -121,10 +121,10 @@ def err(got, ref):
     return float((got.double() - ref).norm() / ref.norm())
 
 
-# (M, N, K, K2) that the cost model cuts along the reduction, with the tile it takes: 256x256 (four waves), 256x128 by two groups,
-# 128x128 (ragged and with eight rows), 128x64, 64x64 (three)
+# (M, N, K, K2) that the cost model cuts along the reduction, with the tile it takes: 256x256 (four waves), 128x128, 128x64, 128x128 with
+# eight rows, 128x64 (two), 64x64 (three), 256x128 by two groups
 SPLIT_SHAPES = [(1032, 2056, 12296, 24), (1016, 1032, 8200, 24), (520, 1032, 4104, 24), (8, 2056, 4104, 16), (72, 72, 1288, 24),
-                (1032, 136, 2312, 24), (136, 56, 1288, 0), (8, 264, 4104, 8), (8, 8, 12296, 0)]
+                (1032, 136, 2312, 24), (136, 56, 1288, 0), (8, 264, 4104, 8), (8, 8, 12296, 0), (1544, 520, 12296, 24)]
 
 
 @pytest.mark.parametrize("shape", SPLIT_SHAPES)

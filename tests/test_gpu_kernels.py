@@ -80,7 +80,7 @@ def test_gemm_layouts_ragged(rp, layout, tile):
 def test_gemm_operands_loaded_straight_into_lds(rp, shape, layout):
     """Tile 7 (what tile 0 picks on 256x256 tiles when the reduction is long): four waves of 128x128, operands fetched from memory
     straight into a ring of LDS units, reduction tails and tiles past the end read through out-of-range offsets.
-    Against the fp64 product, and bit for bit against the staged eight-wave kernel (tile 1: same matrix instruction,
+    Against the fp64 product, and bit for bit against the staged eight-wave kernel (tile 1: a wider matrix instruction,
     same order of the reduction).  Ragged rows and columns against 256/128/64, K and K2 against the K tile of 64 (the
     second pair shorter than one tile, a first pair of one tile exactly, an empty first pair); residual, fp32
     accumulation with alpha, a reduction split merged in slice order."""
